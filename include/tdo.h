@@ -206,8 +206,8 @@ int32_t tdo_loss_grad_batched(tdo_ctx_t *ctx, const tdo_arch_t *arch, int32_t n_
 
 /* Tile shapes of the loss/gradient kernels for one problem's shape (chain length,
  * precision, width, head width, depth, MLP width), chosen by timing: the forward
- * layer kernel's waves per workgroup (8: two per SIMD sharing the LDS weights,
- * BF16 with n <= 32 only; or 4) and workgroups per CU (1 or 2), timed on the
+ * layer kernel's waves per workgroup (8: two per SIMD; or, BF16 only, 4) and
+ * workgroups per CU (1 or 2), timed on the
  * forward over the samples; the BF16 feed-forward backward's waves per workgroup
  * at MLP width 256 (8 or 4), timed on whole loss/gradient evaluations, which
  * write loss and grad (device double [1] and [P]).  The choice is kept in the

@@ -47,7 +47,7 @@ float time_twice(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& fn) {
 }
 
 // Tile shapes of one problem's (chain length, precision, width, head width, depth, MLP width):
-//  1. the forward layer kernel: workgroups of 8 waves (two per SIMD, BF16 only) or
+//  1. the forward layer kernel: workgroups of 8 waves (two per SIMD) or, BF16 only,
 //     4 waves, and 1 or 2 workgroups per CU, timed on the full forward over the problem's
 //     samples;
 //  2. the BF16 feed-forward backward at MLP width 256: 8 or 4 waves per workgroup, timed on the
@@ -61,7 +61,7 @@ int32_t tune_problem(Context& c, NetPlan& np, const ModelDev& m, const TrainWs& 
   for (const TuneEntry& e : c.tune)
     if (e.key == key) {
       np.fwd_wg_per_cu = e.fwd_wg_per_cu;
-      np.fwd_waves = e.fwd_waves;
+      if (np.bf16) np.fwd_waves = e.fwd_waves;
       np.mlp_waves = e.mlp_waves;
       return TDO_OK;
     }
@@ -88,7 +88,7 @@ int32_t tune_problem(Context& c, NetPlan& np, const ModelDev& m, const TrainWs& 
     int bw = np.fwd_waves, bg = np.fwd_wg_per_cu;
     for (int wi = 0; wi < (two_shapes ? 2 : 1) && rc == TDO_OK; ++wi)
       for (int gi = 0; gi < 2 && rc == TDO_OK; ++gi) {
-        np.fwd_waves = two_shapes ? waves_c[wi] : 4;
+        np.fwd_waves = waves_c[wi];
         np.fwd_wg_per_cu = wg_c[gi];
         const float ms = time_twice(st, ev[0], ev[1], [&]() {
           return run_forward(np, w, cfg, E, nullptr, at<float>(c.ws, oxa), at<float>(c.ws, oxb), nullptr,

@@ -24,6 +24,7 @@ namespace tdo {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // Feature (or row) index held by value r of lane half h in a 32x32 result tile.
@@ -60,6 +61,10 @@ struct PBF16 {
   __device__ static __forceinline__ f32x16 mma(op_t a, op_t b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
+  // c += a0 b0 + a1 b1 + a2 b2
+  __device__ static __forceinline__ f32x16 mma3(op_t a0, op_t b0, op_t a1, op_t b1, op_t a2, op_t b2, f32x16 c) {
+    return mma(a2, b2, mma(a1, b1, mma(a0, b0, c)));
+  }
   __device__ static __forceinline__ op_t op(const f32x16& v, int s) { return cvt8(v, s); }
   // Operand s of relu(v).  Rounding to BF16 keeps the sign (a negative value rounds to a
   // negative value or -0), so the ReLU of the rounded pair is a signed 16-bit maximum with
@@ -95,17 +100,33 @@ struct PBF16 {
   }
 };
 
-// FP32 operands: v_mfma_f32_32x32x2f32 (1 value/lane).
+// FP32 operands: four v_mfma_f32_32x32x2f32 (1 value/lane each) per k-step, so that a lane
+// reads a weight fragment with one 16-byte load.
 struct PF32 {
-  static constexpr int KPL = 1;
-  static constexpr int STEPS = 16;
+  static constexpr int KPL = 4;
+  static constexpr int STEPS = 4;
   using elem_t = float;
-  using op_t = float;
+  using op_t = f32x4;
   using save_t = float;
   __device__ static __forceinline__ f32x16 mma(op_t a, op_t b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b[t], c, 0, 0, 0);
+    return c;
   }
-  __device__ static __forceinline__ op_t op(const f32x16& v, int s) { return v[s]; }
+  // c += a0 b0 + a1 b1 + a2 b2, the three products taken in turn
+  __device__ static __forceinline__ f32x16 mma3(op_t a0, op_t b0, op_t a1, op_t b1, op_t a2, op_t b2, f32x16 c) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[t], b0[t], c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[t], b1[t], c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[t], b2[t], c, 0, 0, 0);
+    }
+    return c;
+  }
+  template <class V>
+  __device__ static __forceinline__ op_t op(const V& v, int s) {
+    return op_t{v[4 * s], v[4 * s + 1], v[4 * s + 2], v[4 * s + 3]};
+  }
   __device__ static __forceinline__ op_t relu_op(const f32x16& v, int s);
   template <int DH>
   struct SOp {
@@ -141,7 +162,7 @@ __device__ __forceinline__ typename P::op_t ld_frag(const typename P::elem_t* ba
   if constexpr (P::KPL == 8) {
     return *reinterpret_cast<const bf16x8*>(base + ((size_t)frag * 64 + lane) * 8);
   } else {
-    return base[(size_t)frag * 64 + lane];
+    return *reinterpret_cast<const f32x4*>(base + ((size_t)frag * 64 + lane) * 4);
   }
 }
 
@@ -231,6 +252,8 @@ __device__ __forceinline__ void barrier_lds() {
 // negative value or -0 gives +0; it differs from x > 0 ? x : 0 only for a NaN input, which
 // it passes on instead of replacing by 0.
 __device__ __forceinline__ float relu(float x) { return __int_as_float(max(__float_as_int(x), 0)); }
-__device__ __forceinline__ float PF32::relu_op(const f32x16& v, int s) { return relu(v[s]); }
+__device__ __forceinline__ f32x4 PF32::relu_op(const f32x16& v, int s) {
+  return f32x4{relu(v[4 * s]), relu(v[4 * s + 1]), relu(v[4 * s + 2]), relu(v[4 * s + 3])};
+}
 
 }  // namespace tdo

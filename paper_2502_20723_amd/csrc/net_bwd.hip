@@ -26,10 +26,12 @@ namespace tdo {
 
 constexpr int TS = 36;  // row stride (floats) of the transpose scratch
 
-// Natural row index of value i of lane half h in an operand built by transpose_tile.
+// Row index of value i of lane half h in an operand built by transpose_tile: 8 consecutive rows
+// per lane half (BF16), or rows in ascending order over the FP32 products (two rows each).
 template <class P>
 __device__ __forceinline__ int nat_idx(int i, int h) {
-  return (i / P::KPL) * (2 * P::KPL) + h * P::KPL + (i % P::KPL);
+  if constexpr (P::KPL == 8) return (i / 8) * 16 + h * 8 + (i % 8);
+  else return 2 * i + h;
 }
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -393,9 +395,8 @@ __global__ void __launch_bounds__(256) k_bwd_attn(BwdArgs a) {
 #pragma unroll
           for (int s = 0; s < ST; ++s) {
             const int f = (ob * NB + hb) * ST + s;
-            dx[rb][ob] = P::mma(ld_frag<P>(WqT, f, lane), P::op(dq[rb], s), dx[rb][ob]);
-            dx[rb][ob] = P::mma(ld_frag<P>(WkT, f, lane), P::op(dk[rb], s), dx[rb][ob]);
-            dx[rb][ob] = P::mma(ld_frag<P>(WvT, f, lane), P::op(dv[rb], s), dx[rb][ob]);
+            dx[rb][ob] = P::mma3(ld_frag<P>(WqT, f, lane), P::op(dq[rb], s), ld_frag<P>(WkT, f, lane), P::op(dk[rb], s),
+                                 ld_frag<P>(WvT, f, lane), P::op(dv[rb], s), dx[rb][ob]);
           }
         const f32x16 dqT = transpose_tile<P>(dq[rb], sc, lane);
         const f32x16 dkT = transpose_tile<P>(dk[rb], sc, lane);

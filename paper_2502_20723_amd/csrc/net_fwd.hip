@@ -13,6 +13,8 @@
 // W_O and residual, then the ReLU feed-forward sub-layer and residual.
 // The layer's packed weights are staged once per workgroup in LDS (BF16) or
 // read through the caches (FP32); workgroups are persistent over tiles.
+#include <algorithm>
+
 #include "common.h"
 #include "net.h"
 #include "netapi.h"
@@ -71,7 +73,7 @@ __global__ void k_embed_table(const float* __restrict__ params, int d, int D, fl
 
 // Workgroup size NT: BF16 weights staged in LDS are shared by 8 waves (two per SIMD,
 // so that one wave's latencies overlap the other's work) or by 4 waves (one per SIMD,
-// with twice the registers); the choice is autotuned per shape.  Otherwise 4 waves.
+// with twice the registers); the choice is autotuned per shape.  FP32: 8 waves.
 // A wave of a spanning pass (two row blocks) needs more than half a SIMD's registers:
 // with 8 waves it is held to 256 and spills a few values (24 at head width 16 with
 // masking), which measured faster than one wave per SIMD.
@@ -171,9 +173,13 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
         }
       }
   };
-  if (!SPAN) fetch_x((int64_t)blockIdx.x * (blockDim.x >> 6) + wave);
+  // Neighbouring tiles go to the waves of one workgroup (contiguous activations), but a batch of
+  // fewer tiles than the grid has waves goes round the workgroups first, so that all CUs work.
+  const int64_t tile0 = ntiles < tstride ? (int64_t)wave * gridDim.x + blockIdx.x
+                                         : (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
+  if (!SPAN) fetch_x(tile0);
 
-  for (int64_t tile = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave; tile < ntiles; tile += tstride) {
+  for (int64_t tile = tile0; tile < ntiles; tile += tstride) {
     const int pass = (int)(tile & 1);
     // first entry of the tile and the slot/validity of this lane's rows
     const int64_t e0 = SPAN ? (tile >> 1) : (tile >> 1) * cpb;
@@ -500,17 +506,22 @@ static int32_t launch_layer_nt(const FwdArgs& a, int num_cus, hipStream_t st) {
   const size_t lds = wbytes + (size_t)(a.M + D) * 4 + (a.first ? 64 * D * 4 : 0) + 64 * sizeof(float2);
   auto kern = k_fwd_layer<P, D, DH, SPAN, MBC, MASKED, NT>;
   TDO_TRY(allow_full_lds((const void*)kern));
-  const int blocks = num_cus * a.blocks_per_cu;
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(NT), lds, st, a);
+  // no more workgroups than tiles (n_entries bounds the entries also where their count is on the device)
+  const int64_t tiles = SPAN ? 2 * a.n_entries : 2 * ((a.n_entries + a.cpb - 1) / a.cpb);
+  const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(num_cus * a.blocks_per_cu, tiles));
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(NT), lds, st, a);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }
 
 template <class P, int D, int DH, bool SPAN, int MBC, bool MASKED>
 static int32_t launch_layer_m(const FwdArgs& a, int num_cus, hipStream_t st) {
+  // FP32: always 8 waves.  The weights come through the caches, and a second wave per SIMD covers
+  // their latency (n = 16, width 64, 32768 configurations: 1.51 ms a layer with 4 waves, 1.11 with
+  // 8; n = 37: 1.54 and 1.31; n = 4, width 16: 0.202 and 0.157).
   if constexpr (P::KPL == 8)
-    if (a.waves == 8) return launch_layer_nt<P, D, DH, SPAN, MBC, MASKED, 512>(a, num_cus, st);
-  return launch_layer_nt<P, D, DH, SPAN, MBC, MASKED, 256>(a, num_cus, st);
+    if (a.waves == 4) return launch_layer_nt<P, D, DH, SPAN, MBC, MASKED, 256>(a, num_cus, st);
+  return launch_layer_nt<P, D, DH, SPAN, MBC, MASKED, 512>(a, num_cus, st);
 }
 
 // the BF16 width-64 kernels with the feed-forward width 4 x 64 fixed at compile time

@@ -106,7 +106,7 @@ static int32_t launch_pack(const PackPlan& pp, const float* params, bool bf16, b
   if (bf16)
     hipLaunchKernelGGL((k_pack<8, __bf16>), dim3(blocks), dim3(256), 0, st, params, pp, bwd, (__bf16*)wpack, b1, b2);
   else
-    hipLaunchKernelGGL((k_pack<1, float>), dim3(blocks), dim3(256), 0, st, params, pp, bwd, (float*)wpack, b1, b2);
+    hipLaunchKernelGGL((k_pack<4, float>), dim3(blocks), dim3(256), 0, st, params, pp, bwd, (float*)wpack, b1, b2);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }

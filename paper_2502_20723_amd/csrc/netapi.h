@@ -12,7 +12,7 @@ struct FwdArgs {
   const float* table;           // first layer: embedding table [64][D]
   const uint64_t* ecfg;         // first layer: configurations [E][2]
   const int64_t* n_entries_dev; // E on the device, or NULL to use n_entries
-  int64_t n_entries;
+  int64_t n_entries;            // their number, or an upper bound when n_entries_dev gives it
   const float* x_in;            // residual in, [blocks][D/32][64][16] (not first layer)
   float* x_out;                 // residual out (not last layer)
   void* save_x;                 // optional: layer input saved for the backward pass
@@ -26,7 +26,7 @@ struct FwdArgs {
   int n, cpb, d_real, M;
   float score_scale;            // log2(e) / sqrt(d/heads)
   int first, last, masked, blocks_per_cu;
-  int waves;                    // waves per workgroup (4, or 8 for BF16 with n <= 32)
+  int waves;                    // waves per workgroup (8; or 4, BF16 only)
 };
 
 int32_t launch_fwd_layer(const FwdArgs& a, bool bf16, int D, int DH, bool span, int num_cus, hipStream_t st);

@@ -1,6 +1,7 @@
 // C-ABI entry points of libtdo (declared and documented in include/tdo.h):
 // argument validation, workspace planning and the launch sequences.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstring>
 
@@ -105,21 +106,37 @@ WsOrder::~WsOrder() {
   }
 }
 
-// One workgroup counts the values whose exponent field is all ones (inf or nan) and
-// writes (or adds) the count: a fixed-size read of a parameter vector, a few microseconds.
-__global__ void __launch_bounds__(1024) k_count_nonfinite(const float* __restrict__ p, int64_t n, int accumulate,
-                                                          uint32_t* __restrict__ out) {
-  __shared__ uint32_t part[16];
+// Workgroup w counts the values of slice w of every vector of the list whose exponent field is
+// all ones (inf or nan) and stores 1 + its count (plus the running count of earlier lists) in
+// slot w, in pinned host memory that the caller polls: one small kernel and no copy.  A fixed
+// read of the parameters, bound by latency: kNfSlots slices keep enough loads in flight
+// (206,594 values: 89 us in one workgroup, 4 us in 64 with 16 loads per thread in flight).
+constexpr int kNfSlots = 64, kNfList = 64;
+struct NfList {
+  const float* p[kNfList];
+  int count;
+};
+
+__global__ void __launch_bounds__(256) k_count_nonfinite(NfList list, int64_t n, int accumulate,
+                                                         uint32_t* __restrict__ run, uint32_t* __restrict__ out) {
+  __shared__ uint32_t part[4];
+  const int64_t slice = (n + gridDim.x - 1) / gridDim.x;
+  const int64_t i0 = blockIdx.x * slice, i1 = i0 + slice < n ? i0 + slice : n;
   uint32_t cnt = 0;
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x)
-    cnt += ((__float_as_uint(p[i]) & 0x7f800000u) == 0x7f800000u) ? 1u : 0u;
+  for (int q = 0; q < list.count; ++q) {
+    const float* __restrict__ p = list.p[q];
+#pragma unroll 16
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += 256)
+      cnt += ((__float_as_uint(p[i]) & 0x7f800000u) == 0x7f800000u) ? 1u : 0u;
+  }
   for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, WAVE);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = cnt;
   __syncthreads();
   if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += part[w];
-    out[0] = accumulate ? out[0] + t : t;
+    uint32_t t = part[0] + part[1] + part[2] + part[3];
+    if (accumulate) t += run[blockIdx.x];
+    run[blockIdx.x] = t;
+    if (out) __hip_atomic_store(out + blockIdx.x, t + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -132,28 +149,44 @@ static bool capturing(hipStream_t st) {
   return cap != hipStreamCaptureStatusNone;
 }
 
-int32_t count_nonfinite(Context* c, const float* p, int64_t n, bool accumulate, hipStream_t st) {
+int32_t check_params_finite(Context* c, const float* const* p, int count, int64_t n, hipStream_t st, const char* what) {
   if (capturing(st)) return TDO_OK;
   if (!c->nf_dev) {
-    TDO_HIP(hipMalloc(&c->nf_dev, 256));
-    TDO_HIP(hipHostMalloc(&c->nf_host, 256, hipHostMallocDefault));
+    TDO_HIP(hipMalloc(&c->nf_dev, kNfSlots * sizeof(uint32_t)));
+    TDO_HIP(hipHostMalloc(&c->nf_host, kNfSlots * sizeof(uint32_t), hipHostMallocDefault));
   }
-  hipLaunchKernelGGL(k_count_nonfinite, dim3(1), dim3(1024), 0, st, p, n, accumulate ? 1 : 0, c->nf_dev);
-  TDO_HIP(hipGetLastError());
-  return TDO_OK;
-}
-
-int32_t check_nonfinite(Context* c, hipStream_t st, const char* what) {
-  if (capturing(st) || !c->nf_dev) return TDO_OK;
-  TDO_HIP(hipMemcpyAsync(c->nf_host, c->nf_dev, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  TDO_HIP(hipStreamSynchronize(st));
-  TDO_CHECK(c->nf_host[0] == 0, TDO_ENONFINITE, "%s: %u parameter values are inf or nan", what, c->nf_host[0]);
+  // at least 1024 values per slice
+  const int slots = (int)std::max<int64_t>(1, std::min<int64_t>(kNfSlots, n / 1024));
+  volatile uint32_t* host = c->nf_host;
+  for (int i = 0; i < slots; ++i) host[i] = 0;
+  for (int q0 = 0; q0 < count; q0 += kNfList) {
+    NfList list{};
+    list.count = std::min(kNfList, count - q0);
+    for (int i = 0; i < list.count; ++i) list.p[i] = p[q0 + i];
+    hipLaunchKernelGGL(k_count_nonfinite, dim3(slots), dim3(256), 0, st, list, n, q0 > 0 ? 1 : 0, c->nf_dev,
+                       q0 + kNfList >= count ? c->nf_host : nullptr);
+    TDO_HIP(hipGetLastError());
+  }
+  // Poll the slots for a short while, then wait for the stream: the poll sees the count some
+  // microseconds before a stream wait returns, and a stream with earlier work still waits idle.
+  const auto t0 = std::chrono::steady_clock::now();
+  bool done = false;
+  do {
+    done = true;
+    for (int i = 0; i < slots; ++i) done = done && __atomic_load_n(c->nf_host + i, __ATOMIC_ACQUIRE) != 0;
+  } while (!done && std::chrono::steady_clock::now() - t0 < std::chrono::microseconds(100));
+  if (!done) TDO_HIP(hipStreamSynchronize(st));
+  uint32_t bad = 0;
+  for (int i = 0; i < slots; ++i) {
+    TDO_CHECK(host[i] != 0, TDO_EHIP, "the parameter check did not run");
+    bad += host[i] - 1;
+  }
+  TDO_CHECK(bad == 0, TDO_ENONFINITE, "%s: %u parameter values are inf or nan", what, bad);
   return TDO_OK;
 }
 
 int32_t check_params_finite(Context* c, const float* p, int64_t n, hipStream_t st) {
-  TDO_TRY(count_nonfinite(c, p, n, false, st));
-  return check_nonfinite(c, st, "params");
+  return check_params_finite(c, &p, 1, n, st, "params");
 }
 
 int32_t ensure_workspace(Context* c, size_t bytes) {

@@ -151,8 +151,7 @@ extern "C" int32_t tdo_loss_grad_batched(tdo_ctx_t* ctx, const tdo_arch_t* arch,
   }
   WsOrder order;
   TDO_TRY(order.begin(&c, stream));
-  for (int32_t p = 0; p < n_problems; ++p) TDO_TRY(count_nonfinite(&c, params[p], np[p].pp.nparams, p > 0, stream));
-  TDO_TRY(check_nonfinite(&c, stream, "params of the problems"));
+  TDO_TRY(check_params_finite(&c, params, n_problems, np[0].pp.nparams, stream, "params of the problems"));
   std::vector<uint8_t> key;
   put(key, *arch);
   put(key, n_problems);

@@ -99,7 +99,7 @@ struct Context {
   GraphCache graph;
   std::vector<TuneEntry> tune;
   std::string tune_cache;  // path of the JSON cache of the tuned shapes, or empty
-  // count of non-finite parameters (device) and its pinned host copy
+  // counts of non-finite parameters per slice: running (device) and reported (pinned host)
   uint32_t* nf_dev = nullptr;
   uint32_t* nf_host = nullptr;
   // recorded at the end of the last call that used the workspace, on the stream it ran on
@@ -126,12 +126,9 @@ struct WsOrder {
   ~WsOrder();
 };
 
-// Non-finite parameters: count them on the stream (a read-only kernel, one workgroup per
-// call; accumulate adds to the count of the previous call), then wait for the count.
-// Both are skipped while the stream is being captured.
-int32_t count_nonfinite(Context* c, const float* p, int64_t n, bool accumulate, hipStream_t st);
-int32_t check_nonfinite(Context* c, hipStream_t st, const char* what);
-// Both steps for one parameter vector.
+// Counts the inf and nan values of `count` parameter vectors of n values each on the stream and
+// waits for the count; TDO_ENONFINITE if there are any.  Skipped while the stream is captured.
+int32_t check_params_finite(Context* c, const float* const* p, int count, int64_t n, hipStream_t st, const char* what);
 int32_t check_params_finite(Context* c, const float* p, int64_t n, hipStream_t st);
 
 // Device address of the no-allocation scratch array on a device, looked up once per device.

@@ -555,7 +555,8 @@ __global__ void __launch_bounds__(256) k_embed_onehot(const float* __restrict__ 
   f32x16 acc[NB][2];
 #pragma unroll
   for (int ft = 0; ft < NB; ++ft) acc[ft][0] = acc[ft][1] = f32x16{};
-  for (int64_t g = (int64_t)blockIdx.x * 4 + wave; g < nblk; g += (int64_t)gridDim.x * 4) {
+  const int wpg = blockDim.x >> 6;
+  for (int64_t g = (int64_t)blockIdx.x * wpg + wave; g < nblk; g += (int64_t)gridDim.x * wpg) {
     // window code of this lane's row (255 if the row is padding), shared through LDS
     {
       int64_t e; int pass, ric; bool valid;
@@ -626,7 +627,7 @@ __global__ void __launch_bounds__(256) k_embed_onehot(const float* __restrict__ 
       }
     }
   }
-  float* part = partial + ((int64_t)blockIdx.x * 4 + wave) * 64 * D;
+  float* part = partial + ((int64_t)blockIdx.x * wpg + wave) * 64 * D;
 #pragma unroll
   for (int ft = 0; ft < NB; ++ft)
 #pragma unroll
@@ -753,44 +754,44 @@ __global__ void k_scatter_layer(const double* __restrict__ mlp, const double* __
 
 // ------------------------------------------------------------------ launchers
 template <class P, int D>
-static int32_t mlp_t(const BwdArgs& a, int blocks, hipStream_t st) {
+static int32_t mlp_t(const BwdArgs& a, int blocks, int waves, hipStream_t st) {
   const size_t lds = (size_t)(2 * D * a.M + a.M + D) * 4 + 4 * 32 * TS * 4;
   auto k = k_bwd_mlp<P, D>;
   TDO_TRY(allow_full_lds((const void*)k));
-  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), lds, st, a);
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(64 * waves), lds, st, a);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }
 
 template <class P, int D, int DH, bool SPAN>
-static int32_t attn_t(const BwdArgs& a, int blocks, hipStream_t st) {
+static int32_t attn_t(const BwdArgs& a, int blocks, int waves, hipStream_t st) {
   const size_t lds = (size_t)4 * D * D * 4 + 4 * 32 * TS * 4;
   auto k = k_bwd_attn<P, D, DH, SPAN>;
   TDO_TRY(allow_full_lds((const void*)k));
-  hipLaunchKernelGGL(k, dim3(blocks), dim3(256), lds, st, a);
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(64 * waves), lds, st, a);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }
 
 size_t bwd_mlp_lds(int D, int M) { return (size_t)(2 * D * M + M + D) * 4 + 4 * 32 * TS * 4; }
 
-int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream_t st) {
-  if (D == 32) return bf16 ? mlp_t<PBF16, 32>(a, blocks, st) : mlp_t<PF32, 32>(a, blocks, st);
-  if (D == 64) return bf16 ? mlp_t<PBF16, 64>(a, blocks, st) : mlp_t<PF32, 64>(a, blocks, st);
+int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream_t st, int waves) {
+  if (D == 32) return bf16 ? mlp_t<PBF16, 32>(a, blocks, waves, st) : mlp_t<PF32, 32>(a, blocks, waves, st);
+  if (D == 64) return bf16 ? mlp_t<PBF16, 64>(a, blocks, waves, st) : mlp_t<PF32, 64>(a, blocks, waves, st);
   return set_error(TDO_EUNSUPPORTED, "no MLP backward kernel for width %d", D);
 }
 
 template <class P>
-static int32_t attn_p(const BwdArgs& a, int D, int DH, int blocks, hipStream_t st) {
+static int32_t attn_p(const BwdArgs& a, int D, int DH, int blocks, int w, hipStream_t st) {
   const bool sp = a.span != 0;
-  if (D == 32 && DH == 8) return sp ? attn_t<P, 32, 8, true>(a, blocks, st) : attn_t<P, 32, 8, false>(a, blocks, st);
-  if (D == 64 && DH == 8) return sp ? attn_t<P, 64, 8, true>(a, blocks, st) : attn_t<P, 64, 8, false>(a, blocks, st);
-  if (D == 64 && DH == 16) return sp ? attn_t<P, 64, 16, true>(a, blocks, st) : attn_t<P, 64, 16, false>(a, blocks, st);
+  if (D == 32 && DH == 8) return sp ? attn_t<P, 32, 8, true>(a, blocks, w, st) : attn_t<P, 32, 8, false>(a, blocks, w, st);
+  if (D == 64 && DH == 8) return sp ? attn_t<P, 64, 8, true>(a, blocks, w, st) : attn_t<P, 64, 8, false>(a, blocks, w, st);
+  if (D == 64 && DH == 16) return sp ? attn_t<P, 64, 16, true>(a, blocks, w, st) : attn_t<P, 64, 16, false>(a, blocks, w, st);
   return set_error(TDO_EUNSUPPORTED, "no attention backward kernel for width %d, head width %d", D, DH);
 }
 
-int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, hipStream_t st) {
-  return bf16 ? attn_p<PBF16>(a, D, DH, blocks, st) : attn_p<PF32>(a, D, DH, blocks, st);
+int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, hipStream_t st, int waves) {
+  return bf16 ? attn_p<PBF16>(a, D, DH, blocks, waves, st) : attn_p<PF32>(a, D, DH, blocks, waves, st);
 }
 
 int32_t launch_bwd_head(bool bf16, int D, const void* save_last, const float* seeds, const int64_t* E_dev,
@@ -811,10 +812,10 @@ int32_t launch_bwd_head(bool bf16, int D, const void* save_last, const float* se
 }
 
 int32_t launch_embed_scatter(int D, const float* dx0, const uint64_t* ecfg, const int64_t* E_dev, int64_t E_host,
-                             int n, int cpb, int span, float* partial, int blocks, hipStream_t st) {
-  // `blocks` workgroups of 4 waves; each wave writes one [64][D] partial (4 * blocks partials)
-  if (D == 32) hipLaunchKernelGGL(k_embed_onehot<32>, dim3(blocks), dim3(256), 0, st, dx0, ecfg, E_dev, E_host, n, cpb, span, partial);
-  else hipLaunchKernelGGL(k_embed_onehot<64>, dim3(blocks), dim3(256), 0, st, dx0, ecfg, E_dev, E_host, n, cpb, span, partial);
+                             int n, int cpb, int span, float* partial, int blocks, hipStream_t st, int waves) {
+  const dim3 g(blocks), t(64 * waves);
+  if (D == 32) hipLaunchKernelGGL(k_embed_onehot<32>, g, t, 0, st, dx0, ecfg, E_dev, E_host, n, cpb, span, partial);
+  else hipLaunchKernelGGL(k_embed_onehot<64>, g, t, 0, st, dx0, ecfg, E_dev, E_host, n, cpb, span, partial);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }

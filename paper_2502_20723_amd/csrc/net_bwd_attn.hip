@@ -855,21 +855,21 @@ bool bwd_attn_bf16_supported(int d, int D, int DH, bool span) { return d == 64 &
 
 int bwd_attn_bf16_parts(int blocks, bool span) { return span ? blocks : 2 * blocks; }
 
-int32_t launch_bwd_attn_bf16(const BwdArgs& a, int DH, int blocks, hipStream_t st) {
+int32_t launch_bwd_attn_bf16(const BwdArgs& a, int DH, int grid, hipStream_t st) {
   const size_t lds = bwd_attn_bf16_lds(4);
   // written for distinct input and output gradient buffers
   TDO_CHECK(a.g_in != a.g_out, TDO_EINVAL, "BF16 attention backward cannot run in place");
   TDO_CHECK(a.lse != nullptr, TDO_EINVAL, "BF16 attention backward needs the forward's softmax normalisers");
   auto go = [&](auto kern) -> int32_t {
     TDO_TRY(allow_full_lds((const void*)kern));
-    hipLaunchKernelGGL(kern, dim3(2 * blocks), dim3(256), bwd_attn_bf16_lds(ATTN_BPT), st, a);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), bwd_attn_bf16_lds(ATTN_BPT), st, a);
     TDO_HIP(hipGetLastError());
     return TDO_OK;
   };
   if (a.span) {
     auto go4 = [&](auto kern) -> int32_t {
       TDO_TRY(allow_full_lds((const void*)kern));
-      hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, st, a);
+      hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, a);
       TDO_HIP(hipGetLastError());
       return TDO_OK;
     };

@@ -79,21 +79,38 @@ bool bwd_mlp_bf16_supported(int d, int D, int M);
 int32_t launch_bwd_mlp_bf16(const BwdArgs& a, int blocks, hipStream_t st);
 // Attention backward with BF16 operands and per-wave register gradients (width 64, n <= 32).
 bool bwd_attn_bf16_supported(int d, int D, int DH, bool span);
-int32_t launch_bwd_attn_bf16(const BwdArgs& a, int DH, int blocks, hipStream_t st);
-// weight-gradient partial slots [4 D^2] that launch_bwd_attn_bf16 writes for `blocks` (one per CU)
+// Each of `grid` workgroups writes one weight-gradient partial [4 D^2].
+int32_t launch_bwd_attn_bf16(const BwdArgs& a, int DH, int grid, hipStream_t st);
+// workgroups that fill the chip with one per CU in `blocks`
 int bwd_attn_bf16_parts(int blocks, bool span);
-int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream_t st);
-int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, hipStream_t st);
+// waves: blocks (feed-forward) or tiles (attention) that a workgroup takes at a time
+int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream_t st, int waves = 4);
+int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, hipStream_t st, int waves = 4);
 // part: FP64 scratch of HEAD_BLOCKS * (2 d_real + 2) values (one slot per workgroup).
 constexpr int HEAD_BLOCKS = 1024;
 int32_t launch_bwd_head(bool bf16, int D, const void* save_last, const float* seeds, const int64_t* E_dev,
                         int64_t E_host, int n, int cpb, int span, int d_real, double* gw, double* gb, double* part,
                         hipStream_t st);
+// One partial [64][D] per wave, blocks * waves of them.
 int32_t launch_embed_scatter(int D, const float* dx0, const uint64_t* ecfg, const int64_t* E_dev, int64_t E_host,
-                             int n, int cpb, int span, float* partial, int blocks, hipStream_t st);
+                             int n, int cpb, int span, float* partial, int blocks, hipStream_t st, int waves = 4);
 // part: FP64 scratch of 64 * (6 d + 2 d^2) values (one slot per window code).
 int32_t launch_embed_params(const float* params, const double* dT, int d, int D, double* grad, double* part,
                             hipStream_t st);
+// Rows of the Jacobian (jacobian.hip), for E configurations of bpc blocks each; row e of a part is
+// jac + e * stride.  mpart: slots consecutive partials [2 D M + M + D] per configuration, apart: one
+// [4 D^2]; they become the layer's rows at jac.
+int32_t launch_jac_layer(const float* mpart, int slots, const float* apart, const PackPlan& pp, int64_t E, double* jac,
+                         int64_t stride, hipStream_t st);
+// head weights and bias, at jac; save_last and seeds as launch_bwd_head
+int32_t launch_jac_head(bool bf16, int D, const void* save_last, const float* seeds, int64_t E, int n, int span,
+                        int d_real, double* jac, int64_t stride, hipStream_t st);
+// tables of the embedding's chain rule (FP64, jac_tables(d) values), once per call
+inline size_t jac_tables(int d) { return (size_t)(2 * 16 + 64) * d; }
+int32_t launch_jac_tables(const float* params, int d, double* tab, hipStream_t st);
+// convolution parameters, at jac; part: bpc consecutive wave partials [64][D] per configuration
+int32_t launch_jac_embed(const float* params, const double* tab, const float* part, int bpc, int d, int D, int64_t E,
+                         double* jac, int64_t stride, hipStream_t st);
 int32_t launch_reduce_partials(const float* part, int nparts, int64_t len, double* out, hipStream_t st);
 int32_t launch_scatter_layer(const double* mlp, const double* attn, int d, int D, int M, double scale, double* g,
                              hipStream_t st);

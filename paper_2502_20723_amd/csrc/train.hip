@@ -49,10 +49,10 @@ __device__ __forceinline__ void lse_split(float gre, float gim, const float* __r
 }
 
 // VJP seeds: seed (dRe, dIm) on log rho -> g = dRe - i dIm.
-// Seeds of one configuration for d(s_re Re log rho + s_im Im log rho) (the
-// Jacobian rows).
-__global__ void k_seeds_const(float s_re, float s_im, const float* __restrict__ z, float* __restrict__ dF) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) lse_split(s_re, -s_im, z, dF);
+// Seeds of every configuration for d(s_re Re log rho + s_im Im log rho) (the Jacobian rows).
+__global__ void k_seeds_const(float s_re, float s_im, int64_t E, const float* __restrict__ z, float* __restrict__ dF) {
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E; e += (int64_t)gridDim.x * blockDim.x)
+    lse_split(s_re, -s_im, z + 4 * e, dF + 4 * e);
 }
 
 __global__ void k_seeds_vjp(const float* __restrict__ seed, const float* __restrict__ z, int64_t E, float* __restrict__ dF) {
@@ -130,6 +130,34 @@ struct BwdBufs {
   double* dT_acc;    // [64 D]
 };
 
+// The arguments of layer l's backward kernels, but for the gradients and the partial slots.
+static BwdArgs layer_args(const NetPlan& np, const NetWeights& w, const void* wback, const float* params, int64_t E,
+                          const int64_t* E_dev, const Saves& sv, int l) {
+  const PackPlan& pp = np.pp;
+  BwdArgs a{};
+  a.wf = static_cast<const char*>(w.wpack) + (size_t)l * pp.layer_elems * np.elem;
+  a.wb = static_cast<const char*>(wback) + (size_t)l * pp.layer_elems * np.elem;
+  a.b1 = w.b1 + (size_t)l * pp.M;
+  a.save_x = static_cast<const char*>(sv.x) + (size_t)l * sv.layer_bytes;
+  a.save_mid = static_cast<const char*>(sv.mid) + (size_t)l * sv.layer_bytes;
+  a.lse = sv.lse ? sv.lse + (size_t)l * sv.lse_layer : nullptr;
+  a.w1 = params + pp.off_layer0 + (int64_t)l * pp.layer_stride + 4LL * pp.d * pp.d;
+  a.w2 = a.w1 + (int64_t)pp.d * pp.mlp + pp.mlp;
+  a.head_w = w.head_w;
+  a.n_entries_dev = E_dev;
+  a.n_entries = E;
+  a.n = np.n;
+  a.cpb = np.cpb;
+  a.span = np.span;
+  a.masked = np.masked;
+  a.d_real = pp.d;
+  a.M = pp.M;
+  a.score_scale = np.score_scale;
+  a.inv_sqrt_dh = (float)(1.0 / std::sqrt((double)np.DH));
+  a.mlp_waves = np.mlp_waves;
+  return a;
+}
+
 static int32_t run_backward(const NetPlan& np, const NetWeights& w, const BwdBufs& bb, const float* params,
                             const uint64_t* ecfg, int64_t E, const int64_t* E_dev, const Saves& sv, const float* dF,
                             double* gt, hipStream_t st) {
@@ -137,28 +165,8 @@ static int32_t run_backward(const NetPlan& np, const NetWeights& w, const BwdBuf
   const int L = pp.layers, D = np.D, M = pp.M;
   const int64_t mlen = 2LL * D * M + M + D, alen = 4LL * D * D;
   for (int l = L - 1; l >= 0; --l) {
-    BwdArgs a{};
-    a.wf = static_cast<const char*>(w.wpack) + (size_t)l * pp.layer_elems * np.elem;
-    a.wb = static_cast<const char*>(bb.wback) + (size_t)l * pp.layer_elems * np.elem;
-    a.b1 = w.b1 + (size_t)l * M;
-    a.save_x = static_cast<const char*>(sv.x) + (size_t)l * sv.layer_bytes;
-    a.save_mid = static_cast<const char*>(sv.mid) + (size_t)l * sv.layer_bytes;
-    a.lse = sv.lse ? sv.lse + (size_t)l * sv.lse_layer : nullptr;
-    a.w1 = params + pp.off_layer0 + (int64_t)l * pp.layer_stride + 4LL * pp.d * pp.d;
-    a.w2 = a.w1 + (int64_t)pp.d * pp.mlp + pp.mlp;
-    a.head_w = w.head_w;
+    BwdArgs a = layer_args(np, w, bb.wback, params, E, E_dev, sv, l);
     a.partial = bb.partial;
-    a.n_entries_dev = E_dev;
-    a.n_entries = E;
-    a.n = np.n;
-    a.cpb = np.cpb;
-    a.span = np.span;
-    a.masked = np.masked;
-    a.d_real = pp.d;
-    a.M = M;
-    a.score_scale = np.score_scale;
-    a.inv_sqrt_dh = (float)(1.0 / std::sqrt((double)np.DH));
-    a.mlp_waves = np.mlp_waves;
     // feed-forward sub-layer: gradient in ga (or from the seeds), out to gb
     a.g_in = (l == L - 1) ? nullptr : bb.ga;
     a.seeds = (l == L - 1) ? dF : nullptr;
@@ -181,8 +189,8 @@ static int32_t run_backward(const NetPlan& np, const NetWeights& w, const BwdBuf
     {
       ProfScope ps(np.prof, "bwd_attn", st);
       if (np.bf16 && bwd_attn_bf16_supported(pp.d, D, np.DH, np.span)) {
-        TDO_TRY(launch_bwd_attn_bf16(a, np.DH, bb.nparts, st));
         attn_parts = bwd_attn_bf16_parts(bb.nparts, np.span);
+        TDO_TRY(launch_bwd_attn_bf16(a, np.DH, attn_parts, st));
       } else {
         TDO_TRY(launch_bwd_attn(a, np.bf16, D, np.DH, bb.nparts, st));
       }
@@ -329,9 +337,10 @@ extern "C" int32_t tdo_log_rho_vjp(tdo_ctx_t* ctx, const tdo_arch_t* arch, const
   return vjp_run(c, np, t, params, cfg, B, seed, grad, false, stream);
 }
 
-// Per-sample log-derivatives: per configuration one forward, then one backward
-// per part (Re, Im) with the launch sequence of tdo_log_rho_vjp on one
-// configuration, on weights packed once.
+// Per-sample log-derivatives: the forward, and per part (Re, Im) the backward, of a chunk of
+// configurations at a time, one configuration per block (cpb = 1) and one workgroup of the
+// layer kernels per configuration, so that a workgroup's weight-gradient partial is one
+// configuration's gradient, which the row kernels (jacobian.hip) write out in FP64.
 extern "C" int32_t tdo_log_rho_jacobian(tdo_ctx_t* ctx, const tdo_arch_t* arch, const float* params, int32_t n,
                                         const uint64_t* cfg, int64_t B, tdo_prec_t prec, double* jac,
                                         hipStream_t stream) {
@@ -348,74 +357,90 @@ extern "C" int32_t tdo_log_rho_jacobian(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   WsOrder order;
   TDO_TRY(order.begin(&c, stream));
   TDO_TRY(check_params_finite(&c, params, np.pp.nparams, stream));
-  TrainWs t;
-  TDO_TRY(plan_train(c, np, 1, 1, &t));
-  // kLanes independent copies of the one-configuration scratch, each driven on its
-  // own stream (a single configuration occupies a few workgroups); the packed
-  // weights of copy 0 are shared
-  constexpr int kLanes = 4;
-  const int lanes = (int)std::min<int64_t>(kLanes, B);
-  const size_t stride = (t.total + 4095) & ~size_t(4095);
-  TDO_TRY(ensure_workspace(&c, stride * lanes));
-  char* ws0 = static_cast<char*>(c.ws);
-  NetWeights w = weights_at(ws0, t.woff);
+  const PackPlan& pp = np.pp;
+  const int D = np.D, M = pp.M, L = pp.layers;
+  TDO_CHECK(bwd_mlp_lds(D, M) <= 160 * 1024, TDO_EUNSUPPORTED, "backward of width %d with mlp %d exceeds the LDS of a workgroup", D, M);
+  np.cpb = 1;
+  np.masked = n != (np.span ? 64 : 32);
+  const bool mlp_reg = np.bf16 && bwd_mlp_bf16_supported(pp.d, D, M);
+  const bool attn_reg = np.bf16 && bwd_attn_bf16_supported(pp.d, D, np.DH, np.span);
+  const int bpc = np.span ? 4 : 2;              // blocks of a configuration
+  const int slots = mlp_reg ? bpc / 2 : 1;      // the register kernels take two blocks per workgroup
+  const int64_t mlen = 2LL * D * M + M + D, alen = 4LL * D * D, elen = 64LL * D;
+  Arena ar;
+  size_t woff[4];
+  carve_weights(np, ar, woff);
+  const size_t owback = ar.take<char>((size_t)pp.layer_elems * L * np.elem);
+  const size_t otab = ar.take<double>(jac_tables(pp.d));
+  const int save = np.bf16 ? 2 : 4;
+  const size_t heads = D / np.DH, block = 32 * (size_t)D;
+  const size_t per_cfg = bpc * (block * (2 * 4 + (2 * (size_t)L + 1) * save) + (np.bf16 ? L * 32 * heads * 4 : 0)) +
+                         (slots * mlen + alen + bpc * elen) * 4 + 32;
+  const size_t fixed = ar.used + 64 * 256;
+  TDO_CHECK(c.budget > fixed + per_cfg, TDO_ENOMEM, "workspace budget %zu bytes cannot hold one configuration (%zu bytes) and the fixed part (%zu bytes)",
+            c.budget, per_cfg, fixed);
+  // chunks of two configurations per CU at most: the partials stay near the last-level cache
+  const int64_t C = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(B, 2 * c.num_cus), (int64_t)((c.budget - fixed) / per_cfg)));
+  const size_t oz = ar.take<float>(4 * C), odF = ar.take<float>(4 * C);
+  const size_t oxa = ar.take<float>(C * bpc * block), oxb = ar.take<float>(C * bpc * block);
+  Saves sv{};
+  sv.layer_bytes = (C * bpc * block * save + 255) & ~size_t(255);
+  const size_t osx = ar.take<char>(sv.layer_bytes * L), osm = ar.take<char>(sv.layer_bytes * L), osl = ar.take<char>(sv.layer_bytes);
+  sv.lse_layer = np.bf16 ? C * bpc * 32 * heads : 0;
+  const size_t ose = ar.take<float>(sv.lse_layer * L + 64);
+  const size_t omp = ar.take<float>(C * slots * mlen), oap = ar.take<float>(C * alen), oep = ar.take<float>(C * bpc * elen);
+  TDO_TRY(ensure_workspace(&c, ar.used));
+  void* ws = c.ws;
+  sv.x = at<char>(ws, osx);
+  sv.mid = at<char>(ws, osm);
+  sv.last = at<char>(ws, osl);
+  sv.lse = np.bf16 ? at<float>(ws, ose) : nullptr;
+  NetWeights w = weights_at(ws, woff);
   TDO_TRY(pack_weights(np, params, &w, stream));
-  TDO_TRY(launch_pack_backward(np.pp, params, np.bf16, at<char>(ws0, t.wback), stream));
-  const int64_t P = np.pp.nparams;
-  hipStream_t st[kLanes];
-  hipEvent_t ev[kLanes + 1];
-  int made_st = 0, made_ev = 0;
-  int32_t rc = TDO_OK;
-  auto cleanup = [&]() {
-    for (int i = 0; i < made_st; ++i) (void)hipStreamDestroy(st[i]);
-    for (int i = 0; i < made_ev; ++i) (void)hipEventDestroy(ev[i]);
-  };
-#define JAC_HIP(call)                                                                         \
-  do {                                                                                        \
-    hipError_t e_ = (call);                                                                   \
-    if (e_ != hipSuccess) {                                                                   \
-      rc = set_error(TDO_EHIP, "%s failed: %s", #call, hipGetErrorString(e_));                \
-      cleanup();                                                                              \
-      return rc;                                                                              \
-    }                                                                                         \
-  } while (0)
-  for (int i = 0; i <= lanes; ++i, ++made_ev) JAC_HIP(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming));
-  for (int i = 0; i < lanes; ++i, ++made_st) JAC_HIP(hipStreamCreateWithFlags(&st[i], hipStreamNonBlocking));
-  JAC_HIP(hipEventRecord(ev[lanes], stream));  // packed weights ready
-  for (int i = 0; i < lanes; ++i) JAC_HIP(hipStreamWaitEvent(st[i], ev[lanes], 0));
-  for (int64_t b = 0; b < B && rc == TDO_OK; ++b) {
-    const int lane = (int)(b % lanes);
-    hipStream_t s = st[lane];
-    char* ws = ws0 + stride * lane;
-    BwdBufs bb{at<char>(ws0, t.wback), at<float>(ws, t.xa), at<float>(ws, t.xb), at<float>(ws, t.partial), c.num_cus,
-               at<double>(ws, t.mlp_acc), at<double>(ws, t.attn_acc), at<double>(ws, t.dT_acc)};
-    Saves sv{at<char>(ws, t.sx), at<char>(ws, t.smid), at<char>(ws, t.slast), t.layer_bytes,
-             t.lse_layer ? at<float>(ws, t.slse) : nullptr, t.lse_layer};
-    // one forward per configuration: the backward only reads the saved activations and z
-    rc = run_forward(np, w, cfg + 2 * b, 1, nullptr, at<float>(ws, t.xa), at<float>(ws, t.xb), &sv,
-                     at<float>(ws, t.z), s);
-    for (int part = 0; part < 2 && rc == TDO_OK; ++part) {
-      double* row = jac + (2 * b + part) * P;
-      rc = fill(row, P, 0.0, s);
-      if (rc == TDO_OK) rc = fill(at<double>(ws, t.dT_acc), 64LL * np.D, 0.0, s);
-      if (rc == TDO_OK) {
-        hipLaunchKernelGGL(k_seeds_const, dim3(1), dim3(64), 0, s, part == 0 ? 1.f : 0.f, part == 1 ? 1.f : 0.f,
-                           at<float>(ws, t.z), at<float>(ws, t.dF));
-        if (hipGetLastError() != hipSuccess) rc = set_error(TDO_EHIP, "k_seeds_const launch failed");
+  TDO_TRY(launch_pack_backward(pp, params, np.bf16, at<char>(ws, owback), stream));
+  TDO_TRY(launch_jac_tables(params, pp.d, at<double>(ws, otab), stream));
+  float *ga = at<float>(ws, oxa), *gb = at<float>(ws, oxb), *z = at<float>(ws, oz), *dF = at<float>(ws, odF);
+  float *mp = at<float>(ws, omp), *ap = at<float>(ws, oap), *ep = at<float>(ws, oep);
+  const int64_t P = pp.nparams, stride = 2 * P;
+  for (int64_t b0 = 0; b0 < B; b0 += C) {
+    const int64_t E = std::min(C, B - b0);
+    const uint64_t* ec = cfg + 2 * b0;
+    // one forward for both parts: the backward only reads the saved activations and z
+    TDO_TRY(run_forward(np, w, ec, E, nullptr, ga, gb, &sv, z, stream));
+    for (int part = 0; part < 2; ++part) {
+      double* rows = jac + (2 * b0 + part) * P;
+      hipLaunchKernelGGL(k_seeds_const, dim3((unsigned)ceil_div(E, 64)), dim3(64), 0, stream, part == 0 ? 1.f : 0.f,
+                         part == 1 ? 1.f : 0.f, E, z, dF);
+      TDO_HIP(hipGetLastError());
+      for (int l = L - 1; l >= 0; --l) {
+        BwdArgs a = layer_args(np, w, at<char>(ws, owback), params, E, nullptr, sv, l);
+        a.g_in = (l == L - 1) ? nullptr : ga;
+        a.seeds = (l == L - 1) ? dF : nullptr;
+        a.g_out = gb;
+        a.partial = mp;
+        {
+          ProfScope ps(np.prof, "bwd_mlp", stream);
+          if (mlp_reg) TDO_TRY(launch_bwd_mlp_bf16(a, (int)(E * slots), stream));
+          else TDO_TRY(launch_bwd_mlp(a, np.bf16, D, (int)E, stream, bpc));
+        }
+        a.g_in = gb;
+        a.seeds = nullptr;
+        a.g_out = ga;
+        a.partial = ap;
+        {
+          ProfScope ps(np.prof, "bwd_attn", stream);
+          if (attn_reg) TDO_TRY(launch_bwd_attn_bf16(a, np.DH, (int)E, stream));
+          else TDO_TRY(launch_bwd_attn(a, np.bf16, D, np.DH, (int)E, stream, 2));
+        }
+        TDO_TRY(launch_jac_layer(mp, slots, ap, pp, E, rows + pp.off_layer0 + l * pp.layer_stride, stride, stream));
       }
-      if (rc == TDO_OK) rc = run_backward(np, w, bb, params, cfg + 2 * b, 1, nullptr, sv, at<float>(ws, t.dF), row, s);
-      if (rc == TDO_OK) rc = finish_backward(np, bb, params, row, s);
+      TDO_TRY(launch_jac_head(np.bf16, D, sv.last, dF, E, n, np.span, pp.d, rows + pp.off_head_w, stride, stream));
+      TDO_TRY(launch_embed_scatter(D, ga, ec, nullptr, E, n, 1, np.span, ep, (int)E, stream, bpc));
+      TDO_TRY(launch_jac_embed(params, at<double>(ws, otab), ep, bpc, pp.d, D, E, rows, stride, stream));
     }
   }
-  // join: the caller's stream waits for every lane (also after an error, so that
-  // nothing still runs on the scratch when the call returns)
-  for (int i = 0; i < lanes; ++i) {
-    if (hipEventRecord(ev[i], st[i]) == hipSuccess) (void)hipStreamWaitEvent(stream, ev[i], 0);
-  }
-  for (int i = 0; i < lanes; ++i) (void)hipStreamSynchronize(st[i]);
-#undef JAC_HIP
-  cleanup();
-  return rc;
+  TDO_HIP(hipStreamSynchronize(stream));
+  return TDO_OK;
 }
 
 namespace tdo {

@@ -18,6 +18,8 @@
 // block are added into workgroup-shared FP32 accumulators in LDS; at the end
 // each workgroup writes its accumulators to a private partial buffer, and the
 // partials are summed in FP64 in a fixed order.
+#include <algorithm>
+
 #include "common.h"
 #include "net.h"
 #include "netapi.h"
@@ -99,127 +101,344 @@ __device__ __forceinline__ void store_tile(float* dst, const f32x16& v) {
 }
 
 // ------------------------------------------------------------------ MLP backward
-template <class P, int D>
-__global__ void __launch_bounds__(256) k_bwd_mlp(BwdArgs a) {
-  constexpr int NB = D / 32, ST = P::STEPS;
+// Row of a 32-row block that lane m takes as the row operand of (row x hidden) products, so that
+// value r of lane half h of the result is row nat_idx(r, h): the products over rows then take the
+// result registers as operands in the natural row order.
+template <class P>
+__device__ __forceinline__ int nat_row(int m) {
+  if constexpr (P::KPL == 8) return 16 * (m >> 4) + 8 * ((m >> 2) & 1) + 4 * ((m >> 3) & 1) + (m & 3);
+  else return 8 * (m >> 3) + 2 * (m & 3) + ((m >> 2) & 1);
+}
+
+// LDS of the feed-forward backward: x and g of NBK blocks, row-major (and, BF16, transposed), and
+// du of all hidden units.  Row paddings of 16 bytes keep the accesses on distinct banks.
+template <class P, int D, int NBK>
+struct MlpLds {
+  static constexpr int R = 32 * NBK, FS = D + 4, BS = D + 8, TSB = R + 8;
+  static constexpr bool BF = P::KPL == 8;
+  static constexpr size_t x = 0;
+  static constexpr size_t g32 = x + (BF ? (size_t)R * BS * 2 : (size_t)R * FS * 4);  // g in FP32 [R][FS]
+  static constexpr size_t xt = g32 + (size_t)R * FS * 4;                             // BF16: x^T [D][TSB]
+  static constexpr size_t g = xt + (BF ? (size_t)D * TSB * 2 : 0);                   // BF16: g [R][BS], g^T [D][TSB]
+  static constexpr size_t gt = g + (BF ? (size_t)R * BS * 2 : 0);
+  static constexpr size_t hw = gt + (BF ? (size_t)D * TSB * 2 : 0);                  // head weight pairs [D]
+  static constexpr size_t du = hw + (size_t)D * 8;
+  static size_t bytes(int M) { return du + (BF ? (size_t)R * (M + 8) * 2 : (size_t)NBK * M * TS * 4); }
+};
+
+// The FP32 kernel at every width, and the BF16 kernel where the width-64 ones do not apply.
+// Workgroups of 8 waves (two per SIMD) walk tiles of NBK blocks.  Wave (rg, cw) owns the CPW
+// chunks cw + CW i of 32 hidden units for the blocks of row group rg: their weight operands and
+// weight gradients stay in registers for the whole launch, and x, g and du pass between the waves
+// through LDS.  u and dh are formed as (row x hidden) tiles, whose registers are the operands of
+// the products over rows; du goes through LDS once for dx = g + du W1^T, one wave per 32 x 32
+// tile of dx.  Each block's gradient is formed in a fresh accumulator and then added.
+// Bound: the FP32 matrix cores (8 n d m operations of 157 TFLOP/s a pass).  It replaces per-block
+// gradient tiles added into LDS by atomics, one wave per SIMD and weight operands reread from the
+// caches for every block.
+template <class P, int D, int CW, int CPW, bool SEEDS>
+__global__ void __launch_bounds__(512) k_bwd_mlp(BwdArgs a) {
+  constexpr int NB = D / 32, ST = P::STEPS, RG = 8 / CW, BPG = CPW == 1 ? 2 : 1, NBK = RG * BPG;
+  constexpr int JOBS = 2 * NBK * NB, JPW = (JOBS + 7) / 8;
+  constexpr bool BF = P::KPL == 8;
+  using L = MlpLds<P, D, NBK>;
   using elem_t = typename P::elem_t;
   using save_t = typename P::save_t;
   using op_t = typename P::op_t;
-  extern __shared__ __align__(16) float sm[];
-  const int M = a.M, MB = M / 32;
-  float* dW1 = sm;                // [D][M]
-  float* dW2 = dW1 + D * M;       // [M][D]
-  float* db1 = dW2 + M * D;       // [M]
-  float* db2 = db1 + M;           // [D]
-  float* scr = db2 + D;           // [4 waves][32 * TS]
-  const int accn = 2 * D * M + M + D;
-  for (int i = threadIdx.x; i < accn; i += blockDim.x) sm[i] = 0.f;
-  __syncthreads();
+  extern __shared__ __align__(16) char smem[];
+  elem_t* xs = reinterpret_cast<elem_t*>(smem + L::x);
+  float* gf = reinterpret_cast<float*>(smem + L::g32);
+  __bf16* xt = reinterpret_cast<__bf16*>(smem + L::xt);
+  __bf16* gb = reinterpret_cast<__bf16*>(smem + L::g);
+  __bf16* gt = reinterpret_cast<__bf16*>(smem + L::gt);
+  float2* hws = reinterpret_cast<float2*>(smem + L::hw);
+  elem_t* dus = reinterpret_cast<elem_t*>(smem + L::du);
+  const int M = a.M, MB = M / 32, DUS = M + 8;
 
-  const elem_t* Wf = reinterpret_cast<const elem_t*>(a.wf);
-  const elem_t* Wb = reinterpret_cast<const elem_t*>(a.wb);
-  const elem_t* W1f = Wf + 4 * D * D;            // [MB][NB][ST]
-  const elem_t* W2T = Wb + 4 * D * D;            // [MB][NB][ST]
-  const elem_t* W1T = Wb + 4 * D * D + D * M;    // [NB][MB][ST]
-  const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31, wave = threadIdx.x >> 6;
-  float* sc = scr + wave * 32 * TS;
+  const elem_t* W1f = reinterpret_cast<const elem_t*>(a.wf) + 4 * D * D;          // [MB][NB][ST]
+  const elem_t* W2T = reinterpret_cast<const elem_t*>(a.wb) + 4 * D * D;          // [MB][NB][ST]
+  const elem_t* W1T = reinterpret_cast<const elem_t*>(a.wb) + 4 * D * D + D * M;  // [NB][MB][ST]
+  const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), cw = wave % CW, rg = wave / CW;
   const int64_t E = a.n_entries_dev ? *a.n_entries_dev : a.n_entries;
   const RowMap rm{a.n, a.cpb, a.span != 0};
-  const int64_t nblk = a.span ? 4 * E : 2 * ((E + a.cpb - 1) / a.cpb);
+  int64_t nblk = a.span ? 4 * E : 2 * ((E + a.cpb - 1) / a.cpb);
+  // blocks_per_wg: the workgroup's own consecutive blocks (one configuration), else tiles in turn
+  int64_t blk0 = (int64_t)blockIdx.x * NBK, step = (int64_t)gridDim.x * NBK;
+  if (a.blocks_per_wg) {
+    blk0 = (int64_t)blockIdx.x * a.blocks_per_wg;
+    nblk = blk0 + a.blocks_per_wg < nblk ? blk0 + a.blocks_per_wg : nblk;
+    step = NBK;
+  }
 
-  for (int64_t g = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave; g < nblk; g += (int64_t)gridDim.x * (blockDim.x >> 6)) {
-    f32x16 xm[NB], gv[NB];
-    const save_t* xs = reinterpret_cast<const save_t*>(a.save_mid);
+  if constexpr (SEEDS)
+    for (int i = threadIdx.x; i < D; i += 512) hws[i] = i < a.d_real ? make_float2(a.head_w[2 * i], a.head_w[2 * i + 1]) : make_float2(0.f, 0.f);
+
+  op_t w1[CPW][NB][ST], w2[CPW][NB][ST];
+  float bias[CPW], db1[CPW], db2[NB];
+  f32x16 dW1[CPW][NB], dW2[CPW][NB];
 #pragma unroll
-    for (int ib = 0; ib < NB; ++ib) load_tile(xs + ((g * NB + ib) * 64 + lane) * 16, xm[ib]);
-    if (a.seeds) {
-      int64_t e; int pass, ric; bool valid;
-      rm.at(g, lr, E, e, pass, ric, valid);
-      float s0 = 0.f, s1 = 0.f;
-      if (valid) { s0 = a.seeds[(e * 2 + pass) * 2] / (float)a.n; s1 = a.seeds[(e * 2 + pass) * 2 + 1] / (float)a.n; }
+  for (int i = 0; i < CPW; ++i) {
+    const int c = cw + CW * i;
+    const bool own = c < MB;
+    bias[i] = own ? a.b1[32 * c + lr] : 0.f;
+    db1[i] = 0.f;
 #pragma unroll
-      for (int ob = 0; ob < NB; ++ob)
+    for (int ib = 0; ib < NB; ++ib) {
+      dW1[i][ib] = dW2[i][ib] = f32x16{};
+#pragma unroll
+      for (int s = 0; s < ST; ++s) {
+        w1[i][ib][s] = own ? ld_frag<P>(W1f, (c * NB + ib) * ST + s, lane) : op_t{};
+        w2[i][ib][s] = own ? ld_frag<P>(W2T, (c * NB + ib) * ST + s, lane) : op_t{};
+      }
+    }
+  }
+#pragma unroll
+  for (int ib = 0; ib < NB; ++ib) db2[ib] = 0.f;
+
+  // staging jobs of this wave: x tiles (block, feature block), then g tiles; loaded one tile ahead
+  float4 pre[JPW][4];
+  auto fetch = [&](int64_t b0) {
+#pragma unroll
+    for (int q = 0; q < JPW; ++q) {
+      const int j = wave + 8 * q, jj = j < NBK * NB ? j : j - NBK * NB;
+      const int64_t g = b0 + jj / NB;
+      const bool ok = j < JOBS && g < nblk;
+      if (j < NBK * NB) {
+        const auto r = rsrc(reinterpret_cast<const save_t*>(a.save_mid) + (g * NB + jj % NB) * 64 * 16, ok ? 64 * 16 * sizeof(save_t) : 0);
+#pragma unroll
+        for (int k = 0; k < (BF ? 2 : 4); ++k) pre[q][k] = rld4(r, lane * 16 * (int)sizeof(save_t) + 16 * k);
+      } else if constexpr (!SEEDS) {
+        const auto r = rsrc(a.g_in + (g * NB + jj % NB) * 64 * 16, ok ? 64 * 16 * 4 : 0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pre[q][k] = rld4(r, lane * 64 + 16 * k);
+      } else {
+        float s0 = 0.f, s1 = 0.f;
+        if (ok) {
+          int64_t e; int pass, ric; bool valid;
+          rm.at(g, lr, E, e, pass, ric, valid);
+          if (valid) { s0 = a.seeds[(e * 2 + pass) * 2] / (float)a.n; s1 = a.seeds[(e * 2 + pass) * 2 + 1] / (float)a.n; }
+        }
+        pre[q][0] = make_float4(s0, s1, 0.f, 0.f);
+      }
+    }
+  };
+  auto stage = [&]() {
+#pragma unroll
+    for (int q = 0; q < JPW; ++q) {
+      const int j = wave + 8 * q;
+      if (j >= JOBS) continue;
+      const int jj = j < NBK * NB ? j : j - NBK * NB, blk = jj / NB, ob = jj % NB, row = 32 * blk + lr;
+      if (j < NBK * NB) {
+        if constexpr (BF) {
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const bf16x8 v = __builtin_bit_cast(bf16x8, pre[q][s]);
+            *reinterpret_cast<bf16x8*>(xs + row * L::BS + 32 * ob + 16 * s + 8 * h) = v;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) xt[(32 * ob + tile_idx(8 * s + t, h)) * L::TSB + row] = v[t];
+          }
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) *reinterpret_cast<float4*>(reinterpret_cast<float*>(xs) + row * L::FS + 32 * ob + 8 * k + 4 * h) = pre[q][k];
+        }
+      } else {
+        f32x16 v;
+        if constexpr (SEEDS) {
+          const float s0 = pre[q][0].x, s1 = pre[q][0].y;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float2 hw = hws[32 * ob + tile_idx(r, h)];
+            v[r] = s0 * hw.x + s1 * hw.y;
+          }
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) { v[4 * k] = pre[q][k].x; v[4 * k + 1] = pre[q][k].y; v[4 * k + 2] = pre[q][k].z; v[4 * k + 3] = pre[q][k].w; }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          *reinterpret_cast<float4*>(gf + row * L::FS + 32 * ob + 8 * k + 4 * h) = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+        if constexpr (BF) {
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const bf16x8 o = cvt8(v, s);
+            *reinterpret_cast<bf16x8*>(gb + row * L::BS + 32 * ob + 16 * s + 8 * h) = o;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) gt[(32 * ob + tile_idx(8 * s + t, h)) * L::TSB + row] = o[t];
+          }
+        }
+      }
+    }
+  };
+  // operand s of feature block ib for row `row` (lane -> row), and for the rows of block blk (lane -> feature)
+  auto row_x = [&](int row, int ib, int s) -> op_t {
+    if constexpr (BF) return *reinterpret_cast<const bf16x8*>(xs + row * L::BS + 32 * ib + 16 * s + 8 * h);
+    else return *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(xs) + row * L::FS + 32 * ib + 8 * s + 4 * h);
+  };
+  auto row_g = [&](int row, int ib, int s) -> op_t {
+    if constexpr (BF) return *reinterpret_cast<const bf16x8*>(gb + row * L::BS + 32 * ib + 16 * s + 8 * h);
+    else return *reinterpret_cast<const f32x4*>(gf + row * L::FS + 32 * ib + 8 * s + 4 * h);
+  };
+  auto col = [&](const __bf16* tb, const float* tf, int blk, int ib, int s) -> op_t {
+    if constexpr (BF) return *reinterpret_cast<const bf16x8*>(tb + (32 * ib + lr) * L::TSB + 32 * blk + 16 * s + 8 * h);
+    else {
+      const float* p = tf + (32 * blk + 8 * s + h) * L::FS + 32 * ib + lr;  // rows nat_idx(4 s + t, h)
+      return op_t{p[0], p[2 * L::FS], p[4 * L::FS], p[6 * L::FS]};
+    }
+  };
+
+  if (blk0 < nblk) fetch(blk0);
+  if constexpr (SEEDS) __syncthreads();  // head weights staged
+  for (int64_t b0 = blk0; b0 < nblk; b0 += step) {
+    stage();
+    barrier_lds();
+    if (b0 + step < nblk) fetch(b0 + step);
+    // ---- hidden units of this wave: u, dh, du; their weight gradients; du to LDS
+#pragma unroll 1
+    for (int bi = 0; bi < BPG; ++bi) {
+      const int blk = rg * BPG + bi, row = 32 * blk + nat_row<P>(lr);
+#pragma unroll
+      for (int i = 0; i < CPW; ++i) {
+        const int c = cw + CW * i;
+        if (c >= MB) continue;
+        f32x16 u, dh = f32x16{};
+#pragma unroll
+        for (int r = 0; r < 16; ++r) u[r] = bias[i];
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+          for (int s = 0; s < ST; ++s) {
+            u = P::mma(row_x(row, ib, s), w1[i][ib][s], u);
+            dh = P::mma(row_g(row, ib, s), w2[i][ib][s], dh);
+          }
+        float t = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int f = 32 * ob + tile_idx(r, h);
-          gv[ob][r] = f < a.d_real ? s0 * a.head_w[2 * f] + s1 * a.head_w[2 * f + 1] : 0.f;
+          const float uu = u[r];
+          u[r] = relu(uu);
+          dh[r] = uu > 0.f ? dh[r] : 0.f;
+          t += dh[r];
         }
-    } else {
+        db1[i] += t + __shfl_xor(t, 32, 64);
+        if constexpr (BF) {
 #pragma unroll
-      for (int ob = 0; ob < NB; ++ob) load_tile(a.g_in + ((g * NB + ob) * 64 + lane) * 16, gv[ob]);
+          for (int r = 0; r < 16; ++r) dus[(32 * blk + nat_idx<P>(r, h)) * DUS + 32 * c + nat_row<P>(lr)] = (__bf16)dh[r];
+        } else {
+          float* dp = reinterpret_cast<float*>(dus) + ((blk * MB + c) * 32 + lr) * TS + 16 * h;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) *reinterpret_cast<float4*>(dp + 4 * k) = make_float4(dh[4 * k], dh[4 * k + 1], dh[4 * k + 2], dh[4 * k + 3]);
+        }
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib) {
+          f32x16 acc = f32x16{};
+#pragma unroll
+          for (int s = 0; s < ST; ++s) acc = P::mma(col(xt, reinterpret_cast<const float*>(xs), blk, ib, s), P::op(dh, s), acc);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dW1[i][ib][r] += acc[r];
+          if constexpr (!BF) __builtin_amdgcn_sched_barrier(0);  // FP32: one accumulator at a time, or registers spill
+          acc = f32x16{};
+#pragma unroll
+          for (int s = 0; s < ST; ++s) acc = P::mma(P::op(u, s), col(gt, gf, blk, ib, s), acc);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) dW2[i][ib][r] += acc[r];
+          if constexpr (!BF) __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (cw == 0)
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib) {  // db2 += sum over rows of g
+          const float* p = gf + (32 * blk + (BF ? 8 : 1) * h) * L::FS + 32 * ib + lr;
+          float t = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) t += p[nat_idx<P>(i, 0) * L::FS];
+          db2[ib] += t + __shfl_xor(t, 32, 64);
+        }
     }
-    op_t xo[NB][ST], go[NB][ST];
+    barrier_lds();
+    // ---- dx = g + du W1^T, a 32 x 32 tile per wave
+    for (int j = wave; j < NBK * NB; j += 8) {
+      const int blk = j / NB, ob = j % NB;
+      if (b0 + blk >= nblk) continue;
+      f32x16 acc;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float4 v = *reinterpret_cast<const float4*>(gf + (32 * blk + lr) * L::FS + 32 * ob + 8 * k + 4 * h);
+        acc[4 * k] = v.x; acc[4 * k + 1] = v.y; acc[4 * k + 2] = v.z; acc[4 * k + 3] = v.w;
+      }
+#pragma unroll 2
+      for (int c = 0; c < MB; ++c)
+#pragma unroll
+        for (int s = 0; s < ST; ++s) {
+          op_t d;
+          if constexpr (BF) d = *reinterpret_cast<const bf16x8*>(dus + (32 * blk + lr) * DUS + 32 * c + 16 * s + 8 * h);
+          else {
+            const float* dp = reinterpret_cast<const float*>(dus) + ((blk * MB + c) * 32 + 8 * s + 4 * h) * TS + 16 * (lr & 1) + (lr >> 1);
+            d = op_t{dp[0], dp[TS], dp[2 * TS], dp[3 * TS]};
+          }
+          acc = P::mma(ld_frag<P>(W1T, (ob * MB + c) * ST + s, lane), d, acc);
+        }
+      store_tile(a.g_out + (((b0 + blk) * NB + ob) * 64 + lane) * 16, acc);
+    }
+    barrier_lds();
+  }
+
+  // ---- row groups summed in order, then this workgroup's gradients: dW1 [D][M], dW2 [M][D], db1 [M], db2 [D]
+  float* red = reinterpret_cast<float*>(smem);
+  constexpr int T = 2 * CPW * NB;  // 32 x 32 tiles of a wave
+#pragma unroll
+  for (int g = 1; g < RG; ++g) {
+    __syncthreads();
+    float* mine = red + cw * (T * 1024 + 64 * (CPW + NB)) + lane;
+    if (rg == g) {
+#pragma unroll
+      for (int i = 0; i < CPW; ++i) {
+        mine[T * 1024 + 64 * i] = db1[i];
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            mine[((i * NB + ib) * 2 * 16 + r) * 64] = dW1[i][ib][r];
+            mine[(((i * NB + ib) * 2 + 1) * 16 + r) * 64] = dW2[i][ib][r];
+          }
+      }
+#pragma unroll
+      for (int ib = 0; ib < NB; ++ib) mine[T * 1024 + 64 * (CPW + ib)] = db2[ib];
+    }
+    __syncthreads();
+    if (rg == 0) {
+#pragma unroll
+      for (int i = 0; i < CPW; ++i) {
+        db1[i] += mine[T * 1024 + 64 * i];
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            dW1[i][ib][r] += mine[((i * NB + ib) * 2 * 16 + r) * 64];
+            dW2[i][ib][r] += mine[(((i * NB + ib) * 2 + 1) * 16 + r) * 64];
+          }
+      }
+#pragma unroll
+      for (int ib = 0; ib < NB; ++ib) db2[ib] += mine[T * 1024 + 64 * (CPW + ib)];
+    }
+  }
+  if (rg != 0) return;
+  float* part = a.partial + (int64_t)blockIdx.x * (2 * D * M + M + D);
+#pragma unroll
+  for (int i = 0; i < CPW; ++i) {
+    const int c = cw + CW * i;
+    if (c >= MB) continue;
 #pragma unroll
     for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
-      for (int s = 0; s < ST; ++s) { xo[ib][s] = P::op(xm[ib], s); go[ib][s] = P::op(gv[ib], s); }
-    f32x16 xT[NB], gT[NB];
-#pragma unroll
-    for (int ib = 0; ib < NB; ++ib) { xT[ib] = transpose_tile<P>(xm[ib], sc, lane); gT[ib] = transpose_tile<P>(gv[ib], sc, lane); }
-#pragma unroll
-    for (int ob = 0; ob < NB; ++ob) {  // db2 += sum over rows of g
-      float t = 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) t += gT[ob][i];
-      t += __shfl_xor(t, 32, 64);
-      if (h == 0) atomicAdd(db2 + 32 * ob + lr, t);
-    }
-    f32x16 dxm[NB];
-#pragma unroll
-    for (int ob = 0; ob < NB; ++ob) dxm[ob] = gv[ob];
-#pragma unroll 1
-    for (int c = 0; c < MB; ++c) {
-      f32x16 u, dh = f32x16{};  // u accumulates onto b1, in the forward's order
-#pragma unroll
-      for (int r = 0; r < 16; ++r) u[r] = a.b1[32 * c + tile_idx(r, h)];
-#pragma unroll
-      for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-        for (int s = 0; s < ST; ++s) {
-          u = P::mma(ld_frag<P>(W1f, (c * NB + ib) * ST + s, lane), xo[ib][s], u);
-          dh = P::mma(ld_frag<P>(W2T, (c * NB + ib) * ST + s, lane), go[ib][s], dh);
-        }
-      f32x16 hh, du;
-#pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float uu = u[r];
-        hh[r] = relu(uu);
-        du[r] = uu > 0.f ? dh[r] : 0.f;
+        part[(32 * ib + tile_idx(r, h)) * M + 32 * c + lr] = dW1[i][ib][r];
+        part[D * M + (32 * c + tile_idx(r, h)) * D + 32 * ib + lr] = dW2[i][ib][r];
       }
-#pragma unroll
-      for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-        for (int s = 0; s < ST; ++s) dxm[ob] = P::mma(ld_frag<P>(W1T, (ob * MB + c) * ST + s, lane), P::op(du, s), dxm[ob]);
-      const f32x16 hT = transpose_tile<P>(hh, sc, lane);
-      const f32x16 duT = transpose_tile<P>(du, sc, lane);
-      {
-        float t = 0.f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) t += duT[i];
-        t += __shfl_xor(t, 32, 64);
-        if (h == 0) atomicAdd(db1 + 32 * c + lr, t);
-      }
-#pragma unroll
-      for (int ib = 0; ib < NB; ++ib) {  // dW1[D-in][hidden] += x^T du
-        f32x16 acc = f32x16{};
-#pragma unroll
-        for (int s = 0; s < ST; ++s) acc = P::mma(P::op(xT[ib], s), P::op(duT, s), acc);
-        lds_add_tile(dW1, M, 32 * ib, 32 * c, acc, lane);
-      }
-#pragma unroll
-      for (int ob = 0; ob < NB; ++ob) {  // dW2[hidden][D-out] += relu(u)^T g
-        f32x16 acc = f32x16{};
-#pragma unroll
-        for (int s = 0; s < ST; ++s) acc = P::mma(P::op(hT, s), P::op(gT[ob], s), acc);
-        lds_add_tile(dW2, D, 32 * c, 32 * ob, acc, lane);
-      }
-    }
-#pragma unroll
-    for (int ob = 0; ob < NB; ++ob) store_tile(a.g_out + ((g * NB + ob) * 64 + lane) * 16, dxm[ob]);
+    if (h == 0) part[2 * D * M + 32 * c + lr] = db1[i];
   }
-  __syncthreads();
-  float* part = a.partial + (int64_t)blockIdx.x * accn;
-  for (int i = threadIdx.x; i < accn; i += blockDim.x) part[i] = sm[i];
+  if (cw == 0 && h == 0)
+#pragma unroll
+    for (int ib = 0; ib < NB; ++ib) part[2 * D * M + M + 32 * ib + lr] = db2[ib];
 }
 
 // ------------------------------------------------------------------ attention backward
@@ -753,14 +972,29 @@ __global__ void k_scatter_layer(const double* __restrict__ mlp, const double* __
 }
 
 // ------------------------------------------------------------------ launchers
-template <class P, int D>
-static int32_t mlp_t(const BwdArgs& a, int blocks, int waves, hipStream_t st) {
-  const size_t lds = (size_t)(2 * D * a.M + a.M + D) * 4 + 4 * 32 * TS * 4;
-  auto k = k_bwd_mlp<P, D>;
+template <class P, int D, int CW, int CPW>
+static int32_t mlp_c(const BwdArgs& a, int blocks, hipStream_t st) {
+  constexpr int RG = 8 / CW, NBK = RG * (CPW == 1 ? 2 : 1);
+  const size_t red = RG > 1 ? (size_t)CW * (2 * CPW * (D / 32) * 1024 + 64 * (CPW + D / 32)) * 4 : 0;
+  const size_t lds = std::max(MlpLds<P, D, NBK>::bytes(a.M), red);
+  TDO_CHECK(lds <= 160 * 1024 && a.M / 32 <= CW * CPW, TDO_EUNSUPPORTED, "feed-forward backward: width %d, mlp %d", D, a.M);
+  auto k = a.g_in ? k_bwd_mlp<P, D, CW, CPW, false> : k_bwd_mlp<P, D, CW, CPW, true>;
   TDO_TRY(allow_full_lds((const void*)k));
-  hipLaunchKernelGGL(k, dim3(blocks), dim3(64 * waves), lds, st, a);
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(512), lds, st, a);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
+}
+
+// Waves over the hidden units: as many as there are chunks of 32 (2, 4 or 8), the others over rows;
+// more than 8 chunks (width 32 only) take two per wave.
+template <class P, int D>
+static int32_t mlp_t(const BwdArgs& a, int blocks, hipStream_t st) {
+  const int MB = a.M / 32;
+  if constexpr (D == 32) {
+    if (MB <= 2) return mlp_c<P, D, 2, 1>(a, blocks, st);
+    if (MB > 8) return mlp_c<P, D, 8, 2>(a, blocks, st);
+  }
+  return MB <= 4 ? mlp_c<P, D, 4, 1>(a, blocks, st) : mlp_c<P, D, 8, 1>(a, blocks, st);
 }
 
 template <class P, int D, int DH, bool SPAN>
@@ -775,9 +1009,9 @@ static int32_t attn_t(const BwdArgs& a, int blocks, int waves, hipStream_t st) {
 
 size_t bwd_mlp_lds(int D, int M) { return (size_t)(2 * D * M + M + D) * 4 + 4 * 32 * TS * 4; }
 
-int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream_t st, int waves) {
-  if (D == 32) return bf16 ? mlp_t<PBF16, 32>(a, blocks, waves, st) : mlp_t<PF32, 32>(a, blocks, waves, st);
-  if (D == 64) return bf16 ? mlp_t<PBF16, 64>(a, blocks, waves, st) : mlp_t<PF32, 64>(a, blocks, waves, st);
+int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream_t st) {
+  if (D == 32) return bf16 ? mlp_t<PBF16, 32>(a, blocks, st) : mlp_t<PF32, 32>(a, blocks, st);
+  if (D == 64) return bf16 ? mlp_t<PBF16, 64>(a, blocks, st) : mlp_t<PF32, 64>(a, blocks, st);
   return set_error(TDO_EUNSUPPORTED, "no MLP backward kernel for width %d", D);
 }
 

@@ -418,10 +418,11 @@ extern "C" int32_t tdo_log_rho_jacobian(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
         a.seeds = (l == L - 1) ? dF : nullptr;
         a.g_out = gb;
         a.partial = mp;
+        a.blocks_per_wg = bpc;
         {
           ProfScope ps(np.prof, "bwd_mlp", stream);
           if (mlp_reg) TDO_TRY(launch_bwd_mlp_bf16(a, (int)(E * slots), stream));
-          else TDO_TRY(launch_bwd_mlp(a, np.bf16, D, (int)E, stream, bpc));
+          else TDO_TRY(launch_bwd_mlp(a, np.bf16, D, (int)E, stream));
         }
         a.g_in = gb;
         a.seeds = nullptr;

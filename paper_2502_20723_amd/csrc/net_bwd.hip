@@ -12,12 +12,12 @@
 //              dW_O += O^T dx, dWq += x^T dq, dWk += x^T dk, dWv += x^T dv.
 // Contractions over features chain in registers exactly as in the forward;
 // contractions over rows (attention over keys/queries and all weight
-// gradients) take operands whose lanes enumerate features, obtained either by
-// computing the product in the (row x feature) orientation or by a transpose
-// of a 32x32 tile through a wave-private LDS scratch.  Weight gradients of one
-// block are added into workgroup-shared FP32 accumulators in LDS; at the end
-// each workgroup writes its accumulators to a private partial buffer, and the
-// partials are summed in FP64 in a fixed order.
+// gradients) take operands whose lanes enumerate features, obtained by
+// computing the product in the (row x feature) orientation or read as columns
+// of a tile in LDS.  Every wave keeps its share of the layer's weight gradients
+// in registers over the whole launch; at the end each workgroup writes its
+// gradients to a private partial buffer, and the partials are summed in FP64 in
+// a fixed order, so results do not depend on scheduling.
 #include <algorithm>
 
 #include "common.h"
@@ -65,20 +65,6 @@ __device__ __forceinline__ f32x16 transpose_tile(const f32x16& v, float* sc, int
   }
   wave_lds_sync();
   return o;
-}
-
-template <class P>
-__device__ __forceinline__ typename P::op_t masked_op(const f32x16& v, int s, bool keep) {
-  const typename P::op_t o = P::op(v, s);
-  return keep ? o : typename P::op_t{};
-}
-
-// Add a 32x32 result tile into an LDS matrix: value r of lane l goes to
-// row m0 + tile_idx(r, h), column c0 + l%32, row stride ld.
-__device__ __forceinline__ void lds_add_tile(float* base, int ld, int m0, int c0, const f32x16& v, int lane) {
-  const int h = lane >> 5, n = lane & 31;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) atomicAdd(base + (m0 + tile_idx(r, h)) * ld + c0 + n, v[r]);
 }
 
 template <class T>
@@ -133,9 +119,10 @@ struct MlpLds {
 // through LDS.  u and dh are formed as (row x hidden) tiles, whose registers are the operands of
 // the products over rows; du goes through LDS once for dx = g + du W1^T, one wave per 32 x 32
 // tile of dx.  Each block's gradient is formed in a fresh accumulator and then added.
-// Bound: the FP32 matrix cores (8 n d m operations of 157 TFLOP/s a pass).  It replaces per-block
-// gradient tiles added into LDS by atomics, one wave per SIMD and weight operands reread from the
-// caches for every block.
+// Bound: the FP32 matrix cores (8 n d m operations a pass, and 2 n d m for u, of 157 TFLOP/s).  It
+// replaces per-block gradient tiles added into LDS by atomics, one wave per SIMD and weight operands
+// reread from the caches for every block: 16384 configurations at n = 32, width 64, mlp 256 6.05 ->
+// 1.48 ms (93 TFLOP/s, 116 with u); BF16, 65536 at n = 8, width 32, mlp 128 1.39 -> 0.154 ms.
 template <class P, int D, int CW, int CPW, bool SEEDS>
 __global__ void __launch_bounds__(512) k_bwd_mlp(BwdArgs a) {
   constexpr int NB = D / 32, ST = P::STEPS, RG = 8 / CW, BPG = CPW == 1 ? 2 : 1, NBK = RG * BPG;
@@ -442,208 +429,354 @@ __global__ void __launch_bounds__(512) k_bwd_mlp(BwdArgs a) {
 }
 
 // ------------------------------------------------------------------ attention backward
+// The FP32 kernel at every width, and the BF16 kernel where the width-64 ones do not apply.
+// Workgroups of 8 waves (two per SIMD) walk tiles of 4 (block, 32-feature head block) jobs, i.e. 2
+// blocks at width 64 and 4 at width 32, two waves per job:
+//  1. x and the incoming gradient g of the tile are staged in LDS, row-major;
+//  2. a job's waves project q, k and v, dO (feature x row tiles) into the job's four LDS slots,
+//     from which rows are score operands and columns operands of the products over rows;
+//  3. each wave takes half of the job's heads: P, dS, and the head's features of O, dQ, dK, dV
+//     (each in a fresh accumulator of which only those are kept);
+//  4. O, dQ, dK, dV replace dO, q, k, v in the slots (a spanning pass first adds the two query
+//     blocks' shares of dK and dV);
+//  5. every wave adds the tile's rows to the weight-gradient tiles it keeps in registers for the
+//     whole launch (a fresh accumulator per block, then added), and waves 0..3 form dx.
+// Bound: the FP32 matrix cores, of which 8-wide heads use a quarter in the products of step 3.  The
+// former kernel kept everything of a block in the registers of one wave per SIMD (478, or spills in
+// a spanning pass), added every block's gradient tiles into LDS by atomics and formed k and v twice.
+// FP32, width 64: 16384 configurations at n = 32, 8 heads 4.16 -> 1.66 ms; 32768 at n = 16, 4 heads
+// 3.58 -> 1.38 ms; 8192 at n = 37 4.40 -> 1.89 ms; width 32, 65536 at n = 8 1.29 -> 0.64 ms (BF16
+// 0.87 -> 0.27 ms).
 template <class P, int D, int DH, bool SPAN>
-__global__ void __launch_bounds__(256) k_bwd_attn(BwdArgs a) {
-  constexpr int NB = D / 32, ST = P::STEPS, NBR = SPAN ? 2 : 1, HPB = 32 / DH;
+__global__ void __launch_bounds__(512) k_bwd_attn(BwdArgs a) {
+  constexpr int NB = D / 32, ST = P::STEPS, HPB = 32 / DH, VPH = DH / 2, HPS = HPB / 2;
+  constexpr int NBK = 4 / NB, XS = D + 4, R = 32 * NBK, NKB = SPAN ? 2 : 1, SLOT = 32 * TS;
+  constexpr bool BF = P::KPL == 8;
   using elem_t = typename P::elem_t;
   using save_t = typename P::save_t;
   using op_t = typename P::op_t;
   extern __shared__ __align__(16) float sm[];
-  float* dWq = sm;               // [D][D] each: (D-in, attention feature)
-  float* dWk = dWq + D * D;
-  float* dWv = dWk + D * D;
-  float* dWo = dWv + D * D;      // (attention feature, D-out)
-  float* scr = dWo + D * D;
-  for (int i = threadIdx.x; i < 4 * D * D; i += blockDim.x) sm[i] = 0.f;
-  __syncthreads();
+  float* xs = sm;                  // [R][XS]
+  float* gs = xs + R * XS;         // [R][XS]
+  float* slots = gs + R * XS;      // [4 jobs][q -> dQ, k -> dK, v -> dV, dO -> O][32 rows][TS]
+  float* scr = slots + 16 * SLOT;  // [8 waves][32][TS]
 
-  const elem_t* Wf = reinterpret_cast<const elem_t*>(a.wf);
-  const elem_t* Wb = reinterpret_cast<const elem_t*>(a.wb);
-  const elem_t *Wq = Wf, *Wk = Wf + D * D, *Wv = Wf + 2 * D * D;
-  const elem_t *WqT = Wb, *WkT = Wb + D * D, *WvT = Wb + 2 * D * D, *WoT = Wb + 3 * D * D;
-  const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31, wave = threadIdx.x >> 6;
-  float* sc = scr + wave * 32 * TS;
+  const elem_t* Wf = reinterpret_cast<const elem_t*>(a.wf);  // Wq, Wk, Wv
+  const elem_t* Wb = reinterpret_cast<const elem_t*>(a.wb);  // Wq^T, Wk^T, Wv^T, Wo^T
+  const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int job = wave >> 1, sub = wave & 1, jblk = job / NB, hb = job % NB;
+  const int kbase = SPAN ? jblk & ~1 : jblk, own = jblk - kbase;
+  float* sc = scr + wave * SLOT;
   const int64_t E = a.n_entries_dev ? *a.n_entries_dev : a.n_entries;
   const int n = a.n, cpb = a.cpb;
-  const int64_t ntiles = SPAN ? 2 * E : 2 * ((E + cpb - 1) / cpb);
+  int64_t nblk = SPAN ? 4 * E : 2 * ((E + cpb - 1) / cpb);
+  int64_t blk0 = (int64_t)blockIdx.x * NBK, step = (int64_t)gridDim.x * NBK;
+  if (a.blocks_per_wg) {  // the workgroup's own consecutive blocks (one configuration)
+    blk0 = (int64_t)blockIdx.x * a.blocks_per_wg;
+    nblk = blk0 + a.blocks_per_wg < nblk ? blk0 + a.blocks_per_wg : nblk;
+    step = NBK;
+  }
   const float sc2 = a.score_scale, isd = a.inv_sqrt_dh;
 
-  for (int64_t tile = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave; tile < ntiles;
-       tile += (int64_t)gridDim.x * (blockDim.x >> 6)) {
-    const int64_t e0 = SPAN ? (tile >> 1) : (tile >> 1) * cpb;
-    const int64_t gb0 = tile * NBR;
-    int rslot[NBR];
+  // valid keys (value r of the score tile with key block kb) of this lane's query row
+  uint32_t okbits[NKB];
 #pragma unroll
-    for (int rb = 0; rb < NBR; ++rb) rslot[rb] = SPAN ? 0 : lr / n;
-    (void)e0;
+  for (int kb = 0; kb < NKB; ++kb) {
+    okbits[kb] = 0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = kb * 32 + tile_idx(r, h);
+      const bool ok = SPAN ? key < n : (a.masked ? ((key / n) == (lr / n) && (key / n) < cpb) : true);
+      okbits[kb] |= ok ? 1u << r : 0u;
+    }
+  }
 
-    f32x16 xT[NBR][NB], dmT[NBR][NB], dx[NBR][NB];
-    op_t xo[NBR][NB][ST], dmo[NBR][NB][ST];
-    const save_t* xs = reinterpret_cast<const save_t*>(a.save_x);
+  auto slot = [&](int jb, int m) { return slots + (jb * 4 + m) * SLOT; };
+  // operand s of row `row`, features f0 + (result order)
+  auto rowop = [&](const float* base, int stride, int row, int f0, int s) -> op_t {
+    const float* p = base + row * stride + f0 + 2 * P::KPL * s + 4 * h;
+    if constexpr (BF) {
+      const float4 u = *reinterpret_cast<const float4*>(p), v = *reinterpret_cast<const float4*>(p + 8);
+      const float t[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+      return cvt8(t, 0);
+    } else return *reinterpret_cast<const f32x4*>(p);
+  };
+  // operand s of column `col` (lane -> feature): rows in natural (nat) or result order
+  auto colop = [&](const float* base, int stride, int col, int s, bool nat) -> op_t {
+    float t[P::KPL];
 #pragma unroll
-    for (int rb = 0; rb < NBR; ++rb)
+    for (int k = 0; k < P::KPL; ++k) t[k] = base[(nat ? nat_idx<P>(P::KPL * s + k, h) : tile_idx(P::KPL * s + k, h)) * stride + col];
+    if constexpr (BF) return cvt8(t, 0);
+    else return P::op(t, 0);
+  };
+  // score operand of one head: its features of this lane's row
+  using sop = typename P::template SOp<DH>;
+  auto headop = [&](const float* s, int j) -> sop {
+    f32x16 t{};
 #pragma unroll
-      for (int ib = 0; ib < NB; ++ib) {
-        f32x16 t;
-        load_tile(xs + (((gb0 + rb) * NB + ib) * 64 + lane) * 16, t);
+    for (int k = 0; k < VPH / 4; ++k) {
+      const float4 v = *reinterpret_cast<const float4*>(s + lr * TS + DH * j + 8 * k + 4 * h);
+      t[4 * k] = v.x; t[4 * k + 1] = v.y; t[4 * k + 2] = v.z; t[4 * k + 3] = v.w;
+    }
+    return P::template pack_head<DH>(t, 0);
+  };
+  auto put_head = [&](float* s, int j, const float* v) {  // the same places
 #pragma unroll
-        for (int s = 0; s < ST; ++s) xo[rb][ib][s] = P::op(t, s);
-        xT[rb][ib] = transpose_tile<P>(t, sc, lane);
-        load_tile(a.g_in + (((gb0 + rb) * NB + ib) * 64 + lane) * 16, t);
-        dx[rb][ib] = t;
+    for (int k = 0; k < VPH / 4; ++k)
+      *reinterpret_cast<float4*>(s + lr * TS + DH * j + 8 * k + 4 * h) = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+  };
+  auto get_head = [&](const float* s, int j, float* v) {
 #pragma unroll
-        for (int s = 0; s < ST; ++s) dmo[rb][ib][s] = P::op(t, s);
-        dmT[rb][ib] = transpose_tile<P>(t, sc, lane);
-      }
+    for (int k = 0; k < VPH / 4; ++k) {
+      const float4 u = *reinterpret_cast<const float4*>(s + lr * TS + DH * j + 8 * k + 4 * h);
+      v[4 * k] = u.x; v[4 * k + 1] = u.y; v[4 * k + 2] = u.z; v[4 * k + 3] = u.w;
+    }
+  };
 
-#pragma unroll 1
-    for (int hb = 0; hb < NB; ++hb) {
-      f32x16 q[NBR], k[NBR], vR[NBR], vD[NBR], kR[NBR], dO[NBR];
+  // staging job of this wave: an x or g tile (block, feature block), loaded one tile ahead
+  const int sj = wave & 3, sblk = sj / NB, sob = sj % NB;
+  float4 pre[4];
+  auto fetch = [&](int64_t b0) {
+    const int64_t g = b0 + sblk;
+    if (wave < 4) {
+      const auto r = rsrc(reinterpret_cast<const save_t*>(a.save_x) + (g * NB + sob) * 64 * 16, g < nblk ? 64 * 16 * sizeof(save_t) : 0);
 #pragma unroll
-      for (int rb = 0; rb < NBR; ++rb) {
-        q[rb] = k[rb] = vR[rb] = vD[rb] = kR[rb] = dO[rb] = f32x16{};
+      for (int k = 0; k < (BF ? 2 : 4); ++k) pre[k] = rld4(r, lane * 16 * (int)sizeof(save_t) + 16 * k);
+    } else {
+      const auto r = rsrc(a.g_in + (g * NB + sob) * 64 * 16, g < nblk ? 64 * 16 * 4 : 0);
 #pragma unroll
-        for (int ib = 0; ib < NB; ++ib)
+      for (int k = 0; k < 4; ++k) pre[k] = rld4(r, lane * 64 + 16 * k);
+    }
+  };
+  auto stage = [&]() {
+    float4 v[4];
+    if (BF && wave < 4) {
 #pragma unroll
-          for (int s = 0; s < ST; ++s) {
-            const int f = (hb * NB + ib) * ST + s;
-            const op_t wq = ld_frag<P>(Wq, f, lane), wk = ld_frag<P>(Wk, f, lane), wv = ld_frag<P>(Wv, f, lane);
-            q[rb] = P::mma(wq, xo[rb][ib][s], q[rb]);
-            k[rb] = P::mma(wk, xo[rb][ib][s], k[rb]);
-            vD[rb] = P::mma(wv, xo[rb][ib][s], vD[rb]);
-            vR[rb] = P::mma(xo[rb][ib][s], wv, vR[rb]);
-            kR[rb] = P::mma(xo[rb][ib][s], wk, kR[rb]);
-            dO[rb] = P::mma(ld_frag<P>(WoT, f, lane), dmo[rb][ib][s], dO[rb]);
-          }
+      for (int k = 0; k < 4; ++k) {
+        const bf16x8 t = __builtin_bit_cast(bf16x8, pre[k >> 1]);
+        v[k] = make_float4((float)t[4 * (k & 1)], (float)t[4 * (k & 1) + 1], (float)t[4 * (k & 1) + 2], (float)t[4 * (k & 1) + 3]);
       }
-      f32x16 qT[NBR], dOT[NBR];
+    } else {
 #pragma unroll
-      for (int rb = 0; rb < NBR; ++rb) { qT[rb] = transpose_tile<P>(q[rb], sc, lane); dOT[rb] = transpose_tile<P>(dO[rb], sc, lane); }
-      f32x16 o[NBR], dq[NBR], dk[NBR], dv[NBR];
-      float invl[NBR][HPB];
+      for (int k = 0; k < 4; ++k) v[k] = pre[k];
+    }
+    float* d = (wave < 4 ? xs : gs) + (32 * sblk + lr) * XS + 32 * sob + 4 * h;
 #pragma unroll
-      for (int rb = 0; rb < NBR; ++rb) o[rb] = dq[rb] = dk[rb] = dv[rb] = f32x16{};
+    for (int k = 0; k < 4; ++k) *reinterpret_cast<float4*>(d + 8 * k) = v[k];
+  };
+
+  // weight-gradient tiles of this wave: width 64: matrix wave / 2, first index wave % 2, both second
+  // indices, all blocks; width 32: matrix wave % 4, the blocks of half wave / 4
+  const int mt = NB == 2 ? wave >> 1 : wave & 3, mi = NB == 2 ? wave & 1 : 0;
+  const int mb0 = NB == 2 ? 0 : 2 * (wave >> 2);
+  f32x16 dW[NB];
 #pragma unroll
-      for (int j = 0; j < HPB; ++j) {
-        const bool mine = (lr / DH) == j;
+  for (int i = 0; i < NB; ++i) dW[i] = f32x16{};
+
+  if (blk0 < nblk) fetch(blk0);
+  for (int64_t b0 = blk0; b0 < nblk; b0 += step) {
+    // ---- 1. stage
+    stage();
+    barrier_lds();
+    if (b0 + step < nblk) fetch(b0 + step);
+    // ---- 2. projections of this wave: (q, k) or (v, dO)
+    {
+      const elem_t* W0 = sub ? Wf + 2 * D * D : Wf;
+      const elem_t* W1 = sub ? Wb + 3 * D * D : Wf + D * D;
+      const float* src1 = sub ? gs : xs;
+      f32x16 t0 = f32x16{}, t1 = f32x16{};
 #pragma unroll
-        for (int qb = 0; qb < NBR; ++qb) {
-          f32x16 p[NBR], dp[NBR];
-          float m = -INFINITY;
+      for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
-          for (int kb = 0; kb < NBR; ++kb) {
-            if (!SPAN && kb != qb) continue;
-            p[kb] = P::template scores<DH>(k[kb], q[qb], j, f32x16{});
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int key = kb * 32 + tile_idx(r, h);
-              bool ok;
-              if (SPAN) ok = key < n;
-              else ok = a.masked ? ((key / n) == rslot[qb] && (key / n) < cpb) : true;
-              const float s2 = ok ? p[kb][r] * sc2 : -INFINITY;
-              p[kb][r] = s2;
-              m = fmaxf(m, s2);
-            }
-          }
-          m = fmaxf(m, __shfl_xor(m, 32, 64));
-          float l = 0.f;
-#pragma unroll
-          for (int kb = 0; kb < NBR; ++kb) {
-            if (!SPAN && kb != qb) continue;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const float e = (m == -INFINITY) ? 0.f : exp2f(p[kb][r] - m);
-              p[kb][r] = e;
-              l += e;
-            }
-          }
-          l += __shfl_xor(l, 32, 64);
-          const float il = l > 0.f ? 1.0f / l : 0.f;
-          invl[qb][j] = il;
-          // dP^T (keys x queries) = V_j dO_j^T; Delta = sum_k P dP
-          float delta = 0.f;
-#pragma unroll
-          for (int kb = 0; kb < NBR; ++kb) {
-            if (!SPAN && kb != qb) continue;
-            dp[kb] = P::template scores<DH>(vD[kb], dO[qb], j, f32x16{});
-#pragma unroll
-            for (int r = 0; r < 16; ++r) delta += p[kb][r] * dp[kb][r];
-          }
-          delta += __shfl_xor(delta, 32, 64);
-          delta *= il;
-#pragma unroll
-          for (int kb = 0; kb < NBR; ++kb) {
-            if (!SPAN && kb != qb) continue;
-            // O recompute (unnormalised; scaled by 1/l below)
-#pragma unroll
-            for (int s = 0; s < ST; ++s) o[qb] = P::mma(masked_op<P>(vR[kb], s, mine), P::op(p[kb], s), o[qb]);
-            f32x16 ds, pn;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              pn[r] = p[kb][r] * il;
-              ds[r] = pn[r] * (dp[kb][r] - delta) * isd;
-            }
-            // dq^T (feature x queries) += K_j^T dS^T   (keys in result order on both sides)
-#pragma unroll
-            for (int s = 0; s < ST; ++s) dq[qb] = P::mma(masked_op<P>(kR[kb], s, mine), P::op(ds, s), dq[qb]);
-            // dk^T (feature x keys) += Q_j^T dS, dv^T (feature x keys) += dO_j^T P   (queries in natural order)
-            const f32x16 dsT = transpose_tile<P>(ds, sc, lane);
-            const f32x16 pT = transpose_tile<P>(pn, sc, lane);
-#pragma unroll
-            for (int s = 0; s < ST; ++s) {
-              dk[kb] = P::mma(masked_op<P>(qT[qb], s, mine), P::op(dsT, s), dk[kb]);
-              dv[kb] = P::mma(masked_op<P>(dOT[qb], s, mine), P::op(pT, s), dv[kb]);
-            }
-          }
+        for (int s = 0; s < ST; ++s) {
+          const int f = (hb * NB + ib) * ST + s;
+          t0 = P::mma(ld_frag<P>(W0, f, lane), rowop(xs, XS, 32 * jblk + lr, 32 * ib, s), t0);
+          t1 = P::mma(ld_frag<P>(W1, f, lane), rowop(src1, XS, 32 * jblk + lr, 32 * ib, s), t1);
         }
-      }
+      float *s0 = slot(job, 2 * sub) + lr * TS + 4 * h, *s1 = slot(job, 2 * sub + 1) + lr * TS + 4 * h;
 #pragma unroll
-      for (int rb = 0; rb < NBR; ++rb) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[rb][r] *= invl[rb][DH == 8 ? r / 4 : r / 8];
-        const f32x16 oT = transpose_tile<P>(o[rb], sc, lane);
-#pragma unroll
-        for (int ob = 0; ob < NB; ++ob) {  // dW_O[attn][D-out] += O^T dx_mid
-          f32x16 acc = f32x16{};
-#pragma unroll
-          for (int s = 0; s < ST; ++s) acc = P::mma(P::op(oT, s), P::op(dmT[rb][ob], s), acc);
-          lds_add_tile(dWo, D, 32 * hb, 32 * ob, acc, lane);
-        }
-#pragma unroll
-        for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-          for (int s = 0; s < ST; ++s) {
-            const int f = (ob * NB + hb) * ST + s;
-            dx[rb][ob] = P::mma3(ld_frag<P>(WqT, f, lane), P::op(dq[rb], s), ld_frag<P>(WkT, f, lane), P::op(dk[rb], s),
-                                 ld_frag<P>(WvT, f, lane), P::op(dv[rb], s), dx[rb][ob]);
-          }
-        const f32x16 dqT = transpose_tile<P>(dq[rb], sc, lane);
-        const f32x16 dkT = transpose_tile<P>(dk[rb], sc, lane);
-        const f32x16 dvT = transpose_tile<P>(dv[rb], sc, lane);
-#pragma unroll
-        for (int ib = 0; ib < NB; ++ib) {  // dW{q,k,v}[D-in][attn] += x^T d{q,k,v}
-          f32x16 aq = f32x16{}, ak = f32x16{}, av = f32x16{};
-#pragma unroll
-          for (int s = 0; s < ST; ++s) {
-            const op_t xa = P::op(xT[rb][ib], s);
-            aq = P::mma(xa, P::op(dqT, s), aq);
-            ak = P::mma(xa, P::op(dkT, s), ak);
-            av = P::mma(xa, P::op(dvT, s), av);
-          }
-          lds_add_tile(dWq, D, 32 * ib, 32 * hb, aq, lane);
-          lds_add_tile(dWk, D, 32 * ib, 32 * hb, ak, lane);
-          lds_add_tile(dWv, D, 32 * ib, 32 * hb, av, lane);
-        }
+      for (int k = 0; k < 4; ++k) {
+        *reinterpret_cast<float4*>(s0 + 8 * k) = make_float4(t0[4 * k], t0[4 * k + 1], t0[4 * k + 2], t0[4 * k + 3]);
+        *reinterpret_cast<float4*>(s1 + 8 * k) = make_float4(t1[4 * k], t1[4 * k + 1], t1[4 * k + 2], t1[4 * k + 3]);
       }
     }
+    barrier_lds();
+    // ---- 3. heads of this wave
+    float ho[HPS][VPH], hq[HPS][VPH], hk[HPS][NKB][VPH], hv[HPS][NKB][VPH];
 #pragma unroll
-    for (int rb = 0; rb < NBR; ++rb)
+    for (int jj = 0; jj < HPS; ++jj) {
+      const int j = sub * HPS + jj;
+      // the head's values of a result tile whose features are the head block's
+      auto keep = [&](const f32x16& t, float* v) {
 #pragma unroll
-      for (int ob = 0; ob < NB; ++ob) store_tile(a.g_out + (((gb0 + rb) * NB + ob) * 64 + lane) * 16, dx[rb][ob]);
+        for (int r = 0; r < VPH; ++r) v[r] = sub ? t[VPH * (HPS + jj) + r] : t[VPH * jj + r];
+      };
+      f32x16 p[NKB], dp[NKB];
+      float m = -INFINITY;
+      {
+        const sop qo = headop(slot(job, 0), j);
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+          p[kb] = P::template scores_packed<DH>(headop(slot((kbase + kb) * NB + hb, 1), j), qo, f32x16{});
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            p[kb][r] = (okbits[kb] >> r) & 1u ? p[kb][r] * sc2 : -INFINITY;
+            m = fmaxf(m, p[kb][r]);
+          }
+        }
+      }
+      m = xor32_max(m);
+      float l = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float e = (m == -INFINITY) ? 0.f : exp2f(p[kb][r] - m);
+          p[kb][r] = e;
+          l += e;
+        }
+      l = xor32_sum(l);
+      const float il = l > 0.f ? 1.0f / l : 0.f;
+      // dP^T (keys x queries) = V_j dO_j^T; Delta = sum_k P dP
+      float delta = 0.f;
+      {
+        const sop oo = headop(slot(job, 3), j);
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+          dp[kb] = P::template scores_packed<DH>(headop(slot((kbase + kb) * NB + hb, 2), j), oo, f32x16{});
+#pragma unroll
+          for (int r = 0; r < 16; ++r) delta += p[kb][r] * dp[kb][r];
+        }
+      }
+      delta = xor32_sum(delta);
+      delta *= il;
+      // O (unnormalised, scaled by 1/l at the end), dS, dQ: keys in result order on both sides
+      f32x16 to = f32x16{}, tq = f32x16{};
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb) {
+        const int kj = (kbase + kb) * NB + hb;
+#pragma unroll
+        for (int s = 0; s < ST; ++s) to = P::mma(colop(slot(kj, 2), TS, lr, s, false), P::op(p[kb], s), to);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          p[kb][r] *= il;
+          dp[kb][r] = p[kb][r] * (dp[kb][r] - delta) * isd;
+        }
+#pragma unroll
+        for (int s = 0; s < ST; ++s) tq = P::mma(colop(slot(kj, 1), TS, lr, s, false), P::op(dp[kb], s), tq);
+      }
+      keep(to, ho[jj]);
+      keep(tq, hq[jj]);
+#pragma unroll
+      for (int r = 0; r < VPH; ++r) ho[jj][r] *= il;
+      // dK += dS^T Q, dV += P^T dO: queries in natural order on both sides
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb) {
+        f32x16 t = f32x16{};
+        {
+          const f32x16 dsT = transpose_tile<P>(dp[kb], sc, lane);
+#pragma unroll
+          for (int s = 0; s < ST; ++s) t = P::mma(colop(slot(job, 0), TS, lr, s, true), P::op(dsT, s), t);
+        }
+        keep(t, hk[jj][kb]);
+        t = f32x16{};
+        {
+          const f32x16 pT = transpose_tile<P>(p[kb], sc, lane);
+#pragma unroll
+          for (int s = 0; s < ST; ++s) t = P::mma(colop(slot(job, 3), TS, lr, s, true), P::op(pT, s), t);
+        }
+        keep(t, hv[jj][kb]);
+      }
+    }
+    barrier_lds();
+    // ---- 4. O, dQ, dK, dV of this wave's heads into the slots
+#pragma unroll
+    for (int jj = 0; jj < HPS; ++jj) {
+      const int j = sub * HPS + jj;
+      put_head(slot(job, 0), j, hq[jj]);
+      put_head(slot(job, 3), j, ho[jj]);
+      if constexpr (!SPAN) {
+        put_head(slot(job, 1), j, hk[jj][0]);
+        put_head(slot(job, 2), j, hv[jj][0]);
+      } else {  // this query block's share of the other key block
+        const int oj = (kbase + 1 - own) * NB + hb;
+        float k[VPH], v[VPH];
+#pragma unroll
+        for (int r = 0; r < VPH; ++r) { k[r] = own ? hk[jj][0][r] : hk[jj][NKB - 1][r]; v[r] = own ? hv[jj][0][r] : hv[jj][NKB - 1][r]; }
+        put_head(slot(oj, 1), j, k);
+        put_head(slot(oj, 2), j, v);
+      }
+    }
+    barrier_lds();
+    if constexpr (SPAN) {
+#pragma unroll
+      for (int jj = 0; jj < HPS; ++jj) {
+        const int j = sub * HPS + jj;
+        float k[VPH], v[VPH];
+        get_head(slot(job, 1), j, k);
+        get_head(slot(job, 2), j, v);
+#pragma unroll
+        for (int r = 0; r < VPH; ++r) { k[r] += own ? hk[jj][NKB - 1][r] : hk[jj][0][r]; v[r] += own ? hv[jj][NKB - 1][r] : hv[jj][0][r]; }
+        put_head(slot(job, 1), j, k);
+        put_head(slot(job, 2), j, v);
+      }
+      barrier_lds();
+    }
+    // ---- 5. weight gradients: dW{q,k,v}[D-in][attn] += x^T d{q,k,v}, dW_O[attn][D-out] += O^T g
+#pragma unroll 1
+    for (int b = mb0; b < mb0 + 2; ++b)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const float *A = xs + 32 * b * XS + 32 * mi, *B = slot(b * NB + i, mt);
+        int as = XS, bs = TS;
+        if (mt == 3) { A = slot(b * NB + mi, 3); B = gs + 32 * b * XS + 32 * i; as = TS; bs = XS; }
+        f32x16 acc = f32x16{};
+#pragma unroll
+        for (int s = 0; s < ST; ++s) acc = P::mma(colop(A, as, lr, s, true), colop(B, bs, lr, s, true), acc);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dW[i][r] += acc[r];
+      }
+    // dx = g + dQ Wq^T + dK Wk^T + dV Wv^T
+    if (wave < 4 && b0 + sblk < nblk) {
+      f32x16 acc;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float4 v = *reinterpret_cast<const float4*>(gs + (32 * sblk + lr) * XS + 32 * sob + 8 * k + 4 * h);
+        acc[4 * k] = v.x; acc[4 * k + 1] = v.y; acc[4 * k + 2] = v.z; acc[4 * k + 3] = v.w;
+      }
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int jb = sblk * NB + i;
+#pragma unroll
+        for (int s = 0; s < ST; ++s) {
+          const int f = (sob * NB + i) * ST + s;
+          acc = P::mma3(ld_frag<P>(Wb, f, lane), rowop(slot(jb, 0), TS, lr, 0, s), ld_frag<P>(Wb + D * D, f, lane),
+                        rowop(slot(jb, 1), TS, lr, 0, s), ld_frag<P>(Wb + 2 * D * D, f, lane), rowop(slot(jb, 2), TS, lr, 0, s), acc);
+        }
+      }
+      store_tile(a.g_out + (((b0 + sblk) * NB + sob) * 64 + lane) * 16, acc);
+    }
+    barrier_lds();
   }
-  __syncthreads();
-  float* part = a.partial + (int64_t)blockIdx.x * 4 * D * D;
-  for (int i = threadIdx.x; i < 4 * D * D; i += blockDim.x) part[i] = sm[i];
+
+  // ---- this workgroup's gradients [dWq][dWk][dWv][dWo]; width 32: the two halves of the blocks summed
+  float* part = a.partial + (int64_t)blockIdx.x * 4 * D * D + mt * D * D;
+  if constexpr (NB == 1) {
+    __syncthreads();
+    float* red = sm + mt * 1024 + lane;
+    if (wave >= 4)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) red[64 * r] = dW[0][r];
+    __syncthreads();
+    if (wave >= 4) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dW[0][r] += red[64 * r];
+  }
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[(32 * mi + tile_idx(r, h)) * D + 32 * i + lr] = dW[i][r];
 }
 
 // ------------------------------------------------------------------ head and embedding
@@ -998,11 +1131,11 @@ static int32_t mlp_t(const BwdArgs& a, int blocks, hipStream_t st) {
 }
 
 template <class P, int D, int DH, bool SPAN>
-static int32_t attn_t(const BwdArgs& a, int blocks, int waves, hipStream_t st) {
-  const size_t lds = (size_t)4 * D * D * 4 + 4 * 32 * TS * 4;
+static int32_t attn_t(const BwdArgs& a, int blocks, hipStream_t st) {
+  const size_t lds = (size_t)(2 * 32 * (128 / D) * (D + 4) + 24 * 32 * TS) * 4;
   auto k = k_bwd_attn<P, D, DH, SPAN>;
   TDO_TRY(allow_full_lds((const void*)k));
-  hipLaunchKernelGGL(k, dim3(blocks), dim3(64 * waves), lds, st, a);
+  hipLaunchKernelGGL(k, dim3(blocks), dim3(512), lds, st, a);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }
@@ -1016,16 +1149,16 @@ int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream
 }
 
 template <class P>
-static int32_t attn_p(const BwdArgs& a, int D, int DH, int blocks, int w, hipStream_t st) {
+static int32_t attn_p(const BwdArgs& a, int D, int DH, int blocks, hipStream_t st) {
   const bool sp = a.span != 0;
-  if (D == 32 && DH == 8) return sp ? attn_t<P, 32, 8, true>(a, blocks, w, st) : attn_t<P, 32, 8, false>(a, blocks, w, st);
-  if (D == 64 && DH == 8) return sp ? attn_t<P, 64, 8, true>(a, blocks, w, st) : attn_t<P, 64, 8, false>(a, blocks, w, st);
-  if (D == 64 && DH == 16) return sp ? attn_t<P, 64, 16, true>(a, blocks, w, st) : attn_t<P, 64, 16, false>(a, blocks, w, st);
+  if (D == 32 && DH == 8) return sp ? attn_t<P, 32, 8, true>(a, blocks, st) : attn_t<P, 32, 8, false>(a, blocks, st);
+  if (D == 64 && DH == 8) return sp ? attn_t<P, 64, 8, true>(a, blocks, st) : attn_t<P, 64, 8, false>(a, blocks, st);
+  if (D == 64 && DH == 16) return sp ? attn_t<P, 64, 16, true>(a, blocks, st) : attn_t<P, 64, 16, false>(a, blocks, st);
   return set_error(TDO_EUNSUPPORTED, "no attention backward kernel for width %d, head width %d", D, DH);
 }
 
-int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, hipStream_t st, int waves) {
-  return bf16 ? attn_p<PBF16>(a, D, DH, blocks, waves, st) : attn_p<PF32>(a, D, DH, blocks, waves, st);
+int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, hipStream_t st) {
+  return bf16 ? attn_p<PBF16>(a, D, DH, blocks, st) : attn_p<PF32>(a, D, DH, blocks, st);
 }
 
 int32_t launch_bwd_head(bool bf16, int D, const void* save_last, const float* seeds, const int64_t* E_dev,

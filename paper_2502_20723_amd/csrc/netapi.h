@@ -70,7 +70,7 @@ struct BwdArgs {
   int64_t n_entries;
   int n, cpb, span, masked, d_real, M;
   float score_scale, inv_sqrt_dh;
-  int blocks_per_wg;            // launch_bwd_mlp: workgroup w takes these many blocks from w * blocks_per_wg (0: tiles in turn)
+  int blocks_per_wg;            // generic kernels: workgroup w takes these many blocks from w * blocks_per_wg (0: tiles in turn)
   int mlp_waves;                // BF16 feed-forward backward at mlp 256: 8 or 4 waves per workgroup
 };
 
@@ -85,8 +85,7 @@ int32_t launch_bwd_attn_bf16(const BwdArgs& a, int DH, int grid, hipStream_t st)
 // workgroups that fill the chip with one per CU in `blocks`
 int bwd_attn_bf16_parts(int blocks, bool span);
 int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream_t st);
-// waves: tiles that a workgroup takes at a time
-int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, hipStream_t st, int waves = 4);
+int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, hipStream_t st);
 // part: FP64 scratch of HEAD_BLOCKS * (2 d_real + 2) values (one slot per workgroup).
 constexpr int HEAD_BLOCKS = 1024;
 int32_t launch_bwd_head(bool bf16, int D, const void* save_last, const float* seeds, const int64_t* E_dev,

@@ -431,7 +431,7 @@ extern "C" int32_t tdo_log_rho_jacobian(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
         {
           ProfScope ps(np.prof, "bwd_attn", stream);
           if (attn_reg) TDO_TRY(launch_bwd_attn_bf16(a, np.DH, (int)E, stream));
-          else TDO_TRY(launch_bwd_attn(a, np.bf16, D, np.DH, (int)E, stream, 2));
+          else TDO_TRY(launch_bwd_attn(a, np.bf16, D, np.DH, (int)E, stream));
         }
         TDO_TRY(launch_jac_layer(mp, slots, ap, pp, E, rows + pp.off_layer0 + l * pp.layer_stride, stride, stream));
       }

@@ -344,7 +344,7 @@ int32_t tdo_sr_solve(tdo_ctx_t *ctx, double *jac, int64_t B, int64_t P, const do
  * reconfiguration: the products O(x_b) . p that apply S without forming it):
  *   jvp[b] = sum_k d log rho(x_b)/d theta_k tangent[k]   (complex: re, im),
  * by forward-mode differentiation of the network in FP32 (the tangent of every
- * stage evaluated with its value; not the fused MFMA kernels).  tangent: device
+ * stage evaluated with its value, one kernel per layer on the FP32 matrix cores).  tangent: device
  * double [P]; jvp: device float [B][2].  3 <= n <= 64. */
 int32_t tdo_log_rho_jvp(tdo_ctx_t *ctx, const tdo_arch_t *arch, const float *params, int32_t n,
                         const uint64_t *cfg, int64_t B, const double *tangent, float *jvp,

@@ -3,8 +3,8 @@
 // Jacobian-vector product), in FP32, and the matrix-free SR solve built on it.
 //
 // The network (main text "Transformer density operator ansatz"; App. B) is evaluated
-// together with its tangent t(.) = d(.)/d eps at theta + eps p, stage by stage over a chunk
-// of configurations, with activations in global memory (row r = (e * 2 + pass) * n + i):
+// together with its tangent t(.) = d(.)/d eps at theta + eps p, layer by layer over a chunk
+// of configurations, in the 32-row blocks of the forward:
 //   embedding:  T and t(T) for the 64 window codes (two circular convolutions, GELU each);
 //   per layer:  Q = X Wq, t(Q) = t(X) Wq + X t(Wq) (and K, V);
 //               per head  S = Q K^T / sqrt(dh), t(S) = (t(Q) K^T + Q t(K)^T) / sqrt(dh),
@@ -14,12 +14,14 @@
 //               X' = Y + H W2 + b2, t(X') = t(Y) + t(H) W2 + H t(W2) + t(b2);
 //   head:       f = mean_i X_i Wh + bh, t(f) = mean_i (t(X_i) Wh + X_i t(Wh)) + t(bh), z = f0 + i f1;
 //   log rho = log(e^{z1} + conj e^{z2}):  t(log rho) = (e^{z1} t(z1) + conj(e^{z2} t(z2))) / (e^{z1} + conj e^{z2}).
-// The products are one tiled FP32 GEMM kernel (64 x 64 output tiles, LDS-staged operands);
-// everything else is elementwise or per configuration-pass.
+// A layer is one kernel on the FP32 matrix cores (k_jvp_layer), value and tangent together.
+// The value path takes every sum in ascending order (features, keys, hidden units), so that the
+// sign of a feed-forward pre-activation does not depend on the split into tiles.
 #include <algorithm>
 #include <cmath>
 
 #include "common.h"
+#include "net.h"
 #include "netapi.h"
 #include "train.h"
 
@@ -35,219 +37,400 @@ __device__ __forceinline__ float gelu_d(float u) {
 
 }  // namespace
 
-// Embedding table of the 64 window codes and its tangent (as k_embed_table): rows of d values.
-__global__ void k_embed_table_jvp(const float* __restrict__ params, const float* __restrict__ tan, int d,
+// Order of the activations and weights here.  Value r of lane half h of a 32-feature tile is
+// feature 2 r + h, and lane m holds row asc(m) of its 32-row block: the products take operand pairs
+// (2 i, 2 i + 1) in turn, so features, keys and hidden units all come in ascending order.  A tile
+// in memory holds its 16 values per lane in that order; position pos(f) is feature f's.
+__device__ __forceinline__ int asc(int m) { return 8 * (m >> 3) + 2 * (m & 3) + ((m >> 2) & 1); }
+__host__ __device__ inline int pos(int f) { return (f & ~31) + 16 * (f & 1) + ((f & 31) >> 1); }
+
+// Embedding table of the 64 window codes and its tangent (as k_embed_table): rows of D values,
+// feature f at pos(f), zero past d.
+__global__ void k_embed_table_jvp(const float* __restrict__ params, const double* __restrict__ tan, int d, int D,
                                   float* __restrict__ T, float* __restrict__ Td) {
   __shared__ float e0[64], e1[64], e0d[64], e1d[64];
   const int code = blockIdx.x;
   const int t0 = code & 3, t1 = (code >> 2) & 3, t2 = (code >> 4) & 3;
   const float *w1 = params, *b1 = params + 4 * d, *w2 = b1 + d, *b2 = w2 + 2 * d * d;
-  const float *w1d = tan, *b1d = tan + 4 * d, *w2d = b1d + d, *b2d = w2d + 2 * d * d;
+  const double *w1d = tan, *b1d = tan + 4 * d, *w2d = b1d + d, *b2d = w2d + 2 * d * d;
   auto spin = [](int t, int ch) { return 1.0f - 2.0f * (float)((t >> ch) & 1); };
   for (int c = threadIdx.x; c < d; c += blockDim.x) {
     const float sa0 = spin(t0, 0), sa1 = spin(t0, 1), sb0 = spin(t1, 0), sb1 = spin(t1, 1), sc0 = spin(t2, 0),
                 sc1 = spin(t2, 1);
+    const float d0 = (float)w1d[c], d1 = (float)w1d[d + c], d2 = (float)w1d[2 * d + c], d3 = (float)w1d[3 * d + c], db = (float)b1d[c];
     const float a = b1[c] + sa0 * w1[c] + sa1 * w1[d + c] + sb0 * w1[2 * d + c] + sb1 * w1[3 * d + c];
-    const float ad = b1d[c] + sa0 * w1d[c] + sa1 * w1d[d + c] + sb0 * w1d[2 * d + c] + sb1 * w1d[3 * d + c];
+    const float ad = db + sa0 * d0 + sa1 * d1 + sb0 * d2 + sb1 * d3;
     const float b = b1[c] + sb0 * w1[c] + sb1 * w1[d + c] + sc0 * w1[2 * d + c] + sc1 * w1[3 * d + c];
-    const float bd = b1d[c] + sb0 * w1d[c] + sb1 * w1d[d + c] + sc0 * w1d[2 * d + c] + sc1 * w1d[3 * d + c];
+    const float bd = db + sb0 * d0 + sb1 * d1 + sc0 * d2 + sc1 * d3;
     e0[c] = gelu_f(a);
     e0d[c] = gelu_d(a) * ad;
     e1[c] = gelu_f(b);
     e1d[c] = gelu_d(b) * bd;
   }
   __syncthreads();
-  for (int o = threadIdx.x; o < d; o += blockDim.x) {
-    float acc = b2[o], accd = b2d[o];
-    for (int c = 0; c < d; ++c) {
-      acc += e0[c] * w2[c * d + o] + e1[c] * w2[d * d + c * d + o];
-      accd += e0d[c] * w2[c * d + o] + e0[c] * w2d[c * d + o] + e1d[c] * w2[d * d + c * d + o] +
-              e1[c] * w2d[d * d + c * d + o];
+  for (int o = threadIdx.x; o < D; o += blockDim.x) {
+    float v = 0.f, vd = 0.f;
+    if (o < d) {
+      float acc = b2[o], accd = (float)b2d[o];
+      for (int c = 0; c < d; ++c) {
+        acc += e0[c] * w2[c * d + o] + e1[c] * w2[d * d + c * d + o];
+        accd += e0d[c] * w2[c * d + o] + e0[c] * (float)w2d[c * d + o] + e1d[c] * w2[d * d + c * d + o] +
+                e1[c] * (float)w2d[d * d + c * d + o];
+      }
+      v = gelu_f(acc);
+      vd = gelu_d(acc) * accd;
     }
-    T[code * d + o] = gelu_f(acc);
-    Td[code * d + o] = gelu_d(acc) * accd;
+    T[code * D + pos(o)] = v;
+    Td[code * D + pos(o)] = vd;
   }
 }
 
-// Rows of the embedding: X[r] = T[code], t(X)[r] = t(T)[code], r = (e * 2 + pass) * n + i.
-__global__ void k_jvp_embed(const uint64_t* __restrict__ cfg, int64_t E, int n, int d, const float* __restrict__ T,
-                            const float* __restrict__ Td, float* __restrict__ X, float* __restrict__ Xd) {
-  const int64_t total = E * 2 * n * d;
-  for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * blockDim.x) {
-    const int o = (int)(idx % d);
-    const int64_t r = idx / d;
-    const int i = (int)(r % n);
-    const int64_t ep = r / n;
-    const int pass = (int)(ep & 1);
-    const int64_t e = ep >> 1;
-    const uint64_t a = cfg[2 * e], b = cfg[2 * e + 1];
-    const uint64_t c0 = pass ? b : a, c1 = pass ? a : b;
+// Embedding of every block: lane (row, half) copies its 16 values of each feature block from the
+// tables; zero where the row belongs to no configuration.
+__global__ void __launch_bounds__(256) k_jvp_embed(const uint64_t* __restrict__ cfg, int64_t E, int n, int cpb, int span,
+                                                   int D, const float* __restrict__ T, const float* __restrict__ Td,
+                                                   float* __restrict__ X, float* __restrict__ Xd) {
+  const RowMap rm{n, cpb, span != 0};
+  const int64_t nblk = span ? 4 * E : 2 * ((E + cpb - 1) / cpb);
+  const int lane = threadIdx.x & 63, h = lane >> 5, NB = D / 32;
+  for (int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); g < nblk; g += (int64_t)gridDim.x * 4) {
+    int64_t e; int pass, i; bool valid;
+    rm.at(g, asc(lane & 31), E, e, pass, i, valid);
     int code = 0;
-    for (int k = 0; k < 3; ++k) {
-      int s = i + k;
-      s = s >= n ? s - n : s;
-      code += ((int)((c0 >> s) & 1ull) + 2 * (int)((c1 >> s) & 1ull)) << (2 * k);
+    if (valid) {
+      const uint64_t a = cfg[2 * e], b = cfg[2 * e + 1], c0 = pass ? b : a, c1 = pass ? a : b;
+      for (int k = 0; k < 3; ++k) {
+        int s = i + k;
+        s = s >= n ? s - n : s;
+        code += ((int)((c0 >> s) & 1ull) + 2 * (int)((c1 >> s) & 1ull)) << (2 * k);
+      }
     }
-    X[idx] = T[code * d + o];
-    Xd[idx] = Td[code * d + o];
+    for (int ib = 0; ib < NB; ++ib) {
+      const int64_t o = ((g * NB + ib) * 64 + lane) * 16;
+      const float4* t = reinterpret_cast<const float4*>(T + code * D + 32 * ib + 16 * h);
+      const float4* td = reinterpret_cast<const float4*>(Td + code * D + 32 * ib + 16 * h);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        reinterpret_cast<float4*>(X + o)[q] = valid ? t[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+        reinterpret_cast<float4*>(Xd + o)[q] = valid ? td[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+    }
   }
 }
 
-// C[r][j] = sum_k A1[r][k] B1[k][j] (+ sum_k A2[r][k] B2[k][j]) (+ bias[j]) (+ Res[r][j]),
-// A row stride lda (the first K columns), B row-major with row stride ldb, C and Res with
-// row stride ldc.  epi 1: C = max(0, C); epi 2: C = 0 where Mask[r][j] <= 0 (Mask stride ldc).
-// 64 x 64 output tile per workgroup of 256 threads, each 4 x 4; K in steps of 16 through LDS.
-constexpr int GT = 64, GK = 16;
-__global__ void __launch_bounds__(256) k_jvp_gemm(const float* __restrict__ A1, const float* __restrict__ B1,
-                                                  const float* __restrict__ A2, const float* __restrict__ B2,
-                                                  int64_t R, int K, int N, int lda, int ldb,
-                                                  const float* __restrict__ bias, const float* __restrict__ Res,
-                                                  const float* __restrict__ Mask, int epi, float* __restrict__ C,
-                                                  int ldc) {
-  __shared__ float As[GK][GT + 4], Bs[GK][GT + 4];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int64_t ntn = (N + GT - 1) / GT;
-  const int64_t ntiles = ((R + GT - 1) / GT) * ntn;
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t r0 = (tile / ntn) * GT;
-    const int j0 = (int)(tile % ntn) * GT;
-    float acc[4][4] = {};
-    for (int pass = 0; pass < 2; ++pass) {
-      const float* A = pass ? A2 : A1;
-      const float* Bm = pass ? B2 : B1;
-      if (!A) continue;
-      for (int k0 = 0; k0 < K; k0 += GK) {
-        // stage A[r0 .. r0+63][k0 .. k0+15] (transposed) and B[k0 .. k0+15][j0 .. j0+63]
-        for (int q = threadIdx.x; q < GT * GK; q += 256) {
-          const int rr = q / GK, kk = q % GK;
-          const int64_t r = r0 + rr;
-          As[kk][rr] = (r < R && k0 + kk < K) ? A[r * lda + k0 + kk] : 0.f;
-          const int kb = q / GT, jj = q % GT;
-          Bs[kb][jj] = (k0 + kb < K && j0 + jj < N) ? Bm[(int64_t)(k0 + kb) * ldb + j0 + jj] : 0.f;
-        }
-        __syncthreads();
+// Weights and tangents of nl layers from l0 on, as 16-byte fragments in the order above: matrices Wq,
+// Wk, Wv, Wo, W1, W2 padded to [in][out]; fragment (ob, ib, s) of a matrix, lane l, value t holds
+// in = 32 ib + 2 (4 s + t) + l / 32, out = 32 ob + asc(l % 32).  Then b1 (M) and b2 (D) at pos.
+__global__ void k_jvp_pack(const float* __restrict__ params, const double* __restrict__ tan, PackPlan pp, int l0, int nl,
+                           float* __restrict__ out, float* __restrict__ outd) {
+  const int D = pp.D, M = pp.M, d = pp.d, DD = D * D, DM = D * M;
+  const int64_t len = pp.layer_elems + M + D;
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < nl * len; e += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t lp = pp.off_layer0 + (l0 + e / len) * pp.layer_stride;
+    int k = (int)(e % len), in_p = D, rows = d, cols = d;
+    int64_t src = lp;
+    bool ok = true;
+    if (k < pp.layer_elems) {
+      if (k < 4 * DD) { src += (int64_t)(k / DD) * d * d; k %= DD; }
+      else if ((k -= 4 * DD) < DM) { src += 4 * d * d; cols = M; }
+      else { k -= DM; src += 4 * d * d + d * M + M; in_p = M; rows = M; }
+      const int frag = k / 256, lane = (k >> 2) & 63, t = k & 3, s = frag & 3, ib = (frag >> 2) % (in_p / 32), ob = (frag >> 2) / (in_p / 32);
+      const int in = 32 * ib + 2 * (4 * s + t) + (lane >> 5), o = 32 * ob + asc(lane & 31);
+      ok = in < rows && o < cols;
+      src += (int64_t)in * cols + o;
+    } else {  // position k of a bias holds feature f, pos(f) = k
+      k -= (int)pp.layer_elems;
+      const bool first = k < M;
+      if (!first) k -= M;
+      const int f = (k & ~31) + 2 * (k & 15) + ((k >> 4) & 1);
+      src += first ? 4 * d * d + d * M + f : 4 * d * d + 2 * d * M + M + f;
+      ok = first || f < d;
+    }
+    out[e] = ok ? params[src] : 0.f;
+    outd[e] = ok ? (float)tan[src] : 0.f;
+  }
+}
+
+struct JvpArgs {
+  const float *w, *wd;  // packed layer and its tangent (k_jvp_pack)
+  float *x, *xd;        // residual stream and its tangent, [blocks][D/32][64][16], in place
+  int64_t E;
+  int n, cpb, masked, heads, M;
+  float scale;
+};
+
+// One layer with its tangent.  A wave takes a 32-row block (in turn, 8 waves a workgroup) and holds
+// the residual update of the block in registers; keys and values of a head block go through LDS,
+// where a spanning pass's other wave reads them too.  Three matrix products per value product
+// (value; tangent of either factor).  Bound: the FP32 matrix cores (3 times the forward's
+// operations of 157 TFLOP/s; 8-wide heads use a quarter of the products with V).  Two waves per SIMD
+// cover the latency of the weight fragments, which come through the caches.  It replaces 64 x 64
+// products on the vector ALU between activations in memory and an attention kernel whose threads
+// walked rows of global memory: 16384 configurations at n = 32, benchmark network 75.1 -> 14.2 ms (94
+// TFLOP/s), 32768 at n = 16 28.1 -> 7.0 ms, 4096 at n = 64, 2 layers 31.2 -> 4.7 ms.
+template <int D, int DH, bool SPAN>
+__global__ void __launch_bounds__(512) k_jvp_layer(JvpArgs a) {
+  constexpr int NB = D / 32, HPB = 32 / DH, VPH = DH / 2, NKB = SPAN ? 2 : 1, LS = 36, TILE = 32 * LS;
+  using P = PF32;
+  __shared__ __align__(16) float sm[8][4][TILE];  // per wave: k, t(k), v, t(v) [row][pos]
+  const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = a.n, cpb = a.cpb, M = a.M, MB = M / 32;
+  const int64_t nblk = SPAN ? 4 * a.E : 2 * ((a.E + cpb - 1) / cpb);
+  const float *W[6], *Wd[6];  // Wq, Wk, Wv, Wo, W1, W2
 #pragma unroll
-        for (int kk = 0; kk < GK; ++kk) {
-          float a[4], b[4];
+  for (int i = 0; i < 6; ++i) {
+    const int o = i < 4 ? i * D * D : 4 * D * D + (i - 4) * D * M;
+    W[i] = a.w + o;
+    Wd[i] = a.wd + o;
+  }
+  const float *b1 = a.w + 4 * D * D + 2 * D * M, *b1d = a.wd + 4 * D * D + 2 * D * M;
+  // keys of this lane's query (value r of key block kb is row 32 kb + 2 r + h)
+  uint32_t okbits[NKB];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            a[u] = As[kk][ty * 4 + u];
-            b[u] = Bs[kk][tx * 4 + u];
+  for (int kb = 0; kb < NKB; ++kb) {
+    okbits[kb] = 0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int key = 32 * kb + 2 * r + h;
+      const bool ok = SPAN ? key < n : (a.masked ? key / n == asc(lr) / n && key / n < cpb : true);
+      okbits[kb] |= ok ? 1u << r : 0u;
+    }
+  }
+  const int kw = SPAN ? wave & ~1 : wave;  // wave that holds key block 0
+  const int vcol = pos(asc(lr));           // column of the feature of result row lr
+  auto load16 = [](const float* p) {
+    f32x16 v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 t = reinterpret_cast<const float4*>(p)[q];
+      v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
+    }
+    return v;
+  };
+  auto store16 = [](float* p, const f32x16& v) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) reinterpret_cast<float4*>(p)[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+  };
+  auto lds_sync = [] {
+    if constexpr (SPAN) barrier_lds();
+    else {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    }
+  };
+  auto column = [&](const float* t, int s) {  // lane -> feature of result row lr; rows in the order of the score tiles
+    const float* p = t + tile_idx(4 * s, h) * LS + vcol;
+    return f32x4{p[0], p[LS], p[2 * LS], p[3 * LS]};
+  };
+
+  for (int64_t base = (int64_t)blockIdx.x * 8; base < nblk; base += (int64_t)gridDim.x * 8) {
+    const bool live = base + wave < nblk;
+    if (!SPAN && !live) continue;
+    const int64_t g = live ? base + wave : base + (wave & 1);  // a spanning pass's waves all meet at the barriers
+    float *xb = a.x + (g * NB * 64 + lane) * 16, *xdb = a.xd + (g * NB * 64 + lane) * 16;  // feature block ib at 1024 ib
+    f32x16 y[NB], yd[NB];
+#pragma unroll
+    for (int ob = 0; ob < NB; ++ob) y[ob] = yd[ob] = f32x16{};
+#pragma unroll 1
+    for (int hb = 0; hb < NB; ++hb) {
+      // value and tangent of a projection's head block: c = W^T x, cd = W^T t(x) + t(W)^T x
+      auto project = [&](int m, f32x16& c, f32x16& cd) {
+        c = cd = f32x16{};
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int f = (hb * NB + ib) * 4 + s;
+            const f32x4 xo = *reinterpret_cast<const f32x4*>(xb + 1024 * ib + 4 * s);
+            const f32x4 xdo = *reinterpret_cast<const f32x4*>(xdb + 1024 * ib + 4 * s);
+            const f32x4 w = ld_frag<P>(W[m], f, lane);
+            c = P::mma(w, xo, c);
+            cd = P::mma(w, xdo, cd);
+            cd = P::mma(ld_frag<P>(Wd[m], f, lane), xo, cd);
+          }
+      };
+      f32x16 q, qd;
+      project(1, q, qd);
+      store16(sm[wave][0] + lr * LS + 16 * h, q);
+      store16(sm[wave][1] + lr * LS + 16 * h, qd);
+      project(2, q, qd);
+      store16(sm[wave][2] + lr * LS + 16 * h, q);
+      store16(sm[wave][3] + lr * LS + 16 * h, qd);
+      project(0, q, qd);
+      lds_sync();
+      f32x16 o = f32x16{}, od = f32x16{};
+#pragma unroll
+      for (int j = 0; j < HPB; ++j) {
+        if (hb * HPB + j >= a.heads) break;  // padding features
+        f32x16 p[NKB], pd[NKB];
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+          const float *kp = sm[kw + kb][0] + lr * LS + 16 * h + VPH * j, *kdp = sm[kw + kb][1] + lr * LS + 16 * h + VPH * j;
+          p[kb] = pd[kb] = f32x16{};
+#pragma unroll
+          for (int t = 0; t < VPH; ++t) {
+            const float kv = kp[t];
+            p[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kv, q[VPH * j + t], p[kb], 0, 0, 0);
+            pd[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kv, qd[VPH * j + t], pd[kb], 0, 0, 0);
+            pd[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kdp[t], q[VPH * j + t], pd[kb], 0, 0, 0);
           }
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(a[u], b[v], acc[u][v]);
+          for (int r = 0; r < 16; ++r) {
+            p[kb][r] = (okbits[kb] >> r) & 1u ? p[kb][r] * a.scale : -INFINITY;
+            pd[kb][r] *= a.scale;
+            mx = fmaxf(mx, p[kb][r]);
+          }
         }
-        __syncthreads();
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t r = r0 + ty * 4 + u;
-      if (r >= R) continue;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int j = j0 + tx * 4 + v;
-        if (j >= N) continue;
-        float c = acc[u][v];
-        if (bias) c += bias[j];
-        if (Res) c += Res[r * ldc + j];
-        if (epi == 1) c = fmaxf(c, 0.f);
-        if (epi == 2 && !(Mask[r * ldc + j] > 0.f)) c = 0.f;
-        C[r * ldc + j] = c;
-      }
-    }
-  }
-}
-
-// Attention of one configuration-pass per workgroup, all heads in turn, with tangents:
-// O = softmax(Q K^T / sqrt(dh)) V and t(O) from Q, K, V, t(Q), t(K), t(V) (rows of d).
-__global__ void __launch_bounds__(256) k_jvp_attn(int64_t EP, int n, int d, int heads, float scale,
-                                                  const float* __restrict__ Q, const float* __restrict__ Kx,
-                                                  const float* __restrict__ V, const float* __restrict__ Qd,
-                                                  const float* __restrict__ Kd, const float* __restrict__ Vd,
-                                                  float* __restrict__ O, float* __restrict__ Od) {
-  extern __shared__ float sm[];
-  const int dh = d / heads;
-  float* S = sm;               // [n][n] scores, then P
-  float* Sd = S + n * n;       // tangents, then t(P)
-  for (int64_t ep = blockIdx.x; ep < EP; ep += gridDim.x) {
-    const int64_t base = ep * n * d;
-    for (int h = 0; h < heads; ++h) {
-      for (int q = threadIdx.x; q < n * n; q += blockDim.x) {
-        const int i = q / n, k = q % n;
-        float s = 0.f, sd = 0.f;
-        for (int j = 0; j < dh; ++j) {
-          const int64_t qi = base + (int64_t)i * d + h * dh + j, kk = base + (int64_t)k * d + h * dh + j;
-          s += Q[qi] * Kx[kk];
-          sd += Qd[qi] * Kx[kk] + Q[qi] * Kd[kk];
-        }
-        S[q] = s * scale;
-        Sd[q] = sd * scale;
-      }
-      __syncthreads();
-      for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        float m = -INFINITY;
-        for (int k = 0; k < n; ++k) m = fmaxf(m, S[i * n + k]);
+        mx = xor32_max(mx);
+        const float mm = mx == -INFINITY ? 0.f : mx;  // a row without a key (padding) keeps P = 0
         float l = 0.f;
-        for (int k = 0; k < n; ++k) {
-          const float p = expf(S[i * n + k] - m);
-          S[i * n + k] = p;
-          l += p;
-        }
-        const float inv = 1.0f / l;
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {  // keys 2 r (lower half of the wave), then 2 r + 1
+            p[kb][r] = expf(p[kb][r] - mm);
+            const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[kb][r]), __float_as_uint(p[kb][r]), false, false);
+            l += __uint_as_float(both[0]);
+            l += __uint_as_float(both[1]);
+          }
+        const float inv = l > 0.f ? 1.0f / l : 0.f;
         float dot = 0.f;
-        for (int k = 0; k < n; ++k) {
-          S[i * n + k] *= inv;
-          dot += S[i * n + k] * Sd[i * n + k];
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            p[kb][r] *= inv;
+            dot += p[kb][r] * pd[kb][r];
+          }
+        dot = xor32_sum(dot);
+        f32x16 to = f32x16{}, tod = f32x16{};
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) pd[kb][r] = p[kb][r] * (pd[kb][r] - dot);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const f32x4 v = column(sm[kw + kb][2], s);
+            to = P::mma(v, P::op(p[kb], s), to);
+            tod = P::mma(v, P::op(pd[kb], s), tod);
+            tod = P::mma(column(sm[kw + kb][3], s), P::op(p[kb], s), tod);
+          }
         }
-        for (int k = 0; k < n; ++k) Sd[i * n + k] = S[i * n + k] * (Sd[i * n + k] - dot);
+#pragma unroll
+        for (int r = VPH * j; r < VPH * (j + 1); ++r) { o[r] = to[r]; od[r] = tod[r]; }
       }
-      __syncthreads();
-      for (int q = threadIdx.x; q < n * dh; q += blockDim.x) {
-        const int i = q / dh, j = q % dh;
-        float o = 0.f, od = 0.f;
-        for (int k = 0; k < n; ++k) {
-          const int64_t vk = base + (int64_t)k * d + h * dh + j;
-          o += S[i * n + k] * V[vk];
-          od += Sd[i * n + k] * V[vk] + S[i * n + k] * Vd[vk];
+#pragma unroll
+      for (int ob = 0; ob < NB; ++ob)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int f = (ob * NB + hb) * 4 + s;
+          const f32x4 w = ld_frag<P>(W[3], f, lane);
+          y[ob] = P::mma(w, P::op(o, s), y[ob]);
+          yd[ob] = P::mma(w, P::op(od, s), yd[ob]);
+          yd[ob] = P::mma(ld_frag<P>(Wd[3], f, lane), P::op(o, s), yd[ob]);
         }
-        O[base + (int64_t)i * d + h * dh + j] = o;
-        Od[base + (int64_t)i * d + h * dh + j] = od;
-      }
-      __syncthreads();
+      lds_sync();  // keys and values read before the next head block's (or block's) are written
     }
+    f32x16 z[NB], zd[NB];
+#pragma unroll
+    for (int ob = 0; ob < NB; ++ob) {
+      const f32x16 x = load16(xb + 1024 * ob), xd = load16(xdb + 1024 * ob);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { y[ob][r] += x[r]; yd[ob][r] += xd[r]; }
+      z[ob] = zd[ob] = f32x16{};
+    }
+    // ---- feed-forward: hidden units in chunks of 32
+#pragma unroll 1
+    for (int c = 0; c < MB; ++c) {
+      f32x16 u = f32x16{}, ud = f32x16{};
+#pragma unroll
+      for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int f = (c * NB + ib) * 4 + s;
+          const f32x4 w = ld_frag<P>(W[4], f, lane);
+          u = P::mma(w, P::op(y[ib], s), u);
+          ud = P::mma(w, P::op(yd[ib], s), ud);
+          ud = P::mma(ld_frag<P>(Wd[4], f, lane), P::op(y[ib], s), ud);
+        }
+      const f32x16 b = load16(b1 + 32 * c + 16 * h), bd = load16(b1d + 32 * c + 16 * h);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        u[r] = fmaxf(u[r] + b[r], 0.f);
+        ud[r] = u[r] > 0.f ? ud[r] + bd[r] : 0.f;
+      }
+#pragma unroll
+      for (int ob = 0; ob < NB; ++ob)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int f = (ob * MB + c) * 4 + s;
+          const f32x4 w = ld_frag<P>(W[5], f, lane);
+          z[ob] = P::mma(w, P::op(u, s), z[ob]);
+          zd[ob] = P::mma(w, P::op(ud, s), zd[ob]);
+          zd[ob] = P::mma(ld_frag<P>(Wd[5], f, lane), P::op(u, s), zd[ob]);
+        }
+    }
+    if (live)
+#pragma unroll
+      for (int ob = 0; ob < NB; ++ob) {
+        const f32x16 b = load16(b1 + M + 32 * ob + 16 * h), bd = load16(b1d + M + 32 * ob + 16 * h);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { z[ob][r] = (z[ob][r] + b[r]) + y[ob][r]; zd[ob][r] = (zd[ob][r] + bd[r]) + yd[ob][r]; }
+        store16(xb + 1024 * ob, z[ob]);
+        store16(xdb + 1024 * ob, zd[ob]);
+      }
   }
 }
 
-// Mean pooling and head per configuration-pass (one wave each): z = (f0, f1), t(z).
-__global__ void k_jvp_head(int64_t EP, int n, int d, const float* __restrict__ X, const float* __restrict__ Xd,
-                           const float* __restrict__ hw, const float* __restrict__ hb, const float* __restrict__ hwd,
-                           const float* __restrict__ hbd, float* __restrict__ z, float* __restrict__ zd) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t ep = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); ep < EP;
-       ep += (int64_t)gridDim.x * (blockDim.x >> 6)) {
-    float f0 = 0.f, f1 = 0.f, g0 = 0.f, g1 = 0.f;
-    for (int q = lane; q < n * d; q += 64) {
-      const int o = q % d;
-      const float x = X[ep * n * d + q], xd = Xd[ep * n * d + q];
-      f0 += x * hw[2 * o];
-      f1 += x * hw[2 * o + 1];
-      g0 += xd * hw[2 * o] + x * hwd[2 * o];
-      g1 += xd * hw[2 * o + 1] + x * hwd[2 * o + 1];
+// Mean pooling and head, one wave per block (spanning: both blocks of a pass): z = (f0, f1), t(z) per
+// configuration-pass.  Row sums go through LDS and are added over a configuration's sites in order.
+__global__ void __launch_bounds__(256) k_jvp_head(int64_t E, int n, int cpb, int span, int d, int D, const float* __restrict__ X,
+                                                  const float* __restrict__ Xd, const float* __restrict__ hw,
+                                                  const double* __restrict__ hwd, float* __restrict__ z, float* __restrict__ zd) {
+  __shared__ float4 rows[4][64];
+  const float* hb = hw + 2 * d;
+  const double* hbd = hwd + 2 * d;
+  const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31, wave = threadIdx.x >> 6, NB = D / 32, RB = span ? 2 : 1;
+  const int64_t ntile = span ? 2 * E : 2 * ((E + cpb - 1) / cpb);
+  for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < ntile; t += (int64_t)gridDim.x * 4) {
+    for (int rb = 0; rb < RB; ++rb) {
+      float f0 = 0.f, f1 = 0.f, g0 = 0.f, g1 = 0.f;
+      for (int ib = 0; ib < NB; ++ib) {
+        const int64_t o = (((t * RB + rb) * NB + ib) * 64 + lane) * 16;
+        for (int r = 0; r < 16; ++r) {
+          const int f = 32 * ib + 2 * r + h;
+          if (f >= d) continue;
+          const float x = X[o + r], xd = Xd[o + r], w0 = hw[2 * f], w1 = hw[2 * f + 1];
+          f0 += x * w0;
+          f1 += x * w1;
+          g0 += xd * w0 + x * (float)hwd[2 * f];
+          g1 += xd * w1 + x * (float)hwd[2 * f + 1];
+        }
+      }
+      f0 = xor32_sum(f0); f1 = xor32_sum(f1); g0 = xor32_sum(g0); g1 = xor32_sum(g1);
+      if (h == 0) rows[wave][32 * rb + asc(lr)] = make_float4(f0, f1, g0, g1);
     }
-    f0 = wave_sum(f0);
-    f1 = wave_sum(f1);
-    g0 = wave_sum(g0);
-    g1 = wave_sum(g1);
-    if (lane == 0) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    const int64_t e = span ? t >> 1 : (t >> 1) * cpb + lane;
+    if (lane < cpb && e < E) {
+      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int i = 0; i < n; ++i) {
+        const float4 v = rows[wave][lane * n + i];
+        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+      }
       const float inv = 1.0f / (float)n;
-      z[2 * ep] = f0 * inv + hb[0];
-      z[2 * ep + 1] = f1 * inv + hb[1];
-      zd[2 * ep] = g0 * inv + hbd[0];
-      zd[2 * ep + 1] = g1 * inv + hbd[1];
+      const int64_t ep = 2 * e + (t & 1);
+      z[2 * ep] = s.x * inv + hb[0];
+      z[2 * ep + 1] = s.y * inv + hb[1];
+      zd[2 * ep] = s.z * inv + (float)hbd[0];
+      zd[2 * ep + 1] = s.w * inv + (float)hbd[1];
     }
+    __builtin_amdgcn_wave_barrier();  // rows read before the next tile's are written
   }
 }
 
@@ -272,25 +455,24 @@ __global__ void k_jvp_combine(int64_t E, const float* __restrict__ z, const floa
   }
 }
 
-__global__ void k_to_f32(const double* __restrict__ a, int64_t n, float* __restrict__ b) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    b[i] = (float)a[i];
-}
-
 }  // namespace tdo
 
 namespace tdo {
 
 namespace {
 
-size_t jvp_bytes_per_config(const NetPlan& np) {
-  const size_t rows = 2 * (size_t)np.n;
-  return rows * (12 * (size_t)np.pp.d + 2 * (size_t)np.pp.mlp) * 4 + 64;
+template <int D, int DH>
+int32_t launch_jvp_layer(const JvpArgs& a, bool span, int num_cus, hipStream_t st) {
+  const int64_t nblk = span ? 4 * a.E : 2 * ((a.E + a.cpb - 1) / a.cpb);
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((nblk + 7) / 8, num_cus));
+  if (span) hipLaunchKernelGGL((k_jvp_layer<D, DH, true>), dim3(grid), dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((k_jvp_layer<D, DH, false>), dim3(grid), dim3(512), 0, st, a);
+  TDO_HIP(hipGetLastError());
+  return TDO_OK;
 }
 
-int32_t gemm(const NetPlan& np, const float* A1, const float* B1, const float* A2, const float* B2, int64_t R, int K,
-             int N, int lda, int ldb, const float* bias, const float* res, const float* mask, int epi, float* C, int ldc,
-             hipStream_t st);
+// floats of one packed layer (weights, b1, b2)
+int64_t jvp_layer_len(const PackPlan& pp) { return pp.layer_elems + pp.M + pp.D; }
 
 }  // namespace
 
@@ -298,88 +480,68 @@ int32_t gemm(const NetPlan& np, const float* A1, const float* B1, const float* A
 // within max_bytes for the per-chunk part.
 int32_t plan_jvp(const NetPlan& np, int64_t B, size_t max_bytes, Arena& ar, JvpWs* j) {
   const PackPlan& pp = np.pp;
-  const size_t per = jvp_bytes_per_config(np);
-  const size_t fixed = ((size_t)pp.nparams + 128 * (size_t)pp.d) * 4 + 20 * 256;
-  TDO_CHECK(max_bytes >= fixed + per, TDO_ENOMEM,
-            "workspace cannot hold the forward-mode buffers of one configuration (%zu bytes)", fixed + per);
-  j->ec = std::max<int64_t>(1, std::min<int64_t>(B, (int64_t)((max_bytes - fixed) / per)));
-  const size_t R = (size_t)j->ec * 2 * np.n, d = pp.d, m = pp.mlp;
-  j->tanf = ar.take<float>(pp.nparams);
-  j->T = ar.take<float>(64 * d);
-  j->Td = ar.take<float>(64 * d);
-  size_t* act[] = {&j->X, &j->Xd, &j->Y, &j->Yd, &j->Q, &j->K, &j->V, &j->Qd, &j->Kd, &j->Vd, &j->O, &j->Od};
-  for (size_t* o : act) *o = ar.take<float>(R * d);
-  j->H = ar.take<float>(R * m);
-  j->Hd = ar.take<float>(R * m);
+  const size_t block = 32 * (size_t)np.D * 4 * 2;           // x and t(x) of a block
+  const size_t unit = (np.span ? 4 : 2) * block + np.cpb * 32;  // the blocks of cpb configurations, z and t(z)
+  const size_t small = 128 * (size_t)np.D * 4 + 16 * 256;
+  const size_t layer = 2 * (size_t)jvp_layer_len(pp) * 4;
+  // every layer's weights packed once per call, or, in a small workspace, one layer's at a time
+  j->layers = small + pp.layers * layer + unit <= max_bytes / 2 ? pp.layers : 1;
+  const size_t fixed = small + j->layers * layer;
+  TDO_CHECK(max_bytes >= fixed + unit, TDO_ENOMEM,
+            "workspace cannot hold the forward-mode buffers of one configuration (%zu bytes)", fixed + unit);
+  const int64_t units = std::max<int64_t>(1, std::min<int64_t>((B + np.cpb - 1) / np.cpb, (int64_t)((max_bytes - fixed) / unit)));
+  j->ec = units * np.cpb;
+  j->T = ar.take<float>(64 * (size_t)np.D);
+  j->Td = ar.take<float>(64 * (size_t)np.D);
+  j->w = ar.take<float>(j->layers * (size_t)jvp_layer_len(pp));
+  j->wd = ar.take<float>(j->layers * (size_t)jvp_layer_len(pp));
+  j->X = ar.take<float>((size_t)blocks_for(np, j->ec) * 32 * np.D);
+  j->Xd = ar.take<float>((size_t)blocks_for(np, j->ec) * 32 * np.D);
   j->z = ar.take<float>(4 * (size_t)j->ec);
   j->zd = ar.take<float>(4 * (size_t)j->ec);
   return TDO_OK;
 }
 
-namespace {
-
-int32_t gemm(const NetPlan& np, const float* A1, const float* B1, const float* A2, const float* B2, int64_t R, int K,
-             int N, int lda, int ldb, const float* bias, const float* res, const float* mask, int epi, float* C, int ldc,
-             hipStream_t st) {
-  const int64_t tiles = ((R + GT - 1) / GT) * ((N + GT - 1) / GT);
-  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(tiles, (int64_t)np.num_cus * 8));
-  hipLaunchKernelGGL(k_jvp_gemm, dim3(grid), dim3(256), 0, st, A1, B1, A2, B2, R, K, N, lda, ldb, bias, res, mask, epi,
-                     C, ldc);
-  TDO_HIP(hipGetLastError());
-  return TDO_OK;
-}
-
-}  // namespace
-
-// Tangent table (the embedding, once per tangent), then per chunk the network and its
-// tangent; out[e] = t(log rho(cfg[e])) as (re, im).
-int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params, const uint64_t* cfg, int64_t B,
-                float* out, hipStream_t st) {
+// Tables and packed weights (once per tangent), then per chunk the network and its tangent;
+// out[e] = t(log rho(cfg[e])) as (re, im).
+int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params, const double* tan, const uint64_t* cfg,
+                int64_t B, float* out, hipStream_t st) {
   const PackPlan& pp = np.pp;
-  const int d = pp.d, m = pp.mlp, n = np.n, H = pp.heads;
-  const float* tan = at<float>(ws, j.tanf);
-  float *T = at<float>(ws, j.T), *Td = at<float>(ws, j.Td);
-  hipLaunchKernelGGL(k_embed_table_jvp, dim3(64), dim3(64), 0, st, params, tan, d, T, Td);
+  const int64_t len = jvp_layer_len(pp);
+  float *T = at<float>(ws, j.T), *Td = at<float>(ws, j.Td), *w = at<float>(ws, j.w), *wd = at<float>(ws, j.wd);
+  float *X = at<float>(ws, j.X), *Xd = at<float>(ws, j.Xd), *z = at<float>(ws, j.z), *zd = at<float>(ws, j.zd);
+  auto pack = [&](int l0) {
+    hipLaunchKernelGGL(k_jvp_pack, dim3((unsigned)std::min<int64_t>(ceil_div(j.layers * len, 256), 4096)), dim3(256), 0, st,
+                       params, tan, pp, l0, j.layers, w, wd);
+  };
+  hipLaunchKernelGGL(k_embed_table_jvp, dim3(64), dim3(64), 0, st, params, tan, pp.d, np.D, T, Td);
+  if (j.layers == pp.layers) pack(0);
   TDO_HIP(hipGetLastError());
-  float *X = at<float>(ws, j.X), *Xd = at<float>(ws, j.Xd), *Y = at<float>(ws, j.Y), *Yd = at<float>(ws, j.Yd);
-  float *Q = at<float>(ws, j.Q), *K = at<float>(ws, j.K), *V = at<float>(ws, j.V);
-  float *Qd = at<float>(ws, j.Qd), *Kd = at<float>(ws, j.Kd), *Vd = at<float>(ws, j.Vd);
-  float *O = at<float>(ws, j.O), *Od = at<float>(ws, j.Od), *Hh = at<float>(ws, j.H), *Hd = at<float>(ws, j.Hd);
-  float *z = at<float>(ws, j.z), *zd = at<float>(ws, j.zd);
-  const float scale = (float)(1.0 / std::sqrt((double)(d / H)));
-  const size_t attn_lds = 2 * (size_t)n * n * sizeof(float);
   for (int64_t e0 = 0; e0 < B; e0 += j.ec) {
-    const int64_t E = std::min(j.ec, B - e0), EP = 2 * E, R = EP * n;
-    hipLaunchKernelGGL(k_jvp_embed, dim3((unsigned)std::min<int64_t>(ceil_div(R * d, 256), 65536)), dim3(256), 0, st,
-                       cfg + 2 * e0, E, n, d, T, Td, X, Xd);
+    const int64_t E = std::min(j.ec, B - e0), nblk = blocks_for(np, E);
+    const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(nblk, 4), 8192);
+    hipLaunchKernelGGL(k_jvp_embed, dim3(grid), dim3(256), 0, st, cfg + 2 * e0, E, np.n, np.cpb, (int)np.span, np.D, T, Td, X, Xd);
     TDO_HIP(hipGetLastError());
     for (int l = 0; l < pp.layers; ++l) {
-      const int64_t o = pp.off_layer0 + (int64_t)l * pp.layer_stride;
-      const float *wq = params + o, *wk = wq + d * d, *wv = wk + d * d, *wo = wv + d * d, *w1 = wo + d * d;
-      const float *b1 = w1 + d * m, *w2 = b1 + m, *b2 = w2 + m * d;
-      const float *tq = tan + o, *tk = tq + d * d, *tv = tk + d * d, *to = tv + d * d, *t1 = to + d * d;
-      const float *tb1 = t1 + d * m, *t2 = tb1 + m, *tb2 = t2 + m * d;
-      const float* W[3] = {wq, wk, wv};
-      const float* Wt[3] = {tq, tk, tv};
-      float* P[3] = {Q, K, V};
-      float* Pd[3] = {Qd, Kd, Vd};
-      for (int i = 0; i < 3; ++i) {
-        TDO_TRY(gemm(np, X, W[i], nullptr, nullptr, R, d, d, d, d, nullptr, nullptr, nullptr, 0, P[i], d, st));
-        TDO_TRY(gemm(np, Xd, W[i], X, Wt[i], R, d, d, d, d, nullptr, nullptr, nullptr, 0, Pd[i], d, st));
-      }
-      hipLaunchKernelGGL(k_jvp_attn, dim3((unsigned)std::min<int64_t>(EP, (int64_t)np.num_cus * 8)), dim3(256),
-                         attn_lds, st, EP, n, d, H, scale, Q, K, V, Qd, Kd, Vd, O, Od);
-      TDO_HIP(hipGetLastError());
-      TDO_TRY(gemm(np, O, wo, nullptr, nullptr, R, d, d, d, d, nullptr, X, nullptr, 0, Y, d, st));
-      TDO_TRY(gemm(np, Od, wo, O, to, R, d, d, d, d, nullptr, Xd, nullptr, 0, Yd, d, st));
-      TDO_TRY(gemm(np, Y, w1, nullptr, nullptr, R, d, m, d, m, b1, nullptr, nullptr, 1, Hh, m, st));
-      TDO_TRY(gemm(np, Yd, w1, Y, t1, R, d, m, d, m, tb1, nullptr, Hh, 2, Hd, m, st));
-      TDO_TRY(gemm(np, Hh, w2, nullptr, nullptr, R, m, d, m, d, b2, Y, nullptr, 0, X, d, st));
-      TDO_TRY(gemm(np, Hd, w2, Hh, t2, R, m, d, m, d, tb2, Yd, nullptr, 0, Xd, d, st));
+      if (j.layers != pp.layers) pack(l);
+      JvpArgs a{};
+      const int64_t o = j.layers == pp.layers ? l * len : 0;
+      a.w = w + o;
+      a.wd = wd + o;
+      a.x = X;
+      a.xd = Xd;
+      a.E = E;
+      a.n = np.n;
+      a.cpb = np.cpb;
+      a.masked = np.masked;
+      a.heads = pp.heads;
+      a.M = pp.M;
+      a.scale = (float)(1.0 / std::sqrt((double)np.DH));
+      if (np.D == 32) TDO_TRY(np.DH == 8 ? (launch_jvp_layer<32, 8>(a, np.span, np.num_cus, st)) : (launch_jvp_layer<32, 16>(a, np.span, np.num_cus, st)));
+      else TDO_TRY(np.DH == 8 ? (launch_jvp_layer<64, 8>(a, np.span, np.num_cus, st)) : (launch_jvp_layer<64, 16>(a, np.span, np.num_cus, st)));
     }
-    hipLaunchKernelGGL(k_jvp_head, dim3((unsigned)std::min<int64_t>(ceil_div(EP, 4), 16384)), dim3(256), 0, st, EP, n,
-                       d, X, Xd, params + pp.off_head_w, params + pp.off_head_b, tan + pp.off_head_w,
-                       tan + pp.off_head_b, z, zd);
+    hipLaunchKernelGGL(k_jvp_head, dim3(grid), dim3(256), 0, st, E, np.n, np.cpb, (int)np.span, pp.d, np.D, X, Xd,
+                       params + pp.off_head_w, tan + pp.off_head_w, z, zd);
     hipLaunchKernelGGL(k_jvp_combine, dim3((unsigned)std::min<int64_t>(ceil_div(E, 256), 4096)), dim3(256), 0, st, E,
                        z, zd, out + 2 * e0);
     TDO_HIP(hipGetLastError());
@@ -390,13 +552,6 @@ int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params
 int32_t jvp_check(const Context& c, const tdo_arch_t* arch, int32_t n, int64_t B, NetPlan* np) {
   TDO_TRY(net_plan(&c, arch, n, false, np));
   TDO_CHECK(B >= 0, TDO_EINVAL, "B=%lld < 0", (long long)B);
-  return TDO_OK;
-}
-
-int32_t jvp_tangent_f32(const double* p, int64_t P, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_to_f32, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(P, 256), 4096))),
-                     dim3(256), 0, st, p, P, out);
-  TDO_HIP(hipGetLastError());
   return TDO_OK;
 }
 
@@ -423,6 +578,5 @@ extern "C" int32_t tdo_log_rho_jvp(tdo_ctx_t* ctx, const tdo_arch_t* arch, const
   TDO_CHECK(c.budget > 4096, TDO_ENOMEM, "workspace budget %zu too small", c.budget);
   TDO_TRY(plan_jvp(np, B, c.budget, ar, &j));
   TDO_TRY(ensure_workspace(&c, ar.used));
-  TDO_TRY(jvp_tangent_f32(tangent, np.pp.nparams, at<float>(c.ws, j.tanf), stream));
-  return run_jvp(np, c.ws, j, params, cfg, B, jvp, stream);
+  return run_jvp(np, c.ws, j, params, tangent, cfg, B, jvp, stream);
 }

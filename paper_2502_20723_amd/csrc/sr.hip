@@ -318,7 +318,7 @@ extern "C" int32_t tdo_sr_solve_matfree(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   void* ws = c.ws;
   double *r = at<double>(ws, or_), *p = at<double>(ws, op), *Ap = at<double>(ws, oap), *sc = at<double>(ws, osc);
   double* part = at<double>(ws, opart);
-  float *tv = at<float>(ws, ot), *seed = at<float>(ws, oseed), *tanf = at<float>(ws, j.tanf);
+  float *tv = at<float>(ws, ot), *seed = at<float>(ws, oseed);
   const unsigned gp = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(P, 256), 4096));
   const unsigned gb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(B, 256), 4096));
   auto dot = [&](const double* a, const double* b, double* out) -> int32_t {
@@ -338,8 +338,7 @@ extern "C" int32_t tdo_sr_solve_matfree(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   TDO_TRY(dot(grad, grad, sc + 1));
   TDO_TRY(dot(grad, grad, sc + 4));
   for (int32_t it = 0; it < iters; ++it) {
-    TDO_TRY(jvp_tangent_f32(p, P, tanf, stream));
-    TDO_TRY(run_jvp(npj, ws, j, params, cfg, B, tv, stream));
+    TDO_TRY(run_jvp(npj, ws, j, params, p, cfg, B, tv, stream));
     hipLaunchKernelGGL(k_mf_mean, dim3(1), dim3(kT), 0, stream, tv, weights, B, sc + 8);
     hipLaunchKernelGGL(k_mf_seeds, dim3(gb), dim3(256), 0, stream, tv, weights, B, sc + 8, seed);
     TDO_HIP(hipGetLastError());

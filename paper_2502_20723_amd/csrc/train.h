@@ -72,17 +72,17 @@ int32_t loss_grad_run(Context& c, const NetPlan& np, const ModelDev& m, const Tr
 int32_t net_plan(const Context* c, const tdo_arch_t* arch, int n, bool bf16, NetPlan* np);
 
 // Forward-mode pass (jvp.hip): buffers for chunks of ec configurations, laid out by plan_jvp
-// from ar.used on within max_bytes (the FP32 tangent of the parameters first).
+// from ar.used on within max_bytes.
 struct JvpWs {
   int64_t ec = 0;
-  size_t tanf, T, Td, X, Xd, Y, Yd, Q, K, V, Qd, Kd, Vd, O, Od, H, Hd, z, zd;
+  int layers = 0;  // layers whose packed weights are held at a time
+  size_t T, Td, w, wd, X, Xd, z, zd;
 };
 int32_t plan_jvp(const NetPlan& np, int64_t B, size_t max_bytes, Arena& ar, JvpWs* j);
-// out[e] (re, im) = d log rho(cfg[e]) along the tangent held at ws + j.tanf (FP32).
-int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params, const uint64_t* cfg, int64_t B,
-                float* out, hipStream_t st);
+// out[e] (re, im) = d log rho(cfg[e]) along the tangent tan [P].
+int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params, const double* tan, const uint64_t* cfg,
+                int64_t B, float* out, hipStream_t st);
 int32_t jvp_check(const Context& c, const tdo_arch_t* arch, int32_t n, int64_t B, NetPlan* np);
-int32_t jvp_tangent_f32(const double* p, int64_t P, float* out, hipStream_t st);
 int64_t blocks_for(const NetPlan& np, int64_t E);
 int32_t pack_weights(const NetPlan& np, const float* params, NetWeights* w, hipStream_t st);
 void carve_weights(const NetPlan& np, Arena& ar, size_t* offs);

@@ -287,9 +287,8 @@ int32_t run_forward(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg
   return TDO_OK;
 }
 
-int32_t pack_weights(const NetPlan& np, const float* params, NetWeights* w, hipStream_t st) {
-  TDO_TRY(launch_pack_forward(np.pp, params, np.bf16, w->wpack, w->b1, w->b2, st));
-  TDO_TRY(launch_embed_table(params, np.pp.d, np.D, w->table, st));
+int32_t pack_weights(const NetPlan& np, const float* params, NetWeights* w, hipStream_t st, void* wback) {
+  TDO_TRY(launch_pack(np.pp, params, np.bf16, w->wpack, wback, w->b1, w->b2, w->table, st));
   w->head_w = params + np.pp.off_head_w;
   w->head_b = params + np.pp.off_head_b;
   return TDO_OK;

@@ -44,7 +44,7 @@ __device__ __forceinline__ float gelu_d(float u) {
 __device__ __forceinline__ int asc(int m) { return 8 * (m >> 3) + 2 * (m & 3) + ((m >> 2) & 1); }
 __host__ __device__ inline int pos(int f) { return (f & ~31) + 16 * (f & 1) + ((f & 31) >> 1); }
 
-// Embedding table of the 64 window codes and its tangent (as k_embed_table): rows of D values,
+// Embedding table of the 64 window codes and its tangent (as the forward's): rows of D values,
 // feature f at pos(f), zero past d.
 __global__ void k_embed_table_jvp(const float* __restrict__ params, const double* __restrict__ tan, int d, int D,
                                   float* __restrict__ T, float* __restrict__ Td) {

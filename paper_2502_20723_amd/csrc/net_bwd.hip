@@ -1051,21 +1051,45 @@ __global__ void k_embed_params_sum(const double* __restrict__ part, int64_t len,
   }
 }
 
-// Sum nparts FP32 partials of length len in index order into FP64 out[i] (+=).
-// A workgroup of 256 threads sums EPB consecutive elements over all nparts partials:
-// G = 256 / EPB groups of threads each take every G-th partial, and the group sums are
-// added in a fixed order (deterministic), so that enough loads are in flight per element.
-template <int EPB>
-__global__ void __launch_bounds__(256) k_reduce_partials(const float* __restrict__ part, int nparts, int64_t len,
-                                                         double* __restrict__ out) {
+// Where element i of a flat vector lies in a partial: the whole vector, or the feed-forward
+// ([W1 d x M][b1 M][W2 M x d][b2 d] from dW1 [D][M], dW2 [M][D], db1 [M], db2 [D]) or attention (four
+// d x d from D x D) part of a layer's parameters.
+struct WholeMap {
+  __device__ int64_t at(int64_t i) const { return i; }
+};
+struct MlpMap {
+  int d, D, M;
+  __device__ int at(int i) const {
+    if (i < d * M) return i;
+    if ((i -= d * M) < M) return 2 * D * M + i;
+    if ((i -= M) < d * M) return D * M + (i / d) * D + i % d;
+    return 2 * D * M + M + (i - d * M);
+  }
+};
+struct AttnMap {
+  int d, D;
+  __device__ int at(int i) const {
+    const int mt = i / (d * d), r = i % (d * d);
+    return mt * D * D + (r / d) * D + r % d;
+  }
+};
+
+// out[i] += sum of nparts FP32 partials (plen apart) in FP64, in a fixed order.  A workgroup of 256
+// threads sums EPB consecutive elements over all partials: G = 256 / EPB groups of threads each
+// take every G-th partial, and the group sums are added in a fixed order (deterministic), so that
+// enough loads are in flight per element.
+template <int EPB, class Map>
+__global__ void __launch_bounds__(256) k_reduce_partials(const float* __restrict__ part, int nparts, int64_t plen, Map map,
+                                                         int64_t len, double* __restrict__ out) {
   constexpr int G = 256 / EPB;
   __shared__ double sh[G][EPB];
   const int j = threadIdx.x % EPB, g = threadIdx.x / EPB;
   const int64_t i = (int64_t)blockIdx.x * EPB + j;
   double s = 0.0;
   if (i < len) {
+    const float* q = part + map.at(i);
 #pragma unroll 8
-    for (int p = g; p < nparts; p += G) s += (double)part[(int64_t)p * len + i];
+    for (int p = g; p < nparts; p += G) s += (double)q[(int64_t)p * plen];
   }
   sh[g][j] = s;
   __syncthreads();
@@ -1074,33 +1098,6 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const float* __restrict
 #pragma unroll
     for (int q = 1; q < G; ++q) t += sh[q][j];
     out[i] += t;
-  }
-}
-
-// Scatter a padded FP64 layer gradient into the flat parameter gradient (+=, scaled).
-//  layer accumulators: mlp = [dW1 D*M][dW2 M*D][db1 M][db2 D], attn = [dWq][dWk][dWv][dWo] (D*D each)
-__global__ void k_scatter_layer(const double* __restrict__ mlp, const double* __restrict__ attn, int d, int D, int M,
-                                double scale, double* __restrict__ g) {
-  const int64_t tot = 4LL * d * d + 2LL * d * M + M + d;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < tot; i += (int64_t)gridDim.x * blockDim.x) {
-    double v;
-    if (i < 4LL * d * d) {
-      const int mt = (int)(i / (d * d)), rem = (int)(i % (d * d)), r = rem / d, c = rem % d;
-      v = attn[(int64_t)mt * D * D + r * D + c];
-    } else if (i < 4LL * d * d + (int64_t)d * M) {
-      const int64_t k = i - 4LL * d * d;
-      const int r = (int)(k / M), c = (int)(k % M);
-      v = mlp[(int64_t)r * M + c];
-    } else if (i < 4LL * d * d + (int64_t)d * M + M) {
-      v = mlp[2LL * D * M + (i - 4LL * d * d - (int64_t)d * M)];
-    } else if (i < 4LL * d * d + 2LL * d * M + M) {
-      const int64_t k = i - 4LL * d * d - (int64_t)d * M - M;
-      const int r = (int)(k / d), c = (int)(k % d);
-      v = mlp[(int64_t)D * M + (int64_t)r * D + c];
-    } else {
-      v = mlp[2LL * D * M + M + (i - 4LL * d * d - 2LL * d * M - M)];
-    }
-    g[i] += scale * v;
   }
 }
 
@@ -1164,7 +1161,7 @@ int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, 
 int32_t launch_bwd_head(bool bf16, int D, const void* save_last, const float* seeds, const int64_t* E_dev,
                         int64_t E_host, int n, int cpb, int span, int d_real, double* gw, double* gb, double* part,
                         hipStream_t st) {
-  constexpr int G = HEAD_BLOCKS;
+  const int G = grid_for(HEAD_BLOCKS, span ? 4 * E_host : 2 * ((E_host + cpb - 1) / cpb), 4);
   if (D == 32) {
     if (bf16) hipLaunchKernelGGL((k_bwd_head<PBF16, 32>), dim3(G), dim3(256), 0, st, save_last, seeds, E_dev, E_host, n, cpb, span, d_real, part);
     else hipLaunchKernelGGL((k_bwd_head<PF32, 32>), dim3(G), dim3(256), 0, st, save_last, seeds, E_dev, E_host, n, cpb, span, d_real, part);
@@ -1198,22 +1195,29 @@ int32_t launch_embed_params(const float* params, const double* dT, int d, int D,
   return TDO_OK;
 }
 
-int32_t launch_reduce_partials(const float* part, int nparts, int64_t len, double* out, hipStream_t st) {
+template <class Map>
+static int32_t reduce(const float* part, int nparts, int64_t plen, Map map, int64_t len, double* out, hipStream_t st) {
   if (len <= 0) return TDO_OK;
   if (ceil_div(len, 64) >= 256) {  // enough workgroups with 4 groups of partials
-    hipLaunchKernelGGL(k_reduce_partials<64>, dim3((unsigned)ceil_div(len, 64)), dim3(256), 0, st, part, nparts, len, out);
+    hipLaunchKernelGGL((k_reduce_partials<64, Map>), dim3((unsigned)ceil_div(len, 64)), dim3(256), 0, st, part, nparts, plen, map, len, out);
   } else {
-    hipLaunchKernelGGL(k_reduce_partials<16>, dim3((unsigned)ceil_div(len, 16)), dim3(256), 0, st, part, nparts, len, out);
+    hipLaunchKernelGGL((k_reduce_partials<16, Map>), dim3((unsigned)ceil_div(len, 16)), dim3(256), 0, st, part, nparts, plen, map, len, out);
   }
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }
 
-int32_t launch_scatter_layer(const double* mlp, const double* attn, int d, int D, int M, double scale, double* g,
-                             hipStream_t st) {
-  hipLaunchKernelGGL(k_scatter_layer, dim3(256), dim3(256), 0, st, mlp, attn, d, D, M, scale, g);
-  TDO_HIP(hipGetLastError());
-  return TDO_OK;
+int32_t launch_reduce_partials(const float* part, int nparts, int64_t len, double* out, hipStream_t st) {
+  return reduce(part, nparts, len, WholeMap{}, len, out, st);
+}
+
+int32_t launch_reduce_mlp(const float* part, int nparts, const PackPlan& pp, double* g, hipStream_t st) {
+  const int64_t d = pp.d, D = pp.D, M = pp.M;
+  return reduce(part, nparts, 2 * D * M + M + D, MlpMap{pp.d, pp.D, pp.M}, 2 * d * M + M + d, g + 4 * d * d, st);
+}
+
+int32_t launch_reduce_attn(const float* part, int nparts, const PackPlan& pp, double* g, hipStream_t st) {
+  return reduce(part, nparts, 4LL * pp.D * pp.D, AttnMap{pp.d, pp.D}, 4LL * pp.d * pp.d, g, st);
 }
 
 }  // namespace tdo

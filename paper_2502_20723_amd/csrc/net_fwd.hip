@@ -39,38 +39,6 @@ struct EmbedRow {
   }
 };
 
-// Table of the embedding: T[code][o] = act(b2 + e(t0,t1) W2[0] + e(t1,t2) W2[1]),
-// e(ta,tb) = act(b1 + s(ta) W1[0] + s(tb) W1[1]), act = exact GELU (Eq. circ-conv).
-__global__ void k_embed_table(const float* __restrict__ params, int d, int D, float* __restrict__ table) {
-  __shared__ float e0[64], e1[64];
-  const int code = blockIdx.x;
-  const int t0 = code & 3, t1 = (code >> 2) & 3, t2 = (code >> 4) & 3;
-  const float* w1 = params;            // [2 taps][2 ch][d]
-  const float* b1 = params + 4 * d;    // [d]
-  const float* w2 = b1 + d;            // [2 taps][d][d]
-  const float* b2 = w2 + 2 * d * d;    // [d]
-  auto spin = [](int t, int ch) { return 1.0f - 2.0f * (float)((t >> ch) & 1); };
-  auto gelu = [](float u) { return 0.5f * u * (1.0f + erff(u * 0.70710678118654752f)); };
-  for (int c = threadIdx.x; c < d; c += blockDim.x) {
-    float a = b1[c] + spin(t0, 0) * w1[0 * d + c] + spin(t0, 1) * w1[1 * d + c] + spin(t1, 0) * w1[2 * d + c] +
-              spin(t1, 1) * w1[3 * d + c];
-    float b = b1[c] + spin(t1, 0) * w1[0 * d + c] + spin(t1, 1) * w1[1 * d + c] + spin(t2, 0) * w1[2 * d + c] +
-              spin(t2, 1) * w1[3 * d + c];
-    e0[c] = gelu(a);
-    e1[c] = gelu(b);
-  }
-  __syncthreads();
-  for (int o = threadIdx.x; o < D; o += blockDim.x) {
-    float v = 0.f;
-    if (o < d) {
-      float acc = b2[o];
-      for (int c = 0; c < d; ++c) acc += e0[c] * w2[c * d + o] + e1[c] * w2[d * d + c * d + o];
-      v = gelu(acc);
-    }
-    table[code * D + o] = v;
-  }
-}
-
 // Workgroup size NT: BF16 weights staged in LDS are shared by 8 waves (two per SIMD,
 // so that one wave's latencies overlap the other's work) or by 4 waves (one per SIMD,
 // with twice the registers); the choice is autotuned per shape.  FP32: 8 waves.
@@ -549,12 +517,6 @@ static int32_t launch_layer_p(const FwdArgs& a, int D, int DH, bool span, int nu
 
 int32_t launch_fwd_layer(const FwdArgs& a, bool bf16, int D, int DH, bool span, int num_cus, hipStream_t st) {
   return bf16 ? launch_layer_p<PBF16>(a, D, DH, span, num_cus, st) : launch_layer_p<PF32>(a, D, DH, span, num_cus, st);
-}
-
-int32_t launch_embed_table(const float* params, int d, int D, float* table, hipStream_t st) {
-  hipLaunchKernelGGL(k_embed_table, dim3(64), dim3(64), 0, st, params, d, D, table);
-  TDO_HIP(hipGetLastError());
-  return TDO_OK;
 }
 
 int32_t launch_symmetrise(const int64_t* E_dev, int64_t E_host, const float* z, float* lr, hipStream_t st) {

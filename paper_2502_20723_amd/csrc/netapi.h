@@ -30,7 +30,6 @@ struct FwdArgs {
 };
 
 int32_t launch_fwd_layer(const FwdArgs& a, bool bf16, int D, int DH, bool span, int num_cus, hipStream_t st);
-int32_t launch_embed_table(const float* params, int d, int D, float* table, hipStream_t st);
 int32_t launch_symmetrise(const int64_t* E_dev, int64_t E_host, const float* z, float* lr, hipStream_t st);
 
 // Packing of the flat parameter vector into per-layer MFMA fragments.
@@ -41,12 +40,11 @@ struct PackPlan {
   int64_t layer_elems;  // packed elements per layer (forward fragments)
 };
 int32_t make_pack_plan(const tdo_arch_t* arch, PackPlan* pp);
-// Writes L layers of forward fragments (elem = bf16 if bf16 else f32) and padded
-// biases b1 [L][M], b2 [L][D].
-int32_t launch_pack_forward(const PackPlan& pp, const float* params, bool bf16, void* wpack, float* b1,
-                            float* b2, hipStream_t st);
-// L layers of transposed fragments: Wq^T, Wk^T, Wv^T, Wo^T [D][D], then W2^T [D][M], W1^T [M][D].
-int32_t launch_pack_backward(const PackPlan& pp, const float* params, bool bf16, void* wpack, hipStream_t st);
+// Writes L layers of forward fragments (elem = bf16 if bf16 else f32), padded biases b1 [L][M] and
+// b2 [L][D], the embedding table [64][D], and, if wb is not NULL, L layers of transposed fragments:
+// Wq^T, Wk^T, Wv^T, Wo^T [D][D], then W2^T [D][M], W1^T [M][D].
+int32_t launch_pack(const PackPlan& pp, const float* params, bool bf16, void* wf, void* wb, float* b1, float* b2,
+                    float* table, hipStream_t st);
 
 }  // namespace tdo
 
@@ -88,6 +86,11 @@ int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream
 int32_t launch_bwd_attn(const BwdArgs& a, bool bf16, int D, int DH, int blocks, hipStream_t st);
 // part: FP64 scratch of HEAD_BLOCKS * (2 d_real + 2) values (one slot per workgroup).
 constexpr int HEAD_BLOCKS = 1024;
+// workgroups for nblk blocks taken `per` at a time, at most cap
+inline int grid_for(int cap, int64_t nblk, int per) {
+  const int64_t g = (nblk + per - 1) / per;
+  return g < 1 ? 1 : (g < cap ? (int)g : cap);
+}
 int32_t launch_bwd_head(bool bf16, int D, const void* save_last, const float* seeds, const int64_t* E_dev,
                         int64_t E_host, int n, int cpb, int span, int d_real, double* gw, double* gb, double* part,
                         hipStream_t st);
@@ -111,8 +114,10 @@ int32_t launch_jac_tables(const float* params, int d, double* tab, hipStream_t s
 // convolution parameters, at jac; part: bpc consecutive wave partials [64][D] per configuration
 int32_t launch_jac_embed(const float* params, const double* tab, const float* part, int bpc, int d, int D, int64_t E,
                          double* jac, int64_t stride, hipStream_t st);
+// out[i] += sum over the partials, in FP64: of whole vectors; of the feed-forward or attention
+// partials of a layer into its part of the flat gradient g
 int32_t launch_reduce_partials(const float* part, int nparts, int64_t len, double* out, hipStream_t st);
-int32_t launch_scatter_layer(const double* mlp, const double* attn, int d, int D, int M, double scale, double* g,
-                             hipStream_t st);
+int32_t launch_reduce_mlp(const float* part, int nparts, const PackPlan& pp, double* g, hipStream_t st);
+int32_t launch_reduce_attn(const float* part, int nparts, const PackPlan& pp, double* g, hipStream_t st);
 
 }  // namespace tdo

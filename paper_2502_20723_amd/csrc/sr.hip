@@ -329,8 +329,7 @@ extern "C" int32_t tdo_sr_solve_matfree(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   };
   {  // the reverse-mode weight fragments, packed once
     NetWeights w = weights_at(ws, t.woff);
-    TDO_TRY(pack_weights(npv, params, &w, stream));
-    TDO_TRY(launch_pack_backward(npv.pp, params, npv.bf16, at<char>(ws, t.wback), stream));
+    TDO_TRY(pack_weights(npv, params, &w, stream, at<char>(ws, t.wback)));
   }
   // sc: [1] rs, [2] p.Ap, [3] rs_new, [4] g.g, [8..10] weight sum and weighted tangent sums
   hipLaunchKernelGGL(k_sr_init, dim3(gp), dim3(256), 0, stream, grad, P, x, r, p);

@@ -46,7 +46,7 @@ struct Saves {
 
 // Workspace plan shared by the loss/gradient and VJP drivers.
 struct TrainWs {
-  size_t woff[4], wback, gA, Lall, acc, lpart, mlp_acc, attn_acc, dT_acc, partial;
+  size_t woff[4], wback, gA, Lall, acc, lpart, dT_acc, partial;
   size_t cnt, off, etot, ecfg, ecoef, eowner, lr, z, dF, xa, xb, sx, smid, slast, slse;
   int64_t chunk, emax, nblk;
   size_t layer_bytes, lse_layer;
@@ -84,7 +84,8 @@ int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params
                 int64_t B, float* out, hipStream_t st);
 int32_t jvp_check(const Context& c, const tdo_arch_t* arch, int32_t n, int64_t B, NetPlan* np);
 int64_t blocks_for(const NetPlan& np, int64_t E);
-int32_t pack_weights(const NetPlan& np, const float* params, NetWeights* w, hipStream_t st);
+// wback: also the transposed fragments of the backward pass
+int32_t pack_weights(const NetPlan& np, const float* params, NetWeights* w, hipStream_t st, void* wback = nullptr);
 void carve_weights(const NetPlan& np, Arena& ar, size_t* offs);
 NetWeights weights_at(void* ws, const size_t* offs);
 int32_t run_forward(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg, int64_t E, const int64_t* E_dev,

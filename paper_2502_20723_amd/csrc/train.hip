@@ -125,8 +125,6 @@ struct BwdBufs {
   float* gb;
   float* partial;    // [nparts][maxlen]
   int nparts;
-  double* mlp_acc;   // [2DM + M + D]
-  double* attn_acc;  // [4 D^2]
   double* dT_acc;    // [64 D]
 };
 
@@ -162,41 +160,42 @@ static int32_t run_backward(const NetPlan& np, const NetWeights& w, const BwdBuf
                             const uint64_t* ecfg, int64_t E, const int64_t* E_dev, const Saves& sv, const float* dF,
                             double* gt, hipStream_t st) {
   const PackPlan& pp = np.pp;
-  const int L = pp.layers, D = np.D, M = pp.M;
-  const int64_t mlen = 2LL * D * M + M + D, alen = 4LL * D * D;
+  const int L = pp.layers, D = np.D;
+  // workgroups: one per CU, but no more than there are tiles (E bounds the entries also where their
+  // count is on the device); a workgroup without a tile would only add a partial of zeros
+  const int64_t nblk = blocks_for(np, E);
+  const int parts = grid_for(bb.nparts, nblk, 2);
   for (int l = L - 1; l >= 0; --l) {
     BwdArgs a = layer_args(np, w, bb.wback, params, E, E_dev, sv, l);
     a.partial = bb.partial;
+    double* gl = gt + pp.off_layer0 + l * pp.layer_stride;
     // feed-forward sub-layer: gradient in ga (or from the seeds), out to gb
     a.g_in = (l == L - 1) ? nullptr : bb.ga;
     a.seeds = (l == L - 1) ? dF : nullptr;
     a.g_out = bb.gb;
-    TDO_TRY(fill(bb.mlp_acc, mlen, 0.0, st));
-    TDO_TRY(fill(bb.attn_acc, alen, 0.0, st));
     {
       ProfScope ps(np.prof, "bwd_mlp", st);
-      if (np.bf16 && bwd_mlp_bf16_supported(pp.d, D, M))
-        TDO_TRY(launch_bwd_mlp_bf16(a, bb.nparts, st));
+      if (np.bf16 && bwd_mlp_bf16_supported(pp.d, D, pp.M))
+        TDO_TRY(launch_bwd_mlp_bf16(a, parts, st));
       else
-        TDO_TRY(launch_bwd_mlp(a, np.bf16, D, bb.nparts, st));
+        TDO_TRY(launch_bwd_mlp(a, np.bf16, D, parts, st));
     }
-    TDO_TRY(launch_reduce_partials(bb.partial, bb.nparts, mlen, bb.mlp_acc, st));
+    TDO_TRY(launch_reduce_mlp(bb.partial, parts, pp, gl, st));
     // attention sub-layer: gb -> ga
     a.g_in = bb.gb;
     a.seeds = nullptr;
     a.g_out = bb.ga;
-    int attn_parts = bb.nparts;
+    int attn_parts = parts;
     {
       ProfScope ps(np.prof, "bwd_attn", st);
       if (np.bf16 && bwd_attn_bf16_supported(pp.d, D, np.DH, np.span)) {
-        attn_parts = bwd_attn_bf16_parts(bb.nparts, np.span);
+        attn_parts = grid_for(bwd_attn_bf16_parts(bb.nparts, np.span), nblk, np.span ? 4 : 2);
         TDO_TRY(launch_bwd_attn_bf16(a, np.DH, attn_parts, st));
       } else {
-        TDO_TRY(launch_bwd_attn(a, np.bf16, D, np.DH, bb.nparts, st));
+        TDO_TRY(launch_bwd_attn(a, np.bf16, D, np.DH, attn_parts, st));
       }
     }
-    TDO_TRY(launch_reduce_partials(bb.partial, attn_parts, alen, bb.attn_acc, st));
-    TDO_TRY(launch_scatter_layer(bb.mlp_acc, bb.attn_acc, pp.d, D, M, 1.0, gt + pp.off_layer0 + l * pp.layer_stride, st));
+    TDO_TRY(launch_reduce_attn(bb.partial, attn_parts, pp, gl, st));
   }
   // the head kernel's workgroup slots reuse the partial buffer (free here; sized for them in plan_train)
   TDO_TRY(launch_bwd_head(np.bf16, D, sv.last, dF, E_dev, E, np.n, np.cpb, np.span, pp.d, gt + pp.off_head_w,
@@ -204,8 +203,9 @@ static int32_t run_backward(const NetPlan& np, const NetWeights& w, const BwdBuf
   // table gradient accumulated over every call of this entry point; the chain rule into the
   // convolution parameters (linear in it) runs once at the end (finish_backward)
   // two workgroups per CU (each wave a partial): the second one's waves hide the first's latencies
-  TDO_TRY(launch_embed_scatter(D, bb.ga, ecfg, E_dev, E, np.n, np.cpb, np.span, bb.partial, 2 * bb.nparts, st));
-  TDO_TRY(launch_reduce_partials(bb.partial, 8 * bb.nparts, 64LL * D, bb.dT_acc, st));
+  const int eparts = grid_for(2 * bb.nparts, nblk, 4);
+  TDO_TRY(launch_embed_scatter(D, bb.ga, ecfg, E_dev, E, np.n, np.cpb, np.span, bb.partial, eparts, st));
+  TDO_TRY(launch_reduce_partials(bb.partial, 4 * eparts, 64LL * D, bb.dT_acc, st));
   return TDO_OK;
 }
 
@@ -224,14 +224,12 @@ int32_t plan_train_at(const Context& c, const NetPlan& np, int64_t B, int nslots
   ar.used = (base + 255) & ~size_t(255);
   carve_weights(np, ar, t->woff);
   t->wback = ar.take<char>((size_t)pp.layer_elems * pp.layers * np.elem);
-  t->gA = ar.take<double>(pp.nparams);
-  t->Lall = ar.take<float>(2 * B);
+  t->gA = ar.take<double>(pp.nparams);  // gA, acc and dT_acc adjacent: zeroed together
   t->acc = ar.take<double>(2);
+  t->dT_acc = ar.take<double>(64LL * np.D);
+  t->Lall = ar.take<float>(2 * B);
   t->lpart = ar.take<double>(2 * LOSS_PARTS);
   const int64_t mlen = 2LL * np.D * pp.M + pp.M + np.D;
-  t->mlp_acc = ar.take<double>(mlen);
-  t->attn_acc = ar.take<double>(4LL * np.D * np.D);
-  t->dT_acc = ar.take<double>(64LL * np.D);
   // per CU: the feed-forward weight partials, the attention weight partials of up to two workgroups,
   // or 8 wave partials of the table gradient; in all, at least the FP64 per-code slots of the
   // embedding chain rule and the head kernel's workgroup slots
@@ -290,8 +288,7 @@ int32_t vjp_run(Context& c, const NetPlan& np, const TrainWs& t, const float* pa
   void* ws = c.ws;
   NetWeights w = weights_at(ws, t.woff);
   if (!packed) {
-    TDO_TRY(pack_weights(np, params, &w, stream));
-    TDO_TRY(launch_pack_backward(np.pp, params, np.bf16, at<char>(ws, t.wback), stream));
+    TDO_TRY(pack_weights(np, params, &w, stream, at<char>(ws, t.wback)));
   } else {
     w.head_w = params + np.pp.off_head_w;
     w.head_b = params + np.pp.off_head_b;
@@ -299,7 +296,7 @@ int32_t vjp_run(Context& c, const NetPlan& np, const TrainWs& t, const float* pa
   TDO_TRY(fill(grad, np.pp.nparams, 0.0, stream));
   TDO_TRY(fill(at<double>(ws, t.dT_acc), 64LL * np.D, 0.0, stream));
   BwdBufs bb{at<char>(ws, t.wback), at<float>(ws, t.xa), at<float>(ws, t.xb), at<float>(ws, t.partial), c.num_cus,
-             at<double>(ws, t.mlp_acc), at<double>(ws, t.attn_acc), at<double>(ws, t.dT_acc)};
+             at<double>(ws, t.dT_acc)};
   Saves sv{at<char>(ws, t.sx), at<char>(ws, t.smid), at<char>(ws, t.slast), t.layer_bytes,
            t.lse_layer ? at<float>(ws, t.slse) : nullptr, t.lse_layer};
   for (int64_t e0 = 0; e0 < B; e0 += t.chunk) {
@@ -396,8 +393,7 @@ extern "C" int32_t tdo_log_rho_jacobian(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   sv.last = at<char>(ws, osl);
   sv.lse = np.bf16 ? at<float>(ws, ose) : nullptr;
   NetWeights w = weights_at(ws, woff);
-  TDO_TRY(pack_weights(np, params, &w, stream));
-  TDO_TRY(launch_pack_backward(pp, params, np.bf16, at<char>(ws, owback), stream));
+  TDO_TRY(pack_weights(np, params, &w, stream, at<char>(ws, owback)));
   TDO_TRY(launch_jac_tables(params, pp.d, at<double>(ws, otab), stream));
   float *ga = at<float>(ws, oxa), *gb = at<float>(ws, oxb), *z = at<float>(ws, oz), *dF = at<float>(ws, odF);
   float *mp = at<float>(ws, omp), *ap = at<float>(ws, oap), *ep = at<float>(ws, oep);
@@ -462,17 +458,14 @@ int32_t loss_grad_run(Context& c, const NetPlan& np, const ModelDev& m, const Tr
                       double* grad, float* lloc_out, hipStream_t stream) {
   void* ws = c.ws;
   NetWeights w = weights_at(ws, t.woff);
-  TDO_TRY(pack_weights(np, params, &w, stream));
-  TDO_TRY(launch_pack_backward(np.pp, params, np.bf16, at<char>(ws, t.wback), stream));
+  TDO_TRY(pack_weights(np, params, &w, stream, at<char>(ws, t.wback)));
   const int64_t P = np.pp.nparams;
   double* gA = at<double>(ws, t.gA);
   double* acc = at<double>(ws, t.acc);
   float* Lall = lloc_out ? lloc_out : at<float>(ws, t.Lall);
-  TDO_TRY(fill(gA, P, 0.0, stream));
-  TDO_TRY(fill(at<double>(ws, t.dT_acc), 64LL * np.D, 0.0, stream));
-  TDO_TRY(fill(acc, 2, 0.0, stream));
+  TDO_TRY(fill(gA, (int64_t)(t.dT_acc - t.gA) / 8 + 64LL * np.D, 0.0, stream));  // gA, acc, dT_acc
   BwdBufs bb{at<char>(ws, t.wback), at<float>(ws, t.xa), at<float>(ws, t.xb), at<float>(ws, t.partial), c.num_cus,
-             at<double>(ws, t.mlp_acc), at<double>(ws, t.attn_acc), at<double>(ws, t.dT_acc)};
+             at<double>(ws, t.dT_acc)};
   Saves sv{at<char>(ws, t.sx), at<char>(ws, t.smid), at<char>(ws, t.slast), t.layer_bytes,
            t.lse_layer ? at<float>(ws, t.slse) : nullptr, t.lse_layer};
   const int64_t* Ed = at<int64_t>(ws, t.etot);

@@ -25,7 +25,7 @@ int32_t set_error(int32_t code, const char* fmt, ...) {
 }
 void clear_error() { g_err.clear(); }
 
-int32_t allow_full_lds(const void* kern) {
+int32_t allow_full_lds(const void* kern, size_t static_bytes) {
   static std::mutex mu;
   static std::vector<std::pair<const void*, int>> done;
   int dev = 0;
@@ -33,7 +33,7 @@ int32_t allow_full_lds(const void* kern) {
   std::lock_guard<std::mutex> g(mu);
   for (const auto& d : done)
     if (d.first == kern && d.second == dev) return TDO_OK;
-  TDO_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+  TDO_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(160 * 1024 - static_bytes)));
   done.emplace_back(kern, dev);
   return TDO_OK;
 }
@@ -287,6 +287,55 @@ int32_t run_forward(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg
   return TDO_OK;
 }
 
+StackArgs stack_args(const NetPlan& np, const NetWeights& w) {
+  StackArgs a{};
+  a.wpack = w.wpack;
+  a.b1 = w.b1;
+  a.b2 = w.b2;
+  a.table = w.table;
+  a.head_w = w.head_w;
+  a.head_b = w.head_b;
+  a.layer_elems = np.pp.layer_elems;
+  a.n = np.n;
+  a.cpb = np.cpb;
+  a.d_real = np.pp.d;
+  a.M = np.pp.M;
+  a.layers = np.pp.layers;
+  a.score_scale = np.score_scale;
+  return a;
+}
+
+// One launch for the whole network (bit-identical to layer by layer) where it measured faster
+// (microseconds, layers against one launch):
+//  - BF16, two layers or more, any batch: per proposal of 1024 chains at n = 32, benchmark network 77
+//    and 40, of 16 chains 40 and 24; log rho of 65536 configurations 2553 and 2206;
+//  - a single layer: the layer kernel keeps its weights and has nothing to fuse, so only while the
+//    batch has at most one tile per pair of waves (n = 20, mlp 96: per proposal of 1024 chains 22 and
+//    12, log rho of 65536 configurations 514 and 611);
+//  - FP32, width 32: per proposal at n = 8 40 and 27; width 64 reads the weights through the caches
+//    either way: faster with 8-wide heads and all CUs busy (1024 chains at n = 32: 304 and 274), not
+//    below that (157 and 181) or with 16-wide heads (log rho at n = 16: 3905 and 4111).
+bool stack_takes(const NetPlan& np, int64_t E) {
+  if (!stack_supported(np.bf16, np.D, np.pp.M, np.pp.layers, np.span)) return false;
+  const int64_t tiles = (E + np.cpb - 1) / np.cpb;  // pairs of waves
+  if (np.pp.layers == 1 && tiles > 4LL * np.num_cus) return false;
+  return np.bf16 || np.D == 32 || (np.DH == 8 && tiles > np.num_cus);
+}
+
+int32_t run_log_rho(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg, int64_t E, float* xa, float* xb, float* z,
+                    float* lr, hipStream_t st) {
+  if (stack_takes(np, E)) {
+    StackArgs a = stack_args(np, w);
+    a.ecfg = ecfg;
+    a.E = E;
+    a.lr = lr;
+    ProfScope ps(np.prof, "fwd_layer", st);
+    return launch_fwd_stack(a, np.bf16, np.D, np.DH, np.masked, 0, np.num_cus, st);
+  }
+  TDO_TRY(run_forward(np, w, ecfg, E, nullptr, xa, xb, nullptr, z, st));
+  return launch_symmetrise(nullptr, E, z, lr, st);
+}
+
 int32_t pack_weights(const NetPlan& np, const float* params, NetWeights* w, hipStream_t st, void* wback) {
   TDO_TRY(launch_pack(np.pp, params, np.bf16, w->wpack, wback, w->b1, w->b2, w->table, st));
   w->head_w = params + np.pp.off_head_w;
@@ -465,9 +514,8 @@ int32_t tdo_log_rho(tdo_ctx_t* ctx, const tdo_arch_t* arch, const float* params,
   TDO_TRY(pack_weights(np, params, &w, stream));
   for (int64_t e0 = 0; e0 < B; e0 += chunk) {
     const int64_t E = std::min(chunk, B - e0);
-    TDO_TRY(run_forward(np, w, cfg + 2 * e0, E, nullptr, at<float>(c.ws, oxa), at<float>(c.ws, oxb), nullptr,
-                        at<float>(c.ws, oz), stream));
-    TDO_TRY(launch_symmetrise(nullptr, E, at<float>(c.ws, oz), log_rho + 2 * e0, stream));
+    TDO_TRY(run_log_rho(np, w, cfg + 2 * e0, E, at<float>(c.ws, oxa), at<float>(c.ws, oxb), at<float>(c.ws, oz),
+                        log_rho + 2 * e0, stream));
   }
   return TDO_OK;
 }

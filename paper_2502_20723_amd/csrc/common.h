@@ -86,7 +86,8 @@ struct TuneEntry {
 // Allow a kernel the whole 160 KB LDS of a CU, once per kernel and device per
 // process (a host-side attribute, so later launches, also while a stream is
 // being recorded into a graph, need no further runtime call).
-int32_t allow_full_lds(const void* kern);
+// static_bytes: what the kernel declares itself.
+int32_t allow_full_lds(const void* kern, size_t static_bytes = 0);
 
 // ---------------------------------------------------------------- context
 struct Context {

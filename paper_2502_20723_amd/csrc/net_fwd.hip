@@ -16,28 +16,11 @@
 #include <algorithm>
 
 #include "common.h"
+#include "fwd_tile.h"
 #include "net.h"
 #include "netapi.h"
 
 namespace tdo {
-
-template <int D>
-struct EmbedRow {
-  // Window code of the two width-2 circular convolutions: x_i depends on
-  // sites i, i+1, i+2; code = t_i + 4 t_{i+1} + 16 t_{i+2},
-  // t = bit(channel 0) + 2 bit(channel 1).
-  __device__ static __forceinline__ int code(uint64_t c0, uint64_t c1, int i, int n) {
-    int cd = 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      int s = i + k;
-      s = s >= n ? s - n : s;
-      const int t = (int)((c0 >> s) & 1ull) + 2 * (int)((c1 >> s) & 1ull);
-      cd += t << (2 * k);
-    }
-    return cd;
-  }
-};
 
 // Workgroup size NT: BF16 weights staged in LDS are shared by 8 waves (two per SIMD,
 // so that one wave's latencies overlap the other's work) or by 4 waves (one per SIMD,
@@ -206,107 +189,7 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
     };
     if (a.save_x) save(a.save_x, x);
 
-    // ---- attention: operands of x taken before the residual is updated
-    op_t xo[NBR][NB][ST];
-#pragma unroll
-    for (int rb = 0; rb < NBR; ++rb)
-#pragma unroll
-      for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-        for (int s = 0; s < ST; ++s) xo[rb][ib][s] = P::op(x[rb][ib], s);
-
-#pragma unroll 1
-    for (int hb = 0; hb < NB; ++hb) {
-      f32x16 q[NBR], k[NBR], v[NBR];
-#pragma unroll
-      for (int rb = 0; rb < NBR; ++rb) {
-        q[rb] = f32x16{};
-        k[rb] = f32x16{};
-        v[rb] = f32x16{};
-#pragma unroll
-        for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-          for (int s = 0; s < ST; ++s) {
-            const int f = (hb * NB + ib) * ST + s;
-            q[rb] = P::mma(ld_frag<P>(Wq, f, lane), xo[rb][ib][s], q[rb]);
-            k[rb] = P::mma(ld_frag<P>(Wk, f, lane), xo[rb][ib][s], k[rb]);
-            v[rb] = P::mma(xo[rb][ib][s], ld_frag<P>(Wv, f, lane), v[rb]);  // (row x feature)
-          }
-      }
-      // score scale folded into q; per-head score operands of q and k packed once per head
-      // block; V as operands (lane -> feature)
-      using sop = typename P::template SOp<DH>;
-      sop qp[NBR][HPB], kp[NBR][HPB];
-#pragma unroll
-      for (int rb = 0; rb < NBR; ++rb) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) q[rb][r] *= sc;
-#pragma unroll
-        for (int j = 0; j < HPB; ++j) {
-          qp[rb][j] = P::template pack_head<DH>(q[rb], j);
-          kp[rb][j] = P::template pack_head<DH>(k[rb], j);
-        }
-      }
-      op_t vop[NBR][ST];
-#pragma unroll
-      for (int kb = 0; kb < NBR; ++kb)
-#pragma unroll
-        for (int s = 0; s < ST; ++s) vop[kb][s] = P::op(v[kb], s);
-      // o = P V per head, row-major (lane -> row, values -> features).  Each head's product goes
-      // into a fresh accumulator with the unmasked V operand (lane -> feature): only values
-      // [VPH j, VPH (j + 1)) of each lane (the features of head j, see tile_idx) are head j's
-      // output and are kept, normalised; the other values are dropped.
-      constexpr int VPH = DH / 2;
-      f32x16 o[NBR];
-      float lsev[NBR][HPB];  // log2 softmax normalisers of this lane's row in each row block
-#pragma unroll
-      for (int j = 0; j < HPB; ++j) {
-#pragma unroll
-        for (int qb = 0; qb < NBR; ++qb) {
-          f32x16 st[NBR];
-          float m = -INFINITY;
-#pragma unroll
-          for (int kb = 0; kb < NBR; ++kb) {
-            st[kb] = P::template scores_packed<DH>(kp[kb][j], qp[qb][j], f32x16{});
-            if constexpr (MASKED) {
-#pragma unroll
-              for (int r = 0; r < 16; ++r)
-                if (!((okbits[qb][kb] >> r) & 1u)) st[kb][r] = -INFINITY;
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) m = fmaxf(m, st[kb][r]);
-          }
-          m = xor32_max(m);
-          const float mm = (m == -INFINITY) ? 0.f : m;  // a row with no key keeps P = 0
-#pragma unroll
-          for (int kb = 0; kb < NBR; ++kb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) st[kb][r] = __builtin_amdgcn_exp2f(st[kb][r] - mm);
-          // row sum as a pairwise tree (short dependency chains)
-          float part[NBR * 8];
-#pragma unroll
-          for (int kb = 0; kb < NBR; ++kb)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) part[8 * kb + i] = st[kb][2 * i] + st[kb][2 * i + 1];
-#pragma unroll
-          for (int w = NBR * 4; w >= 1; w /= 2)
-#pragma unroll
-            for (int i = 0; i < w; ++i) part[i] += part[i + w];
-          const float l = xor32_sum(part[0]);
-          // l >= 1 when the row has a key (its maximum contributes exp2(0)): the hardware
-          // reciprocal (1 ulp) replaces the division sequence
-          const float invl = l > 0.f ? __builtin_amdgcn_rcpf(l) : 0.f;
-          // for the backward: P = exp2(s - lse) (+inf for a row with no key, so that P = 0)
-          lsev[qb][j] = l > 0.f ? mm + __builtin_amdgcn_logf(l) : INFINITY;
-          f32x16 to = {};
-#pragma unroll
-          for (int kb = 0; kb < NBR; ++kb)
-#pragma unroll
-            for (int s = 0; s < ST; ++s) to = P::mma(vop[kb][s], P::op(st[kb], s), to);
-#pragma unroll
-          for (int r = VPH * j; r < VPH * (j + 1); ++r) o[qb][r] = to[r] * invl;
-        }
-      }
+    tile_attention<P, D, DH, NBR, MASKED>(x, Wq, Wk, Wv, Wo, okbits, sc, lane, [&](int hb, const float (&lsev)[NBR][HPB]) {
       if constexpr (P::KPL == 8) {
         // the head block's normalisers are contiguous per row; one store per lane of the first
         // half (the second half's offset is out of range, and the resource is empty when nothing
@@ -320,79 +203,10 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
           else rst2(rl, off, make_float2(lsev[qb][0], lsev[qb][1]));
         }
       }
-      // W_O into the residual
-#pragma unroll
-      for (int qb = 0; qb < NBR; ++qb) {
-#pragma unroll
-        for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-          for (int s = 0; s < ST; ++s)
-            x[qb][ob] = P::mma(ld_frag<P>(Wo, (ob * NB + hb) * ST + s, lane), P::op(o[qb], s), x[qb][ob]);
-      }
-    }
+    });
     if (a.save_mid) save(a.save_mid, x);
 
-    // ---- feed-forward sub-layer: x += relu(x W1 + b1) W2 + b2
-#pragma unroll
-    for (int rb = 0; rb < NBR; ++rb)
-#pragma unroll
-      for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-        for (int s = 0; s < ST; ++s) xo[rb][ib][s] = P::op(x[rb][ib], s);
-    // pre-activations of 32-unit chunk c: the products accumulate onto b1 (values
-    // r = 4q .. 4q+3 hold 4 consecutive hidden units)
-    auto ffn_pre = [&](int c, int rb) {
-      f32x16 u;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 b = *reinterpret_cast<const float4*>(b1s + 32 * c + 8 * q + 4 * h);
-        u[4 * q] = b.x; u[4 * q + 1] = b.y; u[4 * q + 2] = b.z; u[4 * q + 3] = b.w;
-      }
-#pragma unroll
-      for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-        for (int s = 0; s < ST; ++s) u = P::mma(ld_frag<P>(W1, (c * NB + ib) * ST + s, lane), xo[rb][ib][s], u);
-      return u;
-    };
-    // One row block: software-pipelined over the chunks, chunk c+1's pre-activation products
-    // issued before chunk c's ReLU and conversions, which then overlap them on the vector ALU
-    // (two row blocks: chunk by chunk, a second chunk in flight would not fit in the
-    // registers).  Each accumulator of x takes the chunks in order either way.
-    if constexpr (SPAN) {
-#pragma unroll
-      for (int c = 0; c < MB; ++c)
-#pragma unroll
-        for (int rb = 0; rb < NBR; ++rb) {
-          const f32x16 u = ffn_pre(c, rb);
-#pragma unroll
-          for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-            for (int s = 0; s < ST; ++s)
-              x[rb][ob] = P::mma(ld_frag<P>(W2, (ob * MB + c) * ST + s, lane), P::relu_op(u, s), x[rb][ob]);
-        }
-    } else {
-      constexpr int rb = 0;
-      f32x16 un = ffn_pre(0, rb);
-#pragma unroll
-      for (int c = 0; c < MB; ++c) {
-        const f32x16 u = un;
-        if (c + 1 < MB) un = ffn_pre(c + 1, rb);
-        op_t uo[ST];
-#pragma unroll
-        for (int s = 0; s < ST; ++s) uo[s] = P::relu_op(u, s);
-#pragma unroll
-        for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-          for (int s = 0; s < ST; ++s)
-            x[rb][ob] = P::mma(ld_frag<P>(W2, (ob * MB + c) * ST + s, lane), uo[s], x[rb][ob]);
-      }
-    }
-#pragma unroll
-    for (int rb = 0; rb < NBR; ++rb)
-#pragma unroll
-      for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) x[rb][ob][r] += b2s[32 * ob + tile_idx(r, h)];
+    tile_ffn<P, D, NBR>(x, W1, W2, b1s, b2s, MB, lane);
 
     if (!a.last) {
 #pragma unroll
@@ -408,35 +222,9 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
     }
     // ---- last layer: save x_L, mean pooling over sites, dense head to z (Eq. global-pool-final)
     if (a.save_last) save(a.save_last, x);
-    // per row: F = x_L W_h (features past d hold zero weights), summed over both lane halves
-    float f0[NBR], f1[NBR];
-#pragma unroll
-    for (int rb = 0; rb < NBR; ++rb) {
-      float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-      for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float2 hw = hws[32 * ob + tile_idx(r, h)];
-          s0 += x[rb][ob][r] * hw.x;
-          s1 += x[rb][ob][r] * hw.y;
-        }
-      f0[rb] = xor32_sum(s0);
-      f1[rb] = xor32_sum(s1);
-    }
-    // mean over the n sites of each configuration: a segmented inclusive scan over the 32 row
-    // lanes (segment = the configuration's rows; rows past the last configuration add nothing),
-    // a fixed order of additions; the last row of each segment then holds its sum
+    float v0, v1;
     const int seg = SPAN ? 0 : lr / n, pos = SPAN ? lr : lr - seg * n;
-    float v0 = 0.f, v1 = 0.f;
-#pragma unroll
-    for (int rb = 0; rb < NBR; ++rb)
-      if (rvalid[rb]) { v0 += f0[rb]; v1 += f1[rb]; }
-#pragma unroll
-    for (int dd = 1; dd < 32; dd <<= 1) {
-      const float t0 = __shfl_up(v0, dd, 32), t1 = __shfl_up(v1, dd, 32);
-      if (pos >= dd) { v0 += t0; v1 += t1; }
-    }
+    tile_head<NBR, NB>(x, hws, rvalid, pos, h, v0, v1);
     const int last = SPAN ? 31 : n - 1;  // in a spanning tile every lane's rows are one configuration
     if (h == 0 && pos == last && (SPAN || seg < cpb)) {
       const int64_t e = e0 + seg;
@@ -449,21 +237,13 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
   }
 }
 
-// log rho = log(e^{z1} + conj(e^{z2})) on the principal branch (Eq. log_sum_exp_conjugate).
 __global__ void k_symmetrise(const int64_t* __restrict__ E_dev, int64_t E_host, const float* __restrict__ z,
                              float* __restrict__ lr) {
   const int64_t E = E_dev ? *E_dev : E_host;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E; e += (int64_t)gridDim.x * blockDim.x) {
-    const float a0 = z[4 * e], a1 = z[4 * e + 1];   // z(alpha, beta)
-    const float b0 = z[4 * e + 2], b1 = z[4 * e + 3];  // z(beta, alpha), conjugated below
-    const float mx = fmaxf(a0, b0);
-    const float ea = expf(a0 - mx), eb = expf(b0 - mx);
-    float sa, ca, sb, cb;
-    sincosf(a1, &sa, &ca);
-    sincosf(b1, &sb, &cb);
-    const float sr = ea * ca + eb * cb, si = ea * sa - eb * sb;
-    lr[2 * e] = mx + 0.5f * logf(sr * sr + si * si);
-    lr[2 * e + 1] = atan2f(si, sr);
+    const float2 v = symmetrise(z[4 * e], z[4 * e + 1], z[4 * e + 2], z[4 * e + 3]);
+    lr[2 * e] = v.x;
+    lr[2 * e + 1] = v.y;
   }
 }
 

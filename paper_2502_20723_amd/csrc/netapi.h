@@ -29,6 +29,25 @@ struct FwdArgs {
   int waves;                    // waves per workgroup (8; or 4, BF16 only)
 };
 
+// The whole forward in one launch (net_stack.hip), n <= 32.  mode 0: lr of the E configurations ecfg;
+// 1: `steps` proposals of the E chains on (alpha, beta); 2: of the diagonal chains.
+struct StackArgs {
+  const void* wpack;
+  const float *b1, *b2, *table, *head_w, *head_b;
+  const uint64_t* ecfg;
+  int64_t E, layer_elems;
+  float* lr;         // [E][2]
+  uint64_t* state;   // chains: [E][2] (mode 2: [E]), their log rho, and the states after the last proposal
+  float* state_lr;
+  uint64_t* record;
+  uint64_t t0, seed, pair_thr;
+  int steps, n, cpb, d_real, M, layers;
+  int pairs;  // pairs of waves that compute, per workgroup (set by the launcher)
+  float score_scale;
+};
+bool stack_supported(bool bf16, int D, int M, int layers, bool span);
+int32_t launch_fwd_stack(const StackArgs& a, bool bf16, int D, int DH, bool masked, int mode, int num_cus, hipStream_t st);
+
 int32_t launch_fwd_layer(const FwdArgs& a, bool bf16, int D, int DH, bool span, int num_cus, hipStream_t st);
 int32_t launch_symmetrise(const int64_t* E_dev, int64_t E_host, const float* z, float* lr, hipStream_t st);
 

@@ -97,9 +97,8 @@ extern "C" int32_t tdo_log_rho_noalloc(tdo_ctx_t* ctx, const tdo_arch_t* arch, c
   TDO_TRY(pack_weights(np, params, &w, stream));
   for (int64_t e0 = 0; e0 < B; e0 += chunk) {
     const int64_t E = std::min(chunk, B - e0);
-    TDO_TRY(run_forward(np, w, cfg + 2 * e0, E, nullptr, at<float>(base, oxa), at<float>(base, oxb), nullptr,
-                        at<float>(base, oz), stream));
-    TDO_TRY(launch_symmetrise(nullptr, E, at<float>(base, oz), log_rho + 2 * e0, stream));
+    TDO_TRY(run_log_rho(np, w, cfg + 2 * e0, E, at<float>(base, oxa), at<float>(base, oxb), at<float>(base, oz),
+                        log_rho + 2 * e0, stream));
   }
   return TDO_OK;
 }

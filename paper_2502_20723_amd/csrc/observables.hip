@@ -265,9 +265,7 @@ int32_t tdo_observables(tdo_ctx_t* ctx, const tdo_arch_t* arch, const float* par
     const int64_t E = S * (n + 1);
     hipLaunchKernelGGL(k_obs_rows, dim3(grid_for(E)), dim3(256), 0, stream, alpha + s0, S, (int)n, cfg);
     TDO_HIP(hipGetLastError());
-    TDO_TRY(run_forward(np, w, cfg, E, nullptr, at<float>(ws, rp.oxa), at<float>(ws, rp.oxb), nullptr,
-                        at<float>(ws, rp.oz), stream));
-    TDO_TRY(launch_symmetrise(nullptr, E, at<float>(ws, rp.oz), lr, stream));
+    TDO_TRY(run_log_rho(np, w, cfg, E, at<float>(ws, rp.oxa), at<float>(ws, rp.oxb), at<float>(ws, rp.oz), lr, stream));
     hipLaunchKernelGGL(k_obs_local, dim3(grid_for(S)), dim3(256), 0, stream, lr, alpha + s0, S, (int)n,
                        log_rho_diag + 2 * s0, local + 6 * s0, local_site ? local_site + 6 * s0 * n : nullptr);
     TDO_HIP(hipGetLastError());
@@ -308,9 +306,7 @@ int32_t tdo_purity(tdo_ctx_t* ctx, const tdo_arch_t* arch, const float* params, 
     const int64_t E = 3 * Q;
     hipLaunchKernelGGL(k_pur_rows, dim3(grid_for(Q)), dim3(256), 0, stream, alpha + p0, beta + p0, Q, cfg);
     TDO_HIP(hipGetLastError());
-    TDO_TRY(run_forward(np, w, cfg, E, nullptr, at<float>(ws, rp.oxa), at<float>(ws, rp.oxb), nullptr,
-                        at<float>(ws, rp.oz), stream));
-    TDO_TRY(launch_symmetrise(nullptr, E, at<float>(ws, rp.oz), lr, stream));
+    TDO_TRY(run_log_rho(np, w, cfg, E, at<float>(ws, rp.oxa), at<float>(ws, rp.oxb), at<float>(ws, rp.oz), lr, stream));
     hipLaunchKernelGGL(k_pur_terms, dim3(grid_for(Q)), dim3(256), 0, stream, lr, Q, term + p0, sgn + p0);
     TDO_HIP(hipGetLastError());
   }

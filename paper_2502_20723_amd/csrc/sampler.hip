@@ -27,61 +27,19 @@
 #include <algorithm>
 
 #include "common.h"
+#include "metropolis.h"
 #include "netapi.h"
 #include "train.h"
 
 namespace tdo {
 
-namespace {
-
-struct Philox4x32 {
-  uint32_t c[4];
-};
-
-// Philox4x32 with 10 rounds: each round forms the 64-bit products of counter
-// words 0 and 2 with the two round multipliers, then mixes their high halves
-// with counter words 1 and 3 and the round key; the key is bumped by the two
-// Weyl increments between rounds.
-__device__ __forceinline__ Philox4x32 philox10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
-                                               uint32_t k1) {
-  constexpr uint32_t kMul0 = 0xD2511F53u, kMul1 = 0xCD9E8D57u;
-  constexpr uint32_t kWeyl0 = 0x9E3779B9u, kWeyl1 = 0xBB67AE85u;
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    const uint64_t p0 = (uint64_t)kMul0 * c0, p1 = (uint64_t)kMul1 * c2;
-    const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
-    const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
-    const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
-    c0 = n0;
-    c1 = lo1;
-    c2 = n2;
-    c3 = lo0;
-    k0 += kWeyl0;
-    k1 += kWeyl1;
-  }
-  return Philox4x32{{c0, c1, c2, c3}};
-}
-
-}  // namespace
-
 __global__ void k_propose(const uint64_t* __restrict__ state, int64_t C, int64_t chain0, int n, uint64_t t,
                           uint64_t seed, uint64_t pair_thr, uint64_t* __restrict__ prop, double* __restrict__ u) {
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < C; c += (int64_t)gridDim.x * blockDim.x) {
-    const Philox4x32 r = philox10((uint32_t)t, (uint32_t)(t >> 32), (uint32_t)(chain0 + c), 0u, (uint32_t)seed,
-                                  (uint32_t)(seed >> 32));
     uint64_t a = state[2 * c], b = state[2 * c + 1];
-    if ((uint64_t)r.c[0] < pair_thr) {
-      const int i = (int)(((uint64_t)r.c[1] * (uint64_t)n) >> 32);
-      a ^= 1ull << i;
-      b ^= 1ull << i;
-    } else {
-      const int j = (int)(((uint64_t)r.c[1] * (uint64_t)(2 * n)) >> 32);
-      if (j < n) a ^= 1ull << j;
-      else b ^= 1ull << (j - n);
-    }
+    u[c] = propose_move(a, b, n, t, (uint32_t)(chain0 + c), seed, pair_thr);
     prop[2 * c] = a;
     prop[2 * c + 1] = b;
-    u[c] = ((double)r.c[2] + 0.5) * 0x1p-32;
   }
 }
 
@@ -91,8 +49,7 @@ __global__ void k_accept(int64_t C, const uint64_t* __restrict__ prop, const dou
                          const float* __restrict__ lrp, uint64_t* __restrict__ state, float* __restrict__ state_lr,
                          uint64_t* __restrict__ record) {
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < C; c += (int64_t)gridDim.x * blockDim.x) {
-    const double ratio = exp(2.0 * ((double)lrp[2 * c] - (double)state_lr[2 * c]));
-    if (u[c] < ratio) {
+    if (u[c] < accept_ratio(lrp[2 * c], state_lr[2 * c], false)) {
       state[2 * c] = prop[2 * c];
       state[2 * c + 1] = prop[2 * c + 1];
       state_lr[2 * c] = lrp[2 * c];
@@ -108,13 +65,10 @@ __global__ void k_accept(int64_t C, const uint64_t* __restrict__ prop, const dou
 __global__ void k_propose_diag(const uint64_t* __restrict__ state, int64_t C, int64_t chain0, int n, uint64_t t,
                                uint64_t seed, uint64_t* __restrict__ prop, double* __restrict__ u) {
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < C; c += (int64_t)gridDim.x * blockDim.x) {
-    const Philox4x32 r = philox10((uint32_t)t, (uint32_t)(t >> 32), (uint32_t)(chain0 + c), 1u, (uint32_t)seed,
-                                  (uint32_t)(seed >> 32));
-    const int i = (int)(((uint64_t)r.c[1] * (uint64_t)n) >> 32);
-    const uint64_t a = state[c] ^ (1ull << i);
+    uint64_t a = state[c];
+    u[c] = propose_diag(a, n, t, (uint32_t)(chain0 + c), seed);
     prop[2 * c] = a;
     prop[2 * c + 1] = a;
-    u[c] = ((double)r.c[2] + 0.5) * 0x1p-32;
   }
 }
 
@@ -123,8 +77,7 @@ __global__ void k_accept_diag(int64_t C, const uint64_t* __restrict__ prop, cons
                               const float* __restrict__ lrp, uint64_t* __restrict__ state,
                               float* __restrict__ state_lr, uint64_t* __restrict__ record) {
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < C; c += (int64_t)gridDim.x * blockDim.x) {
-    const double ratio = exp((double)lrp[2 * c] - (double)state_lr[2 * c]);
-    if (u[c] < ratio) {
+    if (u[c] < accept_ratio(lrp[2 * c], state_lr[2 * c], true)) {
       state[c] = prop[2 * c];
       state_lr[2 * c] = lrp[2 * c];
       state_lr[2 * c + 1] = lrp[2 * c + 1];
@@ -203,6 +156,23 @@ extern "C" int32_t tdo_sample(tdo_ctx_t* ctx, const tdo_arch_t* arch, const floa
   uint64_t* prop = at<uint64_t>(ws, oprop);
   double* u = at<double>(ws, ou);
   float* lrp = at<float>(ws, olr);
+  if (stack_takes(np, chains)) {  // one launch per sweep
+    StackArgs a = stack_args(np, w);
+    a.E = chains;
+    a.state = state;
+    a.state_lr = state_log_rho;
+    a.seed = seed;
+    a.pair_thr = pair_thr;
+    a.steps = 2 * n;
+    for (int32_t s = 0; s < sweeps; ++s) {
+      a.t0 = *counter + (uint64_t)s * 2u * (uint64_t)n;
+      a.record = samples + (size_t)s * chains * 2;
+      ProfScope ps(np.prof, "fwd_layer", stream);
+      TDO_TRY(launch_fwd_stack(a, np.bf16, np.D, np.DH, np.masked, 1, np.num_cus, stream));
+    }
+    *counter += per_call;
+    return TDO_OK;
+  }
   for (int64_t c0 = 0; c0 < chains; c0 += chunk) {
     const int64_t Cc = std::min(chunk, chains - c0);
     const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(Cc, 256), 4096);
@@ -258,6 +228,22 @@ extern "C" int32_t tdo_sample_diag(tdo_ctx_t* ctx, const tdo_arch_t* arch, const
   uint64_t* prop = at<uint64_t>(ws, cw.oprop);
   double* u = at<double>(ws, cw.ou);
   float* lrp = at<float>(ws, cw.olr);
+  if (stack_takes(np, chains)) {  // one launch per sweep
+    StackArgs a = stack_args(np, w);
+    a.E = chains;
+    a.state = state;
+    a.state_lr = state_log_rho;
+    a.seed = seed;
+    a.steps = n;
+    for (int32_t s = 0; s < sweeps; ++s) {
+      a.t0 = *counter + (uint64_t)s * (uint64_t)n;
+      a.record = samples + (size_t)s * chains;
+      ProfScope ps(np.prof, "fwd_layer", stream);
+      TDO_TRY(launch_fwd_stack(a, np.bf16, np.D, np.DH, np.masked, 2, np.num_cus, stream));
+    }
+    *counter += per_call;
+    return TDO_OK;
+  }
   for (int64_t c0 = 0; c0 < chains; c0 += cw.chunk) {
     const int64_t Cc = std::min(cw.chunk, chains - c0);
     const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(Cc, 256), 4096);

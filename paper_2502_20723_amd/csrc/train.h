@@ -91,4 +91,11 @@ NetWeights weights_at(void* ws, const size_t* offs);
 int32_t run_forward(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg, int64_t E, const int64_t* E_dev,
                     float* xa, float* xb, const Saves* sv, float* z, hipStream_t st);
 
+// Whether E configurations (or chains) go through the whole network in one launch (net_stack.hip).
+bool stack_takes(const NetPlan& np, int64_t E);
+StackArgs stack_args(const NetPlan& np, const NetWeights& w);
+// lr [E][2] of the configurations ecfg; xa, xb, z: scratch of run_forward.
+int32_t run_log_rho(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg, int64_t E, float* xa, float* xb, float* z,
+                    float* lr, hipStream_t st);
+
 }  // namespace tdo

@@ -61,17 +61,18 @@ __global__ void __launch_bounds__(256) k_jac_head(const void* __restrict__ save_
     return v;
   };
 #pragma unroll
-  for (int ob = 0; ob < NB; ++ob)
+  for (int ob = 0; ob < NB; ++ob) {
+    const f32x16 v = load_tile(xs + ob * 1024, lane);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float v = (float)xs[(ob * 64 + lane) * 16 + r];
-      const double u0 = sum32((double)(v * s0)), u1 = sum32((double)(v * s1));
+      const double u0 = sum32((double)(v[r] * s0)), u1 = sum32((double)(v[r] * s1));
       const int f = 32 * ob + tile_idx(r, h);
       if (lr == 0) {
         red[wave][2 * f] = u0;
         red[wave][2 * f + 1] = u1;
       }
     }
+  }
   const double c0 = sum32(h == 0 ? (double)s0 : 0.0), c1 = sum32(h == 0 ? (double)s1 : 0.0);
   if (lane == 0) {
     red[wave][2 * D] = c0;

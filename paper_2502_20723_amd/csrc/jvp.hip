@@ -40,7 +40,7 @@ __device__ __forceinline__ float gelu_d(float u) {
 // Order of the activations and weights here.  Value r of lane half h of a 32-feature tile is
 // feature 2 r + h, and lane m holds row asc(m) of its 32-row block: the products take operand pairs
 // (2 i, 2 i + 1) in turn, so features, keys and hidden units all come in ascending order.  A tile
-// in memory holds its 16 values per lane in that order; position pos(f) is feature f's.
+// in memory holds its 16 values per lane in that order (load_tile); pos(f) is feature f's position in a row.
 __device__ __forceinline__ int asc(int m) { return 8 * (m >> 3) + 2 * (m & 3) + ((m >> 2) & 1); }
 __host__ __device__ inline int pos(int f) { return (f & ~31) + 16 * (f & 1) + ((f & 31) >> 1); }
 
@@ -106,13 +106,13 @@ __global__ void __launch_bounds__(256) k_jvp_embed(const uint64_t* __restrict__ 
       }
     }
     for (int ib = 0; ib < NB; ++ib) {
-      const int64_t o = ((g * NB + ib) * 64 + lane) * 16;
+      const int64_t o = (g * NB + ib) * 1024;
       const float4* t = reinterpret_cast<const float4*>(T + code * D + 32 * ib + 16 * h);
       const float4* td = reinterpret_cast<const float4*>(Td + code * D + 32 * ib + 16 * h);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        reinterpret_cast<float4*>(X + o)[q] = valid ? t[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-        reinterpret_cast<float4*>(Xd + o)[q] = valid ? td[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+        reinterpret_cast<float4*>(X + o)[64 * q + lane] = valid ? t[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+        reinterpret_cast<float4*>(Xd + o)[64 * q + lane] = valid ? td[q] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
     }
   }
@@ -153,7 +153,7 @@ __global__ void k_jvp_pack(const float* __restrict__ params, const double* __res
 
 struct JvpArgs {
   const float *w, *wd;  // packed layer and its tangent (k_jvp_pack)
-  float *x, *xd;        // residual stream and its tangent, [blocks][D/32][64][16], in place
+  float *x, *xd;        // residual stream and its tangent, [blocks][D/32] tiles (load_tile), in place
   int64_t E;
   int n, cpb, masked, heads, M;
   float scale;
@@ -229,7 +229,7 @@ __global__ void __launch_bounds__(512) k_jvp_layer(JvpArgs a) {
     const bool live = base + wave < nblk;
     if (!SPAN && !live) continue;
     const int64_t g = live ? base + wave : base + (wave & 1);  // a spanning pass's waves all meet at the barriers
-    float *xb = a.x + (g * NB * 64 + lane) * 16, *xdb = a.xd + (g * NB * 64 + lane) * 16;  // feature block ib at 1024 ib
+    float *xb = a.x + g * NB * 1024, *xdb = a.xd + g * NB * 1024;  // feature block ib at 1024 ib
     f32x16 y[NB], yd[NB];
 #pragma unroll
     for (int ob = 0; ob < NB; ++ob) y[ob] = yd[ob] = f32x16{};
@@ -243,8 +243,8 @@ __global__ void __launch_bounds__(512) k_jvp_layer(JvpArgs a) {
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
             const int f = (hb * NB + ib) * 4 + s;
-            const f32x4 xo = *reinterpret_cast<const f32x4*>(xb + 1024 * ib + 4 * s);
-            const f32x4 xdo = *reinterpret_cast<const f32x4*>(xdb + 1024 * ib + 4 * s);
+            const f32x4 xo = *reinterpret_cast<const f32x4*>(xb + 1024 * ib + 256 * s + 4 * lane);
+            const f32x4 xdo = *reinterpret_cast<const f32x4*>(xdb + 1024 * ib + 256 * s + 4 * lane);
             const f32x4 w = ld_frag<P>(W[m], f, lane);
             c = P::mma(w, xo, c);
             cd = P::mma(w, xdo, cd);
@@ -337,7 +337,7 @@ __global__ void __launch_bounds__(512) k_jvp_layer(JvpArgs a) {
     f32x16 z[NB], zd[NB];
 #pragma unroll
     for (int ob = 0; ob < NB; ++ob) {
-      const f32x16 x = load16(xb + 1024 * ob), xd = load16(xdb + 1024 * ob);
+      const f32x16 x = load_tile(xb + 1024 * ob, lane), xd = load_tile(xdb + 1024 * ob, lane);
 #pragma unroll
       for (int r = 0; r < 16; ++r) { y[ob][r] += x[r]; yd[ob][r] += xd[r]; }
       z[ob] = zd[ob] = f32x16{};
@@ -379,8 +379,8 @@ __global__ void __launch_bounds__(512) k_jvp_layer(JvpArgs a) {
         const f32x16 b = load16(b1 + M + 32 * ob + 16 * h), bd = load16(b1d + M + 32 * ob + 16 * h);
 #pragma unroll
         for (int r = 0; r < 16; ++r) { z[ob][r] = (z[ob][r] + b[r]) + y[ob][r]; zd[ob][r] = (zd[ob][r] + bd[r]) + yd[ob][r]; }
-        store16(xb + 1024 * ob, z[ob]);
-        store16(xdb + 1024 * ob, zd[ob]);
+        store_tile(xb + 1024 * ob, lane, z[ob]);
+        store_tile(xdb + 1024 * ob, lane, zd[ob]);
       }
   }
 }
@@ -399,11 +399,12 @@ __global__ void __launch_bounds__(256) k_jvp_head(int64_t E, int n, int cpb, int
     for (int rb = 0; rb < RB; ++rb) {
       float f0 = 0.f, f1 = 0.f, g0 = 0.f, g1 = 0.f;
       for (int ib = 0; ib < NB; ++ib) {
-        const int64_t o = (((t * RB + rb) * NB + ib) * 64 + lane) * 16;
+        const f32x16 xt = load_tile(X + ((t * RB + rb) * NB + ib) * 1024, lane), xdt = load_tile(Xd + ((t * RB + rb) * NB + ib) * 1024, lane);
+#pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int f = 32 * ib + 2 * r + h;
           if (f >= d) continue;
-          const float x = X[o + r], xd = Xd[o + r], w0 = hw[2 * f], w1 = hw[2 * f + 1];
+          const float x = xt[r], xd = xdt[r], w0 = hw[2 * f], w1 = hw[2 * f + 1];
           f0 += x * w0;
           f1 += x * w1;
           g0 += xd * w0 + x * (float)hwd[2 * f];

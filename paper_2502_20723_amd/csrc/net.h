@@ -213,6 +213,41 @@ __device__ __forceinline__ float xor32_max(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// Activations and gradients in memory: a 32x32 tile is 4 (FP32) or 2 (BF16) pieces of 64 lanes x 16
+// bytes, piece q holding values 4 q .. 4 q + 3 (8 q .. 8 q + 7) of every lane, so that each load or
+// store of a wave covers 1 KB of consecutive bytes.  With the 16 values of a lane together instead, every
+// instruction touched all lines of the tile by 16 bytes each: a plain copy of such tiles ran at
+// 4.5 TB/s against 5.5, and writes alone at 3.6 against 5.7.
+__device__ __forceinline__ f32x16 load_tile(const float* tile, int lane) {
+  f32x16 v;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float4 t = reinterpret_cast<const float4*>(tile)[64 * q + lane];
+    v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
+  }
+  return v;
+}
+__device__ __forceinline__ f32x16 load_tile(const __bf16* tile, int lane) {
+  f32x16 v;
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const bf16x8 t = reinterpret_cast<const bf16x8*>(tile)[64 * s + lane];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[8 * s + r] = (float)t[r];
+  }
+  return v;
+}
+__device__ __forceinline__ void store_tile(float* tile, int lane, const f32x16& v) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    reinterpret_cast<float4*>(tile)[64 * q + lane] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+}
+__device__ __forceinline__ void store_tile(__bf16* tile, int lane, const f32x16& v) {
+  const bf16x8 o[2] = {cvt8(v, 0), cvt8(v, 1)};
+#pragma unroll
+  for (int s = 0; s < 2; ++s) reinterpret_cast<bf16x8*>(tile)[64 * s + lane] = o[s];
+}
+
 // Bounded global access through a buffer resource over [p, p + bytes): loads outside it
 // return 0 and stores outside it are dropped by the hardware.  A wave can then keep one
 // unconditional sequence of memory operations (bytes = 0 disables them): the loads and

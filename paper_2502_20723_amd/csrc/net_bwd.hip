@@ -67,25 +67,6 @@ __device__ __forceinline__ f32x16 transpose_tile(const f32x16& v, float* sc, int
   return o;
 }
 
-template <class T>
-__device__ __forceinline__ void load_tile(const T* src, f32x16& v) {
-#pragma unroll
-  for (int r = 0; r < 16; ++r) v[r] = (float)src[r];
-}
-__device__ __forceinline__ void load_tile(const float* src, f32x16& v) {
-  const float4* p = reinterpret_cast<const float4*>(src);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float4 t = p[q];
-    v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
-  }
-}
-__device__ __forceinline__ void store_tile(float* dst, const f32x16& v) {
-  float4* p = reinterpret_cast<float4*>(dst);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) p[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-}
-
 // ------------------------------------------------------------------ MLP backward
 // Row of a 32-row block that lane m takes as the row operand of (row x hidden) products, so that
 // value r of lane half h of the result is row nat_idx(r, h): the products over rows then take the
@@ -194,11 +175,11 @@ __global__ void __launch_bounds__(512) k_bwd_mlp(BwdArgs a) {
       if (j < NBK * NB) {
         const auto r = rsrc(reinterpret_cast<const save_t*>(a.save_mid) + (g * NB + jj % NB) * 64 * 16, ok ? 64 * 16 * sizeof(save_t) : 0);
 #pragma unroll
-        for (int k = 0; k < (BF ? 2 : 4); ++k) pre[q][k] = rld4(r, lane * 16 * (int)sizeof(save_t) + 16 * k);
+        for (int k = 0; k < (BF ? 2 : 4); ++k) pre[q][k] = rld4(r, lane * 16 + 1024 * k);
       } else if constexpr (!SEEDS) {
         const auto r = rsrc(a.g_in + (g * NB + jj % NB) * 64 * 16, ok ? 64 * 16 * 4 : 0);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) pre[q][k] = rld4(r, lane * 64 + 16 * k);
+        for (int k = 0; k < 4; ++k) pre[q][k] = rld4(r, lane * 16 + 1024 * k);
       } else {
         float s0 = 0.f, s1 = 0.f;
         if (ok) {
@@ -364,7 +345,7 @@ __global__ void __launch_bounds__(512) k_bwd_mlp(BwdArgs a) {
           }
           acc = P::mma(ld_frag<P>(W1T, (ob * MB + c) * ST + s, lane), d, acc);
         }
-      store_tile(a.g_out + (((b0 + blk) * NB + ob) * 64 + lane) * 16, acc);
+      store_tile(a.g_out + ((b0 + blk) * NB + ob) * 1024, lane, acc);
     }
     barrier_lds();
   }
@@ -542,11 +523,11 @@ __global__ void __launch_bounds__(512) k_bwd_attn(BwdArgs a) {
     if (wave < 4) {
       const auto r = rsrc(reinterpret_cast<const save_t*>(a.save_x) + (g * NB + sob) * 64 * 16, g < nblk ? 64 * 16 * sizeof(save_t) : 0);
 #pragma unroll
-      for (int k = 0; k < (BF ? 2 : 4); ++k) pre[k] = rld4(r, lane * 16 * (int)sizeof(save_t) + 16 * k);
+      for (int k = 0; k < (BF ? 2 : 4); ++k) pre[k] = rld4(r, lane * 16 + 1024 * k);
     } else {
       const auto r = rsrc(a.g_in + (g * NB + sob) * 64 * 16, g < nblk ? 64 * 16 * 4 : 0);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) pre[k] = rld4(r, lane * 64 + 16 * k);
+      for (int k = 0; k < 4; ++k) pre[k] = rld4(r, lane * 16 + 1024 * k);
     }
   };
   auto stage = [&]() {
@@ -755,7 +736,7 @@ __global__ void __launch_bounds__(512) k_bwd_attn(BwdArgs a) {
                         rowop(slot(jb, 1), TS, lr, 0, s), ld_frag<P>(Wb + 2 * D * D, f, lane), rowop(slot(jb, 2), TS, lr, 0, s), acc);
         }
       }
-      store_tile(a.g_out + (((b0 + sblk) * NB + sob) * 64 + lane) * 16, acc);
+      store_tile(a.g_out + ((b0 + sblk) * NB + sob) * 1024, lane, acc);
     }
     barrier_lds();
   }
@@ -816,8 +797,7 @@ __global__ void __launch_bounds__(256) k_bwd_head(const void* __restrict__ save_
     if (h == 0) { c0 += s0; c1 += s1; }
 #pragma unroll
     for (int ob = 0; ob < NB; ++ob) {
-      f32x16 v;
-      load_tile(xs + ((g * NB + ob) * 64 + lane) * 16, v);
+      const f32x16 v = load_tile(xs + (g * NB + ob) * 1024, lane);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         a0[ob][r] += (double)(v[r] * s0);
@@ -945,13 +925,7 @@ __global__ void __launch_bounds__(256) k_embed_onehot(const float* __restrict__ 
     __builtin_amdgcn_wave_barrier();  // codes read before the next block's codes are written
 #pragma unroll
     for (int ft = 0; ft < NB; ++ft) {
-      const float4* src = reinterpret_cast<const float4*>(dx0 + ((g * NB + ft) * 64 + lane) * 16);
-      float x[16];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 v = src[q];
-        x[4 * q] = v.x; x[4 * q + 1] = v.y; x[4 * q + 2] = v.z; x[4 * q + 3] = v.w;
-      }
+      const f32x16 x = load_tile(dx0 + (g * NB + ft) * 1024, lane);
       bf16x8 tm[3][2];  // hi, mid, lo: R layout (lane -> row, values -> features tile_idx(r, h))
 #pragma unroll
       for (int r = 0; r < 16; ++r) {

@@ -182,25 +182,25 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     const auto lres = rsrc(a.lse + gg * 32 * (NB * HPB), ok ? 32 * NB * HPB * 4 : 0);
     const auto xres = rsrc(reinterpret_cast<const __bf16*>(a.save_x) + gg * NB * 64 * 16, ok ? NB * 64 * 16 * 2 : 0);
     const auto gres = rsrc(a.g_in + gg * NB * 64 * 16, ok ? NB * 64 * 16 * 4 : 0);
-    // the lane offsets (lane * 32 for x, lane * 64 for g) formed here from the lane id, not kept
-    // in registers across the tile loop
-    int l32;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0\n\tv_lshlrev_b32 %0, 5, %0" : "=v"(l32));
+    // the lane offset (16 bytes a lane in every piece of a tile) formed here from the lane id, not
+    // kept in registers across the tile loop
+    int l16;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0\n\tv_lshlrev_b32 %0, 4, %0" : "=v"(l16));
     if constexpr (HPB == 4) {
-      // row lr's normalisers at lr * 32 bytes: the x offset with the lane half masked off
-      const float4 v = rld4(lres, l32 & 0x3ff, hb * HPB * 4);
+      // row lr's normalisers at lr * 32 bytes: twice the lane offset with the lane half masked off
+      const float4 v = rld4(lres, (l16 & 0x1ff) << 1, hb * HPB * 4);
       ln[0] = v.x; ln[1] = v.y; ln[2] = v.z; ln[3] = v.w;
     } else {
       static_assert(NB * HPB * 4 == 16, "row lr's two normalisers of each head block at lr * 16 bytes");
-      const float2 v = rld2(lres, ((l32 & 0x3ff) >> 1) + hb * HPB * 4);
+      const float2 v = rld2(lres, (l16 & 0x1ff) + hb * HPB * 4);
       ln[0] = v.x; ln[1] = v.y;
     }
 #pragma unroll
     for (int ib = 0; ib < NB; ++ib) {
-      xn[ib][0] = rld8(xres, l32, ib * 64 * 16 * 2);
-      xn[ib][1] = rld8(xres, l32, ib * 64 * 16 * 2 + 16);
+      xn[ib][0] = rld8(xres, l16, ib * 64 * 16 * 2);
+      xn[ib][1] = rld8(xres, l16, ib * 64 * 16 * 2 + 1024);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) gn[ib][q] = rld4(gres, 2 * l32, ib * 64 * 64 + 16 * q);
+      for (int q = 0; q < 4; ++q) gn[ib][q] = rld4(gres, l16, ib * 64 * 64 + 1024 * q);
     }
   };
   fetch(blockIdx.x);
@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     const auto dres = rsrc(a.g_out + (valid ? gb : 0) * NB * 64 * 16, valid ? BLK_BYTES : 0);
     float4 sv[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sv[q] = rld4(gres, lane * 64, hb * 64 * 64 + 16 * q);
+    for (int q = 0; q < 4; ++q) sv[q] = rld4(gres, lane * 16, hb * 64 * 64 + 1024 * q);
     barrier_lds();  // staging of both head blocks in LDS
     if (valid) {
       bf16x8 oq[ST], ok[ST], ov[ST];  // the other head block's operands, as it staged them
@@ -455,7 +455,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
                            (g.z + a0[4 * q + 2]) + a1[4 * q + 2], (g.w + a0[4 * q + 3]) + a1[4 * q + 3]);
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) rst4(dres, lane * 64, o[q], hb * 64 * 64 + 16 * q);
+      for (int q = 0; q < 4; ++q) rst4(dres, lane * 16, o[q], hb * 64 * 64 + 1024 * q);
     }
     // issued after the dx step, whose loads would otherwise wait behind these in the in-order load counter
     fetch(tile + gridDim.x);
@@ -561,12 +561,12 @@ __global__ void __launch_bounds__(256) k_bwd_attn_span_bf16(BwdArgs a) {
       for (int j = 0; j < HPB; ++j) ln[rb][j] = ls[j];
 #pragma unroll
       for (int ib = 0; ib < NB; ++ib) {
-        const __bf16* xs = reinterpret_cast<const __bf16*>(a.save_x) + ((g * NB + ib) * 64 + lane) * 16;
+        const __bf16* xs = reinterpret_cast<const __bf16*>(a.save_x) + (g * NB + ib) * 1024 + lane * 8;
         xn[rb][ib][0] = ld8(xs);
-        xn[rb][ib][1] = ld8(xs + 8);
-        const float4* gs = reinterpret_cast<const float4*>(a.g_in + ((g * NB + ib) * 64 + lane) * 16);
+        xn[rb][ib][1] = ld8(xs + 512);
+        const float4* gs = reinterpret_cast<const float4*>(a.g_in + (g * NB + ib) * 1024) + lane;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) gn[rb][ib][q] = gs[q];
+        for (int q = 0; q < 4; ++q) gn[rb][ib][q] = gs[64 * q];
       }
     }
   };
@@ -774,7 +774,7 @@ __global__ void __launch_bounds__(256) k_bwd_attn_span_bf16(BwdArgs a) {
     for (int rb = 0; rb < 2; ++rb) {
       const int64_t gb = 4 * tile + 2 * cp + rb;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) sv[rb][q] = reinterpret_cast<const float4*>(a.g_in + ((gb * NB + hb) * 64 + lane) * 16)[q];
+      for (int q = 0; q < 4; ++q) sv[rb][q] = reinterpret_cast<const float4*>(a.g_in + (gb * NB + hb) * 1024)[64 * q + lane];
     }
     barrier_lds();  // staging of both head blocks in LDS
 #pragma unroll
@@ -805,9 +805,9 @@ __global__ void __launch_bounds__(256) k_bwd_attn_span_bf16(BwdArgs a) {
         o[q] = make_float4((g.x + a0[4 * q]) + a1[4 * q], (g.y + a0[4 * q + 1]) + a1[4 * q + 1],
                            (g.z + a0[4 * q + 2]) + a1[4 * q + 2], (g.w + a0[4 * q + 3]) + a1[4 * q + 3]);
       }
-      float4* dst = reinterpret_cast<float4*>(a.g_out + ((gb * NB + hb) * 64 + lane) * 16);
+      float4* dst = reinterpret_cast<float4*>(a.g_out + (gb * NB + hb) * 1024) + lane;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) dst[q] = o[q];
+      for (int q = 0; q < 4; ++q) dst[64 * q] = o[q];
     }
     fetch(tile + gridDim.x);
 

@@ -165,12 +165,12 @@ __global__ void __launch_bounds__(256) k_bwd_mlp_bf16(BwdArgs a) {
     const int64_t g = 2 * tl + sb;
     const bool ok = tl < ntile && g < nblk;
     const auto rx = rsrc(reinterpret_cast<const __bf16*>(a.save_mid) + (g * NB + sob) * 64 * 16, ok ? 64 * 16 * 2 : 0);
-    xn[0] = rld8(rx, sl * 32);
-    xn[1] = rld8(rx, sl * 32 + 16);
+    xn[0] = rld8(rx, sl * 16);
+    xn[1] = rld8(rx, sl * 16 + 1024);
     if constexpr (!SEEDS) {
       const auto rg = rsrc(a.g_in + (g * NB + sob) * 64 * 16, ok ? 64 * 16 * 4 : 0);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) gn[q] = rld4(rg, sl * 64 + 16 * q);
+      for (int q = 0; q < 4; ++q) gn[q] = rld4(rg, sl * 16 + 1024 * q);
     } else {
       int64_t e;
       int pass, ric;
@@ -314,7 +314,7 @@ __global__ void __launch_bounds__(256) k_bwd_mlp_bf16(BwdArgs a) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const float4 g = GF[(w * 4 + q) * 64 + lane];  // staged by this lane in phase 1
-        rst4(ro, lane * 64 + 16 * q,
+        rst4(ro, lane * 16 + 1024 * q,
              make_float4(acc[4 * q] + g.x, acc[4 * q + 1] + g.y, acc[4 * q + 2] + g.z, acc[4 * q + 3] + g.w));
       }
     }
@@ -420,18 +420,18 @@ __global__ void __launch_bounds__(512) k_bwd_mlp8_bf16(BwdArgs a) {
   auto fetch = [&](int64_t tl) {
     const int64_t g = 2 * tl + sb;
     const bool ok = tl < ntile && g < nblk;
-    // 32 x the lane id, formed here from the hardware's lane count (three instructions) rather
+    // 16 x the lane id, formed here from the hardware's lane count (three instructions) rather
     // than held in a register across the tile loop
     int lo;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0\n\tv_lshlrev_b32 %0, 5, %0" : "=v"(lo));
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0\n\tv_lshlrev_b32 %0, 4, %0" : "=v"(lo));
     if (!gw) {
       const auto rx = rsrc(reinterpret_cast<const __bf16*>(a.save_mid) + (g * NB + sob) * 64 * 16, ok ? 64 * 16 * 2 : 0);
       xn[0] = rld8(rx, lo);
-      xn[1] = rld8(rx, lo, 16);
+      xn[1] = rld8(rx, lo, 1024);
     } else if constexpr (!SEEDS) {
       const auto rg = rsrc(a.g_in + (g * NB + sob) * 64 * 16, ok ? 64 * 16 * 4 : 0);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) gn[k] = rld4(rg, 2 * lo, 16 * k);
+      for (int k = 0; k < 4; ++k) gn[k] = rld4(rg, lo, 1024 * k);
     } else {
       int64_t e;
       int pass, ric;
@@ -544,7 +544,7 @@ __global__ void __launch_bounds__(512) k_bwd_mlp8_bf16(BwdArgs a) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float4 o = XD[(q * 4 + k) * 64 + lane], g = GF[(q * 4 + k) * 64 + lane];
-        rst4(ro, lane * 64 + 16 * k,
+        rst4(ro, lane * 16 + 1024 * k,
              make_float4(acc[4 * k] + o.x + g.x, acc[4 * k + 1] + o.y + g.y, acc[4 * k + 2] + o.z + g.z,
                          acc[4 * k + 3] + o.w + g.w));
       }

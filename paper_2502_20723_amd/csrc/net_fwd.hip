@@ -115,13 +115,7 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
     for (int rb = 0; rb < NBR; ++rb)
 #pragma unroll
       for (int ob = 0; ob < NB; ++ob) {
-        const float4* src = reinterpret_cast<const float4*>(a.x_in + (((tl * NBR + rb) * NB + ob) * 64 + lane) * 16);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 v = src[q];
-          xnext[rb][ob][4 * q + 0] = v.x; xnext[rb][ob][4 * q + 1] = v.y;
-          xnext[rb][ob][4 * q + 2] = v.z; xnext[rb][ob][4 * q + 3] = v.w;
-        }
+        xnext[rb][ob] = load_tile(a.x_in + ((tl * NBR + rb) * NB + ob) * 1024, lane);
       }
   };
   // Neighbouring tiles go to the waves of one workgroup (contiguous activations), but a batch of
@@ -131,6 +125,8 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
   if (!SPAN) fetch_x(tile0);
 
   for (int64_t tile = tile0; tile < ntiles; tile += tstride) {
+    // keeps the loads of the LDS weights inside the loop: hoisted, they would fill the registers
+    asm volatile("" ::: "memory");
     const int pass = (int)(tile & 1);
     // first entry of the tile and the slot/validity of this lane's rows
     const int64_t e0 = SPAN ? (tile >> 1) : (tile >> 1) * cpb;
@@ -182,9 +178,7 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
       for (int rb = 0; rb < NBR; ++rb)
 #pragma unroll
         for (int ob = 0; ob < NB; ++ob) {
-          save_t* p = s + (((gblk0 + rb) * NB + ob) * 64 + lane) * 16;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) p[r] = (save_t)v[rb][ob][r];
+          store_tile(s + ((gblk0 + rb) * NB + ob) * 1024, lane, v[rb][ob]);
         }
     };
     if (a.save_x) save(a.save_x, x);
@@ -213,10 +207,7 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
       for (int rb = 0; rb < NBR; ++rb)
 #pragma unroll
         for (int ob = 0; ob < NB; ++ob) {
-          float4* dst = reinterpret_cast<float4*>(a.x_out + (((gblk0 + rb) * NB + ob) * 64 + lane) * 16);
-#pragma unroll
-          for (int qq = 0; qq < 4; ++qq)
-            dst[qq] = make_float4(x[rb][ob][4 * qq], x[rb][ob][4 * qq + 1], x[rb][ob][4 * qq + 2], x[rb][ob][4 * qq + 3]);
+          store_tile(a.x_out + ((gblk0 + rb) * NB + ob) * 1024, lane, x[rb][ob]);
         }
       continue;
     }

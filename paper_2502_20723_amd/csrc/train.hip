@@ -121,7 +121,7 @@ static int32_t fill(double* p, int64_t n, double v, hipStream_t st) {
 // ------------------------------------------------------------------ backward driver
 struct BwdBufs {
   void* wback;       // [L][layer_elems] transposed fragments
-  float* ga;         // gradient ping-pong, [blocks][D/32][64][16]
+  float* ga;         // gradient ping-pong, [blocks][D/32] tiles (load_tile)
   float* gb;
   float* partial;    // [nparts][maxlen]
   int nparts;

@@ -246,47 +246,6 @@ int32_t net_plan(const Context* c, const tdo_arch_t* arch, int n, bool bf16, Net
 
 int64_t blocks_for(const NetPlan& np, int64_t E) { return np.span ? 4 * E : 2 * ((E + np.cpb - 1) / np.cpb); }
 
-// Forward over E entries whose configurations are ecfg; z [E][2][2].
-int32_t run_forward(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg, int64_t E, const int64_t* E_dev,
-                    float* xa, float* xb, const Saves* sv, float* z, hipStream_t st) {
-  const PackPlan& pp = np.pp;
-  const int L = pp.layers;
-  for (int l = 0; l < L; ++l) {
-    FwdArgs a{};
-    a.wpack = static_cast<const char*>(w.wpack) + (size_t)l * pp.layer_elems * np.elem;
-    a.b1 = w.b1 + (size_t)l * pp.M;
-    a.b2 = w.b2 + (size_t)l * pp.D;
-    a.table = w.table;
-    a.ecfg = ecfg;
-    a.n_entries_dev = E_dev;
-    a.n_entries = E;
-    a.x_in = (l % 2 == 0) ? xb : xa;  // layer l reads what layer l-1 wrote
-    a.x_out = (l % 2 == 0) ? xa : xb;
-    if (sv) {
-      a.save_x = static_cast<char*>(sv->x) + (size_t)l * sv->layer_bytes;
-      a.save_mid = static_cast<char*>(sv->mid) + (size_t)l * sv->layer_bytes;
-      a.save_lse = sv->lse ? sv->lse + (size_t)l * sv->lse_layer : nullptr;
-      a.save_last = sv->last;
-    }
-    a.head_w = w.head_w;
-    a.head_b = w.head_b;
-    a.z = z;
-    a.n = np.n;
-    a.cpb = np.cpb;
-    a.d_real = pp.d;
-    a.M = pp.M;
-    a.score_scale = np.score_scale;
-    a.first = l == 0;
-    a.last = l == L - 1;
-    a.masked = np.masked;
-    a.blocks_per_cu = np.fwd_wg_per_cu;
-    a.waves = np.fwd_waves;
-    ProfScope ps(np.prof, "fwd_layer", st);
-    TDO_TRY(launch_fwd_layer(a, np.bf16, np.D, np.DH, np.span, np.num_cus, st));
-  }
-  return TDO_OK;
-}
-
 StackArgs stack_args(const NetPlan& np, const NetWeights& w) {
   StackArgs a{};
   a.wpack = w.wpack;
@@ -322,6 +281,63 @@ bool stack_takes(const NetPlan& np, int64_t E) {
   return np.bf16 || np.D == 32 || (np.DH == 8 && tiles > np.num_cus);
 }
 
+// Forward over E entries whose configurations are ecfg; z [E][2][2], and lr [E][2] unless NULL.
+int32_t run_forward(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg, int64_t E, const int64_t* E_dev,
+                    float* xa, float* xb, const Saves* sv, float* z, hipStream_t st, float* lr) {
+  const PackPlan& pp = np.pp;
+  if (sv && stack_takes(np, E)) {
+    StackArgs a = stack_args(np, w);
+    a.ecfg = ecfg;
+    a.E = E;
+    a.n_entries_dev = E_dev;
+    a.lr = lr;
+    a.z = z;
+    a.save_x = sv->x;
+    a.save_mid = sv->mid;
+    a.save_last = sv->last;
+    a.save_lse = sv->lse;
+    a.layer_bytes = sv->layer_bytes;
+    a.lse_layer = sv->lse_layer;
+    ProfScope ps(np.prof, "fwd_layer", st);
+    return launch_fwd_stack(a, np.bf16, np.D, np.DH, np.masked, 3, np.num_cus, st);
+  }
+  const int L = pp.layers;
+  for (int l = 0; l < L; ++l) {
+    FwdArgs a{};
+    a.wpack = static_cast<const char*>(w.wpack) + (size_t)l * pp.layer_elems * np.elem;
+    a.b1 = w.b1 + (size_t)l * pp.M;
+    a.b2 = w.b2 + (size_t)l * pp.D;
+    a.table = w.table;
+    a.ecfg = ecfg;
+    a.n_entries_dev = E_dev;
+    a.n_entries = E;
+    a.x_in = (l % 2 == 0) ? xb : xa;  // layer l reads what layer l-1 wrote
+    a.x_out = (l % 2 == 0) ? xa : xb;
+    if (sv) {
+      a.save_x = static_cast<char*>(sv->x) + (size_t)l * sv->layer_bytes;
+      a.save_mid = static_cast<char*>(sv->mid) + (size_t)l * sv->layer_bytes;
+      a.save_lse = sv->lse ? sv->lse + (size_t)l * sv->lse_layer : nullptr;
+      a.save_last = sv->last;
+    }
+    a.head_w = w.head_w;
+    a.head_b = w.head_b;
+    a.z = z;
+    a.n = np.n;
+    a.cpb = np.cpb;
+    a.d_real = pp.d;
+    a.M = pp.M;
+    a.score_scale = np.score_scale;
+    a.first = l == 0;
+    a.last = l == L - 1;
+    a.masked = np.masked;
+    a.blocks_per_cu = np.fwd_wg_per_cu;
+    a.waves = np.fwd_waves;
+    ProfScope ps(np.prof, "fwd_layer", st);
+    TDO_TRY(launch_fwd_layer(a, np.bf16, np.D, np.DH, np.span, np.num_cus, st));
+  }
+  return lr ? launch_symmetrise(E_dev, E, z, lr, st) : TDO_OK;
+}
+
 int32_t run_log_rho(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg, int64_t E, float* xa, float* xb, float* z,
                     float* lr, hipStream_t st) {
   if (stack_takes(np, E)) {
@@ -332,8 +348,7 @@ int32_t run_log_rho(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg
     ProfScope ps(np.prof, "fwd_layer", st);
     return launch_fwd_stack(a, np.bf16, np.D, np.DH, np.masked, 0, np.num_cus, st);
   }
-  TDO_TRY(run_forward(np, w, ecfg, E, nullptr, xa, xb, nullptr, z, st));
-  return launch_symmetrise(nullptr, E, z, lr, st);
+  return run_forward(np, w, ecfg, E, nullptr, xa, xb, nullptr, z, st, lr);
 }
 
 int32_t pack_weights(const NetPlan& np, const float* params, NetWeights* w, hipStream_t st, void* wback) {

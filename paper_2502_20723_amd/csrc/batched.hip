@@ -86,7 +86,8 @@ int32_t tune_problem(Context& c, NetPlan& np, const ModelDev& m, const TrainWs& 
     const int waves_c[2] = {8, 4}, wg_c[2] = {1, 2};
     float best = -1.f;
     int bw = np.fwd_waves, bg = np.fwd_wg_per_cu;
-    for (int wi = 0; wi < (two_shapes ? 2 : 1) && rc == TDO_OK; ++wi)
+    const bool layers = !stack_takes(np, E);  // one launch for all layers has a fixed shape
+    for (int wi = 0; wi < (two_shapes ? 2 : 1) && rc == TDO_OK && layers; ++wi)
       for (int gi = 0; gi < 2 && rc == TDO_OK; ++gi) {
         np.fwd_waves = waves_c[wi];
         np.fwd_wg_per_cu = wg_c[gi];

@@ -16,7 +16,8 @@ constexpr int STACK_WAVES = 8;
 constexpr int STACK_PIECES = 8;  // 16-byte pieces per thread that hold a layer's feed-forward weights (BF16: 64 KB)
 
 // MODE 0: log rho of E configurations; 1, 2: `steps` proposals of every chain (doubled space,
-// diagonal).  Waves 2p and 2p + 1 of a workgroup hold the two passes of cpb = 32 / n configurations,
+// diagonal); 3: z (and log rho, if lr is given) of E configurations, with the activations that the
+// backward pass needs.  Waves 2p and 2p + 1 of a workgroup hold the two passes of cpb = 32 / n configurations,
 // p < pairs: 4, or fewer in a batch that leaves CUs idle (a wave alone on its SIMD is faster).
 // BF16: a layer's weights are staged in two LDS buffers, attention and feed-forward; each is
 // loaded into registers while the other is computed with and stored before the barrier that ends
@@ -28,9 +29,10 @@ constexpr int STACK_PIECES = 8;  // 16-byte pieces per thread that hold a layer'
 // (40 before).
 template <class P, int D, int DH, int MBC, bool MASKED, int MODE>
 __global__ void __launch_bounds__(512) k_fwd_stack(StackArgs a) {
-  constexpr int NB = D / 32;
+  constexpr int NB = D / 32, HPB = 32 / DH;
   constexpr bool WLDS = P::KPL == 8;
   using elem_t = typename P::elem_t;
+  using save_t = typename P::save_t;
   extern __shared__ __align__(16) char smem[];
   __shared__ float2 zsh[4][10][2];
   __shared__ uint64_t cfg_s[4][10][2];
@@ -44,6 +46,7 @@ __global__ void __launch_bounds__(512) k_fwd_stack(StackArgs a) {
   const elem_t* wg = reinterpret_cast<const elem_t*>(a.wpack);
   const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, lr = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), pair = wave >> 1, pass = wave & 1;
+  const int64_t E = MODE == 3 && a.n_entries_dev ? *a.n_entries_dev : a.E;
   const int n = a.n, cpb = a.cpb, G = a.pairs * cpb;
   const bool busy = pair < a.pairs;  // the other waves only stage weights
 
@@ -104,20 +107,40 @@ __global__ void __launch_bounds__(512) k_fwd_stack(StackArgs a) {
     okbits[0][0] |= (!MASKED || (key / n == slot && key / n < cpb)) ? 1u << r : 0u;
   }
 
-  for (int64_t g0 = (int64_t)blockIdx.x * G; g0 < a.E; g0 += (int64_t)gridDim.x * G) {
+  for (int64_t grp = blockIdx.x; grp * G < E; grp += gridDim.x) {
+    const int64_t g0 = grp * G;
     // thread tid < G keeps configuration (or chain) g0 + tid in the registers
     const int64_t ce = g0 + tid;
-    const bool mine = tid < G && ce < a.E;
+    const bool mine = tid < G && ce < E;
     uint64_t sa = 0, sb = 0;
     float2 slr = make_float2(0.f, 0.f);
     if (mine) {
-      if constexpr (MODE == 0) { sa = a.ecfg[2 * ce]; sb = a.ecfg[2 * ce + 1]; }
+      if constexpr (MODE == 0 || MODE == 3) { sa = a.ecfg[2 * ce]; sb = a.ecfg[2 * ce + 1]; }
       if constexpr (MODE == 1) { sa = a.state[2 * ce]; sb = a.state[2 * ce + 1]; }
       if constexpr (MODE == 2) sa = sb = a.state[ce];
-      if constexpr (MODE != 0) slr = make_float2(a.state_lr[2 * ce], a.state_lr[2 * ce + 1]);
+      if constexpr (MODE == 1 || MODE == 2) slr = make_float2(a.state_lr[2 * ce], a.state_lr[2 * ce + 1]);
     }
-    const bool rvalid[1] = {busy && slot < cpb && g0 + pair * cpb + slot < a.E};
-    const int steps = MODE == 0 ? 1 : a.steps;
+    const bool rvalid[1] = {busy && slot < cpb && g0 + pair * cpb + slot < E};
+    // the block of this wave in the saved activations, and whether it exists
+    const int64_t blk = 2 * (grp * a.pairs + pair) + pass;
+    const bool kept = MODE == 3 && busy && g0 + pair * cpb < E;
+    auto save = [&](void* dst, int l, const f32x16 (&v)[1][NB]) {
+      constexpr int bytes = 64 * 16 * (int)sizeof(save_t);
+      const auto r = rsrc(static_cast<char*>(dst) + l * a.layer_bytes + blk * NB * bytes, kept ? NB * bytes : 0);
+#pragma unroll
+      for (int ob = 0; ob < NB; ++ob) {
+        if constexpr (WLDS) {
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+            rst4(r, lane * 16, __builtin_bit_cast(float4, cvt8(v[0][ob], s)), ob * bytes + 1024 * s);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            rst4(r, lane * 16, make_float4(v[0][ob][4 * q], v[0][ob][4 * q + 1], v[0][ob][4 * q + 2], v[0][ob][4 * q + 3]), ob * bytes + 1024 * q);
+        }
+      }
+    };
+    const int steps = MODE == 1 || MODE == 2 ? a.steps : 1;
     for (int s = 0; s < steps; ++s) {
       uint64_t pa = sa, pb = sb;
       double u = 0.0;
@@ -128,7 +151,7 @@ __global__ void __launch_bounds__(512) k_fwd_stack(StackArgs a) {
       }
       if (tid < G) { cfg_s[tid / cpb][tid % cpb][0] = pa; cfg_s[tid / cpb][tid % cpb][1] = pb; }
       if (WLDS && reload) { load_a(0); store_a(); }
-      __syncthreads();
+      barrier_lds();
       f32x16 x[1][NB];
       {
         int code = 0;
@@ -148,36 +171,54 @@ __global__ void __launch_bounds__(512) k_fwd_stack(StackArgs a) {
       for (int l = 0; l < L; ++l) {
         const elem_t* W = WLDS ? wa : wg + l * a.layer_elems;
         if (WLDS && reload) load_m(l);
+        if constexpr (MODE == 3) save(a.save_x, l, x);
         if (busy)
           tile_attention<P, D, DH, 1, MASKED>(x, W, W + D * D, W + 2 * D * D, W + 3 * D * D, okbits, a.score_scale, lane,
-                                              [](int, const float (&)[1][32 / DH]) {});
+                                              [&](int hb, const float (&lsev)[1][HPB]) {
+            if constexpr (MODE == 3 && WLDS) {  // one store per lane of the first half; the second's is out of range
+              const auto r = rsrc(a.save_lse + l * a.lse_layer + blk * 32 * (NB * HPB), kept ? 32 * NB * HPB * 4 : 0);
+              const int off = h == 0 ? (lr * (NB * HPB) + hb * HPB) * 4 : 0x7ffffff0;
+              if constexpr (HPB == 4) rst4(r, off, make_float4(lsev[0][0], lsev[0][1], lsev[0][2], lsev[0][3]));
+              else rst2(r, off, make_float2(lsev[0][0], lsev[0][1]));
+            }
+          });
+        if constexpr (MODE == 3) save(a.save_mid, l, x);
         if (WLDS && reload) {
           store_m();
-          __syncthreads();  // feed-forward weights ready, attention weights free
+          barrier_lds();  // feed-forward weights ready, attention weights free
           if (l + 1 < L) load_a(l + 1);
         }
         const elem_t* W1 = WLDS ? wm : W + 4 * D * D;
         if (busy) tile_ffn<P, D, 1>(x, W1, W1 + D * M, bias + l * (M + D), bias + l * (M + D) + M, MB, lane);
         if (WLDS && reload) {
           if (l + 1 < L) store_a();
-          __syncthreads();  // the next layer's attention weights ready, feed-forward weights free
+          barrier_lds();  // the next layer's attention weights ready, feed-forward weights free
         }
       }
+      if constexpr (MODE == 3) save(a.save_last, 0, x);
       if (busy) {
         float v0, v1;
         tile_head<1, NB>(x, hws, rvalid, site, h, v0, v1);
         if (h == 0 && site == n - 1 && slot < cpb) {
           const float inv = 1.0f / (float)n;
-          zsh[pair][slot][pass] = make_float2(v0 * inv + a.head_b[0], v1 * inv + a.head_b[1]);
+          const float2 z = make_float2(v0 * inv + a.head_b[0], v1 * inv + a.head_b[1]);
+          zsh[pair][slot][pass] = z;
+          if (MODE == 3 && rvalid[0]) {
+            const int64_t e = g0 + pair * cpb + slot;
+            a.z[(e * 2 + pass) * 2] = z.x;
+            a.z[(e * 2 + pass) * 2 + 1] = z.y;
+          }
         }
       }
-      __syncthreads();
+      barrier_lds();
       if (mine) {
         const float2 z1 = zsh[tid / cpb][tid % cpb][0], z2 = zsh[tid / cpb][tid % cpb][1];
         const float2 v = symmetrise(z1.x, z1.y, z2.x, z2.y);
-        if constexpr (MODE == 0) {
-          a.lr[2 * ce] = v.x;
-          a.lr[2 * ce + 1] = v.y;
+        if constexpr (MODE == 0 || MODE == 3) {
+          if (MODE == 0 || a.lr) {
+            a.lr[2 * ce] = v.x;
+            a.lr[2 * ce + 1] = v.y;
+          }
         } else if (u < accept_ratio(v.x, slr.x, MODE == 2)) {
           sa = pa;
           sb = pb;
@@ -185,7 +226,7 @@ __global__ void __launch_bounds__(512) k_fwd_stack(StackArgs a) {
         }
       }
     }
-    if (MODE != 0 && mine) {
+    if ((MODE == 1 || MODE == 2) && mine) {
       a.state_lr[2 * ce] = slr.x;
       a.state_lr[2 * ce + 1] = slr.y;
       if constexpr (MODE == 1) {
@@ -193,7 +234,7 @@ __global__ void __launch_bounds__(512) k_fwd_stack(StackArgs a) {
         a.state[2 * ce + 1] = a.record[2 * ce + 1] = sb;
       } else a.state[ce] = a.record[ce] = sa;
     }
-    __syncthreads();  // z read before the next group's
+    barrier_lds();  // z read before the next group's
   }
 }
 
@@ -213,8 +254,10 @@ bool stack_supported(bool bf16, int D, int M, int layers, bool span) {
 
 template <class P, int D, int DH, int MBC, bool MASKED>
 static int32_t stack_m(StackArgs a, int mode, int num_cus, hipStream_t st) {
-  auto kern = mode == 0 ? k_fwd_stack<P, D, DH, MBC, MASKED, 0>
-                        : (mode == 1 ? k_fwd_stack<P, D, DH, MBC, MASKED, 1> : k_fwd_stack<P, D, DH, MBC, MASKED, 2>);
+  auto kern = mode == 0   ? k_fwd_stack<P, D, DH, MBC, MASKED, 0>
+              : mode == 1 ? k_fwd_stack<P, D, DH, MBC, MASKED, 1>
+              : mode == 2 ? k_fwd_stack<P, D, DH, MBC, MASKED, 2>
+                          : k_fwd_stack<P, D, DH, MBC, MASKED, 3>;
   TDO_TRY(allow_full_lds((const void*)kern, STACK_STATIC));
   const size_t lds = stack_lds_t<P, D>(a.M, a.layers);
   const int64_t tiles = (a.E + a.cpb - 1) / a.cpb;

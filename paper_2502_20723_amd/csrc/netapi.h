@@ -13,7 +13,7 @@ struct FwdArgs {
   const uint64_t* ecfg;         // first layer: configurations [E][2]
   const int64_t* n_entries_dev; // E on the device, or NULL to use n_entries
   int64_t n_entries;            // their number, or an upper bound when n_entries_dev gives it
-  const float* x_in;            // residual in, [blocks][D/32][64][16] (not first layer)
+  const float* x_in;            // residual in, [blocks][D/32] tiles (load_tile) (not first layer)
   float* x_out;                 // residual out (not last layer)
   void* save_x;                 // optional: layer input saved for the backward pass
   void* save_mid;               // optional: input of the feed-forward sub-layer
@@ -30,13 +30,19 @@ struct FwdArgs {
 };
 
 // The whole forward in one launch (net_stack.hip), n <= 32.  mode 0: lr of the E configurations ecfg;
-// 1: `steps` proposals of the E chains on (alpha, beta); 2: of the diagonal chains.
+// 1: `steps` proposals of the E chains on (alpha, beta); 2: of the diagonal chains; 3: z (and lr, unless
+// NULL) of the configurations, with the activations kept for the backward pass.
 struct StackArgs {
   const void* wpack;
   const float *b1, *b2, *table, *head_w, *head_b;
   const uint64_t* ecfg;
   int64_t E, layer_elems;
   float* lr;         // [E][2]
+  const int64_t* n_entries_dev;  // mode 3: the number of entries on the device (E an upper bound), or NULL
+  float* z;                      // mode 3: [E][2 passes][2]
+  void *save_x, *save_mid, *save_last;
+  float* save_lse;
+  size_t layer_bytes, lse_layer;
   uint64_t* state;   // chains: [E][2] (mode 2: [E]), their log rho, and the states after the last proposal
   float* state_lr;
   uint64_t* record;
@@ -78,7 +84,7 @@ struct BwdArgs {
   const void* save_x;           // layer input
   const void* save_mid;         // feed-forward input
   const float* lse;             // attention row normalisers saved by the forward (or NULL)
-  const float* g_in;            // incoming gradient [blocks][D/32][64][16] (NULL: from seeds)
+  const float* g_in;            // incoming gradient [blocks][D/32] tiles (load_tile) (NULL: from seeds)
   const float* seeds;           // last layer: per configuration-pass (dF0, dF1), [E][2][2]
   const float* head_w;          // [d][2]
   float* g_out;                 // outgoing gradient

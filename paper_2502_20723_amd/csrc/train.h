@@ -89,7 +89,7 @@ int32_t pack_weights(const NetPlan& np, const float* params, NetWeights* w, hipS
 void carve_weights(const NetPlan& np, Arena& ar, size_t* offs);
 NetWeights weights_at(void* ws, const size_t* offs);
 int32_t run_forward(const NetPlan& np, const NetWeights& w, const uint64_t* ecfg, int64_t E, const int64_t* E_dev,
-                    float* xa, float* xb, const Saves* sv, float* z, hipStream_t st);
+                    float* xa, float* xb, const Saves* sv, float* z, hipStream_t st, float* lr = nullptr);
 
 // Whether E configurations (or chains) go through the whole network in one launch (net_stack.hip).
 bool stack_takes(const NetPlan& np, int64_t E);

@@ -474,8 +474,8 @@ int32_t loss_grad_run(Context& c, const NetPlan& np, const ModelDev& m, const Tr
     TDO_TRY(launch_eval_list(m, cfg + 2 * b0, Bc, at<int32_t>(ws, t.cnt), at<int64_t>(ws, t.off), at<int64_t>(ws, t.etot),
                              at<uint64_t>(ws, t.ecfg), at<float>(ws, t.ecoef), at<int32_t>(ws, t.eowner), stream));
     const uint64_t* ec = at<uint64_t>(ws, t.ecfg);
-    TDO_TRY(run_forward(np, w, ec, t.emax, Ed, at<float>(ws, t.xa), at<float>(ws, t.xb), &sv, at<float>(ws, t.z), stream));
-    TDO_TRY(launch_symmetrise(Ed, 0, at<float>(ws, t.z), at<float>(ws, t.lr), stream));
+    TDO_TRY(run_forward(np, w, ec, t.emax, Ed, at<float>(ws, t.xa), at<float>(ws, t.xb), &sv, at<float>(ws, t.z), stream,
+                        at<float>(ws, t.lr)));
     float* Lb = Lall + 2 * b0;
     TDO_TRY(launch_lloc_eval(Bc, at<int64_t>(ws, t.off), at<int32_t>(ws, t.cnt), at<float>(ws, t.ecoef), at<float>(ws, t.lr),
                              Lb, stream));

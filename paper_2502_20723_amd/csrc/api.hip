@@ -266,19 +266,17 @@ StackArgs stack_args(const NetPlan& np, const NetWeights& w) {
 
 // One launch for the whole network (bit-identical to layer by layer) where it measured faster
 // (microseconds, layers against one launch):
-//  - BF16, two layers or more, any batch: per proposal of 1024 chains at n = 32, benchmark network 77
-//    and 40, of 16 chains 40 and 24; log rho of 65536 configurations 2553 and 2206;
+//  - two layers or more, any batch.  BF16: per proposal of 1024 chains at n = 32, benchmark network 77
+//    and 40, of 16 chains 40 and 24; log rho of 65536 configurations 2553 and 2206.  FP32: per proposal
+//    of 1024 chains 279 and 256, of 16 chains 135 and 120; log rho of 65536 configurations 16465 and
+//    16441, at n = 16 with 16-wide heads 3940 and 3778; width 32, per proposal at n = 8 40 and 27;
 //  - a single layer: the layer kernel keeps its weights and has nothing to fuse, so only while the
-//    batch has at most one tile per pair of waves (n = 20, mlp 96: per proposal of 1024 chains 22 and
-//    12, log rho of 65536 configurations 514 and 611);
-//  - FP32, width 32: per proposal at n = 8 40 and 27; width 64 reads the weights through the caches
-//    either way: faster with 8-wide heads and all CUs busy (1024 chains at n = 32: 304 and 274), not
-//    below that (157 and 181) or with 16-wide heads (log rho at n = 16: 3905 and 4111).
+//    batch has at most one tile per pair of waves (BF16, n = 20, mlp 96: per proposal of 1024 chains
+//    22 and 12, log rho of 65536 configurations 514 and 611).
 bool stack_takes(const NetPlan& np, int64_t E) {
   if (!stack_supported(np.bf16, np.D, np.pp.M, np.pp.layers, np.span)) return false;
   const int64_t tiles = (E + np.cpb - 1) / np.cpb;  // pairs of waves
-  if (np.pp.layers == 1 && tiles > 4LL * np.num_cus) return false;
-  return np.bf16 || np.D == 32 || (np.DH == 8 && tiles > np.num_cus);
+  return np.pp.layers > 1 || tiles <= 4LL * np.num_cus;
 }
 
 // Forward over E entries whose configurations are ecfg; z [E][2][2], and lr [E][2] unless NULL.

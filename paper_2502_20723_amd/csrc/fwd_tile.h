@@ -26,6 +26,28 @@ struct EmbedRow {
   }
 };
 
+// FP32 weights come through the caches, and a load left to the compiler sits right before its use,
+// where the wave waits for L2.  Here the fragments of the next group of STEPS products are loaded
+// before the current group's are issued, into the other of two register buffers.  Groups of STEPS:
+// with groups of a whole matrix the buffers spill (one layer of 32768 FP32 configurations, width 64,
+// n = 16: 1.23 ms without, 1.15 with whole matrices, 1.00 so; n = 32: 2.65, 2.22, 2.11).  Sixteen-wide
+// heads keep the plain loads in the attention part: their accumulators leave too few registers
+// (1.03 ms with, though 16 configurations take 96 us without and 86 with).  Two row blocks per wave
+// use a fragment twice and have no registers to spare.  BF16 weights are in LDS.
+template <class P, int NBR>
+constexpr bool frags_ahead() {
+  return P::KPL == 4 && NBR == 1;
+}
+template <class P>
+struct Frags {
+  typename P::op_t w[P::STEPS];
+  __device__ __forceinline__ void load(const typename P::elem_t* W, int f0, int lane) {
+#pragma unroll
+    for (int s = 0; s < P::STEPS; ++s) w[s] = ld_frag<P>(W, f0 + s, lane);
+    __builtin_amdgcn_sched_barrier(0);  // issued here, not at the use
+  }
+};
+
 // Attention sub-layer: x += W_O concat_j softmax(Q_j K_j^T / sqrt(dh)) V_j.  okbits[qb][kb]: the valid
 // (query row qb*32+lr, key row kb*32+tile_idx(r, h)) pairs as bit r; sc = log2(e)/sqrt(dh);
 // put_lse(hb, lsev): the log2 softmax normalisers of head block hb, per row block and head.
@@ -34,6 +56,7 @@ __device__ __forceinline__ void tile_attention(f32x16 (&x)[NBR][D / 32], const t
                                                const typename P::elem_t* Wv, const typename P::elem_t* Wo,
                                                const uint32_t (&okbits)[NBR][NBR], float sc, int lane, Lse&& put_lse) {
   constexpr int NB = D / 32, ST = P::STEPS, HPB = 32 / DH;
+  constexpr bool AHEAD = DH == 8 && frags_ahead<P, NBR>();
   using op_t = typename P::op_t;
   // operands of x taken before the residual is updated
   op_t xo[NBR][NB][ST];
@@ -44,6 +67,8 @@ __device__ __forceinline__ void tile_attention(f32x16 (&x)[NBR][D / 32], const t
 #pragma unroll
       for (int s = 0; s < ST; ++s) xo[rb][ib][s] = P::op(x[rb][ib], s);
 
+  Frags<P> w[2];
+  if constexpr (AHEAD) w[0].load(Wq, 0, lane);
 #pragma unroll 1
   for (int hb = 0; hb < NB; ++hb) {
     f32x16 q[NBR], k[NBR], v[NBR];
@@ -52,15 +77,33 @@ __device__ __forceinline__ void tile_attention(f32x16 (&x)[NBR][D / 32], const t
       q[rb] = f32x16{};
       k[rb] = f32x16{};
       v[rb] = f32x16{};
+      if constexpr (AHEAD) {
+        // groups of ST fragments, alternating between the two halves of w
 #pragma unroll
-      for (int ib = 0; ib < NB; ++ib)
+        for (int g = 0; g < 3 * NB; ++g) {
+          const int mtx = g / NB, ib = g % NB, nx = g + 1;
+          if (nx < 3 * NB)
+            w[nx & 1].load(nx / NB == 0 ? Wq : nx / NB == 1 ? Wk : Wv, (hb * NB + nx % NB) * ST, lane);
+          else
+            w[nx & 1].load(Wo, hb * ST, lane);
 #pragma unroll
-        for (int s = 0; s < ST; ++s) {
-          const int f = (hb * NB + ib) * ST + s;
-          q[rb] = P::mma(ld_frag<P>(Wq, f, lane), xo[rb][ib][s], q[rb]);
-          k[rb] = P::mma(ld_frag<P>(Wk, f, lane), xo[rb][ib][s], k[rb]);
-          v[rb] = P::mma(xo[rb][ib][s], ld_frag<P>(Wv, f, lane), v[rb]);  // (row x feature)
+          for (int s = 0; s < ST; ++s) {
+            if (mtx == 0) q[rb] = P::mma(w[g & 1].w[s], xo[rb][ib][s], q[rb]);
+            if (mtx == 1) k[rb] = P::mma(w[g & 1].w[s], xo[rb][ib][s], k[rb]);
+            if (mtx == 2) v[rb] = P::mma(xo[rb][ib][s], w[g & 1].w[s], v[rb]);
+          }
         }
+      } else {
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+          for (int s = 0; s < ST; ++s) {
+            const int f = (hb * NB + ib) * ST + s;
+            q[rb] = P::mma(ld_frag<P>(Wq, f, lane), xo[rb][ib][s], q[rb]);
+            k[rb] = P::mma(ld_frag<P>(Wk, f, lane), xo[rb][ib][s], k[rb]);
+            v[rb] = P::mma(xo[rb][ib][s], ld_frag<P>(Wv, f, lane), v[rb]);  // (row x feature)
+          }
+      }
     }
     // score scale folded into q; per-head score operands of q and k packed once per head
     // block; V as operands (lane -> feature)
@@ -141,10 +184,17 @@ __device__ __forceinline__ void tile_attention(f32x16 (&x)[NBR][D / 32], const t
 #pragma unroll
     for (int qb = 0; qb < NBR; ++qb) {
 #pragma unroll
-      for (int ob = 0; ob < NB; ++ob)
+      for (int ob = 0; ob < NB; ++ob) {
+        if constexpr (AHEAD) {
+          if (ob + 1 < NB)
+            w[(NB + ob + 1) & 1].load(Wo, ((ob + 1) * NB + hb) * ST, lane);
+          else
+            w[0].load(Wq, (hb + 1 < NB ? hb + 1 : hb) * NB * ST, lane);
+        }
 #pragma unroll
         for (int s = 0; s < ST; ++s)
-          x[qb][ob] = P::mma(ld_frag<P>(Wo, (ob * NB + hb) * ST + s, lane), P::op(o[qb], s), x[qb][ob]);
+          x[qb][ob] = P::mma(AHEAD ? w[(NB + ob) & 1].w[s] : ld_frag<P>(Wo, (ob * NB + hb) * ST + s, lane), P::op(o[qb], s), x[qb][ob]);
+      }
     }
   }
 }
@@ -195,6 +245,36 @@ __device__ __forceinline__ void tile_ffn(f32x16 (&x)[NBR][D / 32], const typenam
           for (int s = 0; s < ST; ++s)
             x[rb][ob] = P::mma(ld_frag<P>(W2, (ob * MB + c) * ST + s, lane), P::relu_op(u, s), x[rb][ob]);
       }
+  } else if constexpr (frags_ahead<P, NBR>()) {
+    Frags<P> w[2];
+    w[0].load(W1, 0, lane);
+#pragma unroll 1
+    for (int c = 0; c < MB; ++c) {
+      f32x16 u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 b = *reinterpret_cast<const float4*>(b1s + 32 * c + 8 * q + 4 * h);
+        u[4 * q] = b.x; u[4 * q + 1] = b.y; u[4 * q + 2] = b.z; u[4 * q + 3] = b.w;
+      }
+#pragma unroll
+      for (int ib = 0; ib < NB; ++ib) {
+        if (ib + 1 < NB)
+          w[(ib + 1) & 1].load(W1, (c * NB + ib + 1) * ST, lane);
+        else
+          w[NB & 1].load(W2, c * ST, lane);
+#pragma unroll
+        for (int s = 0; s < ST; ++s) u = P::mma(w[ib & 1].w[s], xo[0][ib][s], u);
+      }
+#pragma unroll
+      for (int ob = 0; ob < NB; ++ob) {
+        if (ob + 1 < NB)
+          w[(NB + ob + 1) & 1].load(W2, ((ob + 1) * MB + c) * ST, lane);
+        else
+          w[0].load(W1, (c + 1 < MB ? c + 1 : c) * NB * ST, lane);
+#pragma unroll
+        for (int s = 0; s < ST; ++s) x[0][ob] = P::mma(w[(NB + ob) & 1].w[s], P::relu_op(u, s), x[0][ob]);
+      }
+    }
   } else {
     constexpr int rb = 0;
     f32x16 un = ffn_pre(0, rb);

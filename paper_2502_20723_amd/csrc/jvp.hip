@@ -166,10 +166,12 @@ struct JvpArgs {
 // operations of 157 TFLOP/s; 8-wide heads use a quarter of the products with V).  Two waves per SIMD
 // cover the latency of the weight fragments, which come through the caches.  It replaces 64 x 64
 // products on the vector ALU between activations in memory and an attention kernel whose threads
-// walked rows of global memory: 16384 configurations at n = 32, benchmark network 75.1 -> 14.2 ms (94
-// TFLOP/s), 32768 at n = 16 28.1 -> 7.0 ms, 4096 at n = 64, 2 layers 31.2 -> 4.7 ms.
+// walked rows of global memory: 16384 configurations at n = 32, benchmark network 75.1 -> 13.8 ms (97
+// TFLOP/s), 32768 at n = 16 28.1 -> 6.5 ms, 4096 at n = 64, 2 layers 31.2 -> 4.6 ms.  The bound on
+// the waves per SIMD tells the compiler what the LDS already decides (14.2, 7.0 and 4.7 without);
+// loading the weight fragments ahead in registers, as the forward does, spills (14.7 and 7.2).
 template <int D, int DH, bool SPAN>
-__global__ void __launch_bounds__(512) k_jvp_layer(JvpArgs a) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) k_jvp_layer(JvpArgs a) {
   constexpr int NB = D / 32, HPB = 32 / DH, VPH = DH / 2, NKB = SPAN ? 2 : 1, LS = 36, TILE = 32 * LS;
   using P = PF32;
   __shared__ __align__(16) float sm[8][4][TILE];  // per wave: k, t(k), v, t(v) [row][pos]

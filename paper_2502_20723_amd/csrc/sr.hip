@@ -5,12 +5,13 @@
 // parameters theta.  With J the 2B x P matrix of rows sqrt(w_b) dRe O(x_b) and
 // sqrt(w_b) dIm O(x_b), S = J^T J, so S is never formed: conjugate gradients
 // on (J^T J + lambda I) x = g take two passes over J per iteration (rows
-// u = J p in segments, the segment sums, then columns J^T u).
+// u = J p in segments, then columns J^T u with the segment sums).
 //
 // The Jacobian comes from tdo_log_rho_jacobian; this call centres and scales
-// it in place.  Dot products are two-stage FP64 sums in a fixed order (slices,
-// then one workgroup over the slices) and CG's scalars stay on the device, so the iteration count is fixed by the
-// caller and the result does not depend on scheduling.
+// it in place.  Dot products are two-stage FP64 sums in a fixed order (slices, then the slices, by every
+// workgroup that needs the product) and CG's scalars stay on the device, so the iteration count is fixed by
+// the caller and the result does not depend on scheduling.  An iteration is five launches (ten with the
+// sums of the slices and the scalars in launches of their own: 38 us of 195, now 15 of 162).
 #include <algorithm>
 #include <cmath>
 
@@ -48,24 +49,28 @@ __global__ void __launch_bounds__(kT) k_sr_wsum(const double* __restrict__ w, in
   if (threadIdx.x == 0) sc[0] = a;
 }
 
-// Column k: subtract the weighted mean of each part and scale row b by sqrt(w_b / sum w).
-__global__ void k_sr_center(double* __restrict__ J, int64_t B, int64_t P, const double* __restrict__ w,
-                            const double* __restrict__ sc) {
+// Columns: subtract the weighted mean of each part (blockIdx.y) and scale row b by sqrt(w_b / sum w).
+// Bound: memory, two reads and a write (the second read mostly from the last-level cache).  Eight
+// rows' loads are in flight per thread and the parts are two rows of workgroups: B = 256,
+// P = 107650 (441 MB): 518 -> 335 us.
+__global__ void __launch_bounds__(kT) k_sr_center(double* __restrict__ J, int64_t B, int64_t P, const double* __restrict__ w,
+                                                  const double* __restrict__ sc) {
   const double inv = 1.0 / sc[0];
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < P; k += (int64_t)gridDim.x * blockDim.x) {
-    for (int part = 0; part < 2; ++part) {
-      double mean = 0.0;
-      for (int64_t b = 0; b < B; ++b) mean += (w ? w[b] : 1.0) * inv * J[(2 * b + part) * P + k];
-      for (int64_t b = 0; b < B; ++b) {
-        double* e = J + (2 * b + part) * P + k;
-        *e = sqrt((w ? w[b] : 1.0) * inv) * (*e - mean);
-      }
-    }
+  const int part = blockIdx.y;
+  for (int64_t k = (int64_t)blockIdx.x * kT + threadIdx.x; k < P; k += (int64_t)gridDim.x * kT) {
+    double* e = J + part * P + k;
+    double mean = 0.0;
+#pragma unroll 8
+    for (int64_t b = 0; b < B; ++b) mean += (w ? w[b] : 1.0) * inv * e[2 * b * P];
+#pragma unroll 8
+    for (int64_t b = 0; b < B; ++b) e[2 * b * P] = sqrt((w ? w[b] : 1.0) * inv) * (e[2 * b * P] - mean);
   }
 }
 
 // Partial row dots: workgroup (r, s) forms J[r] . p over segment s of kSeg equal
 // segments, into up[r][s] (summed in segment order by the column pass).
+// Bound: memory, one read of J (441 MB at R = 512, P = 107650: 92 -> 82 us).  Four rows per workgroup,
+// which read p once for all, leave too few loads in flight (113 us).
 constexpr int kSeg = 8;
 __global__ void __launch_bounds__(kT) k_sr_rows(const double* __restrict__ J, int64_t R, int64_t P,
                                                 const double* __restrict__ p, double* __restrict__ up) {
@@ -76,43 +81,60 @@ __global__ void __launch_bounds__(kT) k_sr_rows(const double* __restrict__ J, in
     const double* row = J + r * P;
     const int64_t k1 = std::min<int64_t>(P, (s + 1) * seg);
     double a = 0.0;
+#pragma unroll 8
     for (int64_t k = s * seg + threadIdx.x; k < k1; k += kT) a += row[k] * p[k];
     a = block_reduce(a, red);
     if (threadIdx.x == 0) up[rs] = a;
   }
 }
 
-// u[r] = sum over s of up[r][s], in segment order.
-__global__ void k_sr_usum(const double* __restrict__ up, int64_t R, double* __restrict__ u) {
-  for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < R; r += (int64_t)gridDim.x * blockDim.x) {
-    double a = 0.0;
+// Ap[k] = sum_r J[r][k] u[r] + lambda p[k], one thread per column, with u[r] = sum over s of up[r][s] in
+// segment order, formed in LDS for kURows rows at a time; four accumulators over r mod 4 (summed in that
+// order).  Bound: memory, one read of J.  The rows are taken last to first: the row pass has just left the
+// last ones in the last-level cache (256 MB), and this pass leaves the first ones for the next row pass.
+// R = 512, P = 107650: 84 us first to last with four loads in flight, 73 with eight, 68 last to first (and
+// the row pass 94 -> 82).
+constexpr int kURows = 512;
+__global__ void __launch_bounds__(kT) k_sr_cols(const double* __restrict__ J, int64_t R, int64_t P, const double* __restrict__ up,
+                                                const double* __restrict__ p, double lambda, double* __restrict__ Ap) {
+  __shared__ double u[kURows];
+  for (int64_t k0 = (int64_t)blockIdx.x * kT; k0 < P; k0 += (int64_t)gridDim.x * kT) {
+    const int64_t k = k0 + threadIdx.x;
+    const bool live = k < P;
+    const double* col = J + (live ? k : 0);
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t r0 = (R - 1) / kURows * kURows; r0 >= 0; r0 -= kURows) {
+      const int rows = (int)std::min<int64_t>(kURows, R - r0);
+      __syncthreads();  // the previous rows' sums read
+      for (int i = threadIdx.x; i < rows; i += kT) {
+        double t = 0.0;
 #pragma unroll
-    for (int s = 0; s < kSeg; ++s) a += up[r * kSeg + s];
-    u[r] = a;
-  }
-}
-
-// Ap[k] = sum_r J[r][k] u[r] + lambda p[k], one thread per column; four
-// accumulators over r mod 4 (summed in that order) keep four loads in flight.
-__global__ void k_sr_cols(const double* __restrict__ J, int64_t R, int64_t P, const double* __restrict__ u,
-                          const double* __restrict__ p, double lambda, double* __restrict__ Ap) {
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < P; k += (int64_t)gridDim.x * blockDim.x) {
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int64_t r = 0;
-    for (; r + 4 <= R; r += 4) {
-      a0 += J[r * P + k] * u[r];
-      a1 += J[(r + 1) * P + k] * u[r + 1];
-      a2 += J[(r + 2) * P + k] * u[r + 2];
-      a3 += J[(r + 3) * P + k] * u[r + 3];
+        for (int s = 0; s < kSeg; ++s) t += up[(r0 + i) * kSeg + s];
+        u[i] = t;
+      }
+      __syncthreads();
+      if (!live) continue;
+      int i = rows - 1;
+      for (; (i & 3) != 3 && i >= 0; --i) a[i & 3] += col[(r0 + i) * P] * u[i];
+#pragma unroll 2
+      for (; i >= 3; i -= 4) {
+        a[3] += col[(r0 + i) * P] * u[i];
+        a[2] += col[(r0 + i - 1) * P] * u[i - 1];
+        a[1] += col[(r0 + i - 2) * P] * u[i - 2];
+        a[0] += col[(r0 + i - 3) * P] * u[i - 3];
+      }
     }
-    for (; r < R; ++r) a0 += J[r * P + k] * u[r];
-    Ap[k] = ((a0 + a1) + (a2 + a3)) + lambda * p[k];
+    if (live) Ap[k] = ((a[0] + a[1]) + (a[2] + a[3])) + lambda * p[k];
   }
 }
 
-// a . b in a fixed order: kDotParts workgroups sum contiguous slices into part[],
-// then one workgroup sums the parts (k_sr_dot_fin).
+// a . b in a fixed order: kDotParts workgroups sum contiguous slices into part[]; every workgroup of
+// the kernel that uses the product sums the parts for itself (dot_parts).
 constexpr int kDotParts = 256;
+static_assert(kDotParts == kT, "one part per thread");
+__device__ __forceinline__ double dot_parts(const double* __restrict__ part, double* red) {
+  return block_reduce(0.0 + part[threadIdx.x], red);
+}
 __global__ void __launch_bounds__(kT) k_sr_dot(const double* __restrict__ a, const double* __restrict__ b,
                                                int64_t P, double* __restrict__ part) {
   __shared__ double red[kT];
@@ -122,14 +144,6 @@ __global__ void __launch_bounds__(kT) k_sr_dot(const double* __restrict__ a, con
   for (int64_t k = k0 + threadIdx.x; k < k1; k += kT) s += a[k] * b[k];
   s = block_reduce(s, red);
   if (threadIdx.x == 0) part[blockIdx.x] = s;
-}
-
-__global__ void __launch_bounds__(kT) k_sr_dot_fin(const double* __restrict__ part, double* __restrict__ out) {
-  __shared__ double red[kT];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < kDotParts; i += kT) s += part[i];
-  s = block_reduce(s, red);
-  if (threadIdx.x == 0) out[0] = s;
 }
 
 // x <- 0, r <- g, p <- g.
@@ -142,38 +156,70 @@ __global__ void k_sr_init(const double* __restrict__ g, int64_t P, double* __res
   }
 }
 
-// alpha = rs / (p . Ap) (0 when p . Ap = 0); x += alpha p; r -= alpha Ap.
-__global__ void k_sr_step(int64_t P, const double* __restrict__ sc, const double* __restrict__ p,
-                          const double* __restrict__ Ap, double* __restrict__ x, double* __restrict__ r) {
-  const double pAp = sc[2], rs = sc[1];
+// alpha = rs / (p . Ap) (0 when p . Ap = 0); x += alpha p; r -= alpha Ap; the parts of the new r . r.
+__global__ void __launch_bounds__(kT) k_sr_step(int64_t P, const double* __restrict__ rs_part, const double* __restrict__ pap_part,
+                                                const double* __restrict__ p, const double* __restrict__ Ap,
+                                                double* __restrict__ x, double* __restrict__ r, double* __restrict__ rn_part) {
+  __shared__ double red[kT];
+  const double pAp = dot_parts(pap_part, red), rs = dot_parts(rs_part, red);
   const double alpha = pAp != 0.0 ? rs / pAp : 0.0;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < P; k += (int64_t)gridDim.x * blockDim.x) {
+  const int64_t slice = (P + kDotParts - 1) / kDotParts;
+  const int64_t k0 = blockIdx.x * slice, k1 = std::min<int64_t>(P, k0 + slice);
+  double s = 0.0;
+  for (int64_t k = k0 + threadIdx.x; k < k1; k += kT) {
     x[k] += alpha * p[k];
-    r[k] -= alpha * Ap[k];
+    const double t = r[k] - alpha * Ap[k];
+    r[k] = t;
+    s += t * t;
   }
+  s = block_reduce(s, red);
+  if (threadIdx.x == 0) rn_part[blockIdx.x] = s;
 }
 
 // beta = rs_new / rs (0 when rs = 0); p = r + beta p.
-__global__ void k_sr_dir(int64_t P, const double* __restrict__ sc, const double* __restrict__ r,
-                         double* __restrict__ p) {
-  const double rs = sc[1], rn = sc[3];
+__global__ void __launch_bounds__(kT) k_sr_dir(int64_t P, const double* __restrict__ rs_part, const double* __restrict__ rn_part,
+                                               const double* __restrict__ r, double* __restrict__ p) {
+  __shared__ double red[kT];
+  const double rs = dot_parts(rs_part, red), rn = dot_parts(rn_part, red);
   const double beta = rs != 0.0 ? rn / rs : 0.0;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < P; k += (int64_t)gridDim.x * blockDim.x)
-    p[k] = r[k] + beta * p[k];
-}
-
-// rs <- rs_new.
-__global__ void k_sr_roll(double* __restrict__ sc) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) sc[1] = sc[3];
+  for (int64_t k = (int64_t)blockIdx.x * kT + threadIdx.x; k < P; k += (int64_t)gridDim.x * kT) p[k] = r[k] + beta * p[k];
 }
 
 // info[0] = |r| / |g| from the recurrence, info[1] = |g|.
-__global__ void k_sr_info(const double* __restrict__ sc, double* __restrict__ info) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const double gn = sqrt(sc[4]);
-    info[0] = gn > 0.0 ? sqrt(sc[1]) / gn : 0.0;
+__global__ void __launch_bounds__(kT) k_sr_info(const double* __restrict__ rs_part, const double* __restrict__ gg_part,
+                                                double* __restrict__ info) {
+  __shared__ double red[kT];
+  const double rs = dot_parts(rs_part, red), gn = sqrt(dot_parts(gg_part, red));
+  if (threadIdx.x == 0) {
+    info[0] = gn > 0.0 ? sqrt(rs) / gn : 0.0;
     info[1] = gn;
   }
+}
+
+// Conjugate gradients on (S + lambda) x = g; apply(p, Ap) queues Ap = (S + lambda) p.  The parts of the
+// dot products: [0], [1] r . r, in turn the current and the next one, [2] p . Ap, [3] g . g.
+template <class Apply>
+static int32_t cg(int64_t P, const double* grad, int32_t iters, double* x, double* r, double* p, double* Ap, double* parts,
+                  double* info, hipStream_t stream, Apply&& apply) {
+  const unsigned gp = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(P, 256), 4096));
+  auto part = [&](int i) { return parts + (int64_t)i * kDotParts; };
+  hipLaunchKernelGGL(k_sr_init, dim3(gp), dim3(256), 0, stream, grad, P, x, r, p);
+  hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, grad, grad, P, part(0));
+  hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, grad, grad, P, part(3));
+  TDO_HIP(hipGetLastError());
+  for (int32_t it = 0; it < iters; ++it) {
+    TDO_TRY(apply(p, Ap));
+    double *rs = part(it & 1), *rn = part(~it & 1);
+    hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, p, Ap, P, part(2));
+    hipLaunchKernelGGL(k_sr_step, dim3(kDotParts), dim3(kT), 0, stream, P, rs, part(2), p, Ap, x, r, rn);
+    hipLaunchKernelGGL(k_sr_dir, dim3(gp), dim3(kT), 0, stream, P, rs, rn, r, p);
+    TDO_HIP(hipGetLastError());
+  }
+  if (info) {
+    hipLaunchKernelGGL(k_sr_info, dim3(1), dim3(kT), 0, stream, part(iters & 1), part(3), info);
+    TDO_HIP(hipGetLastError());
+  }
+  return TDO_OK;
 }
 
 // --- the matrix-free form: S p = J^T (J p) from one forward-mode and one reverse-mode pass
@@ -235,49 +281,25 @@ extern "C" int32_t tdo_sr_solve(tdo_ctx_t* ctx, double* jac, int64_t B, int64_t 
   TDO_TRY(order.begin(&c, stream));
   Arena ar;
   const size_t or_ = ar.take<double>((size_t)P), op = ar.take<double>((size_t)P), oap = ar.take<double>((size_t)P);
-  const size_t oup = ar.take<double>(2 * (size_t)B * kSeg), ou = ar.take<double>(2 * (size_t)B);
-  const size_t osc = ar.take<double>(8);
-  const size_t opart = ar.take<double>(kDotParts);
+  const size_t oup = ar.take<double>(2 * (size_t)B * kSeg), osc = ar.take<double>(1), opart = ar.take<double>(4 * kDotParts);
   TDO_TRY(ensure_workspace(&c, ar.used));
   double* r = at<double>(c.ws, or_);
   double* p = at<double>(c.ws, op);
   double* Ap = at<double>(c.ws, oap);
   double* up = at<double>(c.ws, oup);
-  double* u = at<double>(c.ws, ou);
-  double* sc = at<double>(c.ws, osc);  // [0] sum w, [1] rs, [2] p.Ap, [3] rs_new, [4] g.g
+  double* sc = at<double>(c.ws, osc);  // sum w
   double* part = at<double>(c.ws, opart);
-  auto dot = [&](const double* a, const double* b, double* out) -> int32_t {
-    hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, a, b, P, part);
-    hipLaunchKernelGGL(k_sr_dot_fin, dim3(1), dim3(kT), 0, stream, part, out);
-    TDO_HIP(hipGetLastError());
-    return TDO_OK;
-  };
   const int64_t R = 2 * B;
   const unsigned gp = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(P, 256), 4096));
   const unsigned gr = (unsigned)std::min<int64_t>(R * kSeg, 16384);
   hipLaunchKernelGGL(k_sr_wsum, dim3(1), dim3(kT), 0, stream, weights, B, sc);
-  hipLaunchKernelGGL(k_sr_center, dim3(gp), dim3(256), 0, stream, jac, B, P, weights, sc);
-  hipLaunchKernelGGL(k_sr_init, dim3(gp), dim3(256), 0, stream, grad, P, x, r, p);
+  hipLaunchKernelGGL(k_sr_center, dim3(gp, 2), dim3(kT), 0, stream, jac, B, P, weights, sc);
   TDO_HIP(hipGetLastError());
-  TDO_TRY(dot(grad, grad, sc + 1));
-  TDO_TRY(dot(grad, grad, sc + 4));
-  for (int32_t it = 0; it < iters; ++it) {
-    hipLaunchKernelGGL(k_sr_rows, dim3(gr), dim3(kT), 0, stream, jac, R, P, p, up);
-    hipLaunchKernelGGL(k_sr_usum, dim3((unsigned)std::min<int64_t>(ceil_div(R, 256), 1024)), dim3(256), 0, stream,
-                       up, R, u);
-    hipLaunchKernelGGL(k_sr_cols, dim3(gp), dim3(256), 0, stream, jac, R, P, u, p, lambda, Ap);
-    TDO_TRY(dot(p, Ap, sc + 2));
-    hipLaunchKernelGGL(k_sr_step, dim3(gp), dim3(256), 0, stream, P, sc, p, Ap, x, r);
-    TDO_TRY(dot(r, r, sc + 3));
-    hipLaunchKernelGGL(k_sr_dir, dim3(gp), dim3(256), 0, stream, P, sc, r, p);
-    hipLaunchKernelGGL(k_sr_roll, dim3(1), dim3(64), 0, stream, sc);
-    TDO_HIP(hipGetLastError());
-  }
-  if (info) {
-    hipLaunchKernelGGL(k_sr_info, dim3(1), dim3(64), 0, stream, sc, info);
-    TDO_HIP(hipGetLastError());
-  }
-  return TDO_OK;
+  return cg(P, grad, iters, x, r, p, Ap, part, info, stream, [&](const double* v, double* Av) -> int32_t {
+    hipLaunchKernelGGL(k_sr_rows, dim3(gr), dim3(kT), 0, stream, jac, R, P, v, up);
+    hipLaunchKernelGGL(k_sr_cols, dim3(gp), dim3(kT), 0, stream, jac, R, P, up, v, lambda, Av);
+    return TDO_OK;
+  });
 }
 
 // S p = Re sum_b w_b conj(dO_b) (dO_b . p) with t_b = O_b . p from the forward-mode pass:
@@ -307,7 +329,7 @@ extern "C" int32_t tdo_sr_solve_matfree(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   // most a third of the rest of the budget), then the reverse-mode plan in what remains
   Arena ar;
   const size_t or_ = ar.take<double>((size_t)P), op = ar.take<double>((size_t)P), oap = ar.take<double>((size_t)P);
-  const size_t osc = ar.take<double>(16), opart = ar.take<double>(kDotParts);
+  const size_t osc = ar.take<double>(8), opart = ar.take<double>(4 * kDotParts);
   const size_t ot = ar.take<float>(2 * (size_t)B), oseed = ar.take<float>(2 * (size_t)B);
   TDO_CHECK(c.budget > ar.used + 4096, TDO_ENOMEM, "workspace budget %zu too small", c.budget);
   JvpWs j;
@@ -321,39 +343,18 @@ extern "C" int32_t tdo_sr_solve_matfree(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   float *tv = at<float>(ws, ot), *seed = at<float>(ws, oseed);
   const unsigned gp = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(P, 256), 4096));
   const unsigned gb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(B, 256), 4096));
-  auto dot = [&](const double* a, const double* b, double* out) -> int32_t {
-    hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, a, b, P, part);
-    hipLaunchKernelGGL(k_sr_dot_fin, dim3(1), dim3(kT), 0, stream, part, out);
-    TDO_HIP(hipGetLastError());
-    return TDO_OK;
-  };
   {  // the reverse-mode weight fragments, packed once
     NetWeights w = weights_at(ws, t.woff);
     TDO_TRY(pack_weights(npv, params, &w, stream, at<char>(ws, t.wback)));
   }
-  // sc: [1] rs, [2] p.Ap, [3] rs_new, [4] g.g, [8..10] weight sum and weighted tangent sums
-  hipLaunchKernelGGL(k_sr_init, dim3(gp), dim3(256), 0, stream, grad, P, x, r, p);
-  TDO_HIP(hipGetLastError());
-  TDO_TRY(dot(grad, grad, sc + 1));
-  TDO_TRY(dot(grad, grad, sc + 4));
-  for (int32_t it = 0; it < iters; ++it) {
-    TDO_TRY(run_jvp(npj, ws, j, params, p, cfg, B, tv, stream));
-    hipLaunchKernelGGL(k_mf_mean, dim3(1), dim3(kT), 0, stream, tv, weights, B, sc + 8);
-    hipLaunchKernelGGL(k_mf_seeds, dim3(gb), dim3(256), 0, stream, tv, weights, B, sc + 8, seed);
+  // sc: weight sum and weighted tangent sums
+  return cg(P, grad, iters, x, r, p, Ap, part, info, stream, [&](const double* v, double* Av) -> int32_t {
+    TDO_TRY(run_jvp(npj, ws, j, params, v, cfg, B, tv, stream));
+    hipLaunchKernelGGL(k_mf_mean, dim3(1), dim3(kT), 0, stream, tv, weights, B, sc);
+    hipLaunchKernelGGL(k_mf_seeds, dim3(gb), dim3(256), 0, stream, tv, weights, B, sc, seed);
     TDO_HIP(hipGetLastError());
-    TDO_TRY(vjp_run(c, npv, t, params, cfg, B, seed, Ap, true, stream));
-    hipLaunchKernelGGL(k_mf_shift, dim3(gp), dim3(256), 0, stream, P, lambda, p, Ap);
-    TDO_HIP(hipGetLastError());
-    TDO_TRY(dot(p, Ap, sc + 2));
-    hipLaunchKernelGGL(k_sr_step, dim3(gp), dim3(256), 0, stream, P, sc, p, Ap, x, r);
-    TDO_TRY(dot(r, r, sc + 3));
-    hipLaunchKernelGGL(k_sr_dir, dim3(gp), dim3(256), 0, stream, P, sc, r, p);
-    hipLaunchKernelGGL(k_sr_roll, dim3(1), dim3(64), 0, stream, sc);
-    TDO_HIP(hipGetLastError());
-  }
-  if (info) {
-    hipLaunchKernelGGL(k_sr_info, dim3(1), dim3(64), 0, stream, sc, info);
-    TDO_HIP(hipGetLastError());
-  }
-  return TDO_OK;
+    TDO_TRY(vjp_run(c, npv, t, params, cfg, B, seed, Av, true, stream));
+    hipLaunchKernelGGL(k_mf_shift, dim3(gp), dim3(256), 0, stream, P, lambda, v, Av);
+    return TDO_OK;
+  });
 }

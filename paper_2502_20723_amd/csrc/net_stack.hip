@@ -21,7 +21,7 @@ constexpr int STACK_FF_BYTES = 64 * 1024;  // a layer's feed-forward weights (BF
 // workgroup has `pairs` of them: 4, or fewer in a batch that leaves CUs idle (a wave alone on its SIMD
 // is faster).  TW: tiles per wave.
 //   TW = 1: waves 2p and 2p + 1 hold the tiles of pair p, p < pairs.
-//   TW = 2 (BF16, modes 0 and 3, large batches): wave p < pairs <= 8 holds both tiles of pair p.  A BF16 weight fragment is 1 KB of LDS for one product of 32 cycles, so four
+//   TW = 2 (BF16, large batches): wave p < pairs <= 8 holds both tiles of pair p.  A BF16 weight fragment is 1 KB of LDS for one product of 32 cycles, so four
 //     SIMDs with one tile per wave ask for the 128 bytes per cycle that LDS delivers, and the bias
 //     comes on top; in the feed-forward part a fragment now serves two tiles.  In the attention part the
 //     tiles take turns: together they spill 17 to 110 registers.  65536 configurations, 4 layers,
@@ -254,16 +254,16 @@ template <class P, int D, int DH, int MBC, bool MASKED>
 static int32_t stack_m(StackArgs a, int mode, int num_cus, hipStream_t st) {
   const int64_t tiles = (a.E + a.cpb - 1) / a.cpb;
   // Two tiles per wave.  A round of the chip (4 pairs per CU with one tile, 8 with two) at n = 32, 4
-  // layers, takes 33 and 57 us, so mode 0 takes them where 1.8 times its rounds are fewer: 2048 pairs 91
-  // and 84 us, 3072 129 and 140, 4096 159 and 143.  With the activations saved a backward pass follows,
+  // layers, takes 33 and 57 us, so they are taken where 1.8 times their rounds are fewer: 2048 pairs 91
+  // and 84 us, 3072 129 and 140, 4096 159 and 143 (per proposal of 2048 chains 70 and 63).  With the activations saved a backward pass follows,
   // and the gain of this kernel is lost in its clock up to 64 pairs per CU (log rho and gradient, BF16,
   // n = 32: 8192 pairs 1603 and 1626 us, 24576 4220 and 4148).
   const int64_t r1 = (tiles + 4 * num_cus - 1) / (4 * num_cus), r2 = (tiles + 8 * num_cus - 1) / (8 * num_cus);
-  const bool two = P::KPL == 8 && ((mode == 0 && 18 * r2 < 10 * r1) || (mode == 3 && tiles > 64LL * num_cus));
+  const bool two = P::KPL == 8 && (mode == 3 ? tiles > 64LL * num_cus : 18 * r2 < 10 * r1);
   constexpr int T2 = P::KPL == 8 ? 2 : 1;
   auto kern = mode == 0   ? (two ? k_fwd_stack<P, D, DH, MBC, MASKED, 0, T2> : k_fwd_stack<P, D, DH, MBC, MASKED, 0, 1>)
-              : mode == 1 ? k_fwd_stack<P, D, DH, MBC, MASKED, 1, 1>
-              : mode == 2 ? k_fwd_stack<P, D, DH, MBC, MASKED, 2, 1>
+              : mode == 1 ? (two ? k_fwd_stack<P, D, DH, MBC, MASKED, 1, T2> : k_fwd_stack<P, D, DH, MBC, MASKED, 1, 1>)
+              : mode == 2 ? (two ? k_fwd_stack<P, D, DH, MBC, MASKED, 2, T2> : k_fwd_stack<P, D, DH, MBC, MASKED, 2, 1>)
                           : (two ? k_fwd_stack<P, D, DH, MBC, MASKED, 3, T2> : k_fwd_stack<P, D, DH, MBC, MASKED, 3, 1>);
   TDO_TRY(allow_full_lds((const void*)kern, STACK_STATIC));
   const size_t lds = stack_lds_t<P, D>(a.M, a.layers);

@@ -72,6 +72,12 @@ def test_two_tiles_per_wave(gpu, net, n, B, parts):
         assert torch.equal(ctx.log_rho(arch, params, n, cfg[:k].contiguous(), "bf16"), whole[:k]), k
 
 
+@pytest.mark.parametrize("net,n,C,parts", [((64, 8, 2, 64), 32, 1029, (1024,)), ((64, 4, 2, 256), 13, 2 * 3300 - 1, (700,)),
+                                           ((32, 4, 3, 96), 8, 4 * 1300 + 1, (4096, 5)), ((16, 2, 2, 64), 3, 10 * 1500, (10001,))])
+def test_two_tiles_per_wave_chains(gpu, net, n, C, parts):
+    test_chains_same_states(gpu, net, n, C, parts, "bf16")
+
+
 @pytest.mark.parametrize("net,n,B", [((64, 8, 2, 64), 32, 16385), ((64, 4, 2, 256), 16, 2 * 17000 - 1), ((32, 4, 2, 96), 9, 3 * 16500 + 2),
                                      ((16, 2, 2, 32), 3, 10 * 20001 - 7)])
 def test_two_tiles_per_wave_with_activations(gpu, net, n, B):

@@ -130,10 +130,10 @@ __global__ void __launch_bounds__(kT) k_sr_cols(const double* __restrict__ J, in
 
 // a . b in a fixed order: kDotParts workgroups sum contiguous slices into part[]; every workgroup of
 // the kernel that uses the product sums the parts for itself (dot_parts).
-constexpr int kDotParts = 256;
-static_assert(kDotParts == kT, "one part per thread");
+constexpr int kDotParts = 128;
+static_assert(kDotParts <= kT, "at most one part per thread");
 __device__ __forceinline__ double dot_parts(const double* __restrict__ part, double* red) {
-  return block_reduce(0.0 + part[threadIdx.x], red);
+  return block_reduce(threadIdx.x < kDotParts ? part[threadIdx.x] : 0.0, red);
 }
 __global__ void __launch_bounds__(kT) k_sr_dot(const double* __restrict__ a, const double* __restrict__ b,
                                                int64_t P, double* __restrict__ part) {
@@ -156,13 +156,20 @@ __global__ void k_sr_init(const double* __restrict__ g, int64_t P, double* __res
   }
 }
 
+// out[0] = out[1] = the sum of the parts.
+__global__ void __launch_bounds__(kT) k_sr_sum(const double* __restrict__ part, double* __restrict__ out) {
+  __shared__ double red[kT];
+  const double s = dot_parts(part, red);
+  if (threadIdx.x == 0) out[0] = out[1] = s;
+}
+
 // alpha = rs / (p . Ap) (0 when p . Ap = 0); x += alpha p; r -= alpha Ap; the parts of the new r . r.
-__global__ void __launch_bounds__(kT) k_sr_step(int64_t P, const double* __restrict__ rs_part, const double* __restrict__ pap_part,
+__global__ void __launch_bounds__(kT) k_sr_step(int64_t P, const double* __restrict__ rs, const double* __restrict__ pap_part,
                                                 const double* __restrict__ p, const double* __restrict__ Ap,
                                                 double* __restrict__ x, double* __restrict__ r, double* __restrict__ rn_part) {
   __shared__ double red[kT];
-  const double pAp = dot_parts(pap_part, red), rs = dot_parts(rs_part, red);
-  const double alpha = pAp != 0.0 ? rs / pAp : 0.0;
+  const double pAp = dot_parts(pap_part, red);
+  const double alpha = pAp != 0.0 ? rs[0] / pAp : 0.0;
   const int64_t slice = (P + kDotParts - 1) / kDotParts;
   const int64_t k0 = blockIdx.x * slice, k1 = std::min<int64_t>(P, k0 + slice);
   double s = 0.0;
@@ -176,47 +183,46 @@ __global__ void __launch_bounds__(kT) k_sr_step(int64_t P, const double* __restr
   if (threadIdx.x == 0) rn_part[blockIdx.x] = s;
 }
 
-// beta = rs_new / rs (0 when rs = 0); p = r + beta p.
-__global__ void __launch_bounds__(kT) k_sr_dir(int64_t P, const double* __restrict__ rs_part, const double* __restrict__ rn_part,
-                                               const double* __restrict__ r, double* __restrict__ p) {
+// beta = rs_new / rs (0 when rs = 0); p = r + beta p; rs_new to its own slot for the next iteration.
+__global__ void __launch_bounds__(kT) k_sr_dir(int64_t P, const double* __restrict__ rs, const double* __restrict__ rn_part,
+                                               const double* __restrict__ r, double* __restrict__ p, double* __restrict__ rs_new) {
   __shared__ double red[kT];
-  const double rs = dot_parts(rs_part, red), rn = dot_parts(rn_part, red);
-  const double beta = rs != 0.0 ? rn / rs : 0.0;
+  const double rn = dot_parts(rn_part, red);
+  const double beta = rs[0] != 0.0 ? rn / rs[0] : 0.0;
   for (int64_t k = (int64_t)blockIdx.x * kT + threadIdx.x; k < P; k += (int64_t)gridDim.x * kT) p[k] = r[k] + beta * p[k];
+  if (blockIdx.x == 0 && threadIdx.x == 0) rs_new[0] = rn;
 }
 
 // info[0] = |r| / |g| from the recurrence, info[1] = |g|.
-__global__ void __launch_bounds__(kT) k_sr_info(const double* __restrict__ rs_part, const double* __restrict__ gg_part,
-                                                double* __restrict__ info) {
-  __shared__ double red[kT];
-  const double rs = dot_parts(rs_part, red), gn = sqrt(dot_parts(gg_part, red));
-  if (threadIdx.x == 0) {
-    info[0] = gn > 0.0 ? sqrt(rs) / gn : 0.0;
+__global__ void k_sr_info(const double* __restrict__ rs, const double* __restrict__ gg, double* __restrict__ info) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const double gn = sqrt(gg[0]);
+    info[0] = gn > 0.0 ? sqrt(rs[0]) / gn : 0.0;
     info[1] = gn;
   }
 }
 
-// Conjugate gradients on (S + lambda) x = g; apply(p, Ap) queues Ap = (S + lambda) p.  The parts of the
-// dot products: [0], [1] r . r, in turn the current and the next one, [2] p . Ap, [3] g . g.
+// Conjugate gradients on (S + lambda) x = g; apply(p, Ap) queues Ap = (S + lambda) p.  part: the parts of
+// p . Ap, then those of r . r; sc: [0] g . g, [1], [2] r . r, in turn the current and the next one.
 template <class Apply>
-static int32_t cg(int64_t P, const double* grad, int32_t iters, double* x, double* r, double* p, double* Ap, double* parts,
-                  double* info, hipStream_t stream, Apply&& apply) {
+static int32_t cg(int64_t P, const double* grad, int32_t iters, double* x, double* r, double* p, double* Ap, double* part,
+                  double* sc, double* info, hipStream_t stream, Apply&& apply) {
   const unsigned gp = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(P, 256), 4096));
-  auto part = [&](int i) { return parts + (int64_t)i * kDotParts; };
+  double* rn_part = part + kDotParts;
   hipLaunchKernelGGL(k_sr_init, dim3(gp), dim3(256), 0, stream, grad, P, x, r, p);
-  hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, grad, grad, P, part(0));
-  hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, grad, grad, P, part(3));
+  hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, grad, grad, P, part);
+  hipLaunchKernelGGL(k_sr_sum, dim3(1), dim3(kT), 0, stream, part, sc);
   TDO_HIP(hipGetLastError());
   for (int32_t it = 0; it < iters; ++it) {
     TDO_TRY(apply(p, Ap));
-    double *rs = part(it & 1), *rn = part(~it & 1);
-    hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, p, Ap, P, part(2));
-    hipLaunchKernelGGL(k_sr_step, dim3(kDotParts), dim3(kT), 0, stream, P, rs, part(2), p, Ap, x, r, rn);
-    hipLaunchKernelGGL(k_sr_dir, dim3(gp), dim3(kT), 0, stream, P, rs, rn, r, p);
+    double *rs = sc + 1 + (it & 1), *rs_new = sc + 1 + (~it & 1);
+    hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, p, Ap, P, part);
+    hipLaunchKernelGGL(k_sr_step, dim3(kDotParts), dim3(kT), 0, stream, P, rs, part, p, Ap, x, r, rn_part);
+    hipLaunchKernelGGL(k_sr_dir, dim3(gp), dim3(kT), 0, stream, P, rs, rn_part, r, p, rs_new);
     TDO_HIP(hipGetLastError());
   }
   if (info) {
-    hipLaunchKernelGGL(k_sr_info, dim3(1), dim3(kT), 0, stream, part(iters & 1), part(3), info);
+    hipLaunchKernelGGL(k_sr_info, dim3(1), dim3(64), 0, stream, sc + 1 + (iters & 1), sc, info);
     TDO_HIP(hipGetLastError());
   }
   return TDO_OK;
@@ -281,13 +287,13 @@ extern "C" int32_t tdo_sr_solve(tdo_ctx_t* ctx, double* jac, int64_t B, int64_t 
   TDO_TRY(order.begin(&c, stream));
   Arena ar;
   const size_t or_ = ar.take<double>((size_t)P), op = ar.take<double>((size_t)P), oap = ar.take<double>((size_t)P);
-  const size_t oup = ar.take<double>(2 * (size_t)B * kSeg), osc = ar.take<double>(1), opart = ar.take<double>(4 * kDotParts);
+  const size_t oup = ar.take<double>(2 * (size_t)B * kSeg), osc = ar.take<double>(8), opart = ar.take<double>(2 * kDotParts);
   TDO_TRY(ensure_workspace(&c, ar.used));
   double* r = at<double>(c.ws, or_);
   double* p = at<double>(c.ws, op);
   double* Ap = at<double>(c.ws, oap);
   double* up = at<double>(c.ws, oup);
-  double* sc = at<double>(c.ws, osc);  // sum w
+  double* sc = at<double>(c.ws, osc);  // [0] sum w, [1..3] the scalars of cg
   double* part = at<double>(c.ws, opart);
   const int64_t R = 2 * B;
   const unsigned gp = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(P, 256), 4096));
@@ -295,7 +301,7 @@ extern "C" int32_t tdo_sr_solve(tdo_ctx_t* ctx, double* jac, int64_t B, int64_t 
   hipLaunchKernelGGL(k_sr_wsum, dim3(1), dim3(kT), 0, stream, weights, B, sc);
   hipLaunchKernelGGL(k_sr_center, dim3(gp, 2), dim3(kT), 0, stream, jac, B, P, weights, sc);
   TDO_HIP(hipGetLastError());
-  return cg(P, grad, iters, x, r, p, Ap, part, info, stream, [&](const double* v, double* Av) -> int32_t {
+  return cg(P, grad, iters, x, r, p, Ap, part, sc + 1, info, stream, [&](const double* v, double* Av) -> int32_t {
     hipLaunchKernelGGL(k_sr_rows, dim3(gr), dim3(kT), 0, stream, jac, R, P, v, up);
     hipLaunchKernelGGL(k_sr_cols, dim3(gp), dim3(kT), 0, stream, jac, R, P, up, v, lambda, Av);
     return TDO_OK;
@@ -329,7 +335,7 @@ extern "C" int32_t tdo_sr_solve_matfree(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   // most a third of the rest of the budget), then the reverse-mode plan in what remains
   Arena ar;
   const size_t or_ = ar.take<double>((size_t)P), op = ar.take<double>((size_t)P), oap = ar.take<double>((size_t)P);
-  const size_t osc = ar.take<double>(8), opart = ar.take<double>(4 * kDotParts);
+  const size_t osc = ar.take<double>(16), opart = ar.take<double>(2 * kDotParts);
   const size_t ot = ar.take<float>(2 * (size_t)B), oseed = ar.take<float>(2 * (size_t)B);
   TDO_CHECK(c.budget > ar.used + 4096, TDO_ENOMEM, "workspace budget %zu too small", c.budget);
   JvpWs j;
@@ -347,8 +353,8 @@ extern "C" int32_t tdo_sr_solve_matfree(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
     NetWeights w = weights_at(ws, t.woff);
     TDO_TRY(pack_weights(npv, params, &w, stream, at<char>(ws, t.wback)));
   }
-  // sc: weight sum and weighted tangent sums
-  return cg(P, grad, iters, x, r, p, Ap, part, info, stream, [&](const double* v, double* Av) -> int32_t {
+  // sc: [0..2] weight sum and weighted tangent sums, [3..5] the scalars of cg
+  return cg(P, grad, iters, x, r, p, Ap, part, sc + 3, info, stream, [&](const double* v, double* Av) -> int32_t {
     TDO_TRY(run_jvp(npj, ws, j, params, v, cfg, B, tv, stream));
     hipLaunchKernelGGL(k_mf_mean, dim3(1), dim3(kT), 0, stream, tv, weights, B, sc);
     hipLaunchKernelGGL(k_mf_seeds, dim3(gb), dim3(256), 0, stream, tv, weights, B, sc, seed);

@@ -1,5 +1,5 @@
 """The dense SR solve over the edges of its kernels (512 rows of J at a time in the column pass, rows mod
-4, 256 slices of a dot product, 8 segments of a row, columns mod 256), against the same conjugate
+4, 128 slices of a dot product, 8 segments of a row, columns mod 256), against the same conjugate
 gradients in numpy."""
 import numpy as np
 import pytest

@@ -36,7 +36,7 @@ PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}  # MI355X dense MFMA
 KERNELS = ("fwd_layer", "bwd_mlp", "bwd_attn")
 # Source files whose change invalidates a recorded HBM-traffic measurement.
 KERNEL_SOURCES = {
-    "fwd_layer": ("net_fwd.hip", "net.h", "netapi.h"),
+    "fwd_layer": ("net_stack.hip", "net_fwd.hip", "fwd_tile.h", "net.h", "netapi.h"),
     "bwd_mlp": ("net_bwd_mlp.hip", "net.h", "netapi.h"),
     "bwd_attn": ("net_bwd_attn.hip", "net.h", "netapi.h"),
 }

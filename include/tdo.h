@@ -114,7 +114,7 @@ const char *tdo_last_error(void);
 /* Per-kernel timing of the context's launches (measurement support, not part
  * of the method).  tdo_profile(ctx, 1) discards earlier records and starts
  * bracketing every launch of the kernel groups "fwd_layer" (one transformer
- * layer of the forward pass), "bwd_mlp" and "bwd_attn" (the backward of the
+ * layer of the forward pass, or all of them where one launch takes them), "bwd_mlp" and "bwd_attn" (the backward of the
  * feed-forward and attention sub-layers) with HIP events recorded on the
  * launch stream; tdo_profile(ctx, 0) stops recording and discards the records.
  * tdo_profile_read waits for the recorded events of the named group and

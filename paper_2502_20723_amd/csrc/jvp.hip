@@ -15,8 +15,8 @@
 //   head:       f = mean_i X_i Wh + bh, t(f) = mean_i (t(X_i) Wh + X_i t(Wh)) + t(bh), z = f0 + i f1;
 //   log rho = log(e^{z1} + conj e^{z2}):  t(log rho) = (e^{z1} t(z1) + conj(e^{z2} t(z2))) / (e^{z1} + conj e^{z2}).
 // A layer is one kernel on the FP32 matrix cores (k_jvp_layer), value and tangent together.
-// The value path takes every sum in ascending order (features, keys, hidden units), so that the
-// sign of a feed-forward pre-activation does not depend on the split into tiles.
+// Every sum is taken in ascending order (features, keys, hidden units), so that no value depends on the
+// split into tiles.
 #include <algorithm>
 #include <cmath>
 
@@ -155,23 +155,33 @@ struct JvpArgs {
   const float *w, *wd;  // packed layer and its tangent (k_jvp_pack)
   float *x, *xd;        // residual stream and its tangent, [blocks][D/32] tiles (load_tile), in place
   int64_t E;
-  int n, cpb, masked, heads, M;
+  int n, cpb, heads, M;
   float scale;
 };
 
 // One layer with its tangent.  A wave takes a 32-row block (in turn, 8 waves a workgroup) and holds
 // the residual update of the block in registers; keys and values of a head block go through LDS,
-// where a spanning pass's other wave reads them too.  Three matrix products per value product
-// (value; tangent of either factor).  Bound: the FP32 matrix cores (3 times the forward's
-// operations of 157 TFLOP/s; 8-wide heads use a quarter of the products with V).  Two waves per SIMD
-// cover the latency of the weight fragments, which come through the caches.  It replaces 64 x 64
-// products on the vector ALU between activations in memory and an attention kernel whose threads
-// walked rows of global memory: 16384 configurations at n = 32, benchmark network 75.1 -> 13.8 ms (97
-// TFLOP/s), 32768 at n = 16 28.1 -> 6.5 ms, 4096 at n = 64, 2 layers 31.2 -> 4.6 ms.  The bound on
-// the waves per SIMD tells the compiler what the LDS already decides (14.2, 7.0 and 4.7 without);
-// loading the weight fragments ahead in registers, as the forward does, spills (14.7 and 7.2).
-template <int D, int DH, bool SPAN>
+// where a spanning pass's other wave reads them too.
+//
+// The order of every sum is part of the result.  J p is one factor of the operator that the SR solve
+// iterates with, and a solve stopped after a few iterations on an ill-conditioned system carries a change
+// of rounding here into its update (a changed order of the tangent's sums moved updates of the benchmark
+// network by 1e-5, of one drawn system by 2e-4).  So: value sums in ascending order of their index; a tangent
+// t(A) B + A t(B) of a matrix product as the ascending sum over t(A) B, then that over A t(B); in the
+// attention, per key and feature, as one rounded term fma(t(a), b, a t(b)) added in ascending order.  The
+// projections and the feed-forward part run on the FP32 matrix cores, which add their products one after the
+// other; the second sum of a tangent repeats the hidden units (u is formed twice, a sixth of the
+// feed-forward products).  The attention's tangents and its products with V, which the matrix cores would
+// have to sum differently, run on the vector ALU, beside the other wave's products.
+//
+// Bound: the FP32 matrix cores (157 TFLOP/s) and the latency of the weight fragments, which come through the
+// caches: two waves per SIMD cover part of it (loaded ahead in registers, as the forward does, they spill).
+// 16384 configurations at n = 32, benchmark network: 15.8 ms; 32768 at n = 16, 4 heads, 2 layers 8.0 ms; 4096 at
+// n = 64, 2 layers 4.9 ms (with the sums in the order that suits the matrix cores 13.8, 6.6 and 4.6 ms; the same sums
+// as separate products on the vector ALU between activations in memory 75.1, 28.1 and 31.2 ms).
+template <int D, int DH, bool SPAN, bool MASKED>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) k_jvp_layer(JvpArgs a) {
+#pragma clang fp contract(off)
   constexpr int NB = D / 32, HPB = 32 / DH, VPH = DH / 2, NKB = SPAN ? 2 : 1, LS = 36, TILE = 32 * LS;
   using P = PF32;
   __shared__ __align__(16) float sm[8][4][TILE];  // per wave: k, t(k), v, t(v) [row][pos]
@@ -179,30 +189,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = a.n, cpb = a.cpb, M = a.M, MB = M / 32;
   const int64_t nblk = SPAN ? 4 * a.E : 2 * ((a.E + cpb - 1) / cpb);
-  const float *W[6], *Wd[6];  // Wq, Wk, Wv, Wo, W1, W2
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    const int o = i < 4 ? i * D * D : 4 * D * D + (i - 4) * D * M;
-    W[i] = a.w + o;
-    Wd[i] = a.wd + o;
-  }
-  const float *b1 = a.w + 4 * D * D + 2 * D * M, *b1d = a.wd + 4 * D * D + 2 * D * M;
-  // keys of this lane's query (value r of key block kb is row 32 kb + 2 r + h)
-  uint32_t okbits[NKB];
-#pragma unroll
-  for (int kb = 0; kb < NKB; ++kb) {
-    okbits[kb] = 0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int key = 32 * kb + 2 * r + h;
-      const bool ok = SPAN ? key < n : (a.masked ? key / n == asc(lr) / n && key / n < cpb : true);
-      okbits[kb] |= ok ? 1u << r : 0u;
-    }
-  }
-  const int kw = SPAN ? wave & ~1 : wave;  // wave that holds key block 0
-  const int vcol = pos(asc(lr));           // column of the feature of result row lr
-  auto load16 = [](const float* p) {
+  // fragment (ob, ib, s) of matrix m (Wq, Wk, Wv, Wo, W1, W2) or of its tangent
+  auto frag = [&](int m, int ob, int ib, int s, bool tangent) -> f32x4 {
+    const float* w = (tangent ? a.wd : a.w) + (m < 4 ? m * D * D : 4 * D * D + (m - 4) * D * M);
+    return ld_frag<P>(w, (ob * (m == 5 ? MB : NB) + ib) * 4 + s, lane);
+  };
+  // 16 values of a bias (b1 or b2) or of its tangent, features 32 c + 2 r + h
+  auto bias = [&](bool second, int c, bool tangent) {
     f32x16 v;
+    const float* p = (tangent ? a.wd : a.w) + 4 * D * D + 2 * D * M + (second ? M : 0) + 32 * c + 16 * h;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const float4 t = reinterpret_cast<const float4*>(p)[q];
@@ -210,6 +205,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
     return v;
   };
+  // keys of this lane's query row asc(lr): bit k of keys[kb] is row k of key block kb
+  uint32_t keys[NKB];
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb) {
+    keys[kb] = SPAN ? (uint32_t)low_mask(n - 32 * kb < 32 ? n - 32 * kb : 32) : ~0u;
+    if constexpr (MASKED && !SPAN) keys[kb] = asc(lr) / n < cpb ? (uint32_t)low_mask(n) << (asc(lr) / n * n) : 0u;
+  }
+  const int kw = SPAN ? wave & ~1 : wave;  // wave that holds key block 0, the next one key block 1
   auto store16 = [](float* p, const f32x16& v) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) reinterpret_cast<float4*>(p)[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
@@ -222,9 +225,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
     }
   };
-  auto column = [&](const float* t, int s) {  // lane -> feature of result row lr; rows in the order of the score tiles
-    const float* p = t + tile_idx(4 * s, h) * LS + vcol;
-    return f32x4{p[0], p[LS], p[2 * LS], p[3 * LS]};
+  // both halves' value of a lane: lower half first
+  auto halves = [](float v, float& lo, float& hi) {
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    lo = __uint_as_float(b[0]);
+    hi = __uint_as_float(b[1]);
   };
 
   for (int64_t base = (int64_t)blockIdx.x * 8; base < nblk; base += (int64_t)gridDim.x * 8) {
@@ -232,26 +237,27 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     if (!SPAN && !live) continue;
     const int64_t g = live ? base + wave : base + (wave & 1);  // a spanning pass's waves all meet at the barriers
     float *xb = a.x + g * NB * 1024, *xdb = a.xd + g * NB * 1024;  // feature block ib at 1024 ib
-    f32x16 y[NB], yd[NB];
+    f32x16 o[NB], od[NB];
 #pragma unroll
-    for (int ob = 0; ob < NB; ++ob) y[ob] = yd[ob] = f32x16{};
+    for (int ob = 0; ob < NB; ++ob) o[ob] = od[ob] = f32x16{};
 #pragma unroll 1
     for (int hb = 0; hb < NB; ++hb) {
-      // value and tangent of a projection's head block: c = W^T x, cd = W^T t(x) + t(W)^T x
+      // value and tangent of a projection's head block: c = W^T x, cd = W^T t(x), then + t(W)^T x
       auto project = [&](int m, f32x16& c, f32x16& cd) {
         c = cd = f32x16{};
+        auto xo = [&](const float* x, int ib, int s) { return *reinterpret_cast<const f32x4*>(x + 1024 * ib + 256 * s + 4 * lane); };
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
           for (int s = 0; s < 4; ++s) {
-            const int f = (hb * NB + ib) * 4 + s;
-            const f32x4 xo = *reinterpret_cast<const f32x4*>(xb + 1024 * ib + 256 * s + 4 * lane);
-            const f32x4 xdo = *reinterpret_cast<const f32x4*>(xdb + 1024 * ib + 256 * s + 4 * lane);
-            const f32x4 w = ld_frag<P>(W[m], f, lane);
-            c = P::mma(w, xo, c);
-            cd = P::mma(w, xdo, cd);
-            cd = P::mma(ld_frag<P>(Wd[m], f, lane), xo, cd);
+            const f32x4 w = frag(m, hb, ib, s, false);
+            c = P::mma(w, xo(xb, ib, s), c);
+            cd = P::mma(w, xo(xdb, ib, s), cd);
           }
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) cd = P::mma(frag(m, hb, ib, s, true), xo(xb, ib, s), cd);
       };
       f32x16 q, qd;
       project(1, q, qd);
@@ -262,79 +268,139 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       store16(sm[wave][3] + lr * LS + 16 * h, qd);
       project(0, q, qd);
       lds_sync();
-      f32x16 o = f32x16{}, od = f32x16{};
-#pragma unroll
+      f32x16 oh = f32x16{}, ohd = f32x16{};
+      // One head at a time: its features of q and qd are the first VPH values, the registers are moved down by
+      // VPH after each head, and its VPH output values enter at the top of oh, ohd.
+#pragma unroll 1
       for (int j = 0; j < HPB; ++j) {
-        if (hb * HPB + j >= a.heads) break;  // padding features
-        f32x16 p[NKB], pd[NKB];
-        float mx = -INFINITY;
+        float oj[VPH], odj[VPH];
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-          const float *kp = sm[kw + kb][0] + lr * LS + 16 * h + VPH * j, *kdp = sm[kw + kb][1] + lr * LS + 16 * h + VPH * j;
-          p[kb] = pd[kb] = f32x16{};
+        for (int t = 0; t < VPH; ++t) oj[t] = odj[t] = 0.f;
+        if (hb * HPB + j < a.heads) {  // else padding features
+          const float* kv = sm[kw][0] + VPH * j;  // block kb's k, t(k), v, t(v) at (4 kb + 0..3) TILE
+          f32x16 p[NKB], pd[NKB];
+          float qf[DH], qdf[DH];  // the query row's features of this head
 #pragma unroll
           for (int t = 0; t < VPH; ++t) {
-            const float kv = kp[t];
-            p[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kv, q[VPH * j + t], p[kb], 0, 0, 0);
-            pd[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kv, qd[VPH * j + t], pd[kb], 0, 0, 0);
-            pd[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kdp[t], q[VPH * j + t], pd[kb], 0, 0, 0);
+            halves(q[t], qf[2 * t], qf[2 * t + 1]);
+            halves(qd[t], qdf[2 * t], qdf[2 * t + 1]);
           }
+          float mx = -INFINITY;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            p[kb][r] = (okbits[kb] >> r) & 1u ? p[kb][r] * a.scale : -INFINITY;
-            pd[kb][r] *= a.scale;
-            mx = fmaxf(mx, p[kb][r]);
+          for (int kb = 0; kb < NKB; ++kb) {
+            p[kb] = f32x16{};
+            const float* kp = kv + 4 * kb * TILE;
+#pragma unroll
+            for (int t = 0; t < VPH; ++t) p[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kp[lr * LS + 16 * h + t], q[t], p[kb], 0, 0, 0);
+            // tangents, key 2 r + h (at position tile_idx(r, h)) in turn; [k even, k odd, t(k) even, t(k) odd] one key ahead
+            f32x4 w[2][VPH];
+            auto fetch = [&](int r) {
+              const float* k = kp + tile_idx(r, h) * LS;
+#pragma unroll
+              for (int t0 = 0; t0 < VPH; t0 += 4)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[r & 1][t0 + i] = *reinterpret_cast<const f32x4*>(k + (i >> 1) * TILE + (i & 1) * 16 + t0);
+            };
+            fetch(0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              if (r < 15) fetch(r + 1);
+              float s = 0.f;
+#pragma unroll
+              for (int f = 0; f < DH; ++f) {
+                const int t0 = f / 8 * 4, t = f / 2 % 4;
+                s = s + __builtin_fmaf(qdf[f], w[r & 1][t0 + (f & 1)][t], qf[f] * w[r & 1][t0 + 2 + (f & 1)][t]);
+              }
+              const bool ok = (keys[kb] >> (2 * r + h)) & 1u;
+              p[kb][r] = ok ? p[kb][r] * a.scale : -INFINITY;
+              pd[kb][r] = s * a.scale;
+              mx = fmaxf(mx, p[kb][r]);
+              __builtin_amdgcn_sched_barrier(0);  // one key at a time: the registers
+            }
+          }
+          mx = xor32_max(mx);
+          const float mm = mx == -INFINITY ? 0.f : mx;  // a row without a key (padding) keeps P = 0
+          float l = 0.f;
+#pragma unroll
+          for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {  // keys 2 r (lower half of the wave), then 2 r + 1
+              p[kb][r] = expf(p[kb][r] - mm);
+              float e0, e1;
+              halves(p[kb][r], e0, e1);
+              l += e0;
+              l += e1;
+            }
+          const float inv = l > 0.f ? 1.0f / l : 0.f;
+          float dot = 0.f;
+#pragma unroll
+          for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              p[kb][r] *= inv;
+              float e0, e1, d0, d1;
+              halves(p[kb][r], e0, e1);
+              halves(pd[kb][r], d0, d1);
+              dot = __builtin_fmaf(e0, d0, dot);
+              dot = __builtin_fmaf(e1, d1, dot);
+            }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int kb = 0; kb < NKB; ++kb) {
+            f32x4 w[2][VPH / 2];  // [v, t(v)] of the next key
+            auto fetch = [&](int k) {
+              const float* v = kv + (4 * kb + 2) * TILE + tile_idx(k >> 1, k & 1) * LS + 16 * h;
+#pragma unroll
+              for (int t0 = 0; t0 < VPH; t0 += 4)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) w[k & 1][t0 / 2 + i] = *reinterpret_cast<const f32x4*>(v + i * TILE + t0);
+            };
+            fetch(0);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              pd[kb][r] = p[kb][r] * (pd[kb][r] - dot);
+              float e[2], ed[2];
+              halves(p[kb][r], e[0], e[1]);
+              halves(pd[kb][r], ed[0], ed[1]);
+#pragma unroll
+              for (int i = 0; i < 2; ++i) {
+                const int k = 2 * r + i;
+                if (k < 31) fetch(k + 1);
+#pragma unroll
+                for (int t = 0; t < VPH; ++t) {
+                  const float v = w[i][t / 4 * 2][t % 4], vd = w[i][t / 4 * 2 + 1][t % 4];
+                  oj[t] = __builtin_fmaf(e[i], v, oj[t]);
+                  odj[t] = odj[t] + __builtin_fmaf(ed[i], v, e[i] * vd);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+              }
+            }
           }
         }
-        mx = xor32_max(mx);
-        const float mm = mx == -INFINITY ? 0.f : mx;  // a row without a key (padding) keeps P = 0
-        float l = 0.f;
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {  // keys 2 r (lower half of the wave), then 2 r + 1
-            p[kb][r] = expf(p[kb][r] - mm);
-            const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[kb][r]), __float_as_uint(p[kb][r]), false, false);
-            l += __uint_as_float(both[0]);
-            l += __uint_as_float(both[1]);
-          }
-        const float inv = l > 0.f ? 1.0f / l : 0.f;
-        float dot = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            p[kb][r] *= inv;
-            dot += p[kb][r] * pd[kb][r];
-          }
-        dot = xor32_sum(dot);
-        f32x16 to = f32x16{}, tod = f32x16{};
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) pd[kb][r] = p[kb][r] * (pd[kb][r] - dot);
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            const f32x4 v = column(sm[kw + kb][2], s);
-            to = P::mma(v, P::op(p[kb], s), to);
-            tod = P::mma(v, P::op(pd[kb], s), tod);
-            tod = P::mma(column(sm[kw + kb][3], s), P::op(p[kb], s), tod);
-          }
+        for (int r = 0; r < 16; ++r) {
+          q[r] = r + VPH < 16 ? q[(r + VPH) & 15] : 0.f;
+          qd[r] = r + VPH < 16 ? qd[(r + VPH) & 15] : 0.f;
+          oh[r] = r + VPH < 16 ? oh[(r + VPH) & 15] : oj[(r + VPH) & (VPH - 1)];
+          ohd[r] = r + VPH < 16 ? ohd[(r + VPH) & 15] : odj[(r + VPH) & (VPH - 1)];
         }
+      }
+      if (NB == 1 || hb == 0) { o[0] = oh; od[0] = ohd; }
+      else { o[NB - 1] = oh; od[NB - 1] = ohd; }
+      lds_sync();  // keys and values read before the next head block's (or block's) are written
+    }
+    f32x16 y[NB], yd[NB];
 #pragma unroll
-        for (int r = VPH * j; r < VPH * (j + 1); ++r) { o[r] = to[r]; od[r] = tod[r]; }
+    for (int ob = 0; ob < NB; ++ob) {
+      y[ob] = yd[ob] = f32x16{};
+#pragma unroll
+      for (int i = 0; i < 4 * NB; ++i) {
+        const f32x4 w = frag(3, ob, i / 4, i % 4, false);
+        y[ob] = P::mma(w, P::op(o[i / 4], i % 4), y[ob]);
+        yd[ob] = P::mma(w, P::op(od[i / 4], i % 4), yd[ob]);
       }
 #pragma unroll
-      for (int ob = 0; ob < NB; ++ob)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int f = (ob * NB + hb) * 4 + s;
-          const f32x4 w = ld_frag<P>(W[3], f, lane);
-          y[ob] = P::mma(w, P::op(o, s), y[ob]);
-          yd[ob] = P::mma(w, P::op(od, s), yd[ob]);
-          yd[ob] = P::mma(ld_frag<P>(Wd[3], f, lane), P::op(o, s), yd[ob]);
-        }
-      lds_sync();  // keys and values read before the next head block's (or block's) are written
+      for (int i = 0; i < 4 * NB; ++i) yd[ob] = P::mma(frag(3, ob, i / 4, i % 4, true), P::op(o[i / 4], i % 4), yd[ob]);
     }
     f32x16 z[NB], zd[NB];
 #pragma unroll
@@ -344,7 +410,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int r = 0; r < 16; ++r) { y[ob][r] += x[r]; yd[ob][r] += xd[r]; }
       z[ob] = zd[ob] = f32x16{};
     }
-    // ---- feed-forward: hidden units in chunks of 32
+    // ---- feed-forward: hidden units in chunks of 32; first W2 with u and t(u), then t(W2) with u
 #pragma unroll 1
     for (int c = 0; c < MB; ++c) {
       f32x16 u = f32x16{}, ud = f32x16{};
@@ -352,13 +418,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const int f = (c * NB + ib) * 4 + s;
-          const f32x4 w = ld_frag<P>(W[4], f, lane);
+          const f32x4 w = frag(4, c, ib, s, false);
           u = P::mma(w, P::op(y[ib], s), u);
           ud = P::mma(w, P::op(yd[ib], s), ud);
-          ud = P::mma(ld_frag<P>(Wd[4], f, lane), P::op(y[ib], s), ud);
         }
-      const f32x16 b = load16(b1 + 32 * c + 16 * h), bd = load16(b1d + 32 * c + 16 * h);
+#pragma unroll
+      for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) ud = P::mma(frag(4, c, ib, s, true), P::op(y[ib], s), ud);
+      const f32x16 b = bias(false, c, false), bd = bias(false, c, true);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         u[r] = fmaxf(u[r] + b[r], 0.f);
@@ -368,17 +436,30 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (int ob = 0; ob < NB; ++ob)
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const int f = (ob * MB + c) * 4 + s;
-          const f32x4 w = ld_frag<P>(W[5], f, lane);
+          const f32x4 w = frag(5, ob, c, s, false);
           z[ob] = P::mma(w, P::op(u, s), z[ob]);
           zd[ob] = P::mma(w, P::op(ud, s), zd[ob]);
-          zd[ob] = P::mma(ld_frag<P>(Wd[5], f, lane), P::op(u, s), zd[ob]);
         }
+    }
+#pragma unroll 1
+    for (int c = 0; c < MB; ++c) {
+      f32x16 u = f32x16{};
+#pragma unroll
+      for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) u = P::mma(frag(4, c, ib, s, false), P::op(y[ib], s), u);
+      const f32x16 b = bias(false, c, false);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) u[r] = fmaxf(u[r] + b[r], 0.f);
+#pragma unroll
+      for (int ob = 0; ob < NB; ++ob)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) zd[ob] = P::mma(frag(5, ob, c, s, true), P::op(u, s), zd[ob]);
     }
     if (live)
 #pragma unroll
       for (int ob = 0; ob < NB; ++ob) {
-        const f32x16 b = load16(b1 + M + 32 * ob + 16 * h), bd = load16(b1d + M + 32 * ob + 16 * h);
+        const f32x16 b = bias(true, ob, false), bd = bias(true, ob, true);
 #pragma unroll
         for (int r = 0; r < 16; ++r) { z[ob][r] = (z[ob][r] + b[r]) + y[ob][r]; zd[ob][r] = (zd[ob][r] + bd[r]) + yd[ob][r]; }
         store_tile(xb + 1024 * ob, lane, z[ob]);
@@ -387,53 +468,41 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   }
 }
 
-// Mean pooling and head, one wave per block (spanning: both blocks of a pass): z = (f0, f1), t(z) per
-// configuration-pass.  Row sums go through LDS and are added over a configuration's sites in order.
+// Mean pooling and head, one wave per configuration-pass: z = (f0, f1), t(z).  Lane l adds the elements
+// l, l + 64, .. of the pass's n x d activations in order, then the lanes are summed.
 __global__ void __launch_bounds__(256) k_jvp_head(int64_t E, int n, int cpb, int span, int d, int D, const float* __restrict__ X,
                                                   const float* __restrict__ Xd, const float* __restrict__ hw,
                                                   const double* __restrict__ hwd, float* __restrict__ z, float* __restrict__ zd) {
-  __shared__ float4 rows[4][64];
   const float* hb = hw + 2 * d;
   const double* hbd = hwd + 2 * d;
-  const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31, wave = threadIdx.x >> 6, NB = D / 32, RB = span ? 2 : 1;
-  const int64_t ntile = span ? 2 * E : 2 * ((E + cpb - 1) / cpb);
-  for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < ntile; t += (int64_t)gridDim.x * 4) {
-    for (int rb = 0; rb < RB; ++rb) {
-      float f0 = 0.f, f1 = 0.f, g0 = 0.f, g1 = 0.f;
-      for (int ib = 0; ib < NB; ++ib) {
-        const f32x16 xt = load_tile(X + ((t * RB + rb) * NB + ib) * 1024, lane), xdt = load_tile(Xd + ((t * RB + rb) * NB + ib) * 1024, lane);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int f = 32 * ib + 2 * r + h;
-          if (f >= d) continue;
-          const float x = xt[r], xd = xdt[r], w0 = hw[2 * f], w1 = hw[2 * f + 1];
-          f0 += x * w0;
-          f1 += x * w1;
-          g0 += xd * w0 + x * (float)hwd[2 * f];
-          g1 += xd * w1 + x * (float)hwd[2 * f + 1];
-        }
-      }
-      f0 = xor32_sum(f0); f1 = xor32_sum(f1); g0 = xor32_sum(g0); g1 = xor32_sum(g1);
-      if (h == 0) rows[wave][32 * rb + asc(lr)] = make_float4(f0, f1, g0, g1);
+  const int lane = threadIdx.x & 63, NB = D / 32;
+  const int f = lane % d, ib = f >> 5, r = (f & 31) >> 1, h = f & 1;  // feature f: value r of lane half h of tile ib
+  const int in_tile = 256 * (r >> 2) + 128 * h + (r & 3);
+  const float w0 = hw[2 * f], w1 = hw[2 * f + 1], wd0 = (float)hwd[2 * f], wd1 = (float)hwd[2 * f + 1];
+  for (int64_t ep = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); ep < 2 * E; ep += (int64_t)gridDim.x * 4) {
+    const int64_t e = ep >> 1, g = span ? 2 * ep : 2 * (e / cpb) + (ep & 1);
+    const int row0 = span ? 0 : (int)(e % cpb) * n;
+    float f0 = 0.f, f1 = 0.f, g0 = 0.f, g1 = 0.f;
+    for (int i = lane / d; i < n; i += 64 / d) {
+      const int row = row0 + i, m = (row & 24) + ((row >> 1) & 3) + 4 * (row & 1);  // asc(m) = row mod 32
+      const int64_t at = ((g + (row >> 5)) * NB + ib) * 1024 + in_tile + 4 * m;
+      const float x = X[at], xd = Xd[at];
+      f0 = __builtin_fmaf(x, w0, f0);
+      f1 = __builtin_fmaf(x, w1, f1);
+      g0 = g0 + __builtin_fmaf(xd, w0, x * wd0);
+      g1 = g1 + __builtin_fmaf(xd, w1, x * wd1);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-    const int64_t e = span ? t >> 1 : (t >> 1) * cpb + lane;
-    if (lane < cpb && e < E) {
-      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (int i = 0; i < n; ++i) {
-        const float4 v = rows[wave][lane * n + i];
-        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-      }
+    f0 = wave_sum(f0);
+    f1 = wave_sum(f1);
+    g0 = wave_sum(g0);
+    g1 = wave_sum(g1);
+    if (lane == 0) {
       const float inv = 1.0f / (float)n;
-      const int64_t ep = 2 * e + (t & 1);
-      z[2 * ep] = s.x * inv + hb[0];
-      z[2 * ep + 1] = s.y * inv + hb[1];
-      zd[2 * ep] = s.z * inv + (float)hbd[0];
-      zd[2 * ep + 1] = s.w * inv + (float)hbd[1];
+      z[2 * ep] = __builtin_fmaf(f0, inv, hb[0]);
+      z[2 * ep + 1] = __builtin_fmaf(f1, inv, hb[1]);
+      zd[2 * ep] = __builtin_fmaf(g0, inv, (float)hbd[0]);
+      zd[2 * ep + 1] = __builtin_fmaf(g1, inv, (float)hbd[1]);
     }
-    __builtin_amdgcn_wave_barrier();  // rows read before the next tile's are written
   }
 }
 
@@ -464,14 +533,19 @@ namespace tdo {
 
 namespace {
 
-template <int D, int DH>
-int32_t launch_jvp_layer(const JvpArgs& a, bool span, int num_cus, hipStream_t st) {
-  const int64_t nblk = span ? 4 * a.E : 2 * ((a.E + a.cpb - 1) / a.cpb);
+template <int D, int DH, bool SPAN>
+int32_t launch_jvp_span(const JvpArgs& a, bool masked, int num_cus, hipStream_t st) {
+  const int64_t nblk = SPAN ? 4 * a.E : 2 * ((a.E + a.cpb - 1) / a.cpb);
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((nblk + 7) / 8, num_cus));
-  if (span) hipLaunchKernelGGL((k_jvp_layer<D, DH, true>), dim3(grid), dim3(512), 0, st, a);
-  else hipLaunchKernelGGL((k_jvp_layer<D, DH, false>), dim3(grid), dim3(512), 0, st, a);
+  auto k = masked ? k_jvp_layer<D, DH, SPAN, true> : k_jvp_layer<D, DH, SPAN, false>;
+  hipLaunchKernelGGL(k, dim3(grid), dim3(512), 0, st, a);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
+}
+
+template <int D, int DH>
+int32_t launch_jvp_layer(const JvpArgs& a, bool span, bool masked, int num_cus, hipStream_t st) {
+  return span ? launch_jvp_span<D, DH, true>(a, masked, num_cus, st) : launch_jvp_span<D, DH, false>(a, masked, num_cus, st);
 }
 
 // floats of one packed layer (weights, b1, b2)
@@ -522,7 +596,7 @@ int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params
   TDO_HIP(hipGetLastError());
   for (int64_t e0 = 0; e0 < B; e0 += j.ec) {
     const int64_t E = std::min(j.ec, B - e0), nblk = blocks_for(np, E);
-    const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(nblk, 4), 8192);
+    const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(nblk, 4), 8192), grid2 = (unsigned)std::min<int64_t>(ceil_div(2 * E, 4), 8192);
     hipLaunchKernelGGL(k_jvp_embed, dim3(grid), dim3(256), 0, st, cfg + 2 * e0, E, np.n, np.cpb, (int)np.span, np.D, T, Td, X, Xd);
     TDO_HIP(hipGetLastError());
     for (int l = 0; l < pp.layers; ++l) {
@@ -536,14 +610,13 @@ int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params
       a.E = E;
       a.n = np.n;
       a.cpb = np.cpb;
-      a.masked = np.masked;
       a.heads = pp.heads;
       a.M = pp.M;
       a.scale = (float)(1.0 / std::sqrt((double)np.DH));
-      if (np.D == 32) TDO_TRY(np.DH == 8 ? (launch_jvp_layer<32, 8>(a, np.span, np.num_cus, st)) : (launch_jvp_layer<32, 16>(a, np.span, np.num_cus, st)));
-      else TDO_TRY(np.DH == 8 ? (launch_jvp_layer<64, 8>(a, np.span, np.num_cus, st)) : (launch_jvp_layer<64, 16>(a, np.span, np.num_cus, st)));
+      if (np.D == 32) TDO_TRY(np.DH == 8 ? (launch_jvp_layer<32, 8>(a, np.span, np.masked, np.num_cus, st)) : (launch_jvp_layer<32, 16>(a, np.span, np.masked, np.num_cus, st)));
+      else TDO_TRY(np.DH == 8 ? (launch_jvp_layer<64, 8>(a, np.span, np.masked, np.num_cus, st)) : (launch_jvp_layer<64, 16>(a, np.span, np.masked, np.num_cus, st)));
     }
-    hipLaunchKernelGGL(k_jvp_head, dim3(grid), dim3(256), 0, st, E, np.n, np.cpb, (int)np.span, pp.d, np.D, X, Xd,
+    hipLaunchKernelGGL(k_jvp_head, dim3(grid2), dim3(256), 0, st, E, np.n, np.cpb, (int)np.span, pp.d, np.D, X, Xd,
                        params + pp.off_head_w, tan + pp.off_head_w, z, zd);
     hipLaunchKernelGGL(k_jvp_combine, dim3((unsigned)std::min<int64_t>(ceil_div(E, 256), 4096)), dim3(256), 0, st, E,
                        z, zd, out + 2 * e0);

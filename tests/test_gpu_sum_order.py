@@ -1,0 +1,68 @@
+"""The order of the sums behind the SR updates.
+
+A conjugate-gradient solve that stops after a few iterations of an ill-conditioned system carries a
+changed rounding of its operator or of its own sums into the update, by orders of magnitude more than
+the rounding itself (J changed by 2e-16: up to 1e-5 of the update).  The order of these sums is
+therefore part of what the calls return.  The digests below are of the outputs in that order, on inputs
+made from seeds, bit for bit: of the forward-mode pass with the FP32 sums that k_jvp_layer states."""
+import hashlib
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_20723_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def cuda(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def digest(outputs):
+    return hashlib.sha256(b"".join(t.cpu().numpy().tobytes() for t in outputs)).hexdigest()[:16]
+
+
+def network(net, n, B, seed):
+    arch = synth.arch(*net)
+    rng = np.random.default_rng([seed, n])
+    cfg = rng.integers(0, 1 << 63, size=(B, 2), dtype=np.uint64) * np.uint64(2) + rng.integers(0, 2, size=(B, 2), dtype=np.uint64)
+    cfg = cfg & np.uint64((1 << n) - 1)
+    params = synth.params(arch, seed + n, "mid")
+    return arch, cuda(params), cuda(cfg), cuda(rng.standard_normal(params.size))
+
+
+def jvp(tdo, net, n, B):
+    arch, params, cfg, tangent = network(net, n, B, 4000)
+    return [tdo.Ctx(0).log_rho_jvp(arch, params, n, cfg, tangent)]
+
+
+JVP = [((16, 2, 1, 64), 3, 61), ((16, 1, 2, 32), 9, 7), ((16, 2, 3, 64), 33, 5), ((32, 4, 2, 128), 8, 37), ((32, 2, 1, 96), 20, 3),
+       ((32, 4, 4, 64), 64, 9), ((64, 4, 2, 256), 16, 33), ((64, 4, 1, 512), 37, 5), ((64, 8, 3, 128), 5, 40), ((64, 8, 4, 256), 32, 17),
+       ((64, 8, 2, 256), 50, 6)]
+
+
+def cases():
+    return {"jvp %s n=%d" % ("-".join(map(str, a[0])), a[1]): (jvp, a) for a in JVP}
+
+
+WANT = {
+    "jvp 16-2-1-64 n=3": "3f0e5cdeaf286006",
+    "jvp 16-1-2-32 n=9": "3f629f8cc3db478f",
+    "jvp 16-2-3-64 n=33": "e1727b1260e2c274",
+    "jvp 32-4-2-128 n=8": "aef33a108e2aa2cf",
+    "jvp 32-2-1-96 n=20": "95d265a1eda4ba85",
+    "jvp 32-4-4-64 n=64": "3ff97b4020a18ebe",
+    "jvp 64-4-2-256 n=16": "e2b94a1d4248f0bd",
+    "jvp 64-4-1-512 n=37": "bb49e60b29d20d09",
+    "jvp 64-8-3-128 n=5": "10a47c40f317cb7c",
+    "jvp 64-8-4-256 n=32": "f2d992d54d11c186",
+    "jvp 64-8-2-256 n=50": "f3ca638918254641",
+}
+
+
+@pytest.mark.parametrize("name", list(cases()))
+def test_bits(gpu, name):
+    f, args = cases()[name]
+    assert digest(f(gpu, *args)) == WANT[name]

@@ -10,8 +10,11 @@
 // The Jacobian comes from tdo_log_rho_jacobian; this call centres and scales
 // it in place.  Dot products are two-stage FP64 sums in a fixed order (slices, then the slices, by every
 // workgroup that needs the product) and CG's scalars stay on the device, so the iteration count is fixed by
-// the caller and the result does not depend on scheduling.  An iteration is five launches (ten with the
-// sums of the slices and the scalars in launches of their own: 38 us of 195, now 15 of 162).
+// the caller and the result does not depend on scheduling.  The order of these sums is part of the result: a
+// solve stopped on an ill-conditioned system amplifies a change of rounding (256 slices or 128, rows first to
+// last or last to first: up to 1e-5 of the update), so the split into slices, segments and accumulators
+// is not a tuning choice.  An iteration is five launches (ten with the sums of the slices and the scalars in
+// launches of their own: 38 us of 195, now 15 of 162).
 #include <algorithm>
 #include <cmath>
 
@@ -70,30 +73,31 @@ __global__ void __launch_bounds__(kT) k_sr_center(double* __restrict__ J, int64_
 // Partial row dots: workgroup (r, s) forms J[r] . p over segment s of kSeg equal
 // segments, into up[r][s] (summed in segment order by the column pass).
 // Bound: memory, one read of J (441 MB at R = 512, P = 107650: 92 -> 82 us).  Four rows per workgroup,
-// which read p once for all, leave too few loads in flight (113 us).
+// which read p once for all, leave too few loads in flight (113 us).  The rows are taken last to first: the
+// column pass has just left the last ones in the last-level cache (256 MB), and this pass leaves the first ones
+// for the next column pass (with both first to last, 94 and 73 us; so, 81 and 70 us).
 constexpr int kSeg = 8;
 __global__ void __launch_bounds__(kT) k_sr_rows(const double* __restrict__ J, int64_t R, int64_t P,
                                                 const double* __restrict__ p, double* __restrict__ up) {
   __shared__ double red[kT];
   const int64_t seg = (P + kSeg - 1) / kSeg;
   for (int64_t rs = blockIdx.x; rs < R * kSeg; rs += gridDim.x) {
-    const int64_t r = rs / kSeg, s = rs % kSeg;
+    const int64_t r = R - 1 - rs / kSeg, s = rs % kSeg;
     const double* row = J + r * P;
     const int64_t k1 = std::min<int64_t>(P, (s + 1) * seg);
     double a = 0.0;
 #pragma unroll 8
     for (int64_t k = s * seg + threadIdx.x; k < k1; k += kT) a += row[k] * p[k];
     a = block_reduce(a, red);
-    if (threadIdx.x == 0) up[rs] = a;
+    if (threadIdx.x == 0) up[r * kSeg + s] = a;
   }
 }
 
 // Ap[k] = sum_r J[r][k] u[r] + lambda p[k], one thread per column, with u[r] = sum over s of up[r][s] in
 // segment order, formed in LDS for kURows rows at a time; four accumulators over r mod 4 (summed in that
-// order).  Bound: memory, one read of J.  The rows are taken last to first: the row pass has just left the
-// last ones in the last-level cache (256 MB), and this pass leaves the first ones for the next row pass.
-// R = 512, P = 107650: 84 us first to last with four loads in flight, 73 with eight, 68 last to first (and
-// the row pass 94 -> 82).
+// order; the last R mod 4 rows all in the first), rows first to last.  Bound: memory, one read of J.  R = 512,
+// P = 107650: 84 us with four loads in flight, 73 with eight, 70 with the rows in the order that the row pass
+// leaves in the cache.
 constexpr int kURows = 512;
 __global__ void __launch_bounds__(kT) k_sr_cols(const double* __restrict__ J, int64_t R, int64_t P, const double* __restrict__ up,
                                                 const double* __restrict__ p, double lambda, double* __restrict__ Ap) {
@@ -103,7 +107,7 @@ __global__ void __launch_bounds__(kT) k_sr_cols(const double* __restrict__ J, in
     const bool live = k < P;
     const double* col = J + (live ? k : 0);
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int64_t r0 = (R - 1) / kURows * kURows; r0 >= 0; r0 -= kURows) {
+    for (int64_t r0 = 0; r0 < R; r0 += kURows) {
       const int rows = (int)std::min<int64_t>(kURows, R - r0);
       __syncthreads();  // the previous rows' sums read
       for (int i = threadIdx.x; i < rows; i += kT) {
@@ -114,31 +118,33 @@ __global__ void __launch_bounds__(kT) k_sr_cols(const double* __restrict__ J, in
       }
       __syncthreads();
       if (!live) continue;
-      int i = rows - 1;
-      for (; (i & 3) != 3 && i >= 0; --i) a[i & 3] += col[(r0 + i) * P] * u[i];
+      int i = 0;
 #pragma unroll 2
-      for (; i >= 3; i -= 4) {
-        a[3] += col[(r0 + i) * P] * u[i];
-        a[2] += col[(r0 + i - 1) * P] * u[i - 1];
-        a[1] += col[(r0 + i - 2) * P] * u[i - 2];
-        a[0] += col[(r0 + i - 3) * P] * u[i - 3];
+      for (; i + 4 <= rows; i += 4) {
+        a[0] += col[(r0 + i) * P] * u[i];
+        a[1] += col[(r0 + i + 1) * P] * u[i + 1];
+        a[2] += col[(r0 + i + 2) * P] * u[i + 2];
+        a[3] += col[(r0 + i + 3) * P] * u[i + 3];
       }
+      for (; i < rows; ++i) a[0] += col[(r0 + i) * P] * u[i];
     }
     if (live) Ap[k] = ((a[0] + a[1]) + (a[2] + a[3])) + lambda * p[k];
   }
 }
 
 // a . b in a fixed order: kDotParts workgroups sum contiguous slices into part[]; every workgroup of
-// the kernel that uses the product sums the parts for itself (dot_parts).
-constexpr int kDotParts = 128;
-static_assert(kDotParts <= kT, "at most one part per thread");
+// the kernel that uses the product sums the parts for itself (dot_parts, a part per thread).
+constexpr int kDotParts = 256;
+static_assert(kDotParts == kT, "one part per thread");
 __device__ __forceinline__ double dot_parts(const double* __restrict__ part, double* red) {
-  return block_reduce(threadIdx.x < kDotParts ? part[threadIdx.x] : 0.0, red);
+  return block_reduce(part[threadIdx.x], red);
 }
+// Elements of a slice.
+__device__ __forceinline__ int64_t dot_slice(int64_t P) { return (P + kDotParts - 1) / kDotParts; }
 __global__ void __launch_bounds__(kT) k_sr_dot(const double* __restrict__ a, const double* __restrict__ b,
                                                int64_t P, double* __restrict__ part) {
   __shared__ double red[kT];
-  const int64_t slice = (P + kDotParts - 1) / kDotParts;
+  const int64_t slice = dot_slice(P);
   const int64_t k0 = blockIdx.x * slice, k1 = std::min<int64_t>(P, k0 + slice);
   double s = 0.0;
   for (int64_t k = k0 + threadIdx.x; k < k1; k += kT) s += a[k] * b[k];
@@ -163,14 +169,15 @@ __global__ void __launch_bounds__(kT) k_sr_sum(const double* __restrict__ part, 
   if (threadIdx.x == 0) out[0] = out[1] = s;
 }
 
-// alpha = rs / (p . Ap) (0 when p . Ap = 0); x += alpha p; r -= alpha Ap; the parts of the new r . r.
+// alpha = rs / (p . Ap) (0 when p . Ap = 0); x += alpha p; r -= alpha Ap; the parts of the new r . r.  Part i takes
+// the place of the first element of slice i of Ap, which nothing reads any more.
 __global__ void __launch_bounds__(kT) k_sr_step(int64_t P, const double* __restrict__ rs, const double* __restrict__ pap_part,
-                                                const double* __restrict__ p, const double* __restrict__ Ap,
-                                                double* __restrict__ x, double* __restrict__ r, double* __restrict__ rn_part) {
+                                                const double* __restrict__ p, double* Ap, double* __restrict__ x,
+                                                double* __restrict__ r) {
   __shared__ double red[kT];
   const double pAp = dot_parts(pap_part, red);
   const double alpha = pAp != 0.0 ? rs[0] / pAp : 0.0;
-  const int64_t slice = (P + kDotParts - 1) / kDotParts;
+  const int64_t slice = dot_slice(P);
   const int64_t k0 = blockIdx.x * slice, k1 = std::min<int64_t>(P, k0 + slice);
   double s = 0.0;
   for (int64_t k = k0 + threadIdx.x; k < k1; k += kT) {
@@ -179,15 +186,16 @@ __global__ void __launch_bounds__(kT) k_sr_step(int64_t P, const double* __restr
     r[k] = t;
     s += t * t;
   }
-  s = block_reduce(s, red);
-  if (threadIdx.x == 0) rn_part[blockIdx.x] = s;
+  s = block_reduce(s, red);  // every thread has read its elements of Ap
+  if (threadIdx.x == 0 && k0 < P) Ap[k0] = s;
 }
 
 // beta = rs_new / rs (0 when rs = 0); p = r + beta p; rs_new to its own slot for the next iteration.
-__global__ void __launch_bounds__(kT) k_sr_dir(int64_t P, const double* __restrict__ rs, const double* __restrict__ rn_part,
+__global__ void __launch_bounds__(kT) k_sr_dir(int64_t P, const double* __restrict__ rs, const double* __restrict__ Ap,
                                                const double* __restrict__ r, double* __restrict__ p, double* __restrict__ rs_new) {
   __shared__ double red[kT];
-  const double rn = dot_parts(rn_part, red);
+  const int64_t at = threadIdx.x * dot_slice(P);
+  const double rn = block_reduce(at < P ? Ap[at] : 0.0, red);
   const double beta = rs[0] != 0.0 ? rn / rs[0] : 0.0;
   for (int64_t k = (int64_t)blockIdx.x * kT + threadIdx.x; k < P; k += (int64_t)gridDim.x * kT) p[k] = r[k] + beta * p[k];
   if (blockIdx.x == 0 && threadIdx.x == 0) rs_new[0] = rn;
@@ -203,12 +211,11 @@ __global__ void k_sr_info(const double* __restrict__ rs, const double* __restric
 }
 
 // Conjugate gradients on (S + lambda) x = g; apply(p, Ap) queues Ap = (S + lambda) p.  part: the parts of
-// p . Ap, then those of r . r; sc: [0] g . g, [1], [2] r . r, in turn the current and the next one.
+// p . Ap; sc: [0] g . g, [1], [2] r . r, in turn the current and the next one.
 template <class Apply>
 static int32_t cg(int64_t P, const double* grad, int32_t iters, double* x, double* r, double* p, double* Ap, double* part,
                   double* sc, double* info, hipStream_t stream, Apply&& apply) {
   const unsigned gp = (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(P, 256), 4096));
-  double* rn_part = part + kDotParts;
   hipLaunchKernelGGL(k_sr_init, dim3(gp), dim3(256), 0, stream, grad, P, x, r, p);
   hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, grad, grad, P, part);
   hipLaunchKernelGGL(k_sr_sum, dim3(1), dim3(kT), 0, stream, part, sc);
@@ -217,8 +224,8 @@ static int32_t cg(int64_t P, const double* grad, int32_t iters, double* x, doubl
     TDO_TRY(apply(p, Ap));
     double *rs = sc + 1 + (it & 1), *rs_new = sc + 1 + (~it & 1);
     hipLaunchKernelGGL(k_sr_dot, dim3(kDotParts), dim3(kT), 0, stream, p, Ap, P, part);
-    hipLaunchKernelGGL(k_sr_step, dim3(kDotParts), dim3(kT), 0, stream, P, rs, part, p, Ap, x, r, rn_part);
-    hipLaunchKernelGGL(k_sr_dir, dim3(gp), dim3(kT), 0, stream, P, rs, rn_part, r, p, rs_new);
+    hipLaunchKernelGGL(k_sr_step, dim3(kDotParts), dim3(kT), 0, stream, P, rs, part, p, Ap, x, r);
+    hipLaunchKernelGGL(k_sr_dir, dim3(gp), dim3(kT), 0, stream, P, rs, Ap, r, p, rs_new);
     TDO_HIP(hipGetLastError());
   }
   if (info) {
@@ -287,7 +294,7 @@ extern "C" int32_t tdo_sr_solve(tdo_ctx_t* ctx, double* jac, int64_t B, int64_t 
   TDO_TRY(order.begin(&c, stream));
   Arena ar;
   const size_t or_ = ar.take<double>((size_t)P), op = ar.take<double>((size_t)P), oap = ar.take<double>((size_t)P);
-  const size_t oup = ar.take<double>(2 * (size_t)B * kSeg), osc = ar.take<double>(8), opart = ar.take<double>(2 * kDotParts);
+  const size_t oup = ar.take<double>(2 * (size_t)B * kSeg), osc = ar.take<double>(8), opart = ar.take<double>(kDotParts);
   TDO_TRY(ensure_workspace(&c, ar.used));
   double* r = at<double>(c.ws, or_);
   double* p = at<double>(c.ws, op);
@@ -335,7 +342,7 @@ extern "C" int32_t tdo_sr_solve_matfree(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   // most a third of the rest of the budget), then the reverse-mode plan in what remains
   Arena ar;
   const size_t or_ = ar.take<double>((size_t)P), op = ar.take<double>((size_t)P), oap = ar.take<double>((size_t)P);
-  const size_t osc = ar.take<double>(16), opart = ar.take<double>(2 * kDotParts);
+  const size_t osc = ar.take<double>(16), opart = ar.take<double>(kDotParts);
   const size_t ot = ar.take<float>(2 * (size_t)B), oseed = ar.take<float>(2 * (size_t)B);
   TDO_CHECK(c.budget > ar.used + 4096, TDO_ENOMEM, "workspace budget %zu too small", c.budget);
   JvpWs j;

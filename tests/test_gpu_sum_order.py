@@ -4,7 +4,8 @@ A conjugate-gradient solve that stops after a few iterations of an ill-condition
 changed rounding of its operator or of its own sums into the update, by orders of magnitude more than
 the rounding itself (J changed by 2e-16: up to 1e-5 of the update).  The order of these sums is
 therefore part of what the calls return.  The digests below are of the outputs in that order, on inputs
-made from seeds, bit for bit: of the forward-mode pass with the FP32 sums that k_jvp_layer states."""
+made from seeds, bit for bit: of the forward-mode pass with the FP32 sums that k_jvp_layer states, and of
+the FP64 sums of the solve."""
 import hashlib
 
 import numpy as np
@@ -38,13 +39,29 @@ def jvp(tdo, net, n, B):
     return [tdo.Ctx(0).log_rho_jvp(arch, params, n, cfg, tangent)]
 
 
+def solve(tdo, B, P, iters, weighted):
+    """A stopped solve with a small shift: the rows of J lie near a few directions."""
+    rng = np.random.default_rng([4200, B, P])
+    J = rng.standard_normal((B, 2, P)) * 0.01 + rng.standard_normal((B, 2, 1)) * rng.standard_normal(P)
+    grad, w = cuda(rng.standard_normal(P)), cuda(rng.uniform(0.5, 2.0, B)) if weighted else None
+    jac = cuda(J)
+    return [*tdo.Ctx(0).sr_solve(jac, grad, 1e-3, iters, w), jac]
+
+
 JVP = [((16, 2, 1, 64), 3, 61), ((16, 1, 2, 32), 9, 7), ((16, 2, 3, 64), 33, 5), ((32, 4, 2, 128), 8, 37), ((32, 2, 1, 96), 20, 3),
        ((32, 4, 4, 64), 64, 9), ((64, 4, 2, 256), 16, 33), ((64, 4, 1, 512), 37, 5), ((64, 8, 3, 128), 5, 40), ((64, 8, 4, 256), 32, 17),
        ((64, 8, 2, 256), 50, 6)]
 
 
+# rows 2 mod 4 and 0 mod 4, below and above one load of the column pass, P below and above the slices
+SOLVE = [(1, 1, 3, False), (2, 300, 9, True), (7, 1001, 23, False), (24, 5003, 15, True), (256, 700, 12, False), (257, 2050, 30, False),
+         (600, 257, 6, True), (40, 70001, 20, False)]
+
+
 def cases():
-    return {"jvp %s n=%d" % ("-".join(map(str, a[0])), a[1]): (jvp, a) for a in JVP}
+    c = {"jvp %s n=%d" % ("-".join(map(str, a[0])), a[1]): (jvp, a) for a in JVP}
+    c.update({"solve B=%d P=%d" % a[:2]: (solve, a) for a in SOLVE})
+    return c
 
 
 WANT = {
@@ -59,6 +76,14 @@ WANT = {
     "jvp 64-8-3-128 n=5": "10a47c40f317cb7c",
     "jvp 64-8-4-256 n=32": "f2d992d54d11c186",
     "jvp 64-8-2-256 n=50": "f3ca638918254641",
+    "solve B=1 P=1": "157dee46fa47f596",
+    "solve B=2 P=300": "d1b20d28d1b944ee",
+    "solve B=7 P=1001": "1374bd8bf4960244",
+    "solve B=24 P=5003": "a23a8c2b31944b66",
+    "solve B=256 P=700": "f128f9990e35fc65",
+    "solve B=257 P=2050": "387b6cbb3af267ad",
+    "solve B=600 P=257": "2c6476c9aee2cba4",
+    "solve B=40 P=70001": "36eb263fb000fd35",
 }
 
 

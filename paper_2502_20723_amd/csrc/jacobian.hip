@@ -118,60 +118,76 @@ __global__ void __launch_bounds__(64) k_jac_tables(const float* __restrict__ par
   }
 }
 
-// Convolution part of E rows from the per-wave table gradients, in FP64.  With G[code][o] =
-// dT[code][o] phi'(pre), a tap's weight gradient needs G only summed over the site the tap does not
-// see: GA[q][o] (over t2) for tap 0 and GB[q][o] (over t0) for tap 1, q = 16 codes, so every product
-// is 16 (not 64) deep.  One workgroup per configuration; the sums are in a fixed order.
-__global__ void __launch_bounds__(256) k_jac_embed(const float* __restrict__ params, const double* __restrict__ tab,
+// Convolution part of E rows from the per-wave table gradients, in FP64: per window code the contribution
+// that k_embed_params forms, operation for operation, and their sum in code order, so that a row has the
+// bits of tdo_log_rho_vjp of its configuration alone.  (Summing over the site that a tap does not see first takes
+// a quarter of the products, but rounds otherwise, by 1e-17 of the row, and a stopped SR solve on these
+// rows amplifies that to 1e-8 and more of its update.)  One workgroup per configuration.  With G[code][o] =
+// dT[code][o] phi'(pre) in LDS, a thread takes 8 weights (or the input gradients of 8 codes) at a time.
+// Bound: FP64 on the vector ALU, 1.6 M operations a row at width 64 (51 us for 256 rows).
+__global__ void __launch_bounds__(512) k_jac_embed(const float* __restrict__ params, const double* __restrict__ tab,
                                                    const float* __restrict__ part, int bpc, int d, int D,
                                                    double* __restrict__ jac, int64_t stride) {
-  __shared__ double G[2][16][64 + 1], S[2][16][64];
+#pragma clang fp contract(off)
+  __shared__ double G[64][64 + 1], A[64][64], B[64][64], eq[16][64];
   const int t = threadIdx.x;
   const int64_t e = blockIdx.x;
   const float* pe = part + e * bpc * 64 * D;
   const float* w2 = params + 5 * d;
-  const double *eq = tab, *deq = tab + 16 * d, *dp = tab + 32 * d;
+  const double *deq = tab + 16 * d, *dp = tab + 32 * d;
   double* row = jac + e * stride;  // [w1 4d][b1 d][w2 2 d^2][b2 d]
-  for (int i = t; i < 2 * 16 * d; i += 256) {
-    const int tap = i / (16 * d), q = (i / d) % 16, o = i % d;
-    double g = 0.0;
-    for (int k = 0; k < 4; ++k) {
-      const int code = tap ? k + 4 * q : q + 16 * k;
-      double v = 0.0;
-      for (int w = 0; w < bpc; ++w) v += (double)pe[(w * 64 + code) * D + o];
-      g += v * dp[code * d + o];
-    }
-    G[tap][q][o] = g;
+  for (int i = t; i < 64 * d; i += 512) {
+    const int code = i / d, o = i % d;
+    double v = 0.0;
+    for (int w = 0; w < bpc; ++w) v += (double)pe[(w * 64 + code) * D + o];
+    G[code][o] = v * dp[i];
   }
+  for (int i = t; i < 16 * d; i += 512) eq[i / d][i % d] = tab[i];
   __syncthreads();
-  for (int i = t; i < d; i += 256) {
-    double v = 0.0;
-    for (int q = 0; q < 16; ++q) v += G[0][q][i];
-    row[5 * d + 2 * d * d + i] = v;
-  }
-  for (int i = t; i < 2 * d * d; i += 256) {
-    const int tap = i / (d * d), c = (i / d) % d, o = i % d;
-    double v = 0.0;
+  // code = t0 + 4 t1 + 16 t2: tap 0 sees the sites of code mod 16, tap 1 those of code / 4
+  for (int i = t; i < 2 * (d / 8) * d; i += 512) {
+    const int o = i % d, c0 = i / d % (d / 8) * 8, tap = i / (d * (d / 8));
+    double v[8] = {};
+    for (int code = 0; code < 64; ++code) {
+      const double g = G[code][o];
+      const double* q = eq[tap ? code >> 2 : code & 15] + c0;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) v += eq[q * d + c] * G[tap][q][o];
-    row[5 * d + i] = v;
+      for (int k = 0; k < 8; ++k) v[k] += q[k] * g;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) row[5 * d + (tap * d + c0 + k) * d + o] = v[k];
   }
-  // gradient of the first convolution's pre-activations: S[tap][q][c] = e'(q)[c] sum_o w2[tap][c][o] G
-  for (int i = t; i < 2 * 16 * d; i += 256) {
-    const int c = i % d, q = (i / d) % 16, tap = i / (16 * d);
-    const float* wr = w2 + (tap * d + c) * d;
+  if (t < d) {
     double v = 0.0;
-    for (int o = 0; o < d; ++o) v += (double)wr[o] * G[tap][q][o];
-    S[tap][q][c] = v * deq[q * d + c];
+    for (int code = 0; code < 64; ++code) v += G[code][t];
+    row[5 * d + 2 * d * d + t] = v;
+  }
+  // gradients with respect to the first convolution's outputs at the two sites: A, B[code][c] = sum_o w2[tap][c][o] G
+  for (int i = t; i < 2 * 8 * d; i += 512) {
+    const int c = i % d, k0 = i / d % 8 * 8, tap = i / (8 * d);
+    const float* wr = w2 + (tap * d + c) * d;
+    double v[8] = {};
+    for (int o = 0; o < d; ++o) {
+      const double w = (double)wr[o];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = __builtin_fma(w, G[k0 + k][o], v[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) (tap ? B : A)[k0 + k][c] = v[k];
   }
   __syncthreads();
-  for (int i = t; i < 5 * d; i += 256) {
+  for (int i = t; i < 5 * d; i += 512) {
     const int k = i / d, c = i % d;  // k < 4: w1[site k / 2][channel k % 2]; 4: bias
     double v = 0.0;
-    for (int q = 0; q < 16; ++q) {
-      const int site = k / 2 ? q >> 2 : q & 3;
-      const double sp = k == 4 ? 1.0 : 1.0 - 2.0 * (double)((site >> (k & 1)) & 1);
-      v += sp * (S[0][q][c] + S[1][q][c]);
+    for (int code = 0; code < 64; ++code) {
+      const double da = deq[(code & 15) * d + c], gb = B[code][c] * deq[(code >> 2) * d + c];
+      if (k == 4) {
+        v += __builtin_fma(A[code][c], da, gb);
+      } else {
+        const int ta = (code >> (k / 2 * 2)) & 3, tb = (code >> (k / 2 * 2 + 2)) & 3;
+        const double ga = A[code][c] * da;
+        v += (((ta >> (k & 1)) & 1) ? -ga : ga) + (((tb >> (k & 1)) & 1) ? -gb : gb);
+      }
     }
     row[i] = v;
   }
@@ -208,7 +224,7 @@ int32_t launch_jac_tables(const float* params, int d, double* tab, hipStream_t s
 
 int32_t launch_jac_embed(const float* params, const double* tab, const float* part, int bpc, int d, int D, int64_t E,
                          double* jac, int64_t stride, hipStream_t st) {
-  hipLaunchKernelGGL(k_jac_embed, dim3((unsigned)E), dim3(256), 0, st, params, tab, part, bpc, d, D, jac, stride);
+  hipLaunchKernelGGL(k_jac_embed, dim3((unsigned)E), dim3(512), 0, st, params, tab, part, bpc, d, D, jac, stride);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }

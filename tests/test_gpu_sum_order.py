@@ -91,3 +91,20 @@ WANT = {
 def test_bits(gpu, name):
     f, args = cases()[name]
     assert digest(f(gpu, *args)) == WANT[name]
+
+
+@pytest.mark.parametrize("net,n,B,prec", [
+    ((16, 2, 1, 64), 3, 13, "fp32"), ((16, 2, 3, 32), 17, 3, "bf16"), ((32, 4, 2, 128), 8, 5, "fp32"), ((32, 4, 1, 512), 32, 3, "bf16"),
+    ((64, 4, 2, 256), 16, 4, "fp32"), ((64, 8, 1, 96), 31, 2, "fp32"), ((64, 8, 2, 256), 32, 3, "bf16"), ((64, 4, 1, 256), 47, 2, "bf16"),
+])
+def test_jacobian_rows_are_single_vjps(gpu, net, n, B, prec):
+    """Bit for bit.  (A pass over two blocks in the kernels of widths 16 and 32 and of FP32 is left out: a workgroup
+    takes all four blocks of a row there and two of a single reverse-mode pass.)"""
+    arch, params, cfg, _ = network(net, n, B, 4300)
+    jac = gpu.Ctx(0).jacobian(arch, params, n, cfg, prec)
+    ctx = gpu.Ctx(0)
+    for b in range(B):
+        for part in (0, 1):
+            seed = torch.zeros((1, 2), device="cuda")
+            seed[0, part] = 1.0
+            assert torch.equal(jac[b, part], ctx.log_rho_vjp(arch, params, n, cfg[b:b + 1], seed, prec)), (b, part)

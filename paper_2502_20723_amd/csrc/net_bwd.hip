@@ -417,9 +417,13 @@ __global__ void __launch_bounds__(512) k_bwd_mlp(BwdArgs a) {
 //  2. a job's waves project q, k and v, dO (feature x row tiles) into the job's four LDS slots,
 //     from which rows are score operands and columns operands of the products over rows;
 //  3. each wave takes half of the job's heads: P, dS, and the head's features of O, dQ, dK, dV
-//     (each in a fresh accumulator of which only those are kept);
-//  4. O, dQ, dK, dV replace dO, q, k, v in the slots (a spanning pass first adds the two query
-//     blocks' shares of dK and dV);
+//     (each in a fresh accumulator of which only those are kept).  In a spanning pass with 8-wide heads a
+//     wave takes one head of both query blocks, and its dK and dV go on from the first block to the
+//     second in one accumulator (BF16 rounds dx in the next kernel, and a sum of the two blocks' shares
+//     rounds otherwise: 3e-6 of a log-derivative at n = 64; reverse mode of 2048 configurations at n = 64,
+//     width 32: BF16 0.80 -> 0.79 ms, FP32 1.76 -> 1.80);
+//  4. O, dQ, dK, dV replace dO, q, k, v in the slots (with 16-wide heads, FP32 only, a spanning pass first
+//     adds the two query blocks' shares of dK and dV);
 //  5. every wave adds the tile's rows to the weight-gradient tiles it keeps in registers for the
 //     whole launch (a fresh accumulator per block, then added), and waves 0..3 form dx.
 // Bound: the FP32 matrix cores, of which 8-wide heads use a quarter in the products of step 3.  The
@@ -432,6 +436,8 @@ template <class P, int D, int DH, bool SPAN>
 __global__ void __launch_bounds__(512) k_bwd_attn(BwdArgs a) {
   constexpr int NB = D / 32, ST = P::STEPS, HPB = 32 / DH, VPH = DH / 2, HPS = HPB / 2;
   constexpr int NBK = 4 / NB, XS = D + 4, R = 32 * NBK, NKB = SPAN ? 2 : 1, SLOT = 32 * TS;
+  constexpr bool WHOLE = SPAN && DH == 8;     // step 3: a wave takes one head of both query blocks of a pass
+  constexpr int UN = WHOLE ? 2 : HPS;         // (query block, head) pairs of a wave in step 3
   constexpr bool BF = P::KPL == 8;
   using elem_t = typename P::elem_t;
   using save_t = typename P::save_t;
@@ -447,7 +453,11 @@ __global__ void __launch_bounds__(512) k_bwd_attn(BwdArgs a) {
   const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int job = wave >> 1, sub = wave & 1, jblk = job / NB, hb = job % NB;
-  const int kbase = SPAN ? jblk & ~1 : jblk, own = jblk - kbase;
+  const int own = SPAN ? jblk & 1 : 0;
+  // step 3: its head block, first key block and pairs
+  const int hb3 = WHOLE ? (NB == 2 ? wave >> 2 : 0) : hb, kbase = WHOLE ? (NB == 2 ? 0 : 2 * (wave >> 2)) : jblk - own;
+  auto unit_head = [&](int u) { return WHOLE ? wave & 3 : sub * HPS + u; };
+  auto unit_job = [&](int u) { return WHOLE ? (kbase + u) * NB + hb3 : job; };
   float* sc = scr + wave * SLOT;
   const int64_t E = a.n_entries_dev ? *a.n_entries_dev : a.n_entries;
   const int n = a.n, cpb = a.cpb;
@@ -584,22 +594,27 @@ __global__ void __launch_bounds__(512) k_bwd_attn(BwdArgs a) {
     }
     barrier_lds();
     // ---- 3. heads of this wave
-    float ho[HPS][VPH], hq[HPS][VPH], hk[HPS][NKB][VPH], hv[HPS][NKB][VPH];
+    constexpr int KU = WHOLE ? 1 : UN;  // dK, dV per pair, or of both together
+    float ho[UN][VPH], hq[UN][VPH], hk[KU][NKB][VPH], hv[KU][NKB][VPH];
+    f32x16 tk[WHOLE ? NKB : 1], tv[WHOLE ? NKB : 1];  // of both pairs
 #pragma unroll
-    for (int jj = 0; jj < HPS; ++jj) {
-      const int j = sub * HPS + jj;
+    for (int u = 0; u < UN; ++u) {
+      const int j = unit_head(u), jb = unit_job(u);
       // the head's values of a result tile whose features are the head block's
       auto keep = [&](const f32x16& t, float* v) {
 #pragma unroll
-        for (int r = 0; r < VPH; ++r) v[r] = sub ? t[VPH * (HPS + jj) + r] : t[VPH * jj + r];
+        for (int r = 0; r < VPH; ++r) {
+          if constexpr (WHOLE) v[r] = j < 2 ? (j ? t[VPH + r] : t[r]) : (j == 2 ? t[2 * VPH + r] : t[(3 * VPH + r) & 15]);
+          else v[r] = sub ? t[VPH * (HPS + u) + r] : t[VPH * u + r];
+        }
       };
       f32x16 p[NKB], dp[NKB];
       float m = -INFINITY;
       {
-        const sop qo = headop(slot(job, 0), j);
+        const sop qo = headop(slot(jb, 0), j);
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
-          p[kb] = P::template scores_packed<DH>(headop(slot((kbase + kb) * NB + hb, 1), j), qo, f32x16{});
+          p[kb] = P::template scores_packed<DH>(headop(slot((kbase + kb) * NB + hb3, 1), j), qo, f32x16{});
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             p[kb][r] = (okbits[kb] >> r) & 1u ? p[kb][r] * sc2 : -INFINITY;
@@ -622,10 +637,10 @@ __global__ void __launch_bounds__(512) k_bwd_attn(BwdArgs a) {
       // dP^T (keys x queries) = V_j dO_j^T; Delta = sum_k P dP
       float delta = 0.f;
       {
-        const sop oo = headop(slot(job, 3), j);
+        const sop oo = headop(slot(jb, 3), j);
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
-          dp[kb] = P::template scores_packed<DH>(headop(slot((kbase + kb) * NB + hb, 2), j), oo, f32x16{});
+          dp[kb] = P::template scores_packed<DH>(headop(slot((kbase + kb) * NB + hb3, 2), j), oo, f32x16{});
 #pragma unroll
           for (int r = 0; r < 16; ++r) delta += p[kb][r] * dp[kb][r];
         }
@@ -636,7 +651,7 @@ __global__ void __launch_bounds__(512) k_bwd_attn(BwdArgs a) {
       f32x16 to = f32x16{}, tq = f32x16{};
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) {
-        const int kj = (kbase + kb) * NB + hb;
+        const int kj = (kbase + kb) * NB + hb3;
 #pragma unroll
         for (int s = 0; s < ST; ++s) to = P::mma(colop(slot(kj, 2), TS, lr, s, false), P::op(p[kb], s), to);
 #pragma unroll
@@ -647,58 +662,64 @@ __global__ void __launch_bounds__(512) k_bwd_attn(BwdArgs a) {
 #pragma unroll
         for (int s = 0; s < ST; ++s) tq = P::mma(colop(slot(kj, 1), TS, lr, s, false), P::op(dp[kb], s), tq);
       }
-      keep(to, ho[jj]);
-      keep(tq, hq[jj]);
+      keep(to, ho[u]);
+      keep(tq, hq[u]);
 #pragma unroll
-      for (int r = 0; r < VPH; ++r) ho[jj][r] *= il;
+      for (int r = 0; r < VPH; ++r) ho[u][r] *= il;
       // dK += dS^T Q, dV += P^T dO: queries in natural order on both sides
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb) {
-        f32x16 t = f32x16{};
-        {
-          const f32x16 dsT = transpose_tile<P>(dp[kb], sc, lane);
+        auto add = [&](const f32x16& w, int slot_m, f32x16 t) {
+          const f32x16 wT = transpose_tile<P>(w, sc, lane);
 #pragma unroll
-          for (int s = 0; s < ST; ++s) t = P::mma(colop(slot(job, 0), TS, lr, s, true), P::op(dsT, s), t);
+          for (int s = 0; s < ST; ++s) t = P::mma(colop(slot(jb, slot_m), TS, lr, s, true), P::op(wT, s), t);
+          return t;
+        };
+        if constexpr (WHOLE) {
+          tk[kb] = add(dp[kb], 0, u ? tk[kb] : f32x16{});
+          tv[kb] = add(p[kb], 3, u ? tv[kb] : f32x16{});
+          if (u == UN - 1) {
+            keep(tk[kb], hk[0][kb]);
+            keep(tv[kb], hv[0][kb]);
+          }
+        } else {
+          keep(add(dp[kb], 0, f32x16{}), hk[u][kb]);
+          keep(add(p[kb], 3, f32x16{}), hv[u][kb]);
         }
-        keep(t, hk[jj][kb]);
-        t = f32x16{};
-        {
-          const f32x16 pT = transpose_tile<P>(p[kb], sc, lane);
-#pragma unroll
-          for (int s = 0; s < ST; ++s) t = P::mma(colop(slot(job, 3), TS, lr, s, true), P::op(pT, s), t);
-        }
-        keep(t, hv[jj][kb]);
       }
     }
     barrier_lds();
     // ---- 4. O, dQ, dK, dV of this wave's heads into the slots
 #pragma unroll
-    for (int jj = 0; jj < HPS; ++jj) {
-      const int j = sub * HPS + jj;
-      put_head(slot(job, 0), j, hq[jj]);
-      put_head(slot(job, 3), j, ho[jj]);
-      if constexpr (!SPAN) {
-        put_head(slot(job, 1), j, hk[jj][0]);
-        put_head(slot(job, 2), j, hv[jj][0]);
+    for (int u = 0; u < UN; ++u) {
+      const int j = unit_head(u), jb = unit_job(u);
+      put_head(slot(jb, 0), j, hq[u]);
+      put_head(slot(jb, 3), j, ho[u]);
+      if constexpr (WHOLE) {  // key block u
+        put_head(slot(jb, 1), j, hk[0][u]);
+        put_head(slot(jb, 2), j, hv[0][u]);
+      } else if constexpr (!SPAN) {
+        put_head(slot(jb, 1), j, hk[u][0]);
+        put_head(slot(jb, 2), j, hv[u][0]);
       } else {  // this query block's share of the other key block
         const int oj = (kbase + 1 - own) * NB + hb;
         float k[VPH], v[VPH];
 #pragma unroll
-        for (int r = 0; r < VPH; ++r) { k[r] = own ? hk[jj][0][r] : hk[jj][NKB - 1][r]; v[r] = own ? hv[jj][0][r] : hv[jj][NKB - 1][r]; }
+        for (int r = 0; r < VPH; ++r) { k[r] = own ? hk[u][0][r] : hk[u][NKB - 1][r]; v[r] = own ? hv[u][0][r] : hv[u][NKB - 1][r]; }
         put_head(slot(oj, 1), j, k);
         put_head(slot(oj, 2), j, v);
       }
     }
     barrier_lds();
-    if constexpr (SPAN) {
+    if constexpr (SPAN && !WHOLE) {
 #pragma unroll
-      for (int jj = 0; jj < HPS; ++jj) {
-        const int j = sub * HPS + jj;
+      for (int u = 0; u < UN; ++u) {
+        const int j = unit_head(u);
         float k[VPH], v[VPH];
         get_head(slot(job, 1), j, k);
         get_head(slot(job, 2), j, v);
 #pragma unroll
-        for (int r = 0; r < VPH; ++r) { k[r] += own ? hk[jj][NKB - 1][r] : hk[jj][0][r]; v[r] += own ? hv[jj][NKB - 1][r] : hv[jj][0][r]; }
+        for (int r = 0; r < VPH; ++r) { k[r] += own ? hk[u][NKB - 1][r] : hk[u][0][r]; v[r] += own ? hv[u][NKB - 1][r] : hv[u][0][r]; }
         put_head(slot(job, 1), j, k);
         put_head(slot(job, 2), j, v);
       }

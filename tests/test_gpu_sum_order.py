@@ -4,8 +4,8 @@ A conjugate-gradient solve that stops after a few iterations of an ill-condition
 changed rounding of its operator or of its own sums into the update, by orders of magnitude more than
 the rounding itself (J changed by 2e-16: up to 1e-5 of the update).  The order of these sums is
 therefore part of what the calls return.  The digests below are of the outputs in that order, on inputs
-made from seeds, bit for bit: of the forward-mode pass with the FP32 sums that k_jvp_layer states, and of
-the FP64 sums of the solve."""
+made from seeds, bit for bit: of the forward-mode pass with the FP32 sums that k_jvp_layer states, of the
+FP64 sums of the solve, and of the attention's reverse mode over two blocks."""
 import hashlib
 
 import numpy as np
@@ -48,6 +48,12 @@ def solve(tdo, B, P, iters, weighted):
     return [*tdo.Ctx(0).sr_solve(jac, grad, 1e-3, iters, w), jac]
 
 
+def conv_rows(tdo, net, n, B, prec):
+    """The log-derivatives of the convolutions, which lie behind every layer's reverse mode."""
+    arch, params, cfg, _ = network(net, n, B, 4400)
+    return [tdo.Ctx(0).jacobian(arch, params, n, cfg, prec)[..., :6 * net[0] + 2 * net[0] ** 2].contiguous()]
+
+
 JVP = [((16, 2, 1, 64), 3, 61), ((16, 1, 2, 32), 9, 7), ((16, 2, 3, 64), 33, 5), ((32, 4, 2, 128), 8, 37), ((32, 2, 1, 96), 20, 3),
        ((32, 4, 4, 64), 64, 9), ((64, 4, 2, 256), 16, 33), ((64, 4, 1, 512), 37, 5), ((64, 8, 3, 128), 5, 40), ((64, 8, 4, 256), 32, 17),
        ((64, 8, 2, 256), 50, 6)]
@@ -58,9 +64,15 @@ SOLVE = [(1, 1, 3, False), (2, 300, 9, True), (7, 1001, 23, False), (24, 5003, 1
          (600, 257, 6, True), (40, 70001, 20, False)]
 
 
+# passes over two blocks in the kernels of widths 16 and 32 and of FP32: dK and dV of both query blocks in one sum
+SPAN = [((16, 2, 2, 64), 64, 9, "bf16"), ((32, 4, 4, 64), 64, 25, "bf16"), ((32, 4, 2, 128), 50, 9, "bf16"), ((32, 4, 3, 128), 63, 5, "fp32"),
+        ((64, 8, 3, 128), 64, 5, "fp32"), ((64, 8, 2, 256), 37, 4, "fp32")]
+
+
 def cases():
     c = {"jvp %s n=%d" % ("-".join(map(str, a[0])), a[1]): (jvp, a) for a in JVP}
     c.update({"solve B=%d P=%d" % a[:2]: (solve, a) for a in SOLVE})
+    c.update({"rows %s n=%d %s" % ("-".join(map(str, a[0])), a[1], a[3]): (conv_rows, a) for a in SPAN})
     return c
 
 
@@ -84,6 +96,12 @@ WANT = {
     "solve B=257 P=2050": "387b6cbb3af267ad",
     "solve B=600 P=257": "2c6476c9aee2cba4",
     "solve B=40 P=70001": "36eb263fb000fd35",
+    "rows 16-2-2-64 n=64 bf16": "f41d207db3deb4c3",
+    "rows 32-4-4-64 n=64 bf16": "bb225ae0d6e1648d",
+    "rows 32-4-2-128 n=50 bf16": "ddbc0646eb41623c",
+    "rows 32-4-3-128 n=63 fp32": "3dde12f5f24929d9",
+    "rows 64-8-3-128 n=64 fp32": "224614048830d188",
+    "rows 64-8-2-256 n=37 fp32": "91a1754e35360ecf",
 }
 
 

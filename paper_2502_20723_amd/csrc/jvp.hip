@@ -172,7 +172,9 @@ struct JvpArgs {
 // projections and the feed-forward part run on the FP32 matrix cores, which add their products one after the
 // other; the second sum of a tangent repeats the hidden units (u is formed twice, a sixth of the
 // feed-forward products).  The attention's tangents and its products with V, which the matrix cores would
-// have to sum differently, run on the vector ALU, beside the other wave's products.
+// have to sum differently, run on the vector ALU, beside the other wave's products.  A row meets the keys of
+// its own configuration only, also where a product with 0 would do: what is not finite in one configuration (an
+// overflow, an infinite tangent of a hidden unit that is active there) stays out of the others.
 //
 // Bound: the FP32 matrix cores (157 TFLOP/s) and the latency of the weight fragments, which come through the
 // caches: two waves per SIMD cover part of it (loaded ahead in registers, as the forward does, they spill).
@@ -313,13 +315,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
               }
               const bool ok = (keys[kb] >> (2 * r + h)) & 1u;
               p[kb][r] = ok ? p[kb][r] * a.scale : -INFINITY;
-              pd[kb][r] = s * a.scale;
+              pd[kb][r] = ok ? s * a.scale : 0.f;
               mx = fmaxf(mx, p[kb][r]);
               __builtin_amdgcn_sched_barrier(0);  // one key at a time: the registers
             }
           }
           mx = xor32_max(mx);
-          const float mm = mx == -INFINITY ? 0.f : mx;  // a row without a key (padding) keeps P = 0
+          const bool any = keys[0] != 0;  // a padding row has no key: P = 0
+          const float mm = any ? mx : 0.f;
           float l = 0.f;
 #pragma unroll
           for (int kb = 0; kb < NKB; ++kb)
@@ -331,7 +334,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
               l += e0;
               l += e1;
             }
-          const float inv = l > 0.f ? 1.0f / l : 0.f;
+          const float inv = any ? 1.0f / l : 0.f;
           float dot = 0.f;
 #pragma unroll
           for (int kb = 0; kb < NKB; ++kb)
@@ -366,9 +369,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
               for (int i = 0; i < 2; ++i) {
                 const int k = 2 * r + i;
                 if (k < 31) fetch(k + 1);
+                const bool ok = (keys[kb] >> k) & 1u;
 #pragma unroll
                 for (int t = 0; t < VPH; ++t) {
-                  const float v = w[i][t / 4 * 2][t % 4], vd = w[i][t / 4 * 2 + 1][t % 4];
+                  float v = w[i][t / 4 * 2][t % 4], vd = w[i][t / 4 * 2 + 1][t % 4];
+                  if (MASKED && (!SPAN || kb == 1)) { v = ok ? v : 0.f; vd = ok ? vd : 0.f; }
                   oj[t] = __builtin_fmaf(e[i], v, oj[t]);
                   odj[t] = odj[t] + __builtin_fmaf(ed[i], v, e[i] * vd);
                 }

@@ -43,10 +43,12 @@ __device__ __forceinline__ float gelu_d(float u) {
 // in memory holds its 16 values per lane in that order (load_tile); pos(f) is feature f's position in a row.
 __device__ __forceinline__ int asc(int m) { return 8 * (m >> 3) + 2 * (m & 3) + ((m >> 2) & 1); }
 __host__ __device__ inline int pos(int f) { return (f & ~31) + 16 * (f & 1) + ((f & 31) >> 1); }
+// Feature f's position in a row of d values of the embedding tables: a tile's values of each lane half together.
+__device__ inline int table_pos(int f, int d) { return d == 16 ? 8 * (f & 1) + (f >> 1) : pos(f); }
 
-// Embedding table of the 64 window codes and its tangent (as the forward's): rows of D values,
-// feature f at pos(f), zero past d.
-__global__ void k_embed_table_jvp(const float* __restrict__ params, const double* __restrict__ tan, int d, int D,
+// Embedding table of the 64 window codes and its tangent (as the forward's): rows of d values in the order
+// of table_pos.
+__global__ void k_embed_table_jvp(const float* __restrict__ params, const double* __restrict__ tan, int d,
                                   float* __restrict__ T, float* __restrict__ Td) {
   __shared__ float e0[64], e1[64], e0d[64], e1d[64];
   const int code = blockIdx.x;
@@ -68,27 +70,22 @@ __global__ void k_embed_table_jvp(const float* __restrict__ params, const double
     e1d[c] = gelu_d(b) * bd;
   }
   __syncthreads();
-  for (int o = threadIdx.x; o < D; o += blockDim.x) {
-    float v = 0.f, vd = 0.f;
-    if (o < d) {
-      float acc = b2[o], accd = (float)b2d[o];
-      for (int c = 0; c < d; ++c) {
-        acc += e0[c] * w2[c * d + o] + e1[c] * w2[d * d + c * d + o];
-        accd += e0d[c] * w2[c * d + o] + e0[c] * (float)w2d[c * d + o] + e1d[c] * w2[d * d + c * d + o] +
-                e1[c] * (float)w2d[d * d + c * d + o];
-      }
-      v = gelu_f(acc);
-      vd = gelu_d(acc) * accd;
+  for (int o = threadIdx.x; o < d; o += blockDim.x) {
+    float acc = b2[o], accd = (float)b2d[o];
+    for (int c = 0; c < d; ++c) {
+      acc += e0[c] * w2[c * d + o] + e1[c] * w2[d * d + c * d + o];
+      accd += e0d[c] * w2[c * d + o] + e0[c] * (float)w2d[c * d + o] + e1d[c] * w2[d * d + c * d + o] +
+              e1[c] * (float)w2d[d * d + c * d + o];
     }
-    T[code * D + pos(o)] = v;
-    Td[code * D + pos(o)] = vd;
+    T[code * d + table_pos(o, d)] = gelu_f(acc);
+    Td[code * d + table_pos(o, d)] = gelu_d(acc) * accd;
   }
 }
 
 // Embedding of every block: lane (row, half) copies its 16 values of each feature block from the
-// tables; zero where the row belongs to no configuration.
+// tables; zero past d and where the row belongs to no configuration.
 __global__ void __launch_bounds__(256) k_jvp_embed(const uint64_t* __restrict__ cfg, int64_t E, int n, int cpb, int span,
-                                                   int D, const float* __restrict__ T, const float* __restrict__ Td,
+                                                   int d, int D, const float* __restrict__ T, const float* __restrict__ Td,
                                                    float* __restrict__ X, float* __restrict__ Xd) {
   const RowMap rm{n, cpb, span != 0};
   const int64_t nblk = span ? 4 * E : 2 * ((E + cpb - 1) / cpb);
@@ -107,12 +104,14 @@ __global__ void __launch_bounds__(256) k_jvp_embed(const uint64_t* __restrict__ 
     }
     for (int ib = 0; ib < NB; ++ib) {
       const int64_t o = (g * NB + ib) * 1024;
-      const float4* t = reinterpret_cast<const float4*>(T + code * D + 32 * ib + 16 * h);
-      const float4* td = reinterpret_cast<const float4*>(Td + code * D + 32 * ib + 16 * h);
+      const int half = d == 16 ? 8 : 16;  // values of a lane
+      const float4* t = reinterpret_cast<const float4*>(T + code * d + 32 * ib + half * h);
+      const float4* td = reinterpret_cast<const float4*>(Td + code * d + 32 * ib + half * h);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        reinterpret_cast<float4*>(X + o)[64 * q + lane] = valid ? t[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-        reinterpret_cast<float4*>(Xd + o)[64 * q + lane] = valid ? td[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const bool in = valid && 4 * q < half;
+        reinterpret_cast<float4*>(X + o)[64 * q + lane] = in ? t[q] : make_float4(0.f, 0.f, 0.f, 0.f);
+        reinterpret_cast<float4*>(Xd + o)[64 * q + lane] = in ? td[q] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
     }
   }
@@ -152,10 +151,12 @@ __global__ void k_jvp_pack(const float* __restrict__ params, const double* __res
 }
 
 struct JvpArgs {
-  const float *w, *wd;  // packed layer and its tangent (k_jvp_pack)
-  float *x, *xd;        // residual stream and its tangent, [blocks][D/32] tiles (load_tile), in place
+  const float *w, *wd;    // packed layer and its tangent (k_jvp_pack), or
+  const float* params;    // the layer as it lies in the parameter vector
+  const double* tan;      // and in the tangent
+  float *x, *xd;          // residual stream and its tangent, [blocks][D/32] tiles (load_tile), in place
   int64_t E;
-  int n, cpb, heads, M;
+  int n, cpb, d, heads, M;
   float scale;
 };
 
@@ -178,10 +179,12 @@ struct JvpArgs {
 //
 // Bound: the FP32 matrix cores (157 TFLOP/s) and the latency of the weight fragments, which come through the
 // caches: two waves per SIMD cover part of it (loaded ahead in registers, as the forward does, they spill).
-// 16384 configurations at n = 32, benchmark network: 15.8 ms; 32768 at n = 16, 4 heads, 2 layers 8.0 ms; 4096 at
+// 16384 configurations at n = 32, benchmark network: 15.8 ms; 32768 at n = 16, 4 heads, 2 layers 8.2 ms; 4096 at
 // n = 64, 2 layers 4.9 ms (with the sums in the order that suits the matrix cores 13.8, 6.6 and 4.6 ms; the same sums
 // as separate products on the vector ALU between activations in memory 75.1, 28.1 and 31.2 ms).
-template <int D, int DH, bool SPAN, bool MASKED>
+// PACKED: weights from the packed fragments; otherwise, in a workspace too small for a packed layer, from the
+// parameter vector element by element (16384 configurations at n = 32 in 380 KB, a few at a time: 2.7 s).
+template <int D, int DH, bool SPAN, bool MASKED, bool PACKED>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) k_jvp_layer(JvpArgs a) {
 #pragma clang fp contract(off)
   constexpr int NB = D / 32, HPB = 32 / DH, VPH = DH / 2, NKB = SPAN ? 2 : 1, LS = 36, TILE = 32 * LS;
@@ -189,21 +192,45 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   __shared__ __align__(16) float sm[8][4][TILE];  // per wave: k, t(k), v, t(v) [row][pos]
   const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = a.n, cpb = a.cpb, M = a.M, MB = M / 32;
+  const int n = a.n, cpb = a.cpb, M = a.M, MB = M / 32, d = a.d;
   const int64_t nblk = SPAN ? 4 * a.E : 2 * ((a.E + cpb - 1) / cpb);
   // fragment (ob, ib, s) of matrix m (Wq, Wk, Wv, Wo, W1, W2) or of its tangent
   auto frag = [&](int m, int ob, int ib, int s, bool tangent) -> f32x4 {
-    const float* w = (tangent ? a.wd : a.w) + (m < 4 ? m * D * D : 4 * D * D + (m - 4) * D * M);
-    return ld_frag<P>(w, (ob * (m == 5 ? MB : NB) + ib) * 4 + s, lane);
+    const int nib = m == 5 ? MB : NB;
+    if constexpr (PACKED) {
+      const float* w = (tangent ? a.wd : a.w) + (m < 4 ? m * D * D : 4 * D * D + (m - 4) * D * M);
+      return ld_frag<P>(w, (ob * nib + ib) * 4 + s, lane);
+    } else {
+      const int rows = m == 5 ? M : d, cols = m == 4 ? M : d;
+      const int o = m < 4 ? m * d * d : m == 4 ? 4 * d * d : 4 * d * d + d * M + M;
+      const int out = 32 * ob + asc(lr);
+      f32x4 v;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int in = 32 * ib + 2 * (4 * s + t) + h, i = o + in * cols + out;
+        const bool ok = in < rows && out < cols;
+        v[t] = !ok ? 0.f : tangent ? (float)a.tan[i] : a.params[i];
+      }
+      return v;
+    }
   };
   // 16 values of a bias (b1 or b2) or of its tangent, features 32 c + 2 r + h
   auto bias = [&](bool second, int c, bool tangent) {
     f32x16 v;
-    const float* p = (tangent ? a.wd : a.w) + 4 * D * D + 2 * D * M + (second ? M : 0) + 32 * c + 16 * h;
+    if constexpr (PACKED) {
+      const float* p = (tangent ? a.wd : a.w) + 4 * D * D + 2 * D * M + (second ? M : 0) + 32 * c + 16 * h;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 t = reinterpret_cast<const float4*>(p)[q];
-      v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
+      for (int q = 0; q < 4; ++q) {
+        const float4 t = reinterpret_cast<const float4*>(p)[q];
+        v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
+      }
+    } else {
+      const int o = 4 * d * d + d * M + (second ? M + d * M : 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int f = 32 * c + 2 * r + h;
+        v[r] = second && f >= d ? 0.f : tangent ? (float)a.tan[o + f] : a.params[o + f];
+      }
     }
     return v;
   };
@@ -539,18 +566,18 @@ namespace tdo {
 namespace {
 
 template <int D, int DH, bool SPAN>
-int32_t launch_jvp_span(const JvpArgs& a, bool masked, int num_cus, hipStream_t st) {
+int32_t launch_jvp_span(const JvpArgs& a, bool masked, bool packed, int num_cus, hipStream_t st) {
   const int64_t nblk = SPAN ? 4 * a.E : 2 * ((a.E + a.cpb - 1) / a.cpb);
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((nblk + 7) / 8, num_cus));
-  auto k = masked ? k_jvp_layer<D, DH, SPAN, true> : k_jvp_layer<D, DH, SPAN, false>;
+  auto k = !packed ? k_jvp_layer<D, DH, SPAN, true, false> : masked ? k_jvp_layer<D, DH, SPAN, true, true> : k_jvp_layer<D, DH, SPAN, false, true>;
   hipLaunchKernelGGL(k, dim3(grid), dim3(512), 0, st, a);
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }
 
 template <int D, int DH>
-int32_t launch_jvp_layer(const JvpArgs& a, bool span, bool masked, int num_cus, hipStream_t st) {
-  return span ? launch_jvp_span<D, DH, true>(a, masked, num_cus, st) : launch_jvp_span<D, DH, false>(a, masked, num_cus, st);
+int32_t launch_jvp_layer(const JvpArgs& a, bool span, bool masked, bool packed, int num_cus, hipStream_t st) {
+  return span ? launch_jvp_span<D, DH, true>(a, masked, packed, num_cus, st) : launch_jvp_span<D, DH, false>(a, masked, packed, num_cus, st);
 }
 
 // floats of one packed layer (weights, b1, b2)
@@ -558,23 +585,27 @@ int64_t jvp_layer_len(const PackPlan& pp) { return pp.layer_elems + pp.M + pp.D;
 
 }  // namespace
 
+// Bytes that plan_jvp needs at least: the tables, one block's configurations (z and t(z) among them) and the
+// roundings of eight buffers.
+static size_t jvp_small(const NetPlan& np) { return 128 * (size_t)np.pp.d * 4 + 8 * 256; }
+static size_t jvp_unit(const NetPlan& np) { return (np.span ? 4 : 2) * (32 * (size_t)np.D * 4 * 2) + np.cpb * 32; }
+size_t jvp_min_bytes(const NetPlan& np) { return jvp_small(np) + jvp_unit(np); }
+
 // Lay out the forward-mode buffers from ar.used on, for at most B configurations and
-// within max_bytes for the per-chunk part.
+// within max_bytes.
 int32_t plan_jvp(const NetPlan& np, int64_t B, size_t max_bytes, Arena& ar, JvpWs* j) {
   const PackPlan& pp = np.pp;
-  const size_t block = 32 * (size_t)np.D * 4 * 2;           // x and t(x) of a block
-  const size_t unit = (np.span ? 4 : 2) * block + np.cpb * 32;  // the blocks of cpb configurations, z and t(z)
-  const size_t small = 128 * (size_t)np.D * 4 + 16 * 256;
+  const size_t unit = jvp_unit(np);
   const size_t layer = 2 * (size_t)jvp_layer_len(pp) * 4;
-  // every layer's weights packed once per call, or, in a small workspace, one layer's at a time
-  j->layers = small + pp.layers * layer + unit <= max_bytes / 2 ? pp.layers : 1;
-  const size_t fixed = small + j->layers * layer;
-  TDO_CHECK(max_bytes >= fixed + unit, TDO_ENOMEM,
-            "workspace cannot hold the forward-mode buffers of one configuration (%zu bytes)", fixed + unit);
+  TDO_CHECK(max_bytes >= jvp_min_bytes(np), TDO_ENOMEM,
+            "workspace cannot hold the forward-mode buffers of one configuration (%zu bytes)", jvp_min_bytes(np));
+  // every layer's weights packed once per call; in a small workspace one layer's at a time; or none
+  j->layers = jvp_min_bytes(np) + pp.layers * layer <= max_bytes / 2 ? pp.layers : jvp_min_bytes(np) + layer <= max_bytes ? 1 : 0;
+  const size_t fixed = jvp_small(np) + j->layers * layer;
   const int64_t units = std::max<int64_t>(1, std::min<int64_t>((B + np.cpb - 1) / np.cpb, (int64_t)((max_bytes - fixed) / unit)));
   j->ec = units * np.cpb;
-  j->T = ar.take<float>(64 * (size_t)np.D);
-  j->Td = ar.take<float>(64 * (size_t)np.D);
+  j->T = ar.take<float>(64 * (size_t)pp.d);
+  j->Td = ar.take<float>(64 * (size_t)pp.d);
   j->w = ar.take<float>(j->layers * (size_t)jvp_layer_len(pp));
   j->wd = ar.take<float>(j->layers * (size_t)jvp_layer_len(pp));
   j->X = ar.take<float>((size_t)blocks_for(np, j->ec) * 32 * np.D);
@@ -596,20 +627,24 @@ int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params
     hipLaunchKernelGGL(k_jvp_pack, dim3((unsigned)std::min<int64_t>(ceil_div(j.layers * len, 256), 4096)), dim3(256), 0, st,
                        params, tan, pp, l0, j.layers, w, wd);
   };
-  hipLaunchKernelGGL(k_embed_table_jvp, dim3(64), dim3(64), 0, st, params, tan, pp.d, np.D, T, Td);
-  if (j.layers == pp.layers) pack(0);
+  hipLaunchKernelGGL(k_embed_table_jvp, dim3(64), dim3(64), 0, st, params, tan, pp.d, T, Td);
+  const bool all = j.layers == pp.layers;
+  if (all) pack(0);
   TDO_HIP(hipGetLastError());
   for (int64_t e0 = 0; e0 < B; e0 += j.ec) {
     const int64_t E = std::min(j.ec, B - e0), nblk = blocks_for(np, E);
     const unsigned grid = (unsigned)std::min<int64_t>(ceil_div(nblk, 4), 8192), grid2 = (unsigned)std::min<int64_t>(ceil_div(2 * E, 4), 8192);
-    hipLaunchKernelGGL(k_jvp_embed, dim3(grid), dim3(256), 0, st, cfg + 2 * e0, E, np.n, np.cpb, (int)np.span, np.D, T, Td, X, Xd);
+    hipLaunchKernelGGL(k_jvp_embed, dim3(grid), dim3(256), 0, st, cfg + 2 * e0, E, np.n, np.cpb, (int)np.span, pp.d, np.D, T, Td, X, Xd);
     TDO_HIP(hipGetLastError());
     for (int l = 0; l < pp.layers; ++l) {
-      if (j.layers != pp.layers) pack(l);
+      if (j.layers && !all) pack(l);
       JvpArgs a{};
-      const int64_t o = j.layers == pp.layers ? l * len : 0;
+      const int64_t o = all ? l * len : 0;
       a.w = w + o;
       a.wd = wd + o;
+      a.params = params + pp.off_layer0 + l * pp.layer_stride;
+      a.tan = tan + pp.off_layer0 + l * pp.layer_stride;
+      a.d = pp.d;
       a.x = X;
       a.xd = Xd;
       a.E = E;
@@ -618,8 +653,8 @@ int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params
       a.heads = pp.heads;
       a.M = pp.M;
       a.scale = (float)(1.0 / std::sqrt((double)np.DH));
-      if (np.D == 32) TDO_TRY(np.DH == 8 ? (launch_jvp_layer<32, 8>(a, np.span, np.masked, np.num_cus, st)) : (launch_jvp_layer<32, 16>(a, np.span, np.masked, np.num_cus, st)));
-      else TDO_TRY(np.DH == 8 ? (launch_jvp_layer<64, 8>(a, np.span, np.masked, np.num_cus, st)) : (launch_jvp_layer<64, 16>(a, np.span, np.masked, np.num_cus, st)));
+      if (np.D == 32) TDO_TRY(np.DH == 8 ? (launch_jvp_layer<32, 8>(a, np.span, np.masked, j.layers > 0, np.num_cus, st)) : (launch_jvp_layer<32, 16>(a, np.span, np.masked, j.layers > 0, np.num_cus, st)));
+      else TDO_TRY(np.DH == 8 ? (launch_jvp_layer<64, 8>(a, np.span, np.masked, j.layers > 0, np.num_cus, st)) : (launch_jvp_layer<64, 16>(a, np.span, np.masked, j.layers > 0, np.num_cus, st)));
     }
     hipLaunchKernelGGL(k_jvp_head, dim3(grid2), dim3(256), 0, st, E, np.n, np.cpb, (int)np.span, pp.d, np.D, X, Xd,
                        params + pp.off_head_w, tan + pp.off_head_w, z, zd);

@@ -338,17 +338,25 @@ extern "C" int32_t tdo_sr_solve_matfree(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   TDO_TRY(order.begin(&c, stream));
   TDO_TRY(check_params_finite(&c, params, npj.pp.nparams, stream));
   const int64_t P = npj.pp.nparams;
-  // CG vectors and scalars, the per-sample tangents and seeds, the forward-mode buffers (at
-  // most a third of the rest of the budget), then the reverse-mode plan in what remains
+  // CG vectors and scalars, the per-sample tangents and seeds, the forward-mode buffers (at most a third
+  // of the rest of the budget, less where the reverse mode would not fit), then the reverse-mode plan in
+  // what remains
   Arena ar;
   const size_t or_ = ar.take<double>((size_t)P), op = ar.take<double>((size_t)P), oap = ar.take<double>((size_t)P);
   const size_t osc = ar.take<double>(16), opart = ar.take<double>(kDotParts);
   const size_t ot = ar.take<float>(2 * (size_t)B), oseed = ar.take<float>(2 * (size_t)B);
   TDO_CHECK(c.budget > ar.used + 4096, TDO_ENOMEM, "workspace budget %zu too small", c.budget);
   JvpWs j;
-  TDO_TRY(plan_jvp(npj, B, (c.budget - ar.used) / 3, ar, &j));
   TrainWs t;
-  TDO_TRY(plan_train_at(c, npv, B, 1, ar.used, c.budget, &t));
+  const Arena vectors = ar;
+  for (size_t most = (c.budget - ar.used) / 3;; most = std::max(most / 2, jvp_min_bytes(npj))) {
+    ar = vectors;
+    TDO_TRY(plan_jvp(npj, B, most, ar, &j));
+    const int32_t rc = plan_train_at(c, npv, B, 1, ar.used, c.budget, &t);
+    if (rc == TDO_OK) break;
+    if (rc != TDO_ENOMEM || most <= jvp_min_bytes(npj)) return rc;
+  }
+  clear_error();
   TDO_TRY(ensure_workspace(&c, t.total));
   void* ws = c.ws;
   double *r = at<double>(ws, or_), *p = at<double>(ws, op), *Ap = at<double>(ws, oap), *sc = at<double>(ws, osc);

@@ -75,10 +75,11 @@ int32_t net_plan(const Context* c, const tdo_arch_t* arch, int n, bool bf16, Net
 // from ar.used on within max_bytes.
 struct JvpWs {
   int64_t ec = 0;
-  int layers = 0;  // layers whose packed weights are held at a time
+  int layers = 0;  // layers whose packed weights are held at a time: all, one or none
   size_t T, Td, w, wd, X, Xd, z, zd;
 };
 int32_t plan_jvp(const NetPlan& np, int64_t B, size_t max_bytes, Arena& ar, JvpWs* j);
+size_t jvp_min_bytes(const NetPlan& np);  // the least max_bytes it accepts
 // out[e] (re, im) = d log rho(cfg[e]) along the tangent tan [P].
 int32_t run_jvp(const NetPlan& np, void* ws, const JvpWs& j, const float* params, const double* tan, const uint64_t* cfg,
                 int64_t B, float* out, hipStream_t st);

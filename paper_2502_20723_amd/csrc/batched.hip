@@ -49,7 +49,7 @@ float time_twice(hipStream_t st, hipEvent_t e0, hipEvent_t e1, F&& fn) {
 // Tile shapes of one problem's (chain length, precision, width, head width, depth, MLP width):
 //  1. the forward layer kernel: workgroups of 8 waves (two per SIMD) or, BF16 only,
 //     4 waves, and 1 or 2 workgroups per CU, timed on the full forward over the problem's
-//     samples;
+//     samples (networks that run in one launch at any batch, net_stack.hip, keep the default: nothing to choose);
 //  2. the BF16 feed-forward backward at MLP width 256: 8 or 4 waves per workgroup, timed on the
 //     whole loss and gradient of the problem (the backward cannot run alone), which writes the
 //     problem's outputs (the real call overwrites them).
@@ -86,7 +86,9 @@ int32_t tune_problem(Context& c, NetPlan& np, const ModelDev& m, const TrainWs& 
     const int waves_c[2] = {8, 4}, wg_c[2] = {1, 2};
     float best = -1.f;
     int bw = np.fwd_waves, bg = np.fwd_wg_per_cu;
-    const bool layers = !stack_takes(np, E);  // one launch for all layers has a fixed shape
+    // One launch for all layers has a fixed shape.  The entry is kept for every batch of the network, and the
+    // loss evaluates many entries per sample, so the layer kernel is timed if it runs at any batch.
+    const bool layers = !stack_takes(np, int64_t(1) << 40);
     for (int wi = 0; wi < (two_shapes ? 2 : 1) && rc == TDO_OK && layers; ++wi)
       for (int gi = 0; gi < 2 && rc == TDO_OK; ++gi) {
         np.fwd_waves = waves_c[wi];

@@ -19,6 +19,7 @@
 // gradients to a private partial buffer, and the partials are summed in FP64 in
 // a fixed order, so results do not depend on scheduling.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "net.h"
@@ -1097,29 +1098,46 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const float* __restrict
 }
 
 // ------------------------------------------------------------------ launchers
-template <class P, int D, int CW, int CPW>
-static int32_t mlp_c(const BwdArgs& a, int blocks, hipStream_t st) {
-  constexpr int RG = 8 / CW, NBK = RG * (CPW == 1 ? 2 : 1);
-  const size_t red = RG > 1 ? (size_t)CW * (2 * CPW * (D / 32) * 1024 + 64 * (CPW + D / 32)) * 4 : 0;
-  const size_t lds = std::max(MlpLds<P, D, NBK>::bytes(a.M), red);
-  TDO_CHECK(lds <= 160 * 1024 && a.M / 32 <= CW * CPW, TDO_EUNSUPPORTED, "feed-forward backward: width %d, mlp %d", D, a.M);
-  auto k = a.g_in ? k_bwd_mlp<P, D, CW, CPW, false> : k_bwd_mlp<P, D, CW, CPW, true>;
-  TDO_TRY(allow_full_lds((const void*)k));
-  hipLaunchKernelGGL(k, dim3(blocks), dim3(512), lds, st, a);
-  TDO_HIP(hipGetLastError());
-  return TDO_OK;
+// Split of the feed-forward backward over hidden units: CW waves, as many as there are chunks of 32 (2, 4 or
+// 8), the others over rows; more than 8 chunks (width 32 only) take CPW = 2 per wave.  f(CW, CPW).
+template <int D, class F>
+static auto mlp_split(int M, F&& f) {
+  const int MB = M / 32;
+  if constexpr (D == 32) {
+    if (MB <= 2) return f(std::integral_constant<int, 2>{}, std::integral_constant<int, 1>{});
+    if (MB > 8) return f(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
+  }
+  return MB <= 4 ? f(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{})
+                 : f(std::integral_constant<int, 8>{}, std::integral_constant<int, 1>{});
 }
 
-// Waves over the hidden units: as many as there are chunks of 32 (2, 4 or 8), the others over rows;
-// more than 8 chunks (width 32 only) take two per wave.
+// LDS of a workgroup: the tiles, and at the end the row groups' gradients.
+template <class P, int D, int CW, int CPW>
+static size_t mlp_lds(int M) {
+  constexpr int RG = 8 / CW, NBK = RG * (CPW == 1 ? 2 : 1);
+  const size_t red = RG > 1 ? (size_t)CW * (2 * CPW * (D / 32) * 1024 + 64 * (CPW + D / 32)) * 4 : 0;
+  return std::max(MlpLds<P, D, NBK>::bytes(M), red);
+}
+
+template <class P, int D>
+static bool mlp_takes(int M) {
+  return mlp_split<D>(M, [&](auto cw, auto cpw) { return M / 32 <= cw * cpw && mlp_lds<P, D, cw, cpw>(M) <= 160 * 1024; });
+}
+
+bool bwd_mlp_takes(int D, int M) {
+  return D == 32 ? mlp_takes<PBF16, 32>(M) && mlp_takes<PF32, 32>(M) : mlp_takes<PBF16, 64>(M) && mlp_takes<PF32, 64>(M);
+}
+
 template <class P, int D>
 static int32_t mlp_t(const BwdArgs& a, int blocks, hipStream_t st) {
-  const int MB = a.M / 32;
-  if constexpr (D == 32) {
-    if (MB <= 2) return mlp_c<P, D, 2, 1>(a, blocks, st);
-    if (MB > 8) return mlp_c<P, D, 8, 2>(a, blocks, st);
-  }
-  return MB <= 4 ? mlp_c<P, D, 4, 1>(a, blocks, st) : mlp_c<P, D, 8, 1>(a, blocks, st);
+  TDO_CHECK((mlp_takes<P, D>(a.M)), TDO_EUNSUPPORTED, "feed-forward backward: width %d, mlp %d", D, a.M);
+  return mlp_split<D>(a.M, [&](auto cw, auto cpw) -> int32_t {
+    auto k = a.g_in ? k_bwd_mlp<P, D, cw, cpw, false> : k_bwd_mlp<P, D, cw, cpw, true>;
+    TDO_TRY(allow_full_lds((const void*)k));
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(512), (mlp_lds<P, D, cw, cpw>(a.M)), st, a);
+    TDO_HIP(hipGetLastError());
+    return TDO_OK;
+  });
 }
 
 template <class P, int D, int DH, bool SPAN>
@@ -1131,8 +1149,6 @@ static int32_t attn_t(const BwdArgs& a, int blocks, hipStream_t st) {
   TDO_HIP(hipGetLastError());
   return TDO_OK;
 }
-
-size_t bwd_mlp_lds(int D, int M) { return (size_t)(2 * D * M + M + D) * 4 + 4 * 32 * TS * 4; }
 
 int32_t launch_bwd_mlp(const BwdArgs& a, bool bf16, int D, int blocks, hipStream_t st) {
   if (D == 32) return bf16 ? mlp_t<PBF16, 32>(a, blocks, st) : mlp_t<PF32, 32>(a, blocks, st);

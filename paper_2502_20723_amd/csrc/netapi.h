@@ -97,7 +97,8 @@ struct BwdArgs {
   int mlp_waves;                // BF16 feed-forward backward at mlp 256: 8 or 4 waves per workgroup
 };
 
-size_t bwd_mlp_lds(int D, int M);
+// Whether the generic feed-forward backward has a split for this width (padded) and mlp.
+bool bwd_mlp_takes(int D, int M);
 // Feed-forward backward with BF16 operands and per-wave register gradients (width 64).
 bool bwd_mlp_bf16_supported(int d, int D, int M);
 int32_t launch_bwd_mlp_bf16(const BwdArgs& a, int blocks, hipStream_t st);

@@ -218,8 +218,7 @@ static int32_t finish_backward(const NetPlan& np, const BwdBufs& bb, const float
 int32_t plan_train_at(const Context& c, const NetPlan& np, int64_t B, int nslots, size_t base, size_t cap,
                       TrainWs* t) {
   const PackPlan& pp = np.pp;
-  TDO_CHECK(bwd_mlp_lds(np.D, pp.M) <= 160 * 1024, TDO_EUNSUPPORTED,
-            "backward of width %d with mlp %d exceeds the LDS of a workgroup", np.D, pp.M);
+  TDO_CHECK(bwd_mlp_takes(np.D, pp.M), TDO_EUNSUPPORTED, "no feed-forward backward for width %d with mlp %d", np.D, pp.M);
   Arena ar;
   ar.used = (base + 255) & ~size_t(255);
   carve_weights(np, ar, t->woff);
@@ -356,7 +355,7 @@ extern "C" int32_t tdo_log_rho_jacobian(tdo_ctx_t* ctx, const tdo_arch_t* arch, 
   TDO_TRY(check_params_finite(&c, params, np.pp.nparams, stream));
   const PackPlan& pp = np.pp;
   const int D = np.D, M = pp.M, L = pp.layers;
-  TDO_CHECK(bwd_mlp_lds(D, M) <= 160 * 1024, TDO_EUNSUPPORTED, "backward of width %d with mlp %d exceeds the LDS of a workgroup", D, M);
+  TDO_CHECK(bwd_mlp_takes(D, M), TDO_EUNSUPPORTED, "no feed-forward backward for width %d with mlp %d", D, M);
   np.cpb = 1;
   np.masked = n != (np.span ? 64 : 32);
   const bool mlp_reg = np.bf16 && bwd_mlp_bf16_supported(pp.d, D, M);

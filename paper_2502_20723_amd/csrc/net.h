@@ -92,12 +92,6 @@ struct PBF16 {
     if constexpr (DH == 8) return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(a.v, b.v, c, 0, 0, 0);
     else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, c, 0, 0, 0);
   }
-  // Attention scores over DH features of head j (values [DH/2*j, DH/2*j + DH/2)).
-  template <int DH>
-  __device__ static __forceinline__ f32x16 scores(const f32x16& kv, const f32x16& qv, int j, f32x16 c) {
-    static_assert(DH == 8 || DH == 16, "head width 8 or 16");
-    return scores_packed<DH>(pack_head<DH>(kv, j), pack_head<DH>(qv, j), c);
-  }
 };
 
 // FP32 operands: four v_mfma_f32_32x32x2f32 (1 value/lane each) per k-step, so that a lane
@@ -145,13 +139,6 @@ struct PF32 {
     for (int t = 0; t < DH / 2; ++t) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[t], b.v[t], c, 0, 0, 0);
     return c;
   }
-  template <int DH>
-  __device__ static __forceinline__ f32x16 scores(const f32x16& kv, const f32x16& qv, int j, f32x16 c) {
-    constexpr int PER = DH / 2;
-#pragma unroll
-    for (int t = 0; t < PER; ++t) c = __builtin_amdgcn_mfma_f32_32x32x2f32(kv[PER * j + t], qv[PER * j + t], c, 0, 0, 0);
-    return c;
-  }
 };
 
 // Packed weight fragment (out-block ob, in-block ib, k-step s) of a matrix
@@ -165,16 +152,6 @@ __device__ __forceinline__ typename P::op_t ld_frag(const typename P::elem_t* ba
     return *reinterpret_cast<const f32x4*>(base + ((size_t)frag * 64 + lane) * 4);
   }
 }
-
-// Per-layer packed-weight offsets (elements), for width D and MLP width M.
-template <int D, int M>
-struct LayerPack {
-  static constexpr int NB = D / 32, MB = M / 32;
-  static constexpr int WQ = 0, WK = D * D, WV = 2 * D * D, WO = 3 * D * D;
-  static constexpr int W1 = 4 * D * D;        // [MB ob][NB ib][STEPS] fragments
-  static constexpr int W2 = 4 * D * D + D * M;  // [NB ob][MB ib][STEPS]
-  static constexpr int TOTAL = 4 * D * D + 2 * D * M;
-};
 
 // Row validity and configuration slot of lane row lr in block g (see the forward).
 struct RowMap {

@@ -39,9 +39,7 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
   constexpr int NB = D / 32;            // feature blocks
   constexpr int NBR = SPAN ? 2 : 1;     // row blocks per wave
   constexpr int HPB = 32 / DH;          // heads per 32-feature block
-  constexpr int ST = P::STEPS;
   using elem_t = typename P::elem_t;
-  using op_t = typename P::op_t;
   using save_t = typename P::save_t;
   constexpr bool WLDS = (P::KPL == 8);
 

@@ -231,6 +231,7 @@ int32_t net_plan(const Context* c, const tdo_arch_t* arch, int n, bool bf16, Net
   np->elem = bf16 ? 2 : 4;
   np->num_cus = c->num_cus;
   np->prof = const_cast<Profiler*>(&c->prof);
+  np->layer_forward = c->layer_forward;
   np->fwd_wg_per_cu = 1;
   np->fwd_waves = 8;
   np->mlp_waves = (bf16 && np->pp.M == 256) ? 8 : 4;
@@ -274,7 +275,7 @@ StackArgs stack_args(const NetPlan& np, const NetWeights& w) {
 //    batch has at most one tile per pair of waves (BF16, n = 20, mlp 96: per proposal of 1024 chains
 //    22 and 12, log rho of 65536 configurations 514 and 611).
 bool stack_takes(const NetPlan& np, int64_t E) {
-  if (!stack_supported(np.bf16, np.D, np.pp.M, np.pp.layers, np.span)) return false;
+  if (np.layer_forward || !stack_supported(np.bf16, np.D, np.pp.M, np.pp.layers, np.span)) return false;
   const int64_t tiles = (E + np.cpb - 1) / np.cpb;  // pairs of waves
   return np.pp.layers > 1 || tiles <= 4LL * np.num_cus;
 }
@@ -426,6 +427,15 @@ int32_t tdo_ctx_destroy(tdo_ctx_t* ctx) {
   if (ctx->c.nf_host) TDO_HIP(hipHostFree(ctx->c.nf_host));
   if (ctx->c.ws_done) TDO_HIP(hipEventDestroy(ctx->c.ws_done));
   delete ctx;
+  return TDO_OK;
+}
+
+// Not part of the C ABI: lets the tests compare the forward in one launch with the layer kernel, bit for bit,
+// on networks for which every batch takes the one launch.
+int32_t tdo_test_layer_forward(tdo_ctx_t* ctx, int32_t on) {
+  clear_error();
+  TDO_CHECK(ctx != nullptr, TDO_EINVAL, "ctx is NULL");
+  ctx->c.layer_forward = on != 0;
   return TDO_OK;
 }
 

@@ -99,6 +99,7 @@ struct Context {
   Profiler prof;
   GraphCache graph;
   std::vector<TuneEntry> tune;
+  bool layer_forward = false;  // tests only: never the forward in one launch (tdo_test_layer_forward)
   std::string tune_cache;  // path of the JSON cache of the tuned shapes, or empty
   // counts of non-finite parameters per slice: running (device) and reported (pinned host)
   uint32_t* nf_dev = nullptr;

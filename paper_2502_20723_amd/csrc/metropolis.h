@@ -40,15 +40,17 @@ __device__ __forceinline__ Philox4x32 philox10(uint32_t c0, uint32_t c1, uint32_
 __device__ __forceinline__ double propose_move(uint64_t& a, uint64_t& b, int n, uint64_t t, uint32_t chain, uint64_t seed,
                                                uint64_t pair_thr) {
   const Philox4x32 r = philox10((uint32_t)t, (uint32_t)(t >> 32), chain, 0u, (uint32_t)seed, (uint32_t)(seed >> 32));
+  // as two masks: a branch that writes a or b puts both on the stack (a proposal of 2000 chains 2.2 -> 2.8 us)
+  uint64_t fa, fb;
   if ((uint64_t)r.c[0] < pair_thr) {
-    const int i = (int)(((uint64_t)r.c[1] * (uint64_t)n) >> 32);
-    a ^= 1ull << i;
-    b ^= 1ull << i;
+    fa = fb = 1ull << (int)(((uint64_t)r.c[1] * (uint64_t)n) >> 32);
   } else {
     const int j = (int)(((uint64_t)r.c[1] * (uint64_t)(2 * n)) >> 32);
-    if (j < n) a ^= 1ull << j;
-    else b ^= 1ull << (j - n);
+    fa = j < n ? 1ull << j : 0ull;
+    fb = j < n ? 0ull : 1ull << (j - n);
   }
+  a ^= fa;
+  b ^= fb;
   return ((double)r.c[2] + 0.5) * 0x1p-32;
 }
 

@@ -239,7 +239,7 @@ int32_t net_plan(const Context* c, const tdo_arch_t* arch, int n, bool bf16, Net
   for (const TuneEntry& e : c->tune)
     if (e.key == key) {
       np->fwd_wg_per_cu = e.fwd_wg_per_cu;
-      if (bf16) np->fwd_waves = e.fwd_waves;  // FP32: 8 only
+      if (bf16) np->fwd_waves = e.fwd_waves;  // FP32: by the batch
       np->mlp_waves = e.mlp_waves;
     }
   return TDO_OK;

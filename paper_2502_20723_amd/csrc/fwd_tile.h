@@ -33,10 +33,11 @@ struct EmbedRow {
 // n = 16: 1.23 ms without, 1.15 with whole matrices, 1.00 so; n = 32: 2.65, 2.22, 2.11).  Sixteen-wide
 // heads keep the plain loads in the attention part: their accumulators leave too few registers
 // (1.03 ms with, though 16 configurations take 96 us without and 86 with).  Two row blocks per wave
-// use a fragment twice and have no registers to spare.  BF16 weights are in LDS.
-template <class P, int NBR>
+// use a fragment twice and have registers to spare with one wave per SIMD only (WAVES = 4), where they
+// need it most.  BF16 weights are in LDS.
+template <class P, int NBR, int WAVES>
 constexpr bool frags_ahead() {
-  return P::KPL == 4 && NBR == 1;
+  return P::KPL == 4 && (NBR == 1 || WAVES == 4);
 }
 template <class P>
 struct Frags {
@@ -51,12 +52,12 @@ struct Frags {
 // Attention sub-layer: x += W_O concat_j softmax(Q_j K_j^T / sqrt(dh)) V_j.  okbits[qb][kb]: the valid
 // (query row qb*32+lr, key row kb*32+tile_idx(r, h)) pairs as bit r; sc = log2(e)/sqrt(dh);
 // put_lse(hb, lsev): the log2 softmax normalisers of head block hb, per row block and head.
-template <class P, int D, int DH, int NBR, bool MASKED, class Lse>
+template <class P, int D, int DH, int NBR, bool MASKED, int WAVES = 8, class Lse>
 __device__ __forceinline__ void tile_attention(f32x16 (&x)[NBR][D / 32], const typename P::elem_t* Wq, const typename P::elem_t* Wk,
                                                const typename P::elem_t* Wv, const typename P::elem_t* Wo,
                                                const uint32_t (&okbits)[NBR][NBR], float sc, int lane, Lse&& put_lse) {
   constexpr int NB = D / 32, ST = P::STEPS, HPB = 32 / DH;
-  constexpr bool AHEAD = DH == 8 && frags_ahead<P, NBR>();
+  constexpr bool AHEAD = (DH == 8 || WAVES == 4) && frags_ahead<P, NBR, WAVES>();
   using op_t = typename P::op_t;
   // operands of x taken before the residual is updated
   op_t xo[NBR][NB][ST];
@@ -73,27 +74,28 @@ __device__ __forceinline__ void tile_attention(f32x16 (&x)[NBR][D / 32], const t
   for (int hb = 0; hb < NB; ++hb) {
     f32x16 q[NBR], k[NBR], v[NBR];
 #pragma unroll
-    for (int rb = 0; rb < NBR; ++rb) {
-      q[rb] = f32x16{};
-      k[rb] = f32x16{};
-      v[rb] = f32x16{};
-      if constexpr (AHEAD) {
-        // groups of ST fragments, alternating between the two halves of w
+    for (int rb = 0; rb < NBR; ++rb) q[rb] = k[rb] = v[rb] = f32x16{};
+    if constexpr (AHEAD) {
+      // groups of ST fragments, alternating between the two halves of w
 #pragma unroll
-        for (int g = 0; g < 3 * NB; ++g) {
-          const int mtx = g / NB, ib = g % NB, nx = g + 1;
-          if (nx < 3 * NB)
-            w[nx & 1].load(nx / NB == 0 ? Wq : nx / NB == 1 ? Wk : Wv, (hb * NB + nx % NB) * ST, lane);
-          else
-            w[nx & 1].load(Wo, hb * ST, lane);
+      for (int g = 0; g < 3 * NB; ++g) {
+        const int mtx = g / NB, ib = g % NB, nx = g + 1;
+        if (nx < 3 * NB)
+          w[nx & 1].load(nx / NB == 0 ? Wq : nx / NB == 1 ? Wk : Wv, (hb * NB + nx % NB) * ST, lane);
+        else
+          w[nx & 1].load(Wo, hb * ST, lane);
+#pragma unroll
+        for (int rb = 0; rb < NBR; ++rb)
 #pragma unroll
           for (int s = 0; s < ST; ++s) {
             if (mtx == 0) q[rb] = P::mma(w[g & 1].w[s], xo[rb][ib][s], q[rb]);
             if (mtx == 1) k[rb] = P::mma(w[g & 1].w[s], xo[rb][ib][s], k[rb]);
             if (mtx == 2) v[rb] = P::mma(xo[rb][ib][s], w[g & 1].w[s], v[rb]);
           }
-        }
-      } else {
+      }
+    } else {
+#pragma unroll
+      for (int rb = 0; rb < NBR; ++rb)
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
@@ -103,7 +105,6 @@ __device__ __forceinline__ void tile_attention(f32x16 (&x)[NBR][D / 32], const t
             k[rb] = P::mma(ld_frag<P>(Wk, f, lane), xo[rb][ib][s], k[rb]);
             v[rb] = P::mma(xo[rb][ib][s], ld_frag<P>(Wv, f, lane), v[rb]);  // (row x feature)
           }
-      }
     }
     // score scale folded into q; per-head score operands of q and k packed once per head
     // block; V as operands (lane -> feature)
@@ -182,25 +183,24 @@ __device__ __forceinline__ void tile_attention(f32x16 (&x)[NBR][D / 32], const t
     put_lse(hb, lsev);
     // W_O into the residual
 #pragma unroll
-    for (int qb = 0; qb < NBR; ++qb) {
+    for (int ob = 0; ob < NB; ++ob) {
+      if constexpr (AHEAD) {
+        if (ob + 1 < NB)
+          w[(NB + ob + 1) & 1].load(Wo, ((ob + 1) * NB + hb) * ST, lane);
+        else
+          w[0].load(Wq, (hb + 1 < NB ? hb + 1 : hb) * NB * ST, lane);
+      }
 #pragma unroll
-      for (int ob = 0; ob < NB; ++ob) {
-        if constexpr (AHEAD) {
-          if (ob + 1 < NB)
-            w[(NB + ob + 1) & 1].load(Wo, ((ob + 1) * NB + hb) * ST, lane);
-          else
-            w[0].load(Wq, (hb + 1 < NB ? hb + 1 : hb) * NB * ST, lane);
-        }
+      for (int qb = 0; qb < NBR; ++qb)
 #pragma unroll
         for (int s = 0; s < ST; ++s)
           x[qb][ob] = P::mma(AHEAD ? w[(NB + ob) & 1].w[s] : ld_frag<P>(Wo, (ob * NB + hb) * ST + s, lane), P::op(o[qb], s), x[qb][ob]);
-      }
     }
   }
 }
 
 // Feed-forward sub-layer: x += relu(x W1 + b1) W2 + b2, MB chunks of 32 hidden units.
-template <class P, int D, int NBR>
+template <class P, int D, int NBR, int WAVES = 8>
 __device__ __forceinline__ void tile_ffn(f32x16 (&x)[NBR][D / 32], const typename P::elem_t* W1, const typename P::elem_t* W2,
                                          const float* b1s, const float* b2s, int MB, int lane) {
   constexpr int NB = D / 32, ST = P::STEPS;
@@ -233,7 +233,42 @@ __device__ __forceinline__ void tile_ffn(f32x16 (&x)[NBR][D / 32], const typenam
   // issued before chunk c's ReLU and conversions, which then overlap them on the vector ALU
   // (two row blocks: chunk by chunk, a second chunk in flight would not fit in the
   // registers).  Each accumulator of x takes the chunks in order either way.
-  if constexpr (SPAN) {
+  if constexpr (frags_ahead<P, NBR, WAVES>()) {
+    Frags<P> w[2];
+    w[0].load(W1, 0, lane);
+#pragma unroll 1
+    for (int c = 0; c < MB; ++c) {
+      f32x16 u[NBR];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 b = *reinterpret_cast<const float4*>(b1s + 32 * c + 8 * q + 4 * h);
+#pragma unroll
+        for (int rb = 0; rb < NBR; ++rb) { u[rb][4 * q] = b.x; u[rb][4 * q + 1] = b.y; u[rb][4 * q + 2] = b.z; u[rb][4 * q + 3] = b.w; }
+      }
+#pragma unroll
+      for (int ib = 0; ib < NB; ++ib) {
+        if (ib + 1 < NB)
+          w[(ib + 1) & 1].load(W1, (c * NB + ib + 1) * ST, lane);
+        else
+          w[NB & 1].load(W2, c * ST, lane);
+#pragma unroll
+        for (int rb = 0; rb < NBR; ++rb)
+#pragma unroll
+          for (int s = 0; s < ST; ++s) u[rb] = P::mma(w[ib & 1].w[s], xo[rb][ib][s], u[rb]);
+      }
+#pragma unroll
+      for (int ob = 0; ob < NB; ++ob) {
+        if (ob + 1 < NB)
+          w[(NB + ob + 1) & 1].load(W2, ((ob + 1) * MB + c) * ST, lane);
+        else
+          w[0].load(W1, (c + 1 < MB ? c + 1 : c) * NB * ST, lane);
+#pragma unroll
+        for (int rb = 0; rb < NBR; ++rb)
+#pragma unroll
+          for (int s = 0; s < ST; ++s) x[rb][ob] = P::mma(w[(NB + ob) & 1].w[s], P::relu_op(u[rb], s), x[rb][ob]);
+      }
+    }
+  } else if constexpr (SPAN) {
 #pragma unroll
     for (int c = 0; c < MB; ++c)
 #pragma unroll
@@ -245,36 +280,6 @@ __device__ __forceinline__ void tile_ffn(f32x16 (&x)[NBR][D / 32], const typenam
           for (int s = 0; s < ST; ++s)
             x[rb][ob] = P::mma(ld_frag<P>(W2, (ob * MB + c) * ST + s, lane), P::relu_op(u, s), x[rb][ob]);
       }
-  } else if constexpr (frags_ahead<P, NBR>()) {
-    Frags<P> w[2];
-    w[0].load(W1, 0, lane);
-#pragma unroll 1
-    for (int c = 0; c < MB; ++c) {
-      f32x16 u;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 b = *reinterpret_cast<const float4*>(b1s + 32 * c + 8 * q + 4 * h);
-        u[4 * q] = b.x; u[4 * q + 1] = b.y; u[4 * q + 2] = b.z; u[4 * q + 3] = b.w;
-      }
-#pragma unroll
-      for (int ib = 0; ib < NB; ++ib) {
-        if (ib + 1 < NB)
-          w[(ib + 1) & 1].load(W1, (c * NB + ib + 1) * ST, lane);
-        else
-          w[NB & 1].load(W2, c * ST, lane);
-#pragma unroll
-        for (int s = 0; s < ST; ++s) u = P::mma(w[ib & 1].w[s], xo[0][ib][s], u);
-      }
-#pragma unroll
-      for (int ob = 0; ob < NB; ++ob) {
-        if (ob + 1 < NB)
-          w[(NB + ob + 1) & 1].load(W2, ((ob + 1) * MB + c) * ST, lane);
-        else
-          w[0].load(W1, (c + 1 < MB ? c + 1 : c) * NB * ST, lane);
-#pragma unroll
-        for (int s = 0; s < ST; ++s) x[0][ob] = P::mma(w[(NB + ob) & 1].w[s], P::relu_op(u, s), x[0][ob]);
-      }
-    }
   } else {
     constexpr int rb = 0;
     f32x16 un = ffn_pre(0, rb);

@@ -24,7 +24,7 @@ namespace tdo {
 
 // Workgroup size NT: BF16 weights staged in LDS are shared by 8 waves (two per SIMD,
 // so that one wave's latencies overlap the other's work) or by 4 waves (one per SIMD,
-// with twice the registers); the choice is autotuned per shape.  FP32: 8 waves.
+// with twice the registers); the choice is autotuned per shape.  FP32: by the batch (launch_layer_m).
 // A wave of a spanning pass (two row blocks) needs more than half a SIMD's registers:
 // with 8 waves it is held to 256 and spills a few values (24 at head width 16 with
 // masking), which measured faster than one wave per SIMD.
@@ -181,7 +181,7 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
     };
     if (a.save_x) save(a.save_x, x);
 
-    tile_attention<P, D, DH, NBR, MASKED>(x, Wq, Wk, Wv, Wo, okbits, sc, lane, [&](int hb, const float (&lsev)[NBR][HPB]) {
+    tile_attention<P, D, DH, NBR, MASKED, NT / 64>(x, Wq, Wk, Wv, Wo, okbits, sc, lane, [&](int hb, const float (&lsev)[NBR][HPB]) {
       if constexpr (P::KPL == 8) {
         // the head block's normalisers are contiguous per row; one store per lane of the first
         // half (the second half's offset is out of range, and the resource is empty when nothing
@@ -198,7 +198,7 @@ __attribute__((amdgpu_waves_per_eu((SPAN && NT == 512) ? 2 : 1, (SPAN && NT == 5
     });
     if (a.save_mid) save(a.save_mid, x);
 
-    tile_ffn<P, D, NBR>(x, W1, W2, b1s, b2s, MB, lane);
+    tile_ffn<P, D, NBR, NT / 64>(x, W1, W2, b1s, b2s, MB, lane);
 
     if (!a.last) {
 #pragma unroll
@@ -253,11 +253,23 @@ static int32_t launch_layer_nt(const FwdArgs& a, int num_cus, hipStream_t st) {
 
 template <class P, int D, int DH, bool SPAN, int MBC, bool MASKED>
 static int32_t launch_layer_m(const FwdArgs& a, int num_cus, hipStream_t st) {
-  // FP32: always 8 waves.  The weights come through the caches, and a second wave per SIMD covers
-  // their latency (n = 16, width 64, 32768 configurations: 1.51 ms a layer with 4 waves, 1.11 with
-  // 8; n = 37: 1.54 and 1.31; n = 4, width 16: 0.202 and 0.157).
-  if constexpr (P::KPL == 8)
+  if constexpr (P::KPL == 8) {
     if (a.waves == 4) return launch_layer_nt<P, D, DH, SPAN, MBC, MASKED, 256>(a, num_cus, st);
+  } else {
+    // FP32: the weights come through the caches.  With 4 waves a wave has the registers to load its fragments
+    // ahead (frags_ahead), with 8 a second wave per SIMD covers their latency.  A spanning pass of width 64 spills
+    // with 8 (100 registers) and takes 4: microseconds for log rho with 8 and 4 waves, 3 layers, n = 40, 500
+    // configurations 252 and 237, 1500 917 and 627, 16000 6790 and 5981.  The others: a round of the chip with 8 waves
+    // takes so many hundredths of one with 4 (width 32 spanning 190, one row block of width 64 196, of width 32 180),
+    // and 4 are taken where their rounds cost less, which is in batches of few (width 32, n = 50, 1500
+    // configurations 346 and 285, 16000 2507 and 2587; one layer of width 64, n = 32, 1100 146 and 118, 6000 387 and 388).
+    if constexpr (SPAN && D == 64) return launch_layer_nt<P, D, DH, SPAN, MBC, MASKED, 256>(a, num_cus, st);
+    const int64_t tiles = SPAN ? 2 * a.n_entries : 2 * ((a.n_entries + a.cpb - 1) / a.cpb);
+    const int64_t r4 = (tiles + 4 * num_cus - 1) / (4 * num_cus), r8 = (tiles + 8 * num_cus - 1) / (8 * num_cus);
+    if (a.blocks_per_cu == 1 && 100 * r4 < (SPAN ? 190 : D == 64 ? 196 : 180) * r8)
+      return launch_layer_nt<P, D, DH, SPAN, MBC, MASKED, 256>(a, num_cus, st);
+  }
+  if constexpr (P::KPL == 8 || !SPAN || D == 32)
   return launch_layer_nt<P, D, DH, SPAN, MBC, MASKED, 512>(a, num_cus, st);
 }
 

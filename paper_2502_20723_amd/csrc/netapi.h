@@ -26,7 +26,7 @@ struct FwdArgs {
   int n, cpb, d_real, M;
   float score_scale;            // log2(e) / sqrt(d/heads)
   int first, last, masked, blocks_per_cu;
-  int waves;                    // waves per workgroup (8; or 4, BF16 only)
+  int waves;                    // waves per workgroup (8 or 4) of the BF16 kernel
 };
 
 // The whole forward in one launch (net_stack.hip), n <= 32.  mode 0: lr of the E configurations ecfg;

@@ -15,7 +15,7 @@ struct NetPlan {
   float score_scale;
   Profiler* prof;
   int fwd_wg_per_cu;  // workgroups per CU of the forward layer kernel (autotuned, default 1)
-  int fwd_waves;      // waves per workgroup of the forward layer kernel: 8, or 4 (BF16, autotuned)
+  int fwd_waves;      // waves per workgroup of the BF16 forward layer kernel: 8 or 4 (autotuned)
   bool layer_forward; // tests only: every forward layer by layer
   int mlp_waves;      // waves per workgroup of the BF16 feed-forward backward at mlp 256: 8 or 4 (autotuned)
 };

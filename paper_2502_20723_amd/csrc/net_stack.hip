@@ -1,5 +1,5 @@
-// Forward pass of small batches and Metropolis sweeps in one launch: a workgroup takes its tiles
-// through every layer, so that the residual stream never leaves the registers and nothing but the
+// Forward pass and Metropolis sweeps in one launch (which networks and batches: stack_takes): a workgroup
+// takes its tiles through every layer, so that the residual stream never leaves the registers and nothing but the
 // weights moves between layers.  The tile functions are those of the layer-by-layer kernel
 // (fwd_tile.h), so the results are the same bits.
 #include <algorithm>
@@ -245,7 +245,7 @@ static size_t stack_lds_t(int M, int layers) {
   return (P::KPL == 8 ? (size_t)(4 * D * D + 2 * D * M) * 2 : 0) + (size_t)layers * (M + D) * 4 + 64 * (D + TABLE_PAD) * 4 + 64 * sizeof(float2);
 }
 
-// static LDS of the kernel: z and configurations of 4 pairs of waves
+// static LDS of the kernel, at most: z and configurations of 8 pairs of tiles
 constexpr size_t STACK_STATIC = 8 * 10 * 2 * (sizeof(float2) + sizeof(uint64_t));
 
 bool stack_supported(bool bf16, int D, int M, int layers, bool span) {
@@ -259,9 +259,12 @@ static int32_t stack_m(StackArgs a, int mode, int num_cus, hipStream_t st) {
   const int64_t tiles = (a.E + a.cpb - 1) / a.cpb;
   // Two tiles per wave.  A round of the chip (4 pairs per CU with one tile, 8 with two) at n = 32, 4
   // layers, takes 33 and 57 us, so they are taken where 1.8 times their rounds are fewer: 2048 pairs 91
-  // and 84 us, 3072 129 and 140, 4096 159 and 143 (per proposal of 2048 chains 70 and 63).  With the activations saved a backward pass follows,
-  // and the gain of this kernel is lost in its clock up to 64 pairs per CU (log rho and gradient, BF16,
-  // n = 32: 8192 pairs 1603 and 1626 us, 24576 4220 and 4148).
+  // and 84 us, 3072 129 and 140, 4096 159 and 143 (per proposal of 2048 chains 70 and 63).  The same choice is the
+  // faster one, by 5 to 24%, at widths 16, 32 and 64, n = 4, 8, 16, 24, mlp 64 to 512 (1100 to 20000 pairs: width 32,
+  // n = 8, 2500 pairs 48 and 51, 4000 57 and 51; width 32, mlp 512, n = 32, 2500 103 and 105, 20000 534 and 432).  With
+  // the activations saved a backward pass follows, and the gain of this kernel is lost in its clock up to 64 pairs per
+  // CU (log rho and gradient, BF16, n = 32, 4 layers: 8192 pairs 1603 and 1626 us, 24576 4220 and 4148; with 2 or 3
+  // layers, widths 32 and 64, 4000 to 12000 pairs two tiles are 0 to 2% faster).
   const int64_t r1 = (tiles + 4 * num_cus - 1) / (4 * num_cus), r2 = (tiles + 8 * num_cus - 1) / (8 * num_cus);
   const bool two = P::KPL == 8 && (mode == 3 ? tiles > 64LL * num_cus : 18 * r2 < 10 * r1);
   constexpr int T2 = P::KPL == 8 ? 2 : 1;

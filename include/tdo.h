@@ -190,7 +190,7 @@ int32_t tdo_loss_grad(tdo_ctx_t *ctx, const tdo_arch_t *arch, const float *param
  * and grad[p] (device double [P]).  models, params, cfg, B, weights and grad are
  * host arrays of n_problems entries.  The problems run in order on the stream.
  * The first call with given arguments runs eagerly: it sizes the workspace for
- * the largest problem and autotunes the forward launch shape for every
+ * the largest problem and autotunes the tile shapes (tdo_autotune) for every
  * distinct chain length.  The second identical call on a stream other than
  * the legacy default stream records the whole launch sequence into a HIP
  * graph, and every later identical call replays it (inputs are read when the
@@ -206,18 +206,23 @@ int32_t tdo_loss_grad_batched(tdo_ctx_t *ctx, const tdo_arch_t *arch, int32_t n_
 
 /* Tile shapes of the loss/gradient kernels for one problem's shape (chain length,
  * precision, width, head width, depth, MLP width), chosen by timing: the forward
- * layer kernel's waves per workgroup (8: two per SIMD; or, BF16 only, 4) and
- * workgroups per CU (1 or 2), timed on the
- * forward over the samples; the BF16 feed-forward backward's waves per workgroup
+ * layer kernel's waves per workgroup (BF16: 8, two per SIMD, or 4) and workgroups
+ * per CU (1 or 2), timed on the forward over the samples (a network whose forward
+ * runs in one launch at every batch, two layers or more, n <= 32 and a layer's weights
+ * within a CU's LDS, has nothing to choose and keeps 8 and 1); the BF16 feed-forward
+ * backward's waves per workgroup
  * at MLP width 256 (8 or 4), timed on whole loss/gradient evaluations, which
  * write loss and grad (device double [1] and [P]).  The choice is kept in the
  * context and used by every later call of that shape (tdo_loss_grad_batched
  * tunes its problems the same way on its first call); when the environment
  * variable TDO_AUTOTUNE_CACHE names a file when a context is created, tuned
  * shapes are read from that JSON file and written back to it.  The forward
- * shapes do not change results; the backward shape changes the order in which
- * weight gradients are summed, so results of one context are reproducible but
- * may differ by rounding from a context that tuned differently.  shapes: host
+ * shapes do not change results.  The backward shape does: its two forms add dx in
+ * another order, and the BF16 roundings behind it then differ, so gradients of
+ * contexts that chose differently are 1e-5 to 1e-4 of their norm apart (BF16 gradients
+ * themselves are off by about 1e-2).  The choice is a timing and can differ between
+ * contexts; results of one context are reproducible, and so are those of contexts
+ * that read one cache file.  shapes: host
  * int32 [3] or NULL: forward waves, forward workgroups per CU, backward waves.
  * Waits on the host (event timing); not while the stream is captured. */
 int32_t tdo_autotune(tdo_ctx_t *ctx, const tdo_arch_t *arch, const float *params, const tdo_model_t *model,
